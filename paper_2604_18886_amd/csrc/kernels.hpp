@@ -43,7 +43,7 @@ constexpr uint32_t kFlagWall = 0x3fu << 16;
 // lies on the parent's face, and the brick's own parent otherwise.
 struct alignas(16) ParentNbrs {
   int32_t across[3];
-  int32_t pad;
+  int32_t leaf_nbr;  // 1: the parent has a leaf brick as a same-level neighbour
 };
 
 struct Topo {
@@ -92,7 +92,7 @@ __device__ __forceinline__ int octant_of(const BrickMeta &M) {
   return (M.coord[0] & 1) | ((M.coord[1] & 1) << 1) | ((M.coord[2] & 1) << 2);
 }
 
-// Coefficient access for one multigrid level: leaf bricks read CL values,
+// Coefficient arrays of one multigrid level: leaf bricks read CL values,
 // inner bricks read CI values multiplied by iscale (FP16 inner coefficients
 // are stored divided by the cell size of their level).  When CL == CI the
 // inner coefficients directly follow the leaf ones in one array.
@@ -100,20 +100,7 @@ template <class V, class CL, class CI>
 struct Coefs {
   const CL *leaf;
   const CI *inner;
-  const CL *tc;  // plus-side T-face coefficients, 48 per slot
-  uint32_t nlb;
   V iscale;
-  __device__ __forceinline__ V get(uint32_t b, int comp, int m) const {
-    if constexpr (std::is_same<CL, CI>::value) {
-      return V(leaf[b * 256u + comp * 64 + m]);
-    } else {
-      if (b < nlb) return V(leaf[b * 256u + comp * 64 + m]);
-      return V(inner[(b - nlb) * 256u + comp * 64 + m]) * iscale;
-    }
-  }
-  __device__ __forceinline__ V tplus(int32_t slot, int a, int fidx) const {
-    return V(tc[uint32_t(slot) * 48u + a * 16 + fidx]);
-  }
 };
 
 template <class V>
@@ -238,7 +225,7 @@ __global__ void __launch_bounds__(kBlock) k_parent_nbrs(Topo T, ParentNbrs *out)
   if (b >= T.nb) return;
   const BrickMeta &M = T.meta[b];
   ParentNbrs r;
-  r.pad = 0;
+  r.leaf_nbr = 0;
   for (int a = 0; a < 3; ++a) {
     r.across[a] = -1;
     if (M.parent >= 0) {
@@ -246,6 +233,11 @@ __global__ void __launch_bounds__(kBlock) k_parent_nbrs(Topo T, ParentNbrs *out)
       r.across[a] = T.meta[M.parent].nbr[2 * a + side];
     }
   }
+  if (M.parent >= 0)
+    for (int d = 0; d < 6; ++d) {
+      int32_t n = T.meta[M.parent].nbr[d];
+      if (n >= 0 && uint32_t(n) < T.nlb) r.leaf_nbr = 1;
+    }
   out[b] = r;
 }
 
@@ -290,7 +282,7 @@ __global__ void __launch_bounds__(kBlock) k_coarsen(uint32_t lo, uint32_t n, Top
   o[192 + q] = kz;
 }
 
-// FP64 coefficients -> FP32 copies (leaf bricks, T-face table)
+// FP64 coefficients -> FP32 copies (leaf bricks)
 __global__ void k_convert_leaf(const double *src, float *dst, int64_t n) {
   int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = float(src[i]);
@@ -695,6 +687,25 @@ __device__ __forceinline__ V prolong_gather(const LevelView<V, CL, CI, CP> &X,
   return bload_bytes<V>(X.u, ou, 0) - bload_bytes<V>(X.us, os, 0);
 }
 
+// What a T-junction adds to the neighbour sum of the transposed level
+// operator: (A^T u)_m = c_m u_m - S_m - E_m with
+//   E_m = kT_m u_m - (1 / n) sum over the sibling group of (kT_i / 2) u_i,
+// kT the cell's coefficients on T-faces and n the group's active cells (its
+// values v[d] across T-faces are 0).  The coarse leaf's row takes its share
+// from face_children_sum.
+template <class V, class CL>
+__device__ __forceinline__ V t_rows_transposed(const LaneC<V, CL> &L, const BrickMeta &M, V u,
+                                               const V (&k)[6]) {
+  V kt = V(0);
+#pragma unroll
+  for (int d = 0; d < 6; ++d)
+    if ((M.flags >> d) & 1u) kt += L.out[d] ? k[d] : V(0);
+  const V ktu = kt * u;
+  const V s = group8_sum(ktu * V(0.5));
+  const int cnt = __popcll((act_mask(M) >> (L.m & 56u)) & 0xffull);
+  return cnt ? ktu - div_by(s, V(cnt)) : ktu;
+}
+
 // T-junction ghosts (Eq. 10) of a brick with T-faces: across each T-face d
 // the lane's value becomes u_m + (u_J - mean of the active siblings) / 2,
 // u_J read from the coarser leaf.  The coarse values of all T-faces are
@@ -741,8 +752,9 @@ __device__ __forceinline__ void t_ghosts(const LevelView<V, CL, CI, CP> &X, cons
 // gets the correction of its parent cell, the T-junction ghosts use the
 // corrected own and sibling values); 2 the half-sweep after it (the
 // ghosts of the colour-`colour` cells add their own, not yet stored,
-// correction).
-template <int PR = 0, class V, class CL, class CI, int CP>
+// correction).  TR: the neighbour sum of the transposed operator
+// (t_rows_transposed in place of the ghosts).
+template <int PR = 0, bool TR = false, class V, class CL, class CI, int CP>
 __device__ __forceinline__ V stencil_sum(const LevelView<V, CL, CI, CP> &X, const LaneC<V, CL> &L,
                                          uint32_t b, const BrickMeta &M, V u, V k0, V k1,
                                          V k2, V &diag, V corr = V(0), int colour = 0) {
@@ -755,8 +767,11 @@ __device__ __forceinline__ V stencil_sum(const LevelView<V, CL, CI, CP> &X, cons
 #pragma unroll
     for (int d = 0; d < 6; ++d) v[d] = v[d] + shfl(corr, L.esrc[d]);
   }
+  V extra = V(0);  // TR only
   if (M.flags & kFlagT) {
-    if constexpr (sizeof(V) == 8) {
+    if constexpr (TR) {
+      extra = t_rows_transposed(L, M, u, k);
+    } else if constexpr (sizeof(V) == 8) {
       t_ghosts<PR>(X, L, M, u, v, corr, colour);
     } else {
       // FP32: the ghosts face by face (each coarse value waited for before
@@ -790,6 +805,7 @@ __device__ __forceinline__ V stencil_sum(const LevelView<V, CL, CI, CP> &X, cons
   V acc = V(0);
 #pragma unroll
   for (int d = 0; d < 6; ++d) acc += k[d] * v[d];
+  if constexpr (TR) acc += extra;
   return acc;
 }
 
@@ -797,8 +813,8 @@ __device__ __forceinline__ V stencil_sum(const LevelView<V, CL, CI, CP> &X, cons
 // of the colour u_m = (b_m + S_m) / c_m, every read taken before the write
 // (the neighbours of a cell all have the other colour).  PR = 1: the first
 // post-smoothing half-sweep with the prolongation folded in; PR = 2: the
-// one after it (see prolong_gather).
-template <bool INNER, int PR, class V, class CL, class CI, int CP>
+// one after it (see prolong_gather).  TR: a half-sweep for A^T.
+template <bool INNER, int PR, bool TR, class V, class CL, class CI, int CP>
 __device__ __forceinline__ void smooth_brick(const LevelView<V, CL, CI, CP> &X, const LaneC<V, CL> &L,
                                              uint32_t b, int colour) {
   const BrickMeta M = load_meta(X.meta, b);
@@ -810,7 +826,7 @@ __device__ __forceinline__ void smooth_brick(const LevelView<V, CL, CI, CP> &X, 
   V u = bload<V>(X.u, L.m, b * 64u);
   V rhs = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
   V c;
-  V S = stencil_sum<PR>(X, L, b, M, u, k0, k1, k2, c, corr, colour);
+  V S = stencil_sum<PR, TR>(X, L, b, M, u, k0, k1, k2, c, corr, colour);
   bool act = (act_mask(M) >> L.m) & 1ull;
   if (act && L.colour == colour) bstore<V>(X.u, L.m, b * 64u, div_by(rhs + S, c));
 }
@@ -869,7 +885,7 @@ __device__ __forceinline__ HalfGather half_gather(const LaneC<V, CL> &L, int col
 
 // One brick of a colour half-sweep with gathered face loads: the values,
 // ghosts and sums of smooth_brick, term for term.
-template <bool INNER, int PR, class V, class CL, class CI, int CP>
+template <bool INNER, int PR, bool TR, class V, class CL, class CI, int CP>
 __device__ __forceinline__ void smooth_brick_gathered(const LevelView<V, CL, CI, CP> &X,
                                                       const LaneC<V, CL> &L, const HalfGather &G,
                                                       uint32_t b, int colour) {
@@ -907,17 +923,23 @@ __device__ __forceinline__ void smooth_brick_gathered(const LevelView<V, CL, CI,
       k[d] = kown;
     }
   }
-  if (M.flags & kFlagT) t_ghosts<PR>(X, L, M, u, v, corr, colour);
+  V extra = V(0);  // TR only
+  if (M.flags & kFlagT) {
+    if constexpr (TR) extra = t_rows_transposed(L, M, u, k);
+    else t_ghosts<PR>(X, L, M, u, v, corr, colour);
+  }
   V c = ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
   V S = V(0);
 #pragma unroll
   for (int d = 0; d < 6; ++d) S += k[d] * v[d];
+  if constexpr (TR) S += extra;
   if (act && L.colour == colour) bstore<V>(X.u, L.m, b * 64u, div_by(rhs + S, c));
 }
 
 // PR: 0 a plain half-sweep, 1 the first post-smoothing half-sweep with the
-// prolongation folded in, 2 the half-sweep after it (smooth_brick).
-template <class V, class CL, class CI, int CP = kCpolDefault, int PR = 0>
+// prolongation folded in, 2 the half-sweep after it (smooth_brick).  TR: a
+// half-sweep of the transposed cycle.
+template <class V, class CL, class CI, int CP = kCpolDefault, int PR = 0, bool TR = false>
 __global__ void __launch_bounds__(kBlock) k_smooth(LevelArgs<V, CL, CI> A, int colour) {
   if (A.done && *A.done) return;
   if constexpr (sizeof(V) == 8) {
@@ -926,16 +948,16 @@ __global__ void __launch_bounds__(kBlock) k_smooth(LevelArgs<V, CL, CI> A, int c
     const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
     const WaveLoop W = wave_loop(A.R.n());
     for (uint32_t i = W.first; i < W.end; i += W.step) {
-      if (i < A.R.n_leaf) smooth_brick_gathered<false, PR>(X, L, G, A.R.leaf_lo + i, colour);
-      else smooth_brick_gathered<true, PR>(X, L, G, A.R.inner_lo + (i - A.R.n_leaf), colour);
+      if (i < A.R.n_leaf) smooth_brick_gathered<false, PR, TR>(X, L, G, A.R.leaf_lo + i, colour);
+      else smooth_brick_gathered<true, PR, TR>(X, L, G, A.R.inner_lo + (i - A.R.n_leaf), colour);
     }
   } else {
     const LaneC<V, CL> L = lane_consts<V, CL>();
     const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
     const WaveLoop W = wave_loop(A.R.n());
     for (uint32_t i = W.first; i < W.end; i += W.step) {
-      if (i < A.R.n_leaf) smooth_brick<false, PR>(X, L, A.R.leaf_lo + i, colour);
-      else smooth_brick<true, PR>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
+      if (i < A.R.n_leaf) smooth_brick<false, PR, TR>(X, L, A.R.leaf_lo + i, colour);
+      else smooth_brick<true, PR, TR>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
     }
   }
 }
@@ -1085,7 +1107,8 @@ __global__ void __launch_bounds__(kBlock) k_prolong(LevelArgs<V, CL, CI> A) {
 }
 
 // Coarsest level: nu RBGS iterations in one workgroup, (R,B) for the first
-// half of the iterations and (B,R) for the rest.  The level is a complete
+// `half` iterations and (B,R) for the rest (the transposed cycle takes the
+// reversed order, half = nu - nu / 2).  The level is a complete
 // grid of at most kCoarsestBricks bricks (no T-junctions), so its iterate
 // stays in LDS and each wave keeps the coefficients of its bricks (at most
 // kCoarsestSlots) in registers for all 2 nu half-sweeps; every value read,
@@ -1094,7 +1117,7 @@ constexpr int kCoarsestBricks = 64;
 constexpr int kCoarsestSlots = kCoarsestBricks / (1024 / kWave);
 
 template <class V, class CL, class CI>
-__global__ void __launch_bounds__(1024) k_coarsest(LevelArgs<V, CL, CI> A, int nu) {
+__global__ void __launch_bounds__(1024) k_coarsest(LevelArgs<V, CL, CI> A, int nu, int half) {
   if (A.done && *A.done) return;
   __shared__ V su[kCoarsestBricks * 64];
   const LaneC<V, CL> L = lane_consts<V, CL>();
@@ -1128,7 +1151,6 @@ __global__ void __launch_bounds__(1024) k_coarsest(LevelArgs<V, CL, CI> A, int n
     su[i * 64u + uint32_t(m)] = bload<V>(X.u, L.m, b * 64u);
   }
   __syncthreads();
-  int half = nu / 2;
   for (int it = 0; it < nu; ++it) {
     for (int h2 = 0; h2 < 2; ++h2) {
       int colour = it < half ? h2 : 1 - h2;
@@ -1183,6 +1205,10 @@ __global__ void __launch_bounds__(1024) k_coarsest(LevelArgs<V, CL, CI> A, int n
 // W-cycle's later visits: it is already in B).  The FP64 cycle takes one
 // step per launch: with the loop its registers spill further (120 against
 // 88 bytes per lane) and the W-cycle got slower.
+// TR: the same step of the transposed cycle (fas_T of level f) when the
+// coarsest level has no leaves: fas = 1 starts from a zero iterate, the
+// restriction hands the plain residual sums down and the coarsest iterate
+// starts from zero, and pscale times it is the correction that comes back.
 constexpr int kBottomCoarse = 1024 / kWave;
 
 // Six local neighbour indices in [-1, 63] packed as bytes (-1: wall).
@@ -1282,10 +1308,11 @@ __device__ __forceinline__ V own_coef_of(const LevelView<V, CL, CI, CP> &X, bool
   return V(rl);
 }
 
-template <class V, class CL, class CI, bool MULTI>
+template <class V, class CL, class CI, bool MULTI, bool TR = false>
 __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelArgs<V, CL, CI> Ac,
-                                                 int nu_pre, int nu_post, int nu_coarse, int mu,
-                                                 int fas, int visits, V scale) {
+                                                 int nu_pre, int nu_post, int nu_coarse, int half,
+                                                 int mu, int fas, int visits, V scale,
+                                                 V pscale) {
   if (Af.done && *Af.done) return;
   // the iterates of level f and of the coarsest level, each with a zero
   // entry after it that FP64's wall reads take (bottom_sum)
@@ -1353,7 +1380,7 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
       bottom_faces(L, i, pack_nbr(M, Af.R, Xf.nlb), kown, kpl, kWf, kf[j], cf[j], lf[j]);
       parf[j] = (Ac.R.n_leaf + uint32_t(M.parent) - Ac.R.inner_lo) * 64u +
                 uint32_t(octant_of(M)) * 8u;
-      uf[i * 64u + m] = ru[j];
+      uf[i * 64u + m] = TR && fas ? V(0) : ru[j];
     }
   } else {
 #pragma unroll
@@ -1373,7 +1400,7 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
       parf[j] = (Ac.R.n_leaf + uint32_t(M.parent) - Ac.R.inner_lo) * 64u +
                 uint32_t(octant_of(M)) * 8u;
       rf[j] = bload<V>(Xf.b, m, b * 64u);
-      uf[i * 64u + m] = bload<V>(Xf.u, m, b * 64u);
+      uf[i * 64u + m] = TR && fas ? V(0) : bload<V>(Xf.u, m, b * 64u);
     }
   }
   // the coarsest level: coefficients (loaded now, used after the
@@ -1445,7 +1472,7 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
   };
   for (int visit = 0; visit < (MULTI ? visits : 1); ++visit) {
     // FAS right-hand side of the inner bricks: b += A u*
-    if (visit == 0 && fas) {
+    if (!TR && visit == 0 && fas) {
 #pragma unroll
       for (int j = 0; j < kCoarsestSlots; ++j) {
         uint32_t i = w + uint32_t(j) * nw;
@@ -1478,7 +1505,7 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
       int cnt = __popcll((af[j] >> (m & 56u)) & 0xffull);
       if ((m & 7u) == 0) {
         uint32_t q = parf[j] + (m >> 3);
-        V ust = cnt ? div_by(us, V(cnt)) : V(0);
+        V ust = !TR && cnt ? div_by(us, V(cnt)) : V(0);
         bc[q] = rs * scale;
         uc[q] = ust;
         sc[q] = ust;
@@ -1492,10 +1519,9 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
       V S = stencil_c(c);
       V u = uc[w * 64u + m];
       bool act = (ac >> m) & 1ull;
-      rc = act ? bc[w * 64u + m] + (c * u - S) : V(0);
+      rc = act ? bc[w * 64u + m] + (c * u - S) : V(0);  // (TR: u = 0)
     }
     __syncthreads();
-    int half = nu_coarse / 2;
     for (int rep = 0; rep < mu; ++rep)
       for (int it = 0; it < nu_coarse; ++it)
         for (int h2 = 0; h2 < 2; ++h2) {
@@ -1518,7 +1544,7 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
         uint32_t i = w + uint32_t(j) * nw;
         if (i >= nf) continue;
         uint32_t q = parf[j] + (m >> 3);
-        un[j] = uf[i * 64u + m] + (uc[q] - sc[q]);
+        un[j] = uf[i * 64u + m] + (TR ? pscale * uc[q] : uc[q] - sc[q]);
       }
 #pragma unroll
       for (int j = 0; j < kCoarsestSlots; ++j) {
@@ -1531,7 +1557,7 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
         uint32_t i = w + uint32_t(j) * nw;
         if (i >= nf) continue;
         uint32_t q = parf[j] + (m >> 3);
-        V corr = uc[q] - sc[q];
+        V corr = TR ? pscale * uc[q] : uc[q] - sc[q];
         if ((af[j] >> m) & 1ull) uf[i * 64u + m] = uf[i * 64u + m] + corr;
       }
     }
@@ -1548,7 +1574,7 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
     uint32_t i = w + uint32_t(j) * nw;
     if (i < nf) bstore<V>(Xf.u, m, Af.R.brick(i) * 64u, uf[i * 64u + m]);
   }
-  if (w < nc) {
+  if (!TR && w < nc) {
     uint32_t b = Ac.R.brick(w);
     bstore<V>(Xc.u, m, b * 64u, uc[w * 64u + m]);
     if (cin) {
@@ -1559,352 +1585,261 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
 }
 
 // ---------------------------------------------------------------------------
-// transpose of the cycle (adjoint solves).  The cycle's linear steps are
-// transposed and taken in reverse order; this gives a cycle for A^T in
-// residual form: RHO (the adjoint of u) is a residual that is reduced, Y
-// (the adjoint of b) accumulates the solution, W is a scratch level vector.
+// transpose of the cycle (adjoint solves): the cycle's linear steps transposed
+// and taken in reverse order, as a cycle for A^T in solution form.  On every
+// level U holds the iterate y (zero at the first visit), B the right-hand
+// side g and Ustar the part of a level's residual that its parent level hands
+// on.  A transposed half-sweep in residual form, w = rho / c on the colour,
+// rho -= A^T w, y += w, with rho = g - A^T y at all times, is one
+// Gauss-Seidel half-sweep of A^T y = g: it reads and writes what a forward
+// half-sweep does, where the residual form reads and writes rho and w on
+// every cell besides.  Bound like the forward cycle; on the 26.3M-leaf
+// workload, FP32, a finest half-sweep takes 101 us against 161 us in
+// residual form and the adjoint solve and gradient 57.9 against 94.2 ms
+// (2.3M leaves: 8.1 against 13.6 ms).
+//
+// The residual that the transposed FAS steps hand from level l - 1 back to
+// level l,  -(what was restricted) + rho + A^T (y on inner cells), is, with
+// rho = g - A^T y, the change of g since the restriction plus the
+// neighbour sums over the same-level leaves (leaf_neighbour_sum): no
+// operator application is needed for it.
 // ---------------------------------------------------------------------------
-template <class V, class CL, class CI>
-struct LevelArgsT {
-  Topo T;
-  Coefs<V, CL, CI> cf;
-  V *RHO;    // nb * 64
-  V *Y;      // nb * 64
-  V *W;      // nb * 64
-  V *W2;     // nb * 64: the next transposed half-sweep's W (written by k_T_apply)
-  V *SBAR;   // (nb - nlb) * 64
-  V *YS;     // (nb - nlb) * 64
-  Range R;
-  V bscale;  // beta_mg / alpha
-  const int *done;  // skip when the solve has stopped (may be null)
-  const CL *pf;     // plus-face coefficients (as LevelArgs::pf)
-};
 
-// Buffer view of the transposed cycle's arrays on one level.
-template <class V, class CL, class CI, int CP = kCpolDefault>
-struct LevelViewT {
-  LevelView<V, CL, CI, CP> c;  // coefficients and plus faces (u = W)
-  __amdgpu_buffer_rsrc_t rho, y, w, w2, sbar, ys;
-};
-
-template <int CP = kCpolDefault, class V, class CL, class CI>
-__device__ __forceinline__ LevelViewT<V, CL, CI, CP> level_view_T(const LevelArgsT<V, CL, CI> &A) {
-  LevelViewT<V, CL, CI, CP> X;
-  uint64_t nb = A.T.nb, nlb = A.T.nlb;
-  X.rho = make_rsrc(A.RHO, nb * 64 * sizeof(V));
-  X.y = make_rsrc(A.Y, nb * 64 * sizeof(V));
-  X.w = make_rsrc(A.W, nb * 64 * sizeof(V));
-  X.w2 = make_rsrc(A.W2, nb * 64 * sizeof(V));
-  X.sbar = make_rsrc(A.SBAR, (nb - nlb) * 64 * sizeof(V));
-  X.ys = make_rsrc(A.YS, (nb - nlb) * 64 * sizeof(V));
-  X.c.u = X.w;
-  X.c.b = X.w;
-  X.c.us = X.w;
-  X.c.cl = make_rsrc(A.cf.leaf, nlb * 256 * sizeof(CL));
-  X.c.ci = make_rsrc(A.cf.inner, (nb - nlb) * 256 * sizeof(CI));
-  X.c.pf = make_rsrc(A.pf, nb * 48 * sizeof(CL));
-  X.c.meta = A.T.meta;
-  X.c.nlb = A.T.nlb;
-  X.c.iscale = A.cf.iscale;
-  return X;
-}
-
-// Transposed level operator at the lane's cell, applied to W (w its own
-// entry):
-//   (c_m - sum_{T faces of m} k) w_m - sum_{other faces} k W_nbr
-//   + (1 / n_active siblings) sum over the sibling group's T-faces (k_i/2) w_i
-// (the coupling to the coarser level, B^T, is applied by coupling_brick).  The
-// loads across T-faces are out of range, so those faces drop out of the
-// neighbour sum by themselves.
+// First half-sweep of a level from a zero iterate: y = g / c on the active
+// cells of the colour, 0 on all others.  The diagonal is the sum of the six
+// face coefficients, as in every half-sweep.
 template <bool INNER, class V, class CL, class CI, int CP>
-__device__ __forceinline__ V level_AuT(const LevelViewT<V, CL, CI, CP> &X, const LaneC<V, CL> &L,
-                                       uint32_t b, const BrickMeta &M, V w, V &diag) {
-  V k0 = own_coef<INNER>(X.c, b, 1, L.m);
-  V k1 = own_coef<INNER>(X.c, b, 2, L.m);
-  V k2 = own_coef<INNER>(X.c, b, 3, L.m);
-  V v[6], k[6];
-  if constexpr (sizeof(V) == 8)
-    face_values_gathered<CP>(X.w, X.c.pf, L, b, M, w, k0, k1, k2, v, k);
-  else
-    face_values<CP>(X.w, X.c.pf, L, b, M, w, k0, k1, k2, v, k);
-  V c = ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
-  diag = c;
-  uint64_t amask = act_mask(M);
-  bool act = (amask >> L.m) & 1ull;
-  V acc = c * w;
-  if (M.flags & kFlagT) {
-    V tpart = V(0);
-#pragma unroll
-    for (int d = 0; d < 6; ++d) {
-      if ((M.flags >> d) & 1u) {
-        V kt = L.out[d] ? k[d] : V(0);
-        acc -= kt * w;
-        tpart += kt * V(0.5) * w;
-      }
-    }
-    V Ssum = group8_sum(tpart);
-    int cnt = __popcll((amask >> (L.m & 56u)) & 0xffull);
-    if (act && cnt) acc += Ssum / V(cnt);
-  }
-#pragma unroll
-  for (int d = 0; d < 6; ++d) acc -= k[d] * v[d];
-  return act ? acc : V(0);
-}
-
-// First half of a transposed half-sweep: W = RHO / c on the active cells of
-// the colour, 0 elsewhere.
-template <bool INNER, class V, class CL, class CI, int CP>
-__device__ __forceinline__ void sweep_w_brick(const LevelViewT<V, CL, CI, CP> &X,
-                                              const LaneC<V, CL> &L, uint32_t b, int colour) {
-  const BrickMeta M = load_meta(X.c.meta, b);
+__device__ __forceinline__ void zero_brick_T(const LevelView<V, CL, CI, CP> &X,
+                                             const LaneC<V, CL> &L, uint32_t b, int colour) {
+  const BrickMeta M = load_meta(X.meta, b);
   bool act = (act_mask(M) >> L.m) & 1ull;
-  // the diagonal the forward half-sweep divides by: the sum of the six face
-  // coefficients the stencil sees (own k on the minus faces, the partner's
-  // or the plus-face table's on the plus faces), summed in the same order
-  V kd[6];
+  V k[6];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    V kown = own_coef<INNER>(X.c, b, 1 + a, L.m);
-    V kl = V(bload_bytes<CL, side_pol(CP)>(X.c.pf, L.foff[a], b * uint32_t(48 * sizeof(CL))));
+    V kown = own_coef<INNER>(X, b, 1 + a, L.m);
+    V kl = V(bload_bytes<CL, side_pol(CP)>(X.pf, L.foff[a], b * uint32_t(48 * sizeof(CL))));
     V ks = shfl(kown, L.p[2 * a + 1]);
-    kd[2 * a] = kown;
-    kd[2 * a + 1] = L.out[2 * a + 1] ? kl : ks;
+    k[2 * a] = kown;
+    k[2 * a + 1] = L.out[2 * a + 1] ? kl : ks;
   }
-  V c = ((kd[0] + kd[1]) + (kd[2] + kd[3])) + (kd[4] + kd[5]);
-  V x = V(0);
-  if (act && L.colour == colour) x = div_by(bload<V>(X.rho, L.m, b * 64u), c);
-  bstore<V>(X.w, L.m, b * 64u, x);
+  V rhs = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
+  V c = ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
+  bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(rhs, c) : V(0));
 }
 
 template <class V, class CL, class CI, int CP = kCpolDefault>
-__global__ void __launch_bounds__(kBlock) k_T_sweep_w(LevelArgsT<V, CL, CI> A, int colour) {
+__global__ void __launch_bounds__(kBlock) k_T_zero(LevelArgs<V, CL, CI> A, int colour) {
   if (A.done && *A.done) return;
   const LaneC<V, CL> L = lane_consts<V, CL>();
-  const LevelViewT<V, CL, CI, CP> X = level_view_T<CP>(A);
+  const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
   const WaveLoop W = wave_loop(A.R.n());
   for (uint32_t i = W.first; i < W.end; i += W.step) {
-    if (i < A.R.n_leaf) sweep_w_brick<false>(X, L, A.R.leaf_lo + i, colour);
-    else sweep_w_brick<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
+    if (i < A.R.n_leaf) zero_brick_T<false>(X, L, A.R.leaf_lo + i, colour);
+    else zero_brick_T<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
   }
 }
 
-// RHO -= A^T W on the bricks of the range; with colour >= 0 (a transposed
-// half-sweep) also Y += W on that colour's cells (W is zero elsewhere).
-// With next >= 0 the first step of the following half-sweep is taken too:
-// W2 = RHO / c on the active cells of colour next (own cells only, so no
-// other wave needs them during this launch), 0 elsewhere.
-template <bool INNER, class V, class CL, class CI, int CP>
-__device__ __forceinline__ void apply_T_brick(const LevelViewT<V, CL, CI, CP> &X,
-                                              const LaneC<V, CL> &L, uint32_t b, int colour,
-                                              int next) {
-  const BrickMeta M = load_meta(X.c.meta, b);
-  V w = bload<V>(X.w, L.m, b * 64u);
-  V c;
-  V t = level_AuT<INNER>(X, L, b, M, w, c);
-  V rho = bload<V>(X.rho, L.m, b * 64u) - t;
-  bstore<V>(X.rho, L.m, b * 64u, rho);
-  // FP32: Y passes the caches non-temporal (its next use is two half-sweeps
-  // later; mixed adjoint 95.3 -> 94.3 ms); FP64 keeps it cached (148.2
-  // against 149.2 ms)
-  constexpr int yp = sizeof(V) == 4 ? kCpolStream : kCpolDefault;
-  if (L.colour == colour)
-    bstore<V, yp>(X.y, L.m, b * 64u, bload<V, yp>(X.y, L.m, b * 64u) + w);
-  if (next >= 0) {
-    bool act = (act_mask(M) >> L.m) & 1ull;
-    bstore<V>(X.w2, L.m, b * 64u, act && L.colour == next ? div_by(rho, c) : V(0));
-  }
+// Sum over the four fine cells across face d of the lane's cell (in a leaf
+// brick whose neighbour nb across d is an inner brick) of (k_f / 2) x_f, k_f
+// the fine cell's T-face coefficient: the coarse leaf's row of the
+// transposed T-junction coupling; 0 on lanes away from the face.  The 8 x 8
+// fine cells on the face are one per lane -- lane 4 j + s holds sub-cell s
+// of the coarse face cell with interleaved in-plane index j -- so the face
+// takes two loads, two exchange steps add each cell's four and one hands it
+// to the face's lane.
+template <class V, class CL>
+__device__ __forceinline__ V face_children_sum(__amdgpu_buffer_rsrc_t x,
+                                               __amdgpu_buffer_rsrc_t cl,
+                                               __amdgpu_buffer_rsrc_t pf, const int32_t *child,
+                                               int32_t nb, int d, int m) {
+  const int a = d >> 1;
+  const int o0 = a == 0 ? 1 : 0;
+  const int o1 = a == 2 ? 1 : 2;
+  const int j = m >> 2;
+  const int cu = (j & 1) | ((j >> 1) & 2);
+  const int cv = ((j >> 1) & 1) | ((j >> 2) & 2);
+  const int32_t *ch = child + 8 * int64_t(nb) + ((d & 1) ? 0 : (1 << a));
+  const int32_t c0 = ch[0], c1 = ch[1 << o0], c2 = ch[1 << o1], c3 = ch[(1 << o0) | (1 << o1)];
+  const uint32_t cb = uint32_t(cv & 2 ? (cu & 2 ? c3 : c2) : (cu & 2 ? c1 : c0));
+  const int fu = ((cu & 1) << 1) | (m & 1);
+  const int fv = ((cv & 1) << 1) | ((m >> 1) & 1);
+  int xyz[3];
+  xyz[a] = (d & 1) ? 0 : 3;
+  xyz[o0] = fu;
+  xyz[o1] = fv;
+  const uint32_t q = uint32_t(dev_morton(xyz[0], xyz[1], xyz[2]));
+  V k;
+  if (d & 1)  // the fine cells' own minus-face coefficients
+    k = V(bload<CL>(cl, cb * 256u + uint32_t(1 + a) * 64u + q, 0u));
+  else        // their plus-face entries
+    k = V(bload<CL>(pf, cb * 48u + uint32_t(a * 16 + fu + 4 * fv), 0u));
+  V s = k * V(0.5) * bload<V>(x, cb * 64u + q, 0u);
+  s = s + shfl_xor(s, 1);
+  s = s + shfl_xor(s, 2);
+  const int mu = dev_coord(m, o0), mv = dev_coord(m, o1);
+  const int jm = (mu & 1) | ((mv & 1) << 1) | ((mu & 2) << 1) | ((mv & 2) << 2);
+  V r = shfl(s, 4 * jm);
+  return dev_outside(m, d) ? r : V(0);
 }
 
-template <class V, class CL, class CI, int CP = kCpolDefault>
-__global__ void __launch_bounds__(kBlock) k_T_apply(LevelArgsT<V, CL, CI> A, int colour,
-                                                    int next) {
-  if (A.done && *A.done) return;
-  const LaneC<V, CL> L = lane_consts<V, CL>();
-  const LevelViewT<V, CL, CI, CP> X = level_view_T<CP>(A);
-  const WaveLoop W = wave_loop(A.R.n());
-  for (uint32_t i = W.first; i < W.end; i += W.step) {
-    if (i < A.R.n_leaf) apply_T_brick<false>(X, L, A.R.leaf_lo + i, colour, next);
-    else apply_T_brick<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour, next);
-  }
-}
-
-// Coupling of level l to the coarser leaves, transposed: on the leaf bricks
-// of level l-1 that have an inner neighbour (a list), RHO_J += sum over the
-// fine T-face cells f next to J of (k_f / 2) W_f (the fine cells are
-// children of J's inner neighbour); this is one listed brick b (lane m).
-template <class V, class CL, class CI>
-__device__ __forceinline__ void coupling_brick(const LevelArgsT<V, CL, CI> &A, uint32_t b,
-                                               int m) {
-  const BrickMeta M = A.T.meta[b];
-  if (!(M.flags & kFlagInner)) return;
-  if (!((act_mask(M) >> m) & 1ull)) return;
+// Coupling of level l to the coarser leaves, transposed: a leaf brick b of
+// level l - 1 with an inner neighbour takes g_J += sum over its fine T-face
+// cells of (k_f / 2) y_f.  `prev` (null when each level is visited once)
+// keeps what was added at the visit before.
+template <class V, class CL, class CI, int CP>
+__device__ __forceinline__ void coupling_brick(const LevelView<V, CL, CI, CP> &X,
+                                               const int32_t *child, V *prev, int first,
+                                               uint32_t b, int m) {
+  const BrickMeta M = load_meta(X.meta, b);
   V acc = V(0);
-  for (int d = 0; d < 6; ++d) {
-    if (!((M.flags >> (8 + d)) & 1u) || !dev_outside(m, d)) continue;
-    int a = d >> 1;
-    int p = dev_partner(m, d);
-    int32_t cb = A.T.child[8 * int64_t(M.nbr[d]) + (p >> 3)];
-    int32_t slot = A.T.meta[cb].tplus;
-    int base = (p & 7) << 3;
-    int facebit = (d & 1) ? 0 : 1;
-    for (int t = 0; t < 8; ++t) {
-      if (((t >> a) & 1) != facebit) continue;
-      int q = base | t;
-      V kc = (d & 1) ? A.cf.get(uint32_t(cb), 1 + a, q) : A.cf.tplus(slot, a, dev_face_index(q, a));
-      acc += kc * V(0.5) * A.W[uint32_t(cb) * 64u + q];
-    }
+#pragma unroll
+  for (int d = 0; d < 6; ++d)
+    if ((M.flags >> (8 + d)) & 1u)
+      acc += face_children_sum<V, CL>(X.u, X.cl, X.pf, child, M.nbr[d], d, m);
+  if (!((act_mask(M) >> m) & 1ull)) acc = V(0);
+  V g = bload<V>(X.b, uint32_t(m), b * 64u);
+  if (prev) {
+    V was = first ? V(0) : prev[b * 64u + uint32_t(m)];
+    prev[b * 64u + uint32_t(m)] = acc;
+    acc -= was;
   }
-  A.RHO[b * 64u + m] += acc;
+  bstore<V>(X.b, uint32_t(m), b * 64u, g + acc);
 }
 
-// A transposed half-sweep's apply step on level l (workgroups [0, g_apply),
-// as k_T_apply) and, in the same launch, the coupling of its w to the
-// coarser leaves (the workgroups after, one wave per listed brick): the coupling reads
-// only w, which the apply step does not write, and writes the residual of
-// level l-1 leaf bricks, which the apply step does not touch.
+// Transposed prolongation: the children's residual sums become the parents'
+// right-hand side; the parents' iterate and handed-back residual start from 0.
+template <bool INNER, class V, class CL, class CI, int CP>
+__device__ __forceinline__ void restrict_brick_T(const LevelView<V, CL, CI, CP> &X,
+                                                 const LaneC<V, CL> &L, uint32_t b) {
+  const BrickMeta M = load_meta(X.meta, b);
+  V k0 = own_coef<INNER>(X, b, 1, L.m);
+  V k1 = own_coef<INNER>(X, b, 2, L.m);
+  V k2 = own_coef<INNER>(X, b, 3, L.m);
+  V u = bload<V>(X.u, L.m, b * 64u);
+  V rhs = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
+  V c;
+  V S = stencil_sum<0, true>(X, L, b, M, u, k0, k1, k2, c);
+  bool act = (act_mask(M) >> L.m) & 1ull;
+  V rs = group8_sum(act ? rhs - (c * u - S) : V(0));
+  if ((L.m & 7u) == 0) {
+    uint32_t base = uint32_t(M.parent) * 64u + uint32_t(octant_of(M)) * 8u;
+    uint32_t q = L.m >> 3;
+    bstore<V>(X.b, q, base, rs);
+    bstore<V>(X.u, q, base, V(0));
+    bstore<V>(X.us, q, base - X.nlb * 64u, V(0));
+  }
+}
+
+// The restriction of level l (workgroups [0, g_restrict)) and, in the same
+// launch, its coupling to the coarser leaves (the workgroups after, one wave
+// per listed brick): both read the level's iterate; the former writes the
+// parents' arrays, the latter the right-hand side of leaves of level l - 1.
 template <class V, class CL, class CI, int CP = kCpolDefault>
-__global__ void __launch_bounds__(kBlock) k_T_apply_couple(LevelArgsT<V, CL, CI> A, int colour,
-                                                           int next, LevelArgsT<V, CL, CI> C,
-                                                           const uint32_t *list, uint32_t n,
-                                                           uint32_t g_apply) {
+__global__ void __launch_bounds__(kBlock) k_T_restrict(LevelArgs<V, CL, CI> A, V *prev, int first,
+                                                       const uint32_t *list, uint32_t n,
+                                                       uint32_t g_restrict) {
   if (A.done && *A.done) return;
-  if (blockIdx.x < g_apply) {
+  const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
+  if (blockIdx.x < g_restrict) {
     const LaneC<V, CL> L = lane_consts<V, CL>();
-    const LevelViewT<V, CL, CI, CP> X = level_view_T<CP>(A);
-    const WaveLoop W = wave_loop_of(A.R.n(), blockIdx.x, g_apply);
+    const WaveLoop W = wave_loop_of(A.R.n(), blockIdx.x, g_restrict);
     for (uint32_t i = W.first; i < W.end; i += W.step) {
-      if (i < A.R.n_leaf) apply_T_brick<false>(X, L, A.R.leaf_lo + i, colour, next);
-      else apply_T_brick<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour, next);
+      if (i < A.R.n_leaf) restrict_brick_T<false>(X, L, A.R.leaf_lo + i);
+      else restrict_brick_T<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf));
     }
   } else {
-    uint32_t i = (blockIdx.x - g_apply) * kWavesPerBlock + wave_id();
-    int m = threadIdx.x & (kWave - 1);
-    if (i < n) coupling_brick(C, list[i], m);
+    uint32_t i = (blockIdx.x - g_restrict) * kWavesPerBlock + wave_id();
+    if (i < n) {
+      uint32_t b = __builtin_amdgcn_readfirstlane(list[i]);
+      coupling_brick(X, A.T.child, prev, first, b, int(threadIdx.x & (kWave - 1)));
+    }
   }
 }
 
-// Transposed prolongation input: the children's residual sums move to the
-// parents, RHO_P += sum_active_children RHO, SBAR_P = -(that sum).
+// Sum over the faces of cell m of inner brick b to same-level leaf bricks of
+// k y (M: the brick's record, iscale: of the brick's level).
+template <class V, class CL, class CI, int CP>
+__device__ __forceinline__ V leaf_neighbour_sum(const LevelView<V, CL, CI, CP> &X, uint32_t b,
+                                                const BrickMeta &M, int m, V iscale) {
+  V q = V(0);
+#pragma unroll
+  for (int d = 0; d < 6; ++d) {
+    const int a = d >> 1;
+    const int32_t n = M.nbr[d];
+    if (n < 0 || uint32_t(n) >= X.nlb || !dev_outside(m, d)) continue;
+    V k;
+    if (d & 1) {
+      k = V(bload<CL>(X.pf, uint32_t(a * 16 + dev_face_index(m, a)), b * 48u));
+    } else {
+      k = V(bload<CI>(X.ci, uint32_t(m), (b - X.nlb) * 256u + uint32_t(1 + a) * 64u));
+      if constexpr (!std::is_same<CL, CI>::value) k = k * iscale;
+    }
+    q += k * bload<V>(X.u, uint32_t(dev_partner(m, d)), uint32_t(n) * 64u);
+  }
+  return q;
+}
+
+// Later visits of a level by a W-cycle (its leaves' iterate is no longer
+// zero): the restricted right-hand side of the inner bricks of A's level and
+// the residual handed back from it start from minus the sums over its
+// same-level leaves.
 template <class V, class CL, class CI>
-__global__ void __launch_bounds__(kBlock) k_T_restrict(LevelArgsT<V, CL, CI> A) {
+__global__ void __launch_bounds__(kBlock) k_T_revisit(LevelArgs<V, CL, CI> A) {
   if (A.done && *A.done) return;
-  uint32_t i = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  if (i >= A.R.n()) return;
-  uint32_t b = A.R.brick(i);
-  const BrickMeta M = A.T.meta[b];
-  bool act = (act_mask(M) >> m) & 1ull;
-  V s = group8_sum(act ? A.RHO[b * 64u + m] : V(0));
-  if ((m & 7) == 0) {
-    uint32_t P = uint32_t(M.parent);
-    int q = (octant_of(M) << 3) | (m >> 3);
-    A.RHO[P * 64u + q] += s;
-    A.SBAR[(P - A.T.nlb) * 64u + q] = -s;
+  const LevelView<V, CL, CI> X = level_view(A);
+  const int m = threadIdx.x & (kWave - 1);
+  const WaveLoop W = wave_loop(A.R.n_inner);
+  for (uint32_t i = W.first; i < W.end; i += W.step) {
+    uint32_t b = A.R.inner_lo + i;
+    const BrickMeta M = load_meta(X.meta, b);
+    V q = leaf_neighbour_sum(X, b, M, m, X.iscale);
+    if (!((act_mask(M) >> m) & 1ull)) q = V(0);
+    V g = bload<V>(X.b, uint32_t(m), b * 64u);
+    bstore<V>(X.b, uint32_t(m), b * 64u, g - q);
+    bstore<V>(X.us, uint32_t(m), (b - X.nlb) * 64u, -q);
   }
 }
 
-// After the coarse recursion, on the bricks of level l-1: inner cells move
-// RHO into SBAR and zero it, keep Y (active) in YS and W, zero Y; leaf
-// bricks set W = 0.
-template <class V, class CL, class CI>
-__global__ void __launch_bounds__(kBlock) k_T_coarse(LevelArgsT<V, CL, CI> A) {
-  if (A.done && *A.done) return;
-  uint32_t i = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  if (i >= A.R.n()) return;
-  uint32_t b = A.R.brick(i);
-  if (b < A.T.nlb) {
-    A.W[b * 64u + m] = V(0);
-    return;
+// After the coarse recursion, on the bricks of level l: active cells take
+// D = (handed-back residual of the parent) / n_active(P) into their
+// right-hand side (and, on inner bricks, into the residual they hand back
+// themselves) and pscale = beta_mg / alpha times the parent's iterate into
+// their own.
+template <bool INNER, class V, class CL, class CI, int CP>
+__device__ __forceinline__ void prolong_brick_T(const LevelView<V, CL, CI, CP> &X,
+                                                const LaneC<V, CL> &L, uint32_t b, V pscale) {
+  const BrickMeta M = load_meta(X.meta, b);
+  const ParentNbrs PN = load_parent_nbrs(X.pnb, b);
+  const uint32_t P = uint32_t(M.parent);
+  const uint32_t oc = uint32_t(octant_of(M)) * 8u;
+  const uint32_t q = L.m >> 3;
+  V D = bload<V>(X.us, q, P * 64u + oc - X.nlb * 64u);
+  V yp = bload<V>(X.u, q, P * 64u + oc);
+  V g = bload<V>(X.b, L.m, b * 64u);
+  V y = bload<V>(X.u, L.m, b * 64u);
+  V sb = V(0);
+  if constexpr (INNER) sb = bload<V>(X.us, L.m, (b - X.nlb) * 64u);
+  if (PN.leaf_nbr)  // (the parent's cell size is twice the level's)
+    D += leaf_neighbour_sum(X, P, load_meta(X.meta, P), int(oc + q), X.iscale * V(2));
+  const uint64_t amask = act_mask(M);
+  const int cnt = __popcll((amask >> (L.m & 56u)) & 0xffull);
+  if ((amask >> L.m) & 1ull) {
+    D = div_by(D, V(cnt));
+    bstore<V>(X.b, L.m, b * 64u, g + D);
+    bstore<V>(X.u, L.m, b * 64u, y + pscale * yp);
+    if constexpr (INNER) bstore<V>(X.us, L.m, (b - X.nlb) * 64u, sb + D);
   }
-  const BrickMeta M = A.T.meta[b];
-  bool act = (act_mask(M) >> m) & 1ull;
-  uint32_t j = (b - A.T.nlb) * 64u + m;
-  A.SBAR[j] += A.RHO[b * 64u + m];
-  A.RHO[b * 64u + m] = V(0);
-  V yb = act ? A.Y[b * 64u + m] : V(0);
-  A.YS[j] = yb;
-  A.W[b * 64u + m] = yb;
-  A.Y[b * 64u + m] = V(0);
 }
 
-// On the bricks of level l-1: t = (A^{l-1})^T W (W = YS on inner cells, 0 on
-// leaves); inner cells SBAR += t, leaf cells RHO += t.
 template <class V, class CL, class CI>
-__global__ void __launch_bounds__(kBlock) k_T_fas(LevelArgsT<V, CL, CI> A) {
+__global__ void __launch_bounds__(kBlock) k_T_prolong(LevelArgs<V, CL, CI> A, V pscale) {
   if (A.done && *A.done) return;
   const LaneC<V, CL> L = lane_consts<V, CL>();
-  const LevelViewT<V, CL, CI> X = level_view_T(A);
+  const LevelView<V, CL, CI> X = level_view(A);
   const WaveLoop W = wave_loop(A.R.n());
   for (uint32_t i = W.first; i < W.end; i += W.step) {
-    if (i < A.R.n_leaf) {
-      uint32_t b = A.R.leaf_lo + i;
-      const BrickMeta M = load_meta(X.c.meta, b);
-      V c;
-      V t = level_AuT<false>(X, L, b, M, bload<V>(X.w, L.m, b * 64u), c);
-      bstore<V>(X.rho, L.m, b * 64u, bload<V>(X.rho, L.m, b * 64u) + t);
-    } else {
-      uint32_t b = A.R.inner_lo + (i - A.R.n_leaf);
-      const BrickMeta M = load_meta(X.c.meta, b);
-      V c;
-      V t = level_AuT<true>(X, L, b, M, bload<V>(X.w, L.m, b * 64u), c);
-      uint32_t j = (b - X.c.nlb) * 64u;
-      bstore<V>(X.sbar, L.m, j, bload<V>(X.sbar, L.m, j) + t);
-    }
-  }
-}
-
-// On the bricks of level l: active cells RHO += SBAR_P / n_active(P),
-// tbar = (beta_mg / alpha) YS_P, Y += tbar, W = tbar (0 on inactive cells).
-template <class V, class CL, class CI>
-__global__ void __launch_bounds__(kBlock) k_T_prolong(LevelArgsT<V, CL, CI> A) {
-  if (A.done && *A.done) return;
-  uint32_t i = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  if (i >= A.R.n()) return;
-  uint32_t b = A.R.brick(i);
-  const BrickMeta M = A.T.meta[b];
-  uint64_t amask = act_mask(M);
-  bool act = (amask >> m) & 1ull;
-  V tb = V(0);
-  if (act) {
-    uint32_t P = uint32_t(M.parent);
-    int q = (octant_of(M) << 3) | (m >> 3);
-    int cnt = __popcll((amask >> (m & 56)) & 0xffull);
-    uint32_t j = (P - A.T.nlb) * 64u + q;
-    A.RHO[b * 64u + m] += A.SBAR[j] / V(cnt);
-    tb = A.bscale * A.YS[j];
-    A.Y[b * 64u + m] += tb;
-  }
-  A.W[b * 64u + m] = tb;
-}
-
-// Coarsest level, transposed: the half-sweeps of k_coarsest in reverse
-// order, each as w = RHO / c on the colour, then RHO -= A^T w, Y += w.
-template <class V, class CL, class CI>
-__global__ void __launch_bounds__(1024) k_T_coarsest(LevelArgsT<V, CL, CI> A, int nu) {
-  if (A.done && *A.done) return;
-  const LaneC<V, CL> L = lane_consts<V, CL>();
-  const LevelViewT<V, CL, CI> X = level_view_T(A);
-  uint32_t w = wave_id();
-  uint32_t nw = blockDim.x / kWave;
-  int half = nu / 2;
-  for (int it = 0; it < nu; ++it) {
-    for (int h2 = 0; h2 < 2; ++h2) {
-      int colour = it < nu - half ? h2 : 1 - h2;
-      for (uint32_t i = w; i < A.R.n(); i += nw) {
-        if (i < A.R.n_leaf) sweep_w_brick<false>(X, L, A.R.leaf_lo + i, colour);
-        else sweep_w_brick<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
-      }
-      __threadfence_block();
-      __syncthreads();
-      for (uint32_t i = w; i < A.R.n(); i += nw) {
-        if (i < A.R.n_leaf) apply_T_brick<false>(X, L, A.R.leaf_lo + i, colour, -1);
-        else apply_T_brick<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour, -1);
-      }
-      __threadfence_block();
-      __syncthreads();
-    }
+    if (i < A.R.n_leaf) prolong_brick_T<false>(X, L, A.R.leaf_lo + i, pscale);
+    else prolong_brick_T<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), pscale);
   }
 }
 
@@ -1919,14 +1854,6 @@ __global__ void k_couple_list(const BrickMeta *meta, uint32_t nlb, const int64_t
                               uint32_t *list) {
   uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
   if (b < nlb && (meta[b].flags & kFlagInner)) list[pos[b]] = b;
-}
-
-// dst = V(src * scale): the transposed cycle's input (scale: the power of
-// two of the solve's scalars, or null for 1)
-template <class V>
-__global__ void k_T_load(const double *src, V *dst, int64_t n, const double *scale) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = V(scale ? src[i] * *scale : src[i]);
 }
 
 template <class V>

@@ -120,16 +120,6 @@ inline unsigned stencil_grid(int64_t bricks) {
   if (waves_override()) return grid_waves(bricks, waves_override());
   return grid_waves(bricks, sizeof(V) == 8 ? kWavesPerXcd64 : cap32(bricks));
 }
-// The transposed cycle's stencils (adjoint solves) keep one brick per wave
-// in FP64: they do not use the gathered face loads, and looping made them
-// slower.  In FP32 they loop with 2048 waves per XCD (3072 made the mixed
-// adjoint solve slower, 93.8 -> 94.6 ms).
-constexpr int64_t kWavesPerXcdT32 = 2048;
-template <class V>
-inline unsigned stencil_grid_T(int64_t bricks) {
-  if (waves_override()) return grid_waves(bricks, waves_override());
-  return grid_waves(bricks, sizeof(V) == 8 ? int64_t(1) << 30 : kWavesPerXcdT32);
-}
 // A stencil launch whose single-use streams (coefficients, plus faces,
 // right-hand side) and iterate together exceed the 256 MB Infinity Cache
 // gains nothing from caching those streams for the next launch, and they
@@ -202,13 +192,13 @@ struct mfmg_hierarchy {
   DevBuf<double> coef64;   // nb * 256 (leaf part = assembled, inner = Algorithm 3)
   DevBuf<float> coef32;    // nlb * 256 (mixed)
   DevBuf<__half> coef16;   // (nb - nlb) * 256 (mixed)
-  DevBuf<float> tc32;      // mixed
   DevBuf<double> pf64;     // plus-face coefficients, nb * 48 (FP64 cycle, composite operator)
   DevBuf<float> pf32;      // plus-face coefficients, nb * 48 (mixed cycle)
   double n_active = 0;     // active leaf cells
   std::vector<char> stream_lv;  // per level: the cycle's stencils stream their coefficients
   bool stream_composite = false;  // the same for the composite operator
   bool fuse_bottom = false;       // level lc + 1 and the coarsest level in one kernel (k_bottom)
+  bool fuse_bottom_T = false;     // the same for the transposed cycle
   bool fuse_prolong = true;       // prolongation folded into the post-smoothing (k_smooth PR)
   std::vector<char> fold_fas;     // per level: FAS right-hand side folded into k_smooth_fas
   // work vectors (device order)
@@ -222,12 +212,14 @@ struct mfmg_hierarchy {
   DevBuf<double> partials;
   DevBuf<Scalars> S;
   DevBuf<double> hist;
-  // transposed cycle (allocated on first use): residual, solution, scratch
-  DevBuf<double> T64[6];  // RHO, Y, W (nb*64), SBAR, YS ((nb-nlb)*64), W2 (nb*64)
+  // transposed cycle (allocated on first use): iterate and right-hand side
+  // (nb*64), handed-back residual ((nb-nlb)*64), and for mu > 1 the coupling
+  // already added to the leaves (nlb*64)
+  DevBuf<double> T64[4];
   // leaf bricks with an inner neighbour (level-major), per level [lo, lo + n)
   DevBuf<uint32_t> couple;
   std::vector<uint32_t> couple_lo, couple_n;
-  DevBuf<float> T32[6];
+  DevBuf<float> T32[4];
   DevBuf<double> rA;              // adjoint PCG residual
   // face arrays for the per-face gradient (allocated on first use)
   DevBuf<int64_t> f_owner, f_other;
@@ -238,13 +230,15 @@ struct mfmg_hierarchy {
   int *host_done_dev = nullptr;  // its device address
   hipEvent_t iter_ev[2] = {nullptr, nullptr};
   hipStream_t cap_stream = nullptr;                 // capture-only stream of the graphs
-  hipGraphExec_t iter_graph[2] = {nullptr, nullptr};  // PCG loop body [null space]
+  // PCG loop body [forward, adjoint][null space]
+  hipGraphExec_t iter_graph[2][2] = {{nullptr, nullptr}, {nullptr, nullptr}};
   void drop_graphs() {
-    for (hipGraphExec_t &g : iter_graph)
-      if (g) {
-        (void)hipGraphExecDestroy(g);
-        g = nullptr;
-      }
+    for (auto &gs : iter_graph)
+      for (hipGraphExec_t &g : gs)
+        if (g) {
+          (void)hipGraphExecDestroy(g);
+          g = nullptr;
+        }
   }
   ~mfmg_hierarchy() {
     drop_graphs();
@@ -885,11 +879,8 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     if (prm->precision == MFMG_MIXED) {
       h->coef32.alloc(size_t(nlb) * 256);
       h->coef16.alloc(size_t(nb - nlb) * 256 + 1);
-      h->tc32.alloc(co->tc.n);
       hipLaunchKernelGGL(k_convert_leaf, dim3(grid_elems(nlb * 256, 256)), dim3(256), 0, s,
                          (const double *)h->coef64.p, h->coef32.p, nlb * 256);
-      hipLaunchKernelGGL(k_convert_leaf, dim3(grid_elems(int64_t(co->tc.n), 256)), dim3(256),
-                         0, s, (const double *)co->tc.p, h->tc32.p, int64_t(co->tc.n));
       if (nb > nlb)
         hipLaunchKernelGGL(k_convert_inner, dim3(grid_for(nb - nlb)), dim3(kBlock), 0, s,
                            (const double *)h->coef64.p, topo, h->coef16.p);
@@ -966,6 +957,8 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
           if (M.flags & kFlagT) ok = false;
       }
       h->fuse_bottom = ok;
+      // (k_bottom's transposed form takes a coarsest level without leaves)
+      h->fuse_bottom_T = ok && D.range[h->lc].n_leaf == 0;
     }
     {
       // MFMG_FUSE_PROLONG=0 (read at each build) keeps the separate
@@ -1114,8 +1107,6 @@ struct Cycle {
     A.T.pnb = h->pnb.p;
     A.cf.leaf = leafc;
     A.cf.inner = innerc;
-    A.cf.tc = nullptr;
-    A.cf.nlb = D.nlb;
     A.cf.iscale = iscale(l);
     A.pf = pf;
     A.U = U;
@@ -1189,7 +1180,7 @@ struct Cycle {
       auto A = args(l, false);
       int threads = int(std::min<int64_t>(16, A.R.n())) * kWave;
       hipLaunchKernelGGL((k_coarsest<V, CL, CI>), dim3(1), dim3(threads), 0, s, A,
-                         p.nu_coarse);
+                         p.nu_coarse, p.nu_coarse / 2);
       return;
     }
     smooth(l, 0, p.nu_pre, zero_start, false, fold);
@@ -1206,11 +1197,13 @@ struct Cycle {
       auto Cc = args(h->lc, false);
       if constexpr (sizeof(V) == 4)
         hipLaunchKernelGGL((k_bottom<V, CL, CI, true>), dim3(1), dim3(1024), 0, s, F, Cc,
-                           p.nu_pre, p.nu_post, p.nu_coarse, p.mu, 1, p.mu, scale);
+                           p.nu_pre, p.nu_post, p.nu_coarse, p.nu_coarse / 2, p.mu, 1, p.mu,
+                           scale, V(0));
       else
         for (int k = 0; k < p.mu; ++k)
           hipLaunchKernelGGL((k_bottom<V, CL, CI, false>), dim3(1), dim3(1024), 0, s, F, Cc,
-                             p.nu_pre, p.nu_post, p.nu_coarse, p.mu, int(k == 0), 1, scale);
+                             p.nu_pre, p.nu_post, p.nu_coarse, p.nu_coarse / 2, p.mu,
+                             int(k == 0), 1, scale, V(0));
     } else {
       auto C = args(l - 1, true);
       bool fold = h->fold_fas[size_t(l - 1)] && p.nu_pre > 0;
@@ -1254,150 +1247,116 @@ void run_cycle(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
 }
 
 // Transpose of the cycle (exact adjoint of run_cycle's linear map), in
-// residual form: RHO leaf part = input, output = Y leaf part.
+// solution form (kernels.hpp): the leaf part of G holds the input, the leaf
+// part of Y ends as the output.
 template <class V, class CL, class CI>
 struct CycleT {
   const mfmg_hierarchy *h;
   const CL *leafc;
   const CI *innerc;
-  const CL *tc;
   const CL *pf;
-  V *RHO, *Y, *W, *SBAR, *YS, *W2;
-  hipStream_t s;
+  V *Y, *G, *Sb, *Cpl;
   const int *done;
+  hipStream_t s;
+  static constexpr int kCpolLevel = Cycle<V, CL, CI>::kCpolLevel;
 
-  V iscale(int l) const {
-    return std::is_same<CI, __half>::value ? V(std::ldexp(1.0, -l)) : V(1);
+  LevelArgs<V, CL, CI> args(int l) const {
+    return Cycle<V, CL, CI>{h, leafc, innerc, pf, Y, G, Sb, done, s}.args(l, false);
   }
-  LevelArgsT<V, CL, CI> args(int l, int part) const {  // part: 0 all, 1 leaf only
-    const DeviceTopology &D = *h->co->dt;
-    LevelArgsT<V, CL, CI> A;
-    A.T = make_topo(D, h->meta.p);
-    A.T.pnb = h->pnb.p;
-    A.cf.leaf = leafc;
-    A.cf.inner = innerc;
-    A.cf.tc = tc;
-    A.cf.nlb = D.nlb;
-    A.cf.iscale = iscale(l);
-    A.RHO = RHO;
-    A.Y = Y;
-    A.W = W;
-    A.W2 = W2;
-    A.SBAR = SBAR;
-    A.YS = YS;
-    A.R = D.range[l];
-    if (part == 1) {
-      A.R.n_inner = 0;
-      A.R.inner_lo = 0;
-    }
-    A.bscale = V(h->prm.beta_mg / h->prm.alpha);
-    A.done = done;
-    A.pf = pf;
-    return A;
-  }
-  // RHO -= A^T w, w in buffer win, and the coupling of w to the coarser
-  // level's leaves; colour >= 0: the apply step of a transposed half-sweep
-  // of that colour; next >= 0: also the next half-sweep's w, into wout
-  void launch_apply(int l, int colour, V *win, int next = -1, V *wout = nullptr) const {
-    auto A = args(l, 0);
-    A.W = win;
-    A.W2 = wout ? wout : win;
-    uint32_t nc = l > h->lc ? h->couple_n[size_t(l - 1)] : 0;
-    if (nc) {
-      // the apply step and the coupling in one launch
-      auto C = args(l - 1, 1);
-      C.W = win;
-      const uint32_t *list = (const uint32_t *)h->couple.p + h->couple_lo[size_t(l - 1)];
-      unsigned ga = stencil_grid_T<V>(A.R.n());
-      dim3 g(ga + grid_for(nc));
-      if (h->stream_lv[size_t(l)])
-        hipLaunchKernelGGL((k_T_apply_couple<V, CL, CI, kCpolStream>), g, dim3(kBlock), 0, s, A,
-                           colour, next, C, list, nc, ga);
-      else
-        hipLaunchKernelGGL((k_T_apply_couple<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour,
-                           next, C, list, nc, ga);
-      return;
-    }
-    if (h->stream_lv[size_t(l)])
-      hipLaunchKernelGGL((k_T_apply<V, CL, CI, kCpolStream>), dim3(stencil_grid_T<V>(A.R.n())),
-                         dim3(kBlock), 0, s, A, colour, next);
-    else
-      hipLaunchKernelGGL((k_T_apply<V, CL, CI>), dim3(stencil_grid_T<V>(A.R.n())), dim3(kBlock),
-                         0, s, A, colour, next);
-  }
-  // Transpose of smooth(l, (c0, 1 - c0), nu): 2 nu half-sweeps with the
-  // colours in reversed order.  Each apply step also forms the w of the
-  // half-sweep after it, alternating between W2 and W: the first w is in
-  // W2 and the last in W (2 nu - 1 is odd).  w_ready: the caller's last
-  // apply already put the first w in W2.
-  void smooth_T(int l, int first, int nu, bool w_ready = false) const {
-    auto A = args(l, 0);
-    if (A.R.n() == 0 || nu == 0) return;
-    if (!w_ready) {
-      A.W = W2;
-      if (h->stream_lv[size_t(l)])
-        hipLaunchKernelGGL((k_T_sweep_w<V, CL, CI, kCpolStream>), dim3(stencil_grid_T<V>(A.R.n())),
-                           dim3(kBlock), 0, s, A, first);
-      else
-        hipLaunchKernelGGL((k_T_sweep_w<V, CL, CI>), dim3(stencil_grid_T<V>(A.R.n())),
-                           dim3(kBlock), 0, s, A, first);
-    }
-    V *buf[2] = {W2, W};
+  bool stream(int l) const { return h->stream_lv[size_t(l)]; }
+  // nu iterations of transposed smoothing, colours (first, 1 - first) each;
+  // zero: from a zero iterate, which the first half-sweep also writes
+  void smooth(int l, int first, int nu, bool zero) const {
+    auto A = args(l);
+    if (A.R.n() == 0) return;
+    dim3 g(stencil_grid<V>(A.R.n()));
     for (int k = 0; k < 2 * nu; ++k) {
       int colour = (k & 1) ? 1 - first : first;
-      int next = k + 1 < 2 * nu ? 1 - colour : -1;
-      launch_apply(l, colour, buf[k & 1], next, buf[(k & 1) ^ 1]);
+      if (zero && k == 0) {
+        if (stream(l))
+          hipLaunchKernelGGL((k_T_zero<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, colour);
+        else
+          hipLaunchKernelGGL((k_T_zero<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour);
+      } else if (stream(l)) {
+        hipLaunchKernelGGL((k_smooth<V, CL, CI, kCpolLevel, 0, true>), g, dim3(kBlock), 0, s, A,
+                           colour);
+      } else {
+        hipLaunchKernelGGL((k_smooth<V, CL, CI, kCpolDefault, 0, true>), g, dim3(kBlock), 0, s,
+                           A, colour);
+      }
     }
   }
-  void fas_T(int l) const {
+  // first: the first visit of level l in this cycle (its iterate is zero)
+  void fas(int l, bool first) const {
     const mfmg_mg_params &p = h->prm;
+    auto A = args(l);
     if (l == h->lc) {
-      auto A = args(l, 0);
       int threads = int(std::min<int64_t>(16, A.R.n())) * kWave;
-      hipLaunchKernelGGL((k_T_coarsest<V, CL, CI>), dim3(1), dim3(threads), 0, s, A,
-                         p.nu_coarse);
+      hipLaunchKernelGGL((k_coarsest<V, CL, CI>), dim3(1), dim3(threads), 0, s, A, p.nu_coarse,
+                         p.nu_coarse - p.nu_coarse / 2);
       return;
     }
-    smooth_T(l, 0, p.nu_post);  // forward post-smoothing is (B,R)^nu
-    auto A = args(l, 0);
-    hipLaunchKernelGGL((k_T_restrict<V, CL, CI>), dim3(grid_for(A.R.n())), dim3(kBlock), 0, s,
-                       A);
-    for (int k = 0; k < p.mu; ++k) fas_T(l - 1);
-    auto C = args(l - 1, 0);
-    hipLaunchKernelGGL((k_T_coarse<V, CL, CI>), dim3(grid_for(C.R.n())), dim3(kBlock), 0, s, C);
-    hipLaunchKernelGGL((k_T_fas<V, CL, CI>), dim3(stencil_grid_T<V>(C.R.n())), dim3(kBlock), 0,
-                       s, C);
-    hipLaunchKernelGGL((k_T_prolong<V, CL, CI>), dim3(grid_for(A.R.n())), dim3(kBlock), 0, s,
-                       A);
-    // forward pre-smoothing is (R,B)^nu; its transpose starts with colour 1
-    if (p.nu_pre > 0) {
-      launch_apply(l, -1, W, 1, W2);
-      smooth_T(l, 1, p.nu_pre, true);
+    smooth(l, 0, p.nu_post, first);  // forward post-smoothing is (B,R)^nu
+    uint32_t nc = h->couple_n[size_t(l - 1)];
+    unsigned gr = stencil_grid<V>(A.R.n());
+    dim3 g(gr + (nc ? grid_for(nc) : 0));
+    const uint32_t *list = (const uint32_t *)h->couple.p + h->couple_lo[size_t(l - 1)];
+    if (stream(l))
+      hipLaunchKernelGGL((k_T_restrict<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, Cpl,
+                         int(first), list, nc, gr);
+    else
+      hipLaunchKernelGGL((k_T_restrict<V, CL, CI>), g, dim3(kBlock), 0, s, A, Cpl, int(first),
+                         list, nc, gr);
+    auto C = args(l - 1);
+    if (!first && C.R.n_leaf && C.R.n_inner)
+      hipLaunchKernelGGL((k_T_revisit<V, CL, CI>), dim3(stencil_grid<V>(C.R.n_inner)),
+                         dim3(kBlock), 0, s, C);
+    V pscale = V(p.beta_mg / p.alpha);
+    if (l - 1 == h->lc + 1 && h->fuse_bottom_T) {
+      auto Cc = args(h->lc);
+      int half = p.nu_coarse - p.nu_coarse / 2;
+      if constexpr (sizeof(V) == 4)
+        hipLaunchKernelGGL((k_bottom<V, CL, CI, true, true>), dim3(1), dim3(1024), 0, s, C, Cc,
+                           p.nu_post, p.nu_pre, p.nu_coarse, half, p.mu, int(first), p.mu, V(1),
+                           pscale);
+      else
+        for (int k = 0; k < p.mu; ++k)
+          hipLaunchKernelGGL((k_bottom<V, CL, CI, false, true>), dim3(1), dim3(1024), 0, s, C,
+                             Cc, p.nu_post, p.nu_pre, p.nu_coarse, half, p.mu,
+                             int(first && k == 0), 1, V(1), pscale);
     } else {
-      launch_apply(l, -1, W);
+      for (int k = 0; k < p.mu; ++k) fas(l - 1, first && k == 0);
     }
+    hipLaunchKernelGGL((k_T_prolong<V, CL, CI>), gr, dim3(kBlock), 0, s, A, pscale);
+    smooth(l, 1, p.nu_pre, false);  // forward pre-smoothing is (R,B)^nu
   }
-  // input: an FP64 leaf vector in device order, multiplied by *scale on
-  // loading (scale may be null)
-  void run(const double *in, const double *scale) const {
-    const DeviceTopology &D = *h->co->dt;
-    int64_t nb64 = int64_t(D.nb) * 64, N = int64_t(D.nlb) * 64;
-    hipLaunchKernelGGL((k_fill<V>), dim3(grid_elems(nb64, 256)), dim3(256), 0, s, Y, nb64, V(0));
-    hipLaunchKernelGGL((k_fill<V>), dim3(grid_elems(nb64 - N, 256)), dim3(256), 0, s, RHO + N,
-                       nb64 - N, V(0));
-    hipLaunchKernelGGL((k_T_load<V>), dim3(grid_elems(N, 256)), dim3(256), 0, s, in, RHO, N,
-                       scale);
-    fas_T(h->L);
+  void zero_leaves(int l) const {
+    const Range &R = h->co->dt->range[size_t(l)];
+    int64_t n = int64_t(R.n_leaf) * 64;
+    if (n)
+      hipLaunchKernelGGL((k_fill<V>), dim3(grid_elems(n, 256)), dim3(256), 0, s,
+                         Y + int64_t(R.leaf_lo) * 64, n, V(0));
+  }
+  void run() const {
+    // the iterates start from zero: a level's first half-sweep and the
+    // restriction onto inner bricks write theirs, the coarsest level's
+    // leaves (and every leaf when there is no first half-sweep) are cleared
+    if (h->prm.nu_post == 0)
+      for (int l = h->lc; l <= h->L; ++l) zero_leaves(l);
+    else
+      zero_leaves(h->lc);
+    fas(h->L, true);
   }
 };
 
 template <class V>
-void alloc_transpose(const mfmg_hierarchy *hc, DevBuf<V> (&T)[6]) {
+void alloc_transpose(const mfmg_hierarchy *hc, DevBuf<V> (&T)[4]) {
   if (T[0].p) return;
   int64_t nb = hc->co->dt->nb, nlb = hc->co->dt->nlb;
-  for (int i = 0; i < 3; ++i) T[i].alloc(size_t(nb) * 64);
-  for (int i = 3; i < 5; ++i) T[i].alloc(size_t(nb - nlb) * 64 + 1);
-  T[5].alloc(size_t(nb) * 64);
+  T[1].alloc(size_t(nb) * 64);
+  T[2].alloc(size_t(nb - nlb) * 64 + 1);
+  if (hc->prm.mu > 1) T[3].alloc(size_t(nlb) * 64);
+  T[0].alloc(size_t(nb) * 64);
 }
 
 // The leaf bricks whose coarse cells take the transposed T-junction coupling
@@ -1432,26 +1391,24 @@ static void ensure_coupling_lists(mfmg_hierarchy *h, hipStream_t s) {
   HIP_CHECK(hipStreamSynchronize(s));  // work is freed on return
 }
 
-// z = M^T r: r, z FP64 leaf vectors in device order; returns the z buffer
-// (the Y leaf part, of the cycle's value type).  In mixed precision the
-// solve passes its scalars' residual scale (scale), so z is M^T (scale r).
-void run_cycle_T(mfmg_hierarchy *h, const double *r, hipStream_t s,
-                 const int *done = nullptr, const double *scale = nullptr) {
+// The transposed cycle's arrays and lists, made at first use.
+void ensure_transpose(mfmg_hierarchy *h, hipStream_t s) {
   ensure_coupling_lists(h, s);
+  if (h->prm.precision == MFMG_MIXED) alloc_transpose(h, h->T32);
+  else alloc_transpose(h, h->T64);
+}
+
+// Y = M^T G on the leaves (after ensure_transpose)
+void run_cycle_T(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
   if (h->prm.precision == MFMG_MIXED) {
-    alloc_transpose(h, h->T32);
-    CycleT<float, float, __half> c{h, h->coef32.p, h->coef16.p, h->tc32.p, h->pf32.p,
-                                   h->T32[0].p, h->T32[1].p, h->T32[2].p, h->T32[3].p,
-                                   h->T32[4].p, h->T32[5].p, s, done};
-    c.run(r, scale);
+    CycleT<float, float, __half> c{h, h->coef32.p, h->coef16.p, h->pf32.p,
+                                   h->T32[0].p, h->T32[1].p, h->T32[2].p, h->T32[3].p, done, s};
+    c.run();
   } else {
-    alloc_transpose(h, h->T64);
     CycleT<double, double, double> c{h, h->coef64.p,
-                                     h->coef64.p + int64_t(h->co->dt->nlb) * 256,
-                                     h->co->tc.p, h->pf64.p, h->T64[0].p, h->T64[1].p,
-                                     h->T64[2].p, h->T64[3].p, h->T64[4].p, h->T64[5].p, s,
-                                     done};
-    c.run(r, nullptr);
+                                     h->coef64.p + int64_t(h->co->dt->nlb) * 256, h->pf64.p,
+                                     h->T64[0].p, h->T64[1].p, h->T64[2].p, h->T64[3].p, done, s};
+    c.run();
   }
 }
 
@@ -1507,15 +1464,20 @@ extern "C" mfmg_status mfmg_apply_precond(mfmg_hierarchy *h, const double *r, do
   try {
     PcgArgs P = pcg_args(h);
     if (transpose) {
-      if (!h->rA.p) h->rA.alloc(size_t(h->co->dt->nlb) * 64);
-      hipLaunchKernelGGL(k_from_canonical<double>, dim3(G), dim3(kBlock), 0, s, P, r, h->rA.p);
-      run_cycle_T(h, h->rA.p, s);
+      ensure_transpose(h, s);
+      if (h->prm.precision == MFMG_MIXED)
+        hipLaunchKernelGGL(k_from_canonical<float>, dim3(G), dim3(kBlock), 0, s, P, r,
+                           h->T32[1].p);
+      else
+        hipLaunchKernelGGL(k_from_canonical<double>, dim3(G), dim3(kBlock), 0, s, P, r,
+                           h->T64[1].p);
+      run_cycle_T(h, s, nullptr);
       if (h->prm.precision == MFMG_MIXED)
         hipLaunchKernelGGL(k_to_canonical<float>, dim3(G), dim3(kBlock), 0, s, P,
-                           (const float *)h->T32[1].p, z);
+                           (const float *)h->T32[0].p, z);
       else
         hipLaunchKernelGGL(k_to_canonical<double>, dim3(G), dim3(kBlock), 0, s, P,
-                           (const double *)h->T64[1].p, z);
+                           (const double *)h->T64[0].p, z);
     } else if (h->prm.precision == MFMG_MIXED) {
       hipLaunchKernelGGL(k_from_canonical<float>, dim3(G), dim3(kBlock), 0, s, P, r, h->B32.p);
       run_cycle(h, s, nullptr);
@@ -1674,16 +1636,23 @@ struct Krylov {
   }
 };
 
-// Loop body of Algorithm 1 (from A p to the next search direction).
+// The preconditioner on the residual copy r_low, or its transpose.
+static void run_precond(const mfmg_hierarchy *h, bool trans, hipStream_t s) {
+  if (trans) run_cycle_T(h, s, &h->S.p->done);
+  else run_cycle(h, s, &h->S.p->done);
+}
+
+// Loop body of Algorithm 1 (from A p to the next search direction), or of
+// the adjoint's with A^T and M^T.
 template <class V>
 static void iteration_body(mfmg_hierarchy *h, double *r, V *r_low, V *z, bool null_space,
-                           hipStream_t s) {
+                           bool trans, hipStream_t s) {
   Reduce R(h, s);
   Krylov<V> K(h, s);
-  K.Ap(false);
+  K.Ap(trans);
   K.update(r, r_low, int(null_space));
   if (null_space) R.shift_mean<V>(r, r_low, std::max(1.0, h->n_active), 1, 0.0);
-  run_cycle(h, s, &h->S.p->done);
+  run_precond(h, trans, s);
   K.rz(r, z, 0);
   K.pupdate(z, 0);
 }
@@ -1705,14 +1674,14 @@ inline bool graphs_enabled() {
 // memset or copy.  Captured on a private stream, launched on the caller's.
 template <class V>
 static hipGraphExec_t iteration_graph(mfmg_hierarchy *h, double *r, V *r_low, V *z,
-                                      bool null_space) {
-  hipGraphExec_t &ge = h->iter_graph[null_space ? 1 : 0];
+                                      bool null_space, bool trans) {
+  hipGraphExec_t &ge = h->iter_graph[trans ? 1 : 0][null_space ? 1 : 0];
   if (ge) return ge;
   if (!h->cap_stream) HIP_CHECK(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
   HIP_CHECK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
   hipGraph_t g = nullptr;
   try {
-    iteration_body<V>(h, r, r_low, z, null_space, h->cap_stream);
+    iteration_body<V>(h, r, r_low, z, null_space, trans, h->cap_stream);
   } catch (...) {
     (void)hipStreamEndCapture(h->cap_stream, &g);
     if (g) (void)hipGraphDestroy(g);
@@ -1751,12 +1720,12 @@ static bool restart_wanted(const Scalars &S, int max_iter, double prev_tr) {
 // seen or n have been queued.
 template <class V>
 static void run_iterations(mfmg_hierarchy *h, double *r, V *r_low, V *z, bool null_space,
-                           int n, hipGraphExec_t body, hipStream_t s) {
+                           bool trans, int n, hipGraphExec_t body, hipStream_t s) {
   for (int it = 0; it < n; ++it) {
     if (body)
       HIP_CHECK(hipGraphLaunch(body, s));
     else
-      iteration_body<V>(h, r, r_low, z, null_space, s);
+      iteration_body<V>(h, r, r_low, z, null_space, trans, s);
     // The stop flag of iteration it is read on the host only after
     // iteration it + 1 is queued, so the GPU never idles on the round trip;
     // every kernel of an iteration queued after the stop returns at once.
@@ -1798,12 +1767,12 @@ static void pcg_iterate(mfmg_hierarchy *h, const double *rhs, double *r, V *r_lo
   K.rz(r, z, 1);
   K.pupdate(z, 1);
   hipGraphExec_t body = graphs_enabled() && sp->max_iter > 0
-                           ? iteration_graph<V>(h, r, r_low, z, null_space)
+                           ? iteration_graph<V>(h, r, r_low, z, null_space, false)
                            : nullptr;
   double prev_tr = INFINITY;
   int left = sp->max_iter;
   for (;;) {
-    run_iterations<V>(h, r, r_low, z, null_space, left, body, s);
+    run_iterations<V>(h, r, r_low, z, null_space, false, left, body, s);
     K.finish_x();
     // zero-mean solution, then the true residual (shifted to zero mean)
     if (null_space) R.shift_mean<double>(x, (double *)nullptr, na, 3, 0.0);
@@ -1905,40 +1874,29 @@ extern "C" mfmg_status mfmg_pcg_solve(mfmg_hierarchy *h, const double *rhs, doub
 // solve.  On return Xf holds the true residual g - A^T lambda in device
 // order (shifted to zero mean with the null space) and S->tr its norm.
 template <class V>
-static void pcg_adjoint_iterate(mfmg_hierarchy *h, const double *g, V *z,
+static void pcg_adjoint_iterate(mfmg_hierarchy *h, const double *g, V *r_low, V *z,
                                 const mfmg_solve_params *sp, bool null_space, hipStream_t s) {
   PcgArgs P = pcg_args(h);
   unsigned G = grid_reduce(h->co->dt->nlb);
   Reduce R(h, s);
   double na = std::max(1.0, h->n_active);
   double *x = h->x.p, *r = h->rA.p;
-  const int *done = &h->S.p->done;
-  const double *scale = &h->S.p->rscale;  // 1 in FP64
   __atomic_store_n(h->host_done, 0, __ATOMIC_RELEASE);  // the stream is idle here
   R.init<V>(g, r, (V *)nullptr, x, sp->rtol);
   if (null_space) R.shift_mean<V>(r, (V *)nullptr, na, 0, sp->rtol);
+  // the cycle's input (it changes its right-hand side, so FP64 keeps a copy too)
+  hipLaunchKernelGGL(k_scale_low<V>, dim3(G), dim3(kBlock), 0, s, P, r, r_low);
   Krylov<V> K(h, s);
-  run_cycle_T(h, r, s, done, scale);
+  run_precond(h, true, s);
   K.rz(r, z, 1);
   K.pupdate(z, 1);
+  hipGraphExec_t body = graphs_enabled() && sp->max_iter > 0
+                           ? iteration_graph<V>(h, r, r_low, z, null_space, true)
+                           : nullptr;
   double prev_tr = INFINITY;
   int left = sp->max_iter;
   for (;;) {
-    for (int it = 0; it < left; ++it) {
-      K.Ap(true);
-      K.update(r, (V *)nullptr, int(null_space));
-      if (null_space) R.shift_mean<V>(r, (V *)nullptr, na, 1, sp->rtol);
-      run_cycle_T(h, r, s, done, scale);
-      K.rz(r, z, 0);
-      K.pupdate(z, 0);
-      // stop flag of iteration it read after iteration it + 1 is queued (as in
-      // the forward solve); kernels queued after the stop return at once
-      HIP_CHECK(hipEventRecord(h->iter_ev[it & 1], s));
-      if (it > 0) {
-        HIP_CHECK(hipEventSynchronize(h->iter_ev[(it - 1) & 1]));
-        if (__atomic_load_n(h->host_done, __ATOMIC_ACQUIRE)) break;
-      }
-    }
+    run_iterations<V>(h, r, r_low, z, null_space, true, left, body, s);
     K.finish_x();
     if (null_space) R.shift_mean<double>(x, (double *)nullptr, na, 3, 0.0);
     // true residual g - A^T lambda (into Xf) and its norm
@@ -1957,7 +1915,8 @@ static void pcg_adjoint_iterate(mfmg_hierarchy *h, const double *g, V *z,
     left = sp->max_iter - S.iters;
     hipLaunchKernelGGL(k_restart, dim3(G), dim3(kBlock), 0, s, P, (const double *)h->Xf.p, r);
     R.finish(G, kFinRestart);
-    run_cycle_T(h, r, s, done, scale);
+    hipLaunchKernelGGL(k_scale_low<V>, dim3(G), dim3(kBlock), 0, s, P, r, r_low);
+    run_precond(h, true, s);
     K.rz(r, z, 1);
     K.pupdate(z, 1);
   }
@@ -1990,18 +1949,16 @@ extern "C" mfmg_status mfmg_pcg_solve_adjoint(mfmg_hierarchy *h, const double *p
                   "no Dirichlet face and the null-space shift is off, but dL/dp does not "
                   "sum to zero over the active cells");
     if (!h->rA.p) h->rA.alloc(size_t(D.nlb) * 64);
+    ensure_transpose(h, s);
     ensure_face_list(h, s);
     hipEvent_t e0, e1;
     HIP_CHECK(hipEventCreate(&e0));
     HIP_CHECK(hipEventCreate(&e1));
     HIP_CHECK(hipEventRecord(e0, s));
-    if (h->prm.precision == MFMG_MIXED) {
-      alloc_transpose(h, h->T32);
-      pcg_adjoint_iterate<float>(h, dL_dp, h->T32[1].p, sp, ns, s);
-    } else {
-      alloc_transpose(h, h->T64);
-      pcg_adjoint_iterate<double>(h, dL_dp, h->T64[1].p, sp, ns, s);
-    }
+    if (h->prm.precision == MFMG_MIXED)
+      pcg_adjoint_iterate<float>(h, dL_dp, h->T32[1].p, h->T32[0].p, sp, ns, s);
+    else
+      pcg_adjoint_iterate<double>(h, dL_dp, h->T64[1].p, h->T64[0].p, sp, ns, s);
     PcgArgs P = pcg_args(h);
     unsigned G = grid_for(D.nlb);
     hipLaunchKernelGGL(k_to_canonical<double>, dim3(G), dim3(kBlock), 0, s, P,
