@@ -82,6 +82,18 @@ __device__ __forceinline__ ParentNbrs load_parent_nbrs(const ParentNbrs *pnb, ui
 #endif
 }
 
+// The eight child bricks of an inner brick.
+struct alignas(32) Children {
+  int32_t id[8];
+};
+__device__ __forceinline__ Children load_children(const int32_t *child, uint32_t b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return ((const __attribute__((address_space(4))) Children *)child)[b];
+#else
+  return ((const Children *)child)[b];  // host pass: never executed
+#endif
+}
+
 __device__ __forceinline__ uint32_t wave_id() {
   return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 }
@@ -1639,47 +1651,71 @@ __global__ void __launch_bounds__(kBlock) k_T_zero(LevelArgs<V, CL, CI> A, int c
   }
 }
 
-// Sum over the four fine cells across face d of the lane's cell (in a leaf
-// brick whose neighbour nb across d is an inner brick) of (k_f / 2) x_f, k_f
-// the fine cell's T-face coefficient: the coarse leaf's row of the
-// transposed T-junction coupling; 0 on lanes away from the face.  The 8 x 8
-// fine cells on the face are one per lane -- lane 4 j + s holds sub-cell s
-// of the coarse face cell with interleaved in-plane index j -- so the face
-// takes two loads, two exchange steps add each cell's four and one hands it
-// to the face's lane.
+// On a leaf brick with inner same-level neighbours (record M): the sum over
+// the fine cells next to the lane's cell, across all its faces to finer
+// leaves, of (k_f / 2) x_f, k_f the fine cell's T-face coefficient -- the
+// coarse leaf's row of the transposed T-junction coupling.  The 8 x 8 fine
+// cells on a face are one per lane -- lane 4 j + s holds sub-cell s of the
+// coarse face cell with interleaved in-plane index j -- so a face takes two
+// loads, two exchange steps add each cell's four and one hands the sum to the
+// face's lane.  Every face's child ids, then every face's values are
+// requested before any is used.
 template <class V, class CL>
 __device__ __forceinline__ V face_children_sum(__amdgpu_buffer_rsrc_t x,
                                                __amdgpu_buffer_rsrc_t cl,
                                                __amdgpu_buffer_rsrc_t pf, const int32_t *child,
-                                               int32_t nb, int d, int m) {
-  const int a = d >> 1;
-  const int o0 = a == 0 ? 1 : 0;
-  const int o1 = a == 2 ? 1 : 2;
+                                               const BrickMeta &M, int m) {
   const int j = m >> 2;
   const int cu = (j & 1) | ((j >> 1) & 2);
   const int cv = ((j >> 1) & 1) | ((j >> 2) & 2);
-  const int32_t *ch = child + 8 * int64_t(nb) + ((d & 1) ? 0 : (1 << a));
-  const int32_t c0 = ch[0], c1 = ch[1 << o0], c2 = ch[1 << o1], c3 = ch[(1 << o0) | (1 << o1)];
-  const uint32_t cb = uint32_t(cv & 2 ? (cu & 2 ? c3 : c2) : (cu & 2 ? c1 : c0));
   const int fu = ((cu & 1) << 1) | (m & 1);
   const int fv = ((cv & 1) << 1) | ((m >> 1) & 1);
-  int xyz[3];
-  xyz[a] = (d & 1) ? 0 : 3;
-  xyz[o0] = fu;
-  xyz[o1] = fv;
-  const uint32_t q = uint32_t(dev_morton(xyz[0], xyz[1], xyz[2]));
-  V k;
-  if (d & 1)  // the fine cells' own minus-face coefficients
-    k = V(bload<CL>(cl, cb * 256u + uint32_t(1 + a) * 64u + q, 0u));
-  else        // their plus-face entries
-    k = V(bload<CL>(pf, cb * 48u + uint32_t(a * 16 + fu + 4 * fv), 0u));
-  V s = k * V(0.5) * bload<V>(x, cb * 64u + q, 0u);
-  s = s + shfl_xor(s, 1);
-  s = s + shfl_xor(s, 2);
-  const int mu = dev_coord(m, o0), mv = dev_coord(m, o1);
-  const int jm = (mu & 1) | ((mv & 1) << 1) | ((mu & 2) << 1) | ((mv & 2) << 2);
-  V r = shfl(s, 4 * jm);
-  return dev_outside(m, d) ? r : V(0);
+  uint32_t cb[6];
+#pragma unroll
+  for (int d = 0; d < 6; ++d) {
+    cb[d] = 0u;
+    if ((M.flags >> (8 + d)) & 1u) {
+      const int a = d >> 1, o0 = a == 0 ? 1 : 0, o1 = a == 2 ? 1 : 2;
+      const Children C = load_children(child, uint32_t(M.nbr[d]));
+      const int c = (d & 1) ? 0 : (1 << a);
+      cb[d] = uint32_t((cv & 2) ? ((cu & 2) ? C.id[c | (1 << o0) | (1 << o1)] : C.id[c | (1 << o1)])
+                                : ((cu & 2) ? C.id[c | (1 << o0)] : C.id[c]));
+    }
+  }
+  V v[6], k[6];
+#pragma unroll
+  for (int d = 0; d < 6; ++d) {
+    v[d] = V(0);
+    k[d] = V(0);
+    if ((M.flags >> (8 + d)) & 1u) {
+      const int a = d >> 1, o0 = a == 0 ? 1 : 0, o1 = a == 2 ? 1 : 2;
+      int xyz[3];
+      xyz[a] = (d & 1) ? 0 : 3;
+      xyz[o0] = fu;
+      xyz[o1] = fv;
+      const uint32_t q = uint32_t(dev_morton(xyz[0], xyz[1], xyz[2]));
+      v[d] = bload<V>(x, cb[d] * 64u + q, 0u);
+      if (d & 1)  // the fine cells' own minus-face coefficients
+        k[d] = V(bload<CL>(cl, cb[d] * 256u + uint32_t(1 + a) * 64u + q, 0u));
+      else        // their plus-face entries
+        k[d] = V(bload<CL>(pf, cb[d] * 48u + uint32_t(a * 16 + fu + 4 * fv), 0u));
+    }
+  }
+  V acc = V(0);
+#pragma unroll
+  for (int d = 0; d < 6; ++d) {
+    if ((M.flags >> (8 + d)) & 1u) {
+      const int a = d >> 1, o0 = a == 0 ? 1 : 0, o1 = a == 2 ? 1 : 2;
+      V s = k[d] * V(0.5) * v[d];
+      s = s + shfl_xor(s, 1);
+      s = s + shfl_xor(s, 2);
+      const int mu = dev_coord(m, o0), mv = dev_coord(m, o1);
+      const int jm = (mu & 1) | ((mv & 1) << 1) | ((mu & 2) << 1) | ((mv & 2) << 2);
+      const V r = shfl(s, 4 * jm);
+      acc += dev_outside(m, d) ? r : V(0);
+    }
+  }
+  return acc;
 }
 
 // Coupling of level l to the coarser leaves, transposed: a leaf brick b of
@@ -1691,13 +1727,9 @@ __device__ __forceinline__ void coupling_brick(const LevelView<V, CL, CI, CP> &X
                                                const int32_t *child, V *prev, int first,
                                                uint32_t b, int m) {
   const BrickMeta M = load_meta(X.meta, b);
-  V acc = V(0);
-#pragma unroll
-  for (int d = 0; d < 6; ++d)
-    if ((M.flags >> (8 + d)) & 1u)
-      acc += face_children_sum<V, CL>(X.u, X.cl, X.pf, child, M.nbr[d], d, m);
-  if (!((act_mask(M) >> m) & 1ull)) acc = V(0);
   V g = bload<V>(X.b, uint32_t(m), b * 64u);
+  V acc = face_children_sum<V, CL>(X.u, X.cl, X.pf, child, M, m);
+  if (!((act_mask(M) >> m) & 1ull)) acc = V(0);
   if (prev) {
     V was = first ? V(0) : prev[b * 64u + uint32_t(m)];
     prev[b * 64u + uint32_t(m)] = acc;

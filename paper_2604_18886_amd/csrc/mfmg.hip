@@ -218,6 +218,7 @@ struct mfmg_hierarchy {
   DevBuf<double> T64[4];
   // leaf bricks with an inner neighbour (level-major), per level [lo, lo + n)
   DevBuf<uint32_t> couple;
+  DevBuf<double> fc;  // their fine neighbours' sums (composite_row_T), 96 per inner brick
   std::vector<uint32_t> couple_lo, couple_n;
   DevBuf<float> T32[4];
   DevBuf<double> rA;              // adjoint PCG residual
@@ -900,8 +901,9 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     h->pd.alloc(size_t(nb) * 64);
     h->Xf.alloc(size_t(nb) * 64);
     h->Ap.alloc(size_t(N));
-    h->partials.alloc(std::max<int64_t>({kMaxReduceBlocks, int64_t(grid_for(nlb)) + 8,
-                                         int64_t(level_grid(nlb))}));
+    // (the adjoint's operator stores those of its coupling launch after its own)
+    h->partials.alloc(std::max<int64_t>(kMaxReduceBlocks,
+                                        int64_t(level_grid(nlb)) + kMaxReduceBlocks));
     h->S.alloc(1);
     HIP_CHECK(hipMemsetAsync(h->S.p, 0, sizeof(Scalars), s));
     HIP_CHECK(hipHostMalloc(&h->hostS, sizeof(Scalars), hipHostMallocDefault));
@@ -1377,6 +1379,7 @@ static void ensure_coupling_lists(mfmg_hierarchy *h, hipStream_t s) {
   HIP_CHECK(hipMemcpyAsync(pos.data() + nlb, total.p, sizeof(int64_t), hipMemcpyDeviceToHost, s));
   HIP_CHECK(hipStreamSynchronize(s));
   h->couple.alloc(std::max<size_t>(size_t(pos[nlb]), 1));
+  h->fc.alloc(size_t(D.nb - nlb) * 96 + 1);
   hipLaunchKernelGGL(k_couple_list, dim3(grid_elems(nlb, 256)), dim3(256), 0, s,
                      (const BrickMeta *)D.meta.p, nlb, (const int64_t *)work.p, h->couple.p);
   HIP_CHECK(hipGetLastError());
@@ -1416,7 +1419,6 @@ PcgArgs pcg_args(mfmg_hierarchy *h) {
   PcgArgs P;
   P.T = make_topo(*h->co->dt, h->meta.p);
   P.C = h->coef64.p;
-  P.TC = h->co->tc.p;
   P.PF = h->pf64.p;
   P.canon = h->co->dt->canon.p;
   P.S = h->S.p;
@@ -1429,6 +1431,8 @@ PcgArgs pcg_args(mfmg_hierarchy *h) {
 
 }  // namespace
 
+static void apply_T(mfmg_hierarchy *h, PcgArgs P, const double *X, double *y, hipStream_t s);
+
 // --------------------------------------------------------------------------
 // component entry points
 // --------------------------------------------------------------------------
@@ -1440,10 +1444,10 @@ extern "C" mfmg_status mfmg_apply_operator(mfmg_hierarchy *h, const double *x, d
   try {
     PcgArgs P = pcg_args(h);
     hipLaunchKernelGGL(k_full, dim3(G), dim3(kBlock), 0, s, P, x, h->Xf.p, 1);
-    if (transpose)
-      hipLaunchKernelGGL(k_applyT, dim3(G), dim3(kBlock), 0, s, P, (const double *)h->Xf.p,
-                         h->Ap.p);
-    else
+    if (transpose) {
+      ensure_coupling_lists(h, s);
+      apply_T(h, P, (const double *)h->Xf.p, h->Ap.p, s);
+    } else
       hipLaunchKernelGGL(k_apply, dim3(level_grid(h->co->dt->nlb)), dim3(kBlock), 0, s, P,
                          (const double *)h->Xf.p, h->Ap.p);
     hipLaunchKernelGGL(k_to_canonical<double>, dim3(G), dim3(kBlock), 0, s, P,
@@ -1582,6 +1586,26 @@ static bool incompatible_rhs(mfmg_hierarchy *h, const double *rhs, hipStream_t s
   return std::fabs(sum) > 1e-10 * mag;
 }
 
+// y += the coarse leaves' coupling rows of A^T X, after the kernel that wrote
+// the other rows; returns the number of partial sums stored from slot `base`.
+static unsigned couple_T(mfmg_hierarchy *h, const PcgArgs &P, const double *X, double *y,
+                         unsigned base, const int *done, hipStream_t s) {
+  uint32_t n = 0;
+  for (uint32_t c : h->couple_n) n += c;
+  if (n == 0) return 0;
+  unsigned g = grid_reduce(n);
+  hipLaunchKernelGGL(k_couple_T, dim3(g), dim3(kBlock), 0, s, P, (const uint32_t *)h->couple.p, n,
+                     X, y, (const double *)h->fc.p, base, done);
+  return g;
+}
+// y = A^T X on the leaves (X full size)
+static void apply_T(mfmg_hierarchy *h, PcgArgs P, const double *X, double *y, hipStream_t s) {
+  hipLaunchKernelGGL(k_applyT, dim3(level_grid(h->co->dt->nlb)), dim3(kBlock), 0, s, P, X, y,
+                     h->fc.p);
+  P.partials = nullptr;
+  couple_T(h, P, X, y, 0, nullptr, s);
+}
+
 // Launch helpers of one Krylov iteration (Algorithm 1).
 template <class V>
 struct Krylov {
@@ -1589,14 +1613,12 @@ struct Krylov {
   PcgArgs P;
   hipStream_t s;
   unsigned G;   // grid of the flat vector kernels
-  unsigned GB;  // one wave per leaf brick (transposed operator)
-  unsigned GA;  // wave_loop grid of the forward operator
+  unsigned GA;  // wave_loop grid of the operator
   int64_t n2;   // leaf entries / 2
 
   Krylov(mfmg_hierarchy *h_, hipStream_t s_) : h(h_), s(s_) {
     P = pcg_args(h);
     G = grid_reduce(h->co->dt->nlb);
-    GB = grid_for(h->co->dt->nlb);
     GA = level_grid(h->co->dt->nlb);
     n2 = int64_t(h->co->dt->nlb) * 32;
   }
@@ -1609,17 +1631,22 @@ struct Krylov {
     hipLaunchKernelGGL(k_pcg_p<V>, dim3(GA), dim3(kBlock), 0, s, P, z, h->pd.p, h->x.p, first);
   }
   void Ap(bool trans) const {
-    if (trans)
-      hipLaunchKernelGGL(k_pcg_ApT, dim3(GB), dim3(kBlock), 0, s, P, (const double *)h->pd.p,
-                         h->Ap.p);
+    unsigned n = GA;
+    if (trans && h->stream_composite)
+      hipLaunchKernelGGL(k_pcg_ApT<kCpolStream>, dim3(GA), dim3(kBlock), 0, s, P,
+                         (const double *)h->pd.p, h->Ap.p, h->fc.p);
+    else if (trans)
+      hipLaunchKernelGGL(k_pcg_ApT<>, dim3(GA), dim3(kBlock), 0, s, P, (const double *)h->pd.p,
+                         h->Ap.p, h->fc.p);
     else if (h->stream_composite)
       hipLaunchKernelGGL(k_pcg_Ap<kCpolStream>, dim3(GA), dim3(kBlock), 0, s, P,
                          (const double *)h->pd.p, h->Ap.p);
     else
       hipLaunchKernelGGL(k_pcg_Ap<>, dim3(GA), dim3(kBlock), 0, s, P, (const double *)h->pd.p,
                          h->Ap.p);
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, P, int64_t(trans ? GB : GA),
-                       int(kFinAlpha), 0, 0.0);
+    if (trans) n += couple_T(h, P, h->pd.p, h->Ap.p, GA, &h->S.p->done, s);
+    hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, P, int64_t(n), int(kFinAlpha), 0,
+                       0.0);
   }
   void update(double *r, V *r_low, int defer) const {
     hipLaunchKernelGGL(k_pcg_update<V>, dim3(G), dim3(kBlock), 0, s, P, r, r_low,
@@ -1901,8 +1928,7 @@ static void pcg_adjoint_iterate(mfmg_hierarchy *h, const double *g, V *r_low, V 
     if (null_space) R.shift_mean<double>(x, (double *)nullptr, na, 3, 0.0);
     // true residual g - A^T lambda (into Xf) and its norm
     hipLaunchKernelGGL(k_full, dim3(G), dim3(kBlock), 0, s, P, (const double *)x, h->Xf.p, 0);
-    hipLaunchKernelGGL(k_applyT, dim3(G), dim3(kBlock), 0, s, P, (const double *)h->Xf.p,
-                       h->Ap.p);
+    apply_T(h, P, (const double *)h->Xf.p, h->Ap.p, s);
     hipLaunchKernelGGL(k_resid_T, dim3(G), dim3(kBlock), 0, s, P, g, (const double *)h->Ap.p,
                        h->Xf.p);
     R.finish(G, kFinTrue);

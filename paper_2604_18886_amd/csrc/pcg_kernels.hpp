@@ -12,7 +12,6 @@ namespace mfmg {
 struct PcgArgs {
   Topo T;
   const double *C;       // FP64 coefficients of all bricks (device order)
-  const double *TC;      // FP64 plus-side T-face coefficients
   const double *PF;      // FP64 plus-face coefficients of all bricks, 48 per brick
   const int32_t *canon;  // device leaf brick -> canonical leaf brick
   Scalars *S;
@@ -32,77 +31,6 @@ __device__ __forceinline__ double low_scale(const PcgArgs &P, double rr) {
   if (!P.scale_low || !(rr > 0.0) || !(rr < INFINITY)) return 1.0;
   int e = ilogb(rr / (64.0 * double(P.T.nlb)));
   return ldexp(1.0, -(e / 2));
-}
-
-__device__ __forceinline__ void leaf_cell(const PcgArgs &P, uint32_t b, int m, double &c,
-                                          double &k0, double &k1, double &k2) {
-  const double *cf = P.C + b * 256u;
-  c = cf[m];
-  k0 = cf[64 + m];
-  k1 = cf[128 + m];
-  k2 = cf[192 + m];
-}
-
-// Transposed composite operator (adjoint path).  Its T-junction blocks are
-// the transposes of the rank-one blocks of A: a fine cell's row gets, for
-// every active sibling, (1/n) sum over the sibling group's T-faces of
-// (k/2)(x_i - x_J); a coarse leaf's row gets - sum_f (k_f/2) x_f over the
-// fine face cells f in place of K_F times their parent's mean.  X is a
-// leaf-sized vector in device order; inner neighbours are read through
-// their children.
-__device__ __forceinline__ double composite_AuT(const Topo &T, const double *__restrict__ C,
-                                                const double *__restrict__ TC,
-                                                const double *__restrict__ X,
-                                                const BrickMeta &M, int m, double u, double c,
-                                                double k0, double k1, double k2) {
-  uint64_t amask = act_mask(M);
-  bool act = (amask >> m) & 1ull;
-  int cnt = __popcll((amask >> (m & 56)) & 0xffull);
-  double acc = c * u;
-  double tpart = 0.0;  // this cell's sum of (k/2)(x_m - x_J) over its T-faces
-  for (int d = 0; d < 6; ++d) {
-    int a = d >> 1;
-    int p = dev_partner(m, d);
-    double kown = a == 0 ? k0 : (a == 1 ? k1 : k2);
-    double v = shfl(u, p);
-    double kp = shfl(kown, p);
-    double k = (d & 1) ? kp : kown;
-    if (dev_outside(m, d)) {
-      int32_t nb = M.nbr[d];
-      if (nb >= 0 && uint32_t(nb) < T.nlb) {
-        v = X[uint32_t(nb) * 64u + p];
-        if (d & 1) k = C[uint32_t(nb) * 256u + (1 + a) * 64 + p];
-      } else if (nb >= 0) {
-        int32_t cb = T.child[8 * int64_t(nb) + (p >> 3)];
-        int32_t slot = T.meta[cb].tplus;
-        int base = (p & 7) << 3;
-        int facebit = (d & 1) ? 0 : 1;  // children on P's face toward this cell
-        double sumkv = 0.0;
-        for (int t = 0; t < 8; ++t) {
-          if (((t >> a) & 1) != facebit) continue;
-          int q = base | t;
-          double kc = (d & 1) ? C[uint32_t(cb) * 256u + (1 + a) * 64 + q]
-                              : TC[uint32_t(slot) * 48u + a * 16 + dev_face_index(q, a)];
-          sumkv += kc * 0.5 * X[uint32_t(cb) * 64u + q];
-        }
-        acc -= sumkv;
-        continue;
-      } else if (nb == dWall) {
-        v = 0.0;
-      } else {
-        int32_t J = dev_decode_coarse(nb);
-        double uJ = X[uint32_t(J) * 64u + coarse_local(M, m, d)];
-        if (d & 1) k = TC[uint32_t(M.tplus) * 48u + a * 16 + dev_face_index(m, a)];
-        acc -= k * u;
-        tpart += k * 0.5 * (u - uJ);
-        continue;
-      }
-    }
-    acc -= k * v;
-  }
-  double S = group8_sum(tpart);
-  if (act && cnt) acc += S / double(cnt);
-  return act ? acc : 0.0;
 }
 
 // Mean of the active cells of each aligned sibling group of a leaf brick
@@ -155,6 +83,73 @@ __device__ __forceinline__ double composite_row(const LevelView<double, double, 
   double S = stencil_sum(V, L, b, M, u, k0, k1, k2, c);
   bool act = (act_mask(M) >> L.m) & 1ull;
   return act ? c * u - S : 0.0;
+}
+
+// Transposed composite operator (adjoint path): y = (A^T X)_m at the lane's
+// cell of leaf brick b (0 on inactive cells); u = X_m.  Between same-level
+// leaves the rows are those of A.  The T-junction blocks are the transposes
+// of A's rank-one blocks: a fine cell's row gets, for every active sibling,
+// (1/n) sum over the sibling group's T-faces of (k/2)(x_i - x_J); a coarse
+// leaf's row gets - sum_f (k_f/2) x_f over the fine face cells f.  The fine
+// bricks, which hold k_f and x_f here, store those sums (four per T-face) in
+// fc -- 96 entries per inner brick, entry d * 16 + f for its cell with face
+// index f across face d -- and k_couple_T adds them on the coarse leaves.  X
+// is read on leaf bricks only; the faces towards inner bricks are out of range
+// in the face loads.
+// Bound like the forward operator.  26.3M leaves: 296 us with the coupling
+// launch; 369 us with rows read cell by cell from the neighbours; 398 us with
+// the coarse leaves reading the fine cells' values and coefficients here, 335
+// us in a launch of their own (a face cell costs the whole cache line around
+// it, twice).
+template <int CP>
+__device__ __forceinline__ double composite_row_T(const LevelView<double, double, double, CP> &V,
+                                                  const LaneC<double, double> &L,
+                                                  double *fc, uint32_t b, double &u) {
+  const BrickMeta M = load_meta(V.meta, b);
+  double k0 = own_coef<false>(V, b, 1, L.m);
+  double k1 = own_coef<false>(V, b, 2, L.m);
+  double k2 = own_coef<false>(V, b, 3, L.m);
+  u = bload<double>(V.u, L.m, b * 64u);
+  BrickMeta Ml = M;
+#pragma unroll
+  for (int d = 0; d < 6; ++d) Ml.nbr[d] = M.nbr[d] < int32_t(V.nlb) ? M.nbr[d] : -1;
+  double v[6], k[6];
+  face_values_gathered<CP>(V.u, V.pf, L, b, Ml, u, k0, k1, k2, v, k);
+  const uint64_t amask = act_mask(M);
+  // (towards an inner brick the face coefficient is part of the diagonal, the
+  // neighbour value 0)
+  double acc = (((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5])) * u;
+#pragma unroll
+  for (int d = 0; d < 6; ++d) acc -= k[d] * v[d];
+  if (M.flags & kFlagT) {
+    double uJ[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      uJ[d] = 0.0;
+      if ((M.flags >> d) & 1u)
+        uJ[d] = bload<double>(V.u, uint32_t(coarse_local(M, int(L.m), d)),
+                              uint32_t(dev_decode_coarse(M.nbr[d])) * 64u);
+    }
+    double t = 0.0;
+    const int pc = octant_of(M) * 8 + int(L.m >> 3);  // the parent cell
+#pragma unroll
+    for (int d = 0; d < 6; ++d)
+      if ((M.flags >> d) & 1u) {
+        const int a = d >> 1, o0 = a == 0 ? 1 : 0, o1 = a == 2 ? 1 : 2;
+        double kt = L.out[d] ? k[d] : 0.0;
+        acc -= kt * u;
+        t += kt * 0.5 * (u - uJ[d]);
+        double f = kt * 0.5 * u;
+        f = f + shfl_xor(f, 1 << o0);
+        f = f + shfl_xor(f, 1 << o1);
+        if (L.out[d] && !((L.m >> o0) & 1u) && !((L.m >> o1) & 1u))
+          fc[uint64_t(uint32_t(M.parent) - V.nlb) * 96u + uint32_t(d * 16 + dev_face_index(pc, a))] = f;
+      }
+    double s = group8_sum(t);
+    int cnt = __popcll((amask >> (L.m & 56u)) & 0xffull);
+    if (cnt) acc += s / double(cnt);
+  }
+  return (amask >> L.m) & 1ull ? acc : 0.0;
 }
 
 // per-workgroup partial of a wave-private sum, in fixed order
@@ -299,22 +294,51 @@ __global__ void __launch_bounds__(kBlock) k_pcg_Ap(PcgArgs P, const double *p, d
   block_partial(part, P.partials);
 }
 
-// Ap = A^T p (adjoint solves), one wave per leaf brick.
-__global__ void __launch_bounds__(kBlock) k_pcg_ApT(PcgArgs P, const double *p, double *Ap) {
+// Ap = A^T p (adjoint solves), as k_pcg_Ap.
+template <int CP = kCpolDefault>
+__global__ void __launch_bounds__(kBlock) k_pcg_ApT(PcgArgs P, const double *p, double *Ap,
+                                                    double *fc) {
   if (P.S->done) return;
-  uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
+  const LevelView<double, double, double, CP> V = composite_view<CP>(P, p);
+  const LaneC<double, double> L = lane_consts<double, double>();
+  const __amdgpu_buffer_rsrc_t out = make_rsrc(Ap, uint64_t(P.T.nlb) * 64 * sizeof(double));
+  const WaveLoop W = wave_loop(P.T.nlb);
   double part = 0.0;
-  if (b < P.T.nlb) {
-    const BrickMeta M = P.T.meta[b];
-    double c, k0, k1, k2;
-    leaf_cell(P, b, m, c, k0, k1, k2);
-    double u = p[b * 64u + m];
-    double y = composite_AuT(P.T, P.C, P.TC, p, M, m, u, c, k0, k1, k2);
-    Ap[b * 64u + m] = y;
-    part = u * y;
+  for (uint32_t b = W.first; b < W.end; b += W.step) {
+    double u;
+    double y = composite_row_T(V, L, fc, b, u);
+    bstore<double>(out, L.m, b * 64u, y);
+    part += u * y;
   }
   block_partial(part, P.partials);
+}
+
+// The coarse leaves' part of A^T X: on the listed leaf bricks y -= the sums
+// fc of the fine cells next to a cell (composite_row_T); the partials of
+// (X, that) go to the slots from `base` on.  partials null: no partial.
+__global__ void __launch_bounds__(kBlock) k_couple_T(PcgArgs P, const uint32_t *list, uint32_t n,
+                                                     const double *X, double *y,
+                                                     const double *fc, unsigned base,
+                                                     const int *done) {
+  if (done && *done) return;
+  const uint32_t m = threadIdx.x & (kWave - 1);
+  double part = 0.0;
+  for (uint32_t i = blockIdx.x * kWavesPerBlock + wave_id(); i < n;
+       i += gridDim.x * kWavesPerBlock) {
+    const uint32_t b = __builtin_amdgcn_readfirstlane(list[i]);
+    const BrickMeta M = load_meta(P.T.meta, b);
+    const double yo = y[b * 64u + m], u = X[b * 64u + m];
+    double r = 0.0;
+#pragma unroll
+    for (int d = 0; d < 6; ++d)
+      if (((M.flags >> (8 + d)) & 1u) && dev_outside(int(m), d))
+        r -= fc[uint64_t(uint32_t(M.nbr[d]) - P.T.nlb) * 96u +
+                uint32_t((d ^ 1) * 16 + dev_face_index(int(m), d >> 1))];
+    if (!((act_mask(M) >> m) & 1ull)) r = 0.0;
+    y[b * 64u + m] = yo + r;
+    part += u * r;
+  }
+  if (P.partials) block_partial(part, P.partials + base);
 }
 
 // Second stage of every PCG reduction: the per-workgroup partials of the
@@ -516,14 +540,17 @@ __global__ void __launch_bounds__(kBlock) k_apply(PcgArgs P, const double *X, do
   }
 }
 
-// y = A^T X, y in device order
-__global__ void __launch_bounds__(kBlock) k_applyT(PcgArgs P, const double *X, double *y) {
-  LEAF_LOOP(P) {
-    const BrickMeta M = P.T.meta[b];
-    double c, k0, k1, k2;
-    leaf_cell(P, b, m, c, k0, k1, k2);
-    double u = X[b * 64u + m];
-    y[b * 64u + m] = composite_AuT(P.T, P.C, P.TC, X, M, m, u, c, k0, k1, k2);
+// y = A^T X, y in device order (wave_loop grid)
+__global__ void __launch_bounds__(kBlock) k_applyT(PcgArgs P, const double *X, double *y,
+                                                   double *fc) {
+  const LevelView<double, double, double> V = composite_view(P, X);
+  const LaneC<double, double> L = lane_consts<double, double>();
+  const __amdgpu_buffer_rsrc_t out = make_rsrc(y, uint64_t(P.T.nlb) * 64 * sizeof(double));
+  const WaveLoop W = wave_loop(P.T.nlb);
+  for (uint32_t b = W.first; b < W.end; b += W.step) {
+    double u;
+    double v = composite_row_T(V, L, fc, b, u);
+    bstore<double>(out, L.m, b * 64u, v);
   }
 }
 
