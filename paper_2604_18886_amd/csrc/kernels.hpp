@@ -43,7 +43,7 @@ constexpr uint32_t kFlagWall = 0x3fu << 16;
 // lies on the parent's face, and the brick's own parent otherwise.
 struct alignas(16) ParentNbrs {
   int32_t across[3];
-  int32_t leaf_nbr;  // 1: the parent has a leaf brick as a same-level neighbour
+  int32_t pad;
 };
 
 struct Topo {
@@ -237,7 +237,7 @@ __global__ void __launch_bounds__(kBlock) k_parent_nbrs(Topo T, ParentNbrs *out)
   if (b >= T.nb) return;
   const BrickMeta &M = T.meta[b];
   ParentNbrs r;
-  r.leaf_nbr = 0;
+  r.pad = 0;
   for (int a = 0; a < 3; ++a) {
     r.across[a] = -1;
     if (M.parent >= 0) {
@@ -245,11 +245,6 @@ __global__ void __launch_bounds__(kBlock) k_parent_nbrs(Topo T, ParentNbrs *out)
       r.across[a] = T.meta[M.parent].nbr[2 * a + side];
     }
   }
-  if (M.parent >= 0)
-    for (int d = 0; d < 6; ++d) {
-      int32_t n = T.meta[M.parent].nbr[d];
-      if (n >= 0 && uint32_t(n) < T.nlb) r.leaf_nbr = 1;
-    }
   out[b] = r;
 }
 
@@ -396,6 +391,7 @@ struct LevelArgs {
   V *U;              // iterate, nb * 64
   V *B;              // right-hand side, nb * 64 (leaf part: the PCG residual)
   V *Ustar;          // FAS initial guess of inner cells, (nb - nlb) * 64
+  V pscale;          // transposed cycle: beta_mg / alpha
   Range R;
   const int *done;   // skip when the solve has stopped
 };
@@ -509,6 +505,7 @@ struct LevelView {
   const ParentNbrs *pnb;
   uint32_t nlb;
   V iscale;
+  V pscale;
 };
 
 template <int CP = kCpolDefault, class V, class CL, class CI>
@@ -525,6 +522,7 @@ __device__ __forceinline__ LevelView<V, CL, CI, CP> level_view(const LevelArgs<V
   X.pnb = A.T.pnb;
   X.nlb = A.T.nlb;
   X.iscale = A.cf.iscale;
+  X.pscale = A.pscale;
   return X;
 }
 
@@ -640,11 +638,13 @@ __device__ __forceinline__ void face_values_gathered(__amdgpu_buffer_rsrc_t x,
 // The FAS correction u_P - u*_P of the parent cell of the lane's cell
 // (Algorithm 4, prolongation): the brick covers octant o of its parent
 // brick, whose cells o * 8 .. o * 8 + 7 are the parents of its 2^3 blocks.
-template <class V, class CL, class CI, int CP>
+// TR: in the transposed cycle it is pscale times the parent's iterate.
+template <bool TR = false, class V, class CL, class CI, int CP>
 __device__ __forceinline__ V own_correction(const LevelView<V, CL, CI, CP> &X,
                                             const LaneC<V, CL> &L, const BrickMeta &M) {
   uint32_t base = uint32_t(M.parent) * 64u + uint32_t(octant_of(M)) * 8u;
   uint32_t q = L.m >> 3;
+  if constexpr (TR) return X.pscale * bload<V>(X.u, q, base);
   return bload<V>(X.u, q, base) - bload<V>(X.us, q, base - X.nlb * 64u);
 }
 
@@ -669,7 +669,8 @@ __device__ __forceinline__ V own_correction(const LevelView<V, CL, CI, CP> &X,
 // takes the correction of its own parent cell from lane m >> 3 and that of
 // its neighbour across face d (in the brick or beyond it) from lane
 // L.esrc[d].
-template <class V, class CL, class CI, int CP>
+// TR as in own_correction.
+template <bool TR = false, class V, class CL, class CI, int CP>
 __device__ __forceinline__ V prolong_gather(const LevelView<V, CL, CI, CP> &X,
                                             const LaneC<V, CL> &L, const BrickMeta &M,
                                             const ParentNbrs &PN) {
@@ -695,6 +696,7 @@ __device__ __forceinline__ V prolong_gather(const LevelView<V, CL, CI, CP> &X,
   valid = valid && has_parent;
   const uint32_t cell = pb * 64u + oc * 8u + (L.m & 7u);
   const uint32_t ou = valid ? cell * uint32_t(sizeof(V)) : kOutOfRange;
+  if constexpr (TR) return X.pscale * bload_bytes<V>(X.u, ou, 0);
   const uint32_t os = valid ? (cell - X.nlb * 64u) * uint32_t(sizeof(V)) : kOutOfRange;
   return bload_bytes<V>(X.u, ou, 0) - bload_bytes<V>(X.us, os, 0);
 }
@@ -704,10 +706,14 @@ __device__ __forceinline__ V prolong_gather(const LevelView<V, CL, CI, CP> &X,
 //   E_m = kT_m u_m - (1 / n) sum over the sibling group of (kT_i / 2) u_i,
 // kT the cell's coefficients on T-faces and n the group's active cells (its
 // values v[d] across T-faces are 0).  The coarse leaf's row takes its share
-// from face_children_sum.
-template <class V, class CL>
-__device__ __forceinline__ V t_rows_transposed(const LaneC<V, CL> &L, const BrickMeta &M, V u,
-                                               const V (&k)[6]) {
+// from face_children_sum.  PR as in stencil_sum: the own values get the
+// correction first.
+template <int PR, class V, class CL, class CI, int CP>
+__device__ __forceinline__ V t_rows_transposed(const LevelView<V, CL, CI, CP> &X,
+                                               const LaneC<V, CL> &L, const BrickMeta &M, V u,
+                                               const V (&k)[6], V corr, int colour) {
+  if constexpr (PR == 1) u = u + shfl(corr, int(L.m >> 3));
+  if constexpr (PR == 2) u = L.colour == colour ? u + own_correction<true>(X, L, M) : u;
   V kt = V(0);
 #pragma unroll
   for (int d = 0; d < 6; ++d)
@@ -782,7 +788,7 @@ __device__ __forceinline__ V stencil_sum(const LevelView<V, CL, CI, CP> &X, cons
   V extra = V(0);  // TR only
   if (M.flags & kFlagT) {
     if constexpr (TR) {
-      extra = t_rows_transposed(L, M, u, k);
+      extra = t_rows_transposed<PR>(X, L, M, u, k, corr, colour);
     } else if constexpr (sizeof(V) == 8) {
       t_ghosts<PR>(X, L, M, u, v, corr, colour);
     } else {
@@ -821,6 +827,65 @@ __device__ __forceinline__ V stencil_sum(const LevelView<V, CL, CI, CP> &X, cons
   return acc;
 }
 
+// Transposed prolongation, right-hand side: the active cells of brick b take
+// D = (handed-back residual of the parent cell) / (active siblings) into
+// their right-hand side and, on inner bricks, into the residual they hand back
+// themselves.  The handed-back residual is what the parent's level stored plus
+// the parent cell's sum of k y over its faces to same-level leaves: those
+// lie across the brick's own T-faces.  Their loads are requested before any
+// is used.  Returns the new right-hand side of the lane's cell.
+// Taken by the first half-sweep after the coarse visit together with the
+// iterate's correction; finest level of the 26.3M-leaf workload, FP32: 177 us
+// for that half-sweep (a plain one 95 us and a pass of its own 100 us, 190 us
+// while the sums went through the parent's record), 2.3M leaves 17 against
+// 9 + 10 us.
+template <bool INNER, class V, class CL, class CI, int CP>
+__device__ __forceinline__ V take_residual_T(const LevelView<V, CL, CI, CP> &X,
+                                             const LaneC<V, CL> &L, uint32_t b,
+                                             const BrickMeta &M, V rhs) {
+  const uint32_t P = uint32_t(M.parent);
+  const uint32_t oc = uint32_t(octant_of(M)) * 8u;
+  const uint32_t q = L.m >> 3;
+  V D = bload<V>(X.us, q, (P - X.nlb) * 64u + oc);
+  V sb = V(0);
+  if constexpr (INNER) sb = bload<V>(X.us, L.m, (b - X.nlb) * 64u);
+  if (!INNER && (M.flags & kFlagT)) {  // (an inner brick has no T-face)
+    const int pc = int(oc + q);
+    V y[6], k[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      const int a = d >> 1;
+      y[d] = V(0);
+      k[d] = V(0);
+      if ((M.flags >> d) & 1u) {
+        const uint32_t out = dev_outside(pc, d) ? 0u : kOutOfRange;
+        y[d] = bload_bytes<V>(X.u, out + uint32_t(dev_partner(pc, d)) * uint32_t(sizeof(V)),
+                              uint32_t(dev_decode_coarse(M.nbr[d])) * uint32_t(64 * sizeof(V)));
+        if (d & 1)
+          k[d] = V(bload<CL>(X.pf, uint32_t(a * 16 + dev_face_index(pc, a)), P * 48u));
+        else
+          k[d] = V(bload<CI>(X.ci, uint32_t(pc), (P - X.nlb) * 256u + uint32_t(1 + a) * 64u));
+      }
+    }
+#pragma unroll
+    for (int d = 0; d < 6; ++d)
+      if ((M.flags >> d) & 1u) {
+        // (the parent's cell size is twice the level's)
+        if (!(d & 1) && !std::is_same<CL, CI>::value) k[d] = k[d] * (X.iscale * V(2));
+        D += k[d] * y[d];
+      }
+  }
+  const uint64_t amask = act_mask(M);
+  const int cnt = __popcll((amask >> (L.m & 56u)) & 0xffull);
+  if ((amask >> L.m) & 1ull) {
+    D = div_by(D, V(cnt));
+    rhs = rhs + D;
+    bstore<V>(X.b, L.m, b * 64u, rhs);
+    if constexpr (INNER) bstore<V>(X.us, L.m, (b - X.nlb) * 64u, sb + D);
+  }
+  return rhs;
+}
+
 // One brick of a colour half-sweep of red-black Gauss-Seidel: on the cells
 // of the colour u_m = (b_m + S_m) / c_m, every read taken before the write
 // (the neighbours of a cell all have the other colour).  PR = 1: the first
@@ -831,12 +896,13 @@ __device__ __forceinline__ void smooth_brick(const LevelView<V, CL, CI, CP> &X, 
                                              uint32_t b, int colour) {
   const BrickMeta M = load_meta(X.meta, b);
   V corr = V(0);
-  if constexpr (PR == 1) corr = prolong_gather(X, L, M, load_parent_nbrs(X.pnb, b));
+  if constexpr (PR == 1) corr = prolong_gather<TR>(X, L, M, load_parent_nbrs(X.pnb, b));
   V k0 = own_coef<INNER>(X, b, 1, L.m);
   V k1 = own_coef<INNER>(X, b, 2, L.m);
   V k2 = own_coef<INNER>(X, b, 3, L.m);
   V u = bload<V>(X.u, L.m, b * 64u);
   V rhs = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
+  if constexpr (TR && PR == 1) rhs = take_residual_T<INNER>(X, L, b, M, rhs);
   V c;
   V S = stencil_sum<PR, TR>(X, L, b, M, u, k0, k1, k2, c, corr, colour);
   bool act = (act_mask(M) >> L.m) & 1ull;
@@ -909,7 +975,8 @@ __device__ __forceinline__ void smooth_brick_gathered(const LevelView<V, CL, CI,
   V rhs = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
   const bool act = (act_mask(M) >> L.m) & 1ull;
   V corr = V(0);
-  if constexpr (PR == 1) corr = prolong_gather(X, L, M, load_parent_nbrs(X.pnb, b));
+  if constexpr (PR == 1) corr = prolong_gather<TR>(X, L, M, load_parent_nbrs(X.pnb, b));
+  if constexpr (TR && PR == 1) rhs = take_residual_T<INNER>(X, L, b, M, rhs);
   uint32_t gb = 0u;  // byte offset of the brick across the lane's gather face
 #pragma unroll
   for (int d = 0; d < 6; ++d) {
@@ -937,7 +1004,7 @@ __device__ __forceinline__ void smooth_brick_gathered(const LevelView<V, CL, CI,
   }
   V extra = V(0);  // TR only
   if (M.flags & kFlagT) {
-    if constexpr (TR) extra = t_rows_transposed(L, M, u, k);
+    if constexpr (TR) extra = t_rows_transposed<PR>(X, L, M, u, k, corr, colour);
     else t_ghosts<PR>(X, L, M, u, v, corr, colour);
   }
   V c = ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
@@ -1606,9 +1673,9 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
 // Gauss-Seidel half-sweep of A^T y = g: it reads and writes what a forward
 // half-sweep does, where the residual form reads and writes rho and w on
 // every cell besides.  Bound like the forward cycle; on the 26.3M-leaf
-// workload, FP32, a finest half-sweep takes 101 us against 161 us in
-// residual form and the adjoint solve and gradient 57.9 against 94.2 ms
-// (2.3M leaves: 8.1 against 13.6 ms).
+// workload, FP32, a finest half-sweep takes 95 us against 161 us in residual
+// form and the adjoint solve and gradient 57.9 against 94.2 ms (2.3M leaves:
+// 8.1 against 13.6 ms) from that alone.
 //
 // The residual that the transposed FAS steps hand from level l - 1 back to
 // level l,  -(what was restricted) + rho + A^T (y on inner cells), is, with
@@ -1618,13 +1685,20 @@ __global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelA
 // ---------------------------------------------------------------------------
 
 // First half-sweep of a level from a zero iterate: y = g / c on the active
-// cells of the colour, 0 on all others.  The diagonal is the sum of the six
-// face coefficients, as in every half-sweep.
+// cells of the colour, 0 on all others.  On inner bricks the diagonal is the
+// sum of the six face coefficients, as in every half-sweep (the stored FP16
+// diagonal is rounded on its own).
 template <bool INNER, class V, class CL, class CI, int CP>
 __device__ __forceinline__ void zero_brick_T(const LevelView<V, CL, CI, CP> &X,
                                              const LaneC<V, CL> &L, uint32_t b, int colour) {
   const BrickMeta M = load_meta(X.meta, b);
   bool act = (act_mask(M) >> L.m) & 1ull;
+  if constexpr (!INNER) {  // leaves store it unrounded (k_smooth_zero reads it too)
+    V c = own_coef<false>(X, b, 0, L.m);
+    V g = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
+    bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(g, c) : V(0));
+    return;
+  }
   V k[6];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
@@ -1832,46 +1906,28 @@ __global__ void __launch_bounds__(kBlock) k_T_revisit(LevelArgs<V, CL, CI> A) {
   }
 }
 
-// After the coarse recursion, on the bricks of level l: active cells take
-// D = (handed-back residual of the parent) / n_active(P) into their
-// right-hand side (and, on inner bricks, into the residual they hand back
-// themselves) and pscale = beta_mg / alpha times the parent's iterate into
-// their own.
+// After the coarse recursion, on the bricks of level l, when no half-sweep
+// follows to take it along: take_residual_T, and pscale times the parent's
+// iterate into the active cells' own.
 template <bool INNER, class V, class CL, class CI, int CP>
 __device__ __forceinline__ void prolong_brick_T(const LevelView<V, CL, CI, CP> &X,
-                                                const LaneC<V, CL> &L, uint32_t b, V pscale) {
+                                                const LaneC<V, CL> &L, uint32_t b) {
   const BrickMeta M = load_meta(X.meta, b);
-  const ParentNbrs PN = load_parent_nbrs(X.pnb, b);
-  const uint32_t P = uint32_t(M.parent);
-  const uint32_t oc = uint32_t(octant_of(M)) * 8u;
-  const uint32_t q = L.m >> 3;
-  V D = bload<V>(X.us, q, P * 64u + oc - X.nlb * 64u);
-  V yp = bload<V>(X.u, q, P * 64u + oc);
-  V g = bload<V>(X.b, L.m, b * 64u);
   V y = bload<V>(X.u, L.m, b * 64u);
-  V sb = V(0);
-  if constexpr (INNER) sb = bload<V>(X.us, L.m, (b - X.nlb) * 64u);
-  if (PN.leaf_nbr)  // (the parent's cell size is twice the level's)
-    D += leaf_neighbour_sum(X, P, load_meta(X.meta, P), int(oc + q), X.iscale * V(2));
-  const uint64_t amask = act_mask(M);
-  const int cnt = __popcll((amask >> (L.m & 56u)) & 0xffull);
-  if ((amask >> L.m) & 1ull) {
-    D = div_by(D, V(cnt));
-    bstore<V>(X.b, L.m, b * 64u, g + D);
-    bstore<V>(X.u, L.m, b * 64u, y + pscale * yp);
-    if constexpr (INNER) bstore<V>(X.us, L.m, (b - X.nlb) * 64u, sb + D);
-  }
+  take_residual_T<INNER>(X, L, b, M, bload<V>(X.b, L.m, b * 64u));
+  V corr = own_correction<true>(X, L, M);
+  if ((act_mask(M) >> L.m) & 1ull) bstore<V>(X.u, L.m, b * 64u, y + corr);
 }
 
 template <class V, class CL, class CI>
-__global__ void __launch_bounds__(kBlock) k_T_prolong(LevelArgs<V, CL, CI> A, V pscale) {
+__global__ void __launch_bounds__(kBlock) k_T_prolong(LevelArgs<V, CL, CI> A) {
   if (A.done && *A.done) return;
   const LaneC<V, CL> L = lane_consts<V, CL>();
   const LevelView<V, CL, CI> X = level_view(A);
   const WaveLoop W = wave_loop(A.R.n());
   for (uint32_t i = W.first; i < W.end; i += W.step) {
-    if (i < A.R.n_leaf) prolong_brick_T<false>(X, L, A.R.leaf_lo + i, pscale);
-    else prolong_brick_T<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), pscale);
+    if (i < A.R.n_leaf) prolong_brick_T<false>(X, L, A.R.leaf_lo + i);
+    else prolong_brick_T<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf));
   }
 }
 

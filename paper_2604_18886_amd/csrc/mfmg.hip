@@ -1114,6 +1114,7 @@ struct Cycle {
     A.U = U;
     A.B = B;
     A.Ustar = Ust;
+    A.pscale = V(h->prm.beta_mg / h->prm.alpha);
     A.R = D.range[l];
     if (inner_only) {
       A.R.n_leaf = 0;
@@ -1266,9 +1267,21 @@ struct CycleT {
     return Cycle<V, CL, CI>{h, leafc, innerc, pf, Y, G, Sb, done, s}.args(l, false);
   }
   bool stream(int l) const { return h->stream_lv[size_t(l)]; }
-  // nu iterations of transposed smoothing, colours (first, 1 - first) each;
-  // zero: from a zero iterate, which the first half-sweep also writes
-  void smooth(int l, int first, int nu, bool zero) const {
+  template <int PR>
+  void half_sweep(int l, const LevelArgs<V, CL, CI> &A, int colour) const {
+    dim3 g(stencil_grid<V>(A.R.n()));
+    if (stream(l))
+      hipLaunchKernelGGL((k_smooth<V, CL, CI, kCpolLevel, PR, true>), g, dim3(kBlock), 0, s, A,
+                         colour);
+    else
+      hipLaunchKernelGGL((k_smooth<V, CL, CI, kCpolDefault, PR, true>), g, dim3(kBlock), 0, s, A,
+                         colour);
+  }
+  // nu iterations of transposed smoothing, colours (first, 1 - first) each.
+  // zero: from a zero iterate, which the first half-sweep also writes;
+  // prolong: the transposed prolongation is still to be taken (by the first
+  // two half-sweeps)
+  void smooth(int l, int first, int nu, bool zero, bool prolong) const {
     auto A = args(l);
     if (A.R.n() == 0) return;
     dim3 g(stencil_grid<V>(A.R.n()));
@@ -1279,12 +1292,12 @@ struct CycleT {
           hipLaunchKernelGGL((k_T_zero<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, colour);
         else
           hipLaunchKernelGGL((k_T_zero<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour);
-      } else if (stream(l)) {
-        hipLaunchKernelGGL((k_smooth<V, CL, CI, kCpolLevel, 0, true>), g, dim3(kBlock), 0, s, A,
-                           colour);
+      } else if (prolong && k == 0) {
+        half_sweep<1>(l, A, colour);
+      } else if (prolong && k == 1) {
+        half_sweep<2>(l, A, colour);
       } else {
-        hipLaunchKernelGGL((k_smooth<V, CL, CI, kCpolDefault, 0, true>), g, dim3(kBlock), 0, s,
-                           A, colour);
+        half_sweep<0>(l, A, colour);
       }
     }
   }
@@ -1298,7 +1311,7 @@ struct CycleT {
                          p.nu_coarse - p.nu_coarse / 2);
       return;
     }
-    smooth(l, 0, p.nu_post, first);  // forward post-smoothing is (B,R)^nu
+    smooth(l, 0, p.nu_post, first, false);  // forward post-smoothing is (B,R)^nu
     uint32_t nc = h->couple_n[size_t(l - 1)];
     unsigned gr = stencil_grid<V>(A.R.n());
     dim3 g(gr + (nc ? grid_for(nc) : 0));
@@ -1329,8 +1342,10 @@ struct CycleT {
     } else {
       for (int k = 0; k < p.mu; ++k) fas(l - 1, first && k == 0);
     }
-    hipLaunchKernelGGL((k_T_prolong<V, CL, CI>), gr, dim3(kBlock), 0, s, A, pscale);
-    smooth(l, 1, p.nu_pre, false);  // forward pre-smoothing is (R,B)^nu
+    // forward pre-smoothing is (R,B)^nu
+    bool fused = h->fuse_prolong && p.nu_pre > 0;
+    if (!fused) hipLaunchKernelGGL((k_T_prolong<V, CL, CI>), gr, dim3(kBlock), 0, s, A);
+    smooth(l, 1, p.nu_pre, false, fused);
   }
   void zero_leaves(int l) const {
     const Range &R = h->co->dt->range[size_t(l)];

@@ -3,8 +3,6 @@ cycle, over what its branches depend on: cycle index (a level visited once or
 several times), smoothing counts, the bottom of the cycle in one kernel or in
 separate ones, leaves on the coarsest level and on the one above it, walls."""
 
-import os
-
 import numpy as np
 import pytest
 
@@ -34,21 +32,20 @@ def case(request):
     return CASES[request.param]()
 
 
-@pytest.mark.parametrize("bottom", ["1", "0"])
+# bottom "1"/"0": the bottom of the cycle in one kernel or in separate ones;
+# "p": separate, and the prolongation in a pass of its own
+@pytest.mark.parametrize("bottom", ["1", "0", "p"])
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("prm", PARAMS, ids=[str(i) for i in range(len(PARAMS))])
 def test_transposed_cycle(case, prm, precision, bottom):
     from paper_2604_18886_amd import mfmg
     H = M.Hierarchy(case.disc, coarsest=3, **prm)
-    saved = os.environ.get("MFMG_FUSE_BOTTOM")
-    os.environ["MFMG_FUSE_BOTTOM"] = bottom
-    try:
+    env = {"MFMG_FUSE_BOTTOM": "1" if bottom == "1" else "0",
+           "MFMG_FUSE_PROLONG": "0" if bottom == "p" else "1"}
+    with pytest.MonkeyPatch.context() as mp:
+        for k, v in env.items():
+            mp.setenv(k, v)
         h = case.gpu_hierarchy(precision=precision, **prm)
-    finally:
-        if saved is None:
-            del os.environ["MFMG_FUSE_BOTTOM"]
-        else:
-            os.environ["MFMG_FUSE_BOTTOM"] = saved
     rng = np.random.default_rng(77)
     r = np.where(case.disc.active, rng.uniform(-1, 1, case.T.n), 0.0)
     for _ in range(2):  # the second call finds the first one's arrays
