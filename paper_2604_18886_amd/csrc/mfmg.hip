@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "../../include/mfmg.h"
+#include "face_kernels.hpp"
 #include "kernels.hpp"
 #include "octree_kernels.hpp"
 #include "pcg_kernels.hpp"
@@ -222,10 +223,6 @@ struct mfmg_hierarchy {
   std::vector<uint32_t> couple_lo, couple_n;
   DevBuf<float> T32[4];
   DevBuf<double> rA;              // adjoint PCG residual
-  // face arrays for the per-face gradient (allocated on first use)
-  DevBuf<int64_t> f_owner, f_other;
-  DevBuf<int8_t> f_dir, f_kind, leaf_level;
-  DevBuf<uint64_t> canon_act;
   Scalars *hostS = nullptr;      // pinned: the scalars read back after a solve
   int *host_done = nullptr;      // pinned, mapped: stop flag written by k_finish
   int *host_done_dev = nullptr;  // its device address
@@ -901,8 +898,9 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     h->pd.alloc(size_t(nb) * 64);
     h->Xf.alloc(size_t(nb) * 64);
     h->Ap.alloc(size_t(N));
-    // (the adjoint's operator stores those of its coupling launch after its own)
-    h->partials.alloc(std::max<int64_t>(kMaxReduceBlocks,
+    // (the adjoint's operator stores those of its coupling launch after its
+    // own, the divergence RMS two sets)
+    h->partials.alloc(std::max<int64_t>(2 * kMaxReduceBlocks,
                                         int64_t(level_grid(nlb)) + kMaxReduceBlocks));
     h->S.alloc(1);
     HIP_CHECK(hipMemsetAsync(h->S.p, 0, sizeof(Scalars), s));
@@ -1561,32 +1559,10 @@ struct Reduce {
   }
 };
 
-// The canonical face list with the per-brick levels and activity masks in
-// canonical order (for per-face kernels), made at first use and kept.
-static void ensure_face_list(mfmg_hierarchy *h, hipStream_t s) {
-  if (h->f_owner.p) return;
+// Face addressing with the hierarchy's records (activity masks).
+static FaceTables face_tables(const mfmg_hierarchy *h) {
   const DeviceTopology &D = *h->co->dt;
-  size_t nf = size_t(std::max<int64_t>(h->co->tree->n_faces, 1));
-  h->f_owner.alloc(nf);
-  h->f_other.alloc(nf);
-  h->f_dir.alloc(nf);
-  h->f_kind.alloc(nf);
-  h->leaf_level.alloc(size_t(D.nlb));
-  h->canon_act.alloc(size_t(D.nlb));
-  if (D.nlb) {
-    hipLaunchKernelGGL(k_oct_faces, dim3(grid_for(D.nlb)), dim3(kBlock), 0, s,
-                       (const BrickMeta *)D.meta.p, (const int32_t *)D.canon.p,
-                       (const int64_t *)D.fbase.p, (const uint8_t *)D.fmask.p, D.nlb,
-                       h->f_owner.p, h->f_dir.p, h->f_other.p, h->f_kind.p);
-    hipLaunchKernelGGL(k_oct_canon_level, dim3(grid_elems(D.nlb, 256)), dim3(256), 0, s,
-                       (const BrickMeta *)D.meta.p, (const int32_t *)D.canon.p, D.nlb,
-                       h->leaf_level.p);
-    hipLaunchKernelGGL(k_canonical_act, dim3(grid_elems(D.nlb, 256)), dim3(256), 0, s,
-                       (const BrickMeta *)h->meta.p, (const int32_t *)D.canon.p, D.nlb,
-                       h->canon_act.p);
-  }
-  HIP_CHECK(hipGetLastError());
-  HIP_CHECK(hipStreamSynchronize(s));
+  return FaceTables{make_topo(D, h->meta.p), D.fbase.p, D.canon.p};
 }
 
 // Without a Dirichlet face A is singular on the constants of the active
@@ -1977,7 +1953,6 @@ extern "C" mfmg_status mfmg_pcg_solve_adjoint(mfmg_hierarchy *h, const double *p
   bool ns = sp->null_space == 1 || (sp->null_space == -1 && !h->co->has_dirichlet);
   if (sp->warm_start) return fail(MFMG_ERR_INVALID_ARG, "the adjoint solve starts from zero");
   hipStream_t s = (hipStream_t)stream;
-  const mfmg_octree &T = *h->co->tree;
   const DeviceTopology &D = *h->co->dt;
   mfmg_status st = MFMG_OK;
   try {
@@ -1991,7 +1966,6 @@ extern "C" mfmg_status mfmg_pcg_solve_adjoint(mfmg_hierarchy *h, const double *p
                   "sum to zero over the active cells");
     if (!h->rA.p) h->rA.alloc(size_t(D.nlb) * 64);
     ensure_transpose(h, s);
-    ensure_face_list(h, s);
     hipEvent_t e0, e1;
     HIP_CHECK(hipEventCreate(&e0));
     HIP_CHECK(hipEventCreate(&e1));
@@ -2005,19 +1979,14 @@ extern "C" mfmg_status mfmg_pcg_solve_adjoint(mfmg_hierarchy *h, const double *p
     hipLaunchKernelGGL(k_to_canonical<double>, dim3(G), dim3(kBlock), 0, s, P,
                        (const double *)h->x.p, lambda);
     GradArgs A;
-    A.owner = h->f_owner.p;
-    A.other = h->f_other.p;
-    A.dir = h->f_dir.p;
-    A.kind = h->f_kind.p;
-    A.level = h->leaf_level.p;
-    A.act = h->canon_act.p;
+    A.F = face_tables(h);
     A.lam = lambda;
     A.p = p;
     for (int d = 0; d < 6; ++d) A.bc[d] = h->co->bc.bc[d];
     A.theta = h->co->bc.theta;
-    A.n_faces = T.n_faces;
     A.g = dL_dbeta;
-    hipLaunchKernelGGL(k_face_gradient, dim3(grid_elems(T.n_faces, 256)), dim3(256), 0, s, A);
+    if (D.nlb)
+      hipLaunchKernelGGL(k_face_gradient, dim3(level_grid(D.nlb)), dim3(kBlock), 0, s, A);
     HIP_CHECK(hipEventRecord(e1, s));
     HIP_CHECK(hipMemcpyAsync(h->hostS, h->S.p, sizeof(Scalars), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
@@ -2172,14 +2141,16 @@ extern "C" mfmg_status mfmg_divergence(mfmg_hierarchy *h, const double *face_bet
   try {
     const DeviceTopology &D = *h->co->dt;
     DivArgs A;
-    A.T = make_topo(D, h->meta.p);
-    A.fbase = D.fbase.p;
-    A.fmask = D.fmask.p;
-    A.canon = D.canon.p;
+    A.F = face_tables(h);
     A.beta = face_beta;
     A.u = face_u;
     A.div = div;
-    if (D.nlb) hipLaunchKernelGGL(k_divergence, dim3(grid_for(D.nlb)), dim3(kBlock), 0, s, A);
+    if (D.nlb) {
+      int64_t groups = (int64_t(D.nlb) + kDivWaves - 1) / kDivWaves;
+      unsigned g = unsigned(8 * std::min<int64_t>((groups + 7) / 8, kWavesPerXcd32 / kDivWaves));
+      hipLaunchKernelGGL(k_divergence, dim3(g), dim3(kDivWaves * kWave), 0, s, A);
+      hipLaunchKernelGGL(k_divergence_fine, dim3(grid_for(D.nlb)), dim3(kBlock), 0, s, A);
+    }
     HIP_CHECK(hipGetLastError());
   } catch (const HipError &e) {
     return hip_fail(e);
@@ -2192,49 +2163,21 @@ extern "C" mfmg_status mfmg_project_velocity(mfmg_hierarchy *h, const double *fa
   if (!h || !face_beta || !p || !face_u) return fail(MFMG_ERR_INVALID_ARG, "NULL argument");
   hipStream_t s = (hipStream_t)stream;
   try {
-    ensure_face_list(h, s);
+    const DeviceTopology &D = *h->co->dt;
     FluxArgs A;
-    A.owner = h->f_owner.p;
-    A.other = h->f_other.p;
-    A.dir = h->f_dir.p;
-    A.kind = h->f_kind.p;
-    A.level = h->leaf_level.p;
-    A.act = h->canon_act.p;
+    A.F = face_tables(h);
     A.beta = face_beta;
     A.p = p;
     for (int d = 0; d < 6; ++d) A.bc[d] = h->co->bc.bc[d];
     A.theta = h->co->bc.theta;
-    A.n_faces = h->co->tree->n_faces;
     A.u = face_u;
-    if (A.n_faces)
-      hipLaunchKernelGGL(k_project_velocity, dim3(grid_elems(A.n_faces, 256)), dim3(256), 0, s,
-                         A);
+    if (D.nlb)
+      hipLaunchKernelGGL(k_project_velocity, dim3(level_grid(D.nlb)), dim3(kBlock), 0, s, A);
     HIP_CHECK(hipGetLastError());
   } catch (const HipError &e) {
     return hip_fail(e);
   } catch (const std::bad_alloc &) {
     return fail(MFMG_ERR_OOM, "host allocation failed");
-  }
-  return MFMG_OK;
-}
-
-extern "C" mfmg_status mfmg_divergence_rms(mfmg_hierarchy *h, const double *div, double *rms,
-                                           void *stream) {
-  if (!h || !div || !rms) return fail(MFMG_ERR_INVALID_ARG, "NULL argument");
-  hipStream_t s = (hipStream_t)stream;
-  try {
-    Reduce R(h, s);
-    const double *dev_sum = &h->S.p->sum;
-    double part[2];
-    for (int what = 0; what < 2; ++what) {
-      hipLaunchKernelGGL(k_div_rms_part, dim3(R.G), dim3(kBlock), 0, s, R.P, div, what);
-      R.finish(R.G, kFinSum);
-      HIP_CHECK(hipMemcpyAsync(&part[what], dev_sum, sizeof(double), hipMemcpyDeviceToHost, s));
-    }
-    HIP_CHECK(hipStreamSynchronize(s));
-    *rms = part[1] > 0.0 ? std::sqrt(part[0] / part[1]) : 0.0;
-  } catch (const HipError &e) {
-    return hip_fail(e);
   }
   return MFMG_OK;
 }
@@ -2297,6 +2240,29 @@ __global__ void __launch_bounds__(1024) k_rms_finish(const double *parts, int64_
 
 }  // namespace
 
+// The sums' partials in the hierarchy's own buffer (at least 2 x
+// kMaxReduceBlocks slots) and the result in its scalars.
+extern "C" mfmg_status mfmg_divergence_rms(mfmg_hierarchy *h, const double *div, double *rms,
+                                           void *stream) {
+  if (!h || !div || !rms) return fail(MFMG_ERR_INVALID_ARG, "NULL argument");
+  hipStream_t s = (hipStream_t)stream;
+  try {
+    PcgArgs P = pcg_args(h);
+    unsigned G = grid_reduce(h->co->dt->nlb);
+    double *dev = &h->S.p->sum;
+    hipLaunchKernelGGL(k_div_rms_part, dim3(G), dim3(kBlock), 0, s, P, div,
+                       P.partials + kMaxReduceBlocks);
+    hipLaunchKernelGGL(k_rms_finish, dim3(1), dim3(1024), 0, s, (const double *)P.partials,
+                       int64_t(G), dev);
+    HIP_CHECK(hipGetLastError());
+    HIP_CHECK(hipMemcpyAsync(rms, dev, sizeof(double), hipMemcpyDeviceToHost, s));
+    HIP_CHECK(hipStreamSynchronize(s));
+  } catch (const HipError &e) {
+    return hip_fail(e);
+  }
+  return MFMG_OK;
+}
+
 extern "C" mfmg_status mfmg_divergence_rms_noalloc(mfmg_hierarchy *h, const double *div,
                                                    double *rms, void *stream) {
   if (!h || !div || !rms) return fail(MFMG_ERR_INVALID_ARG, "NULL argument");
@@ -2309,10 +2275,9 @@ extern "C" mfmg_status mfmg_divergence_rms_noalloc(mfmg_hierarchy *h, const doub
   unsigned G = grid_reduce(h->co->dt->nlb);
   if (int64_t(G) > kMaxReduceBlocks)
     return fail(MFMG_ERR_INVALID_ARG, "reduction grid larger than the fixed partial-sum array");
-  for (int what = 0; what < 2; ++what) {
-    P.partials = parts + what * kMaxReduceBlocks;
-    hipLaunchKernelGGL(k_div_rms_part, dim3(G), dim3(kBlock), 0, s, P, div, what);
-  }
+  P.partials = parts;
+  hipLaunchKernelGGL(k_div_rms_part, dim3(G), dim3(kBlock), 0, s, P, div,
+                     parts + kMaxReduceBlocks);
   hipLaunchKernelGGL(k_rms_finish, dim3(1), dim3(1024), 0, s, (const double *)parts,
                      int64_t(G), rms);
   e = hipGetLastError();

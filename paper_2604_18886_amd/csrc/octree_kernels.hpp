@@ -584,11 +584,4 @@ __global__ void __launch_bounds__(kBlock) k_oct_faces(const BrickMeta *meta, con
   }
 }
 
-// level of each leaf brick at its canonical position
-__global__ void k_oct_canon_level(const BrickMeta *meta, const int32_t *canon, uint32_t nlb,
-                                  int8_t *out) {
-  uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < nlb) out[canon[b]] = int8_t(meta[b].level);
-}
-
 }  // namespace mfmg

@@ -682,65 +682,4 @@ __global__ void __launch_bounds__(256) k_stream_copy(const f32x4 *__restrict__ s
     if (i + k * 256 < n) __builtin_nontemporal_store(v[k], dst + i + k * 256);
 }
 
-// ---------------------------------------------------------------------------
-// per-face gradient of the adjoint: dL/dbeta_f = -lambda^T (dA/dbeta_f) p
-// (canonical face and leaf order)
-// ---------------------------------------------------------------------------
-struct GradArgs {
-  const int64_t *owner;
-  const int64_t *other;
-  const int8_t *dir;
-  const int8_t *kind;         // 0 wall, 1 same level, 2 T-junction (owner finer)
-  const int8_t *level;        // per canonical leaf brick
-  const uint64_t *act;        // per canonical leaf brick
-  const double *lam;
-  const double *p;
-  int bc[6];
-  double theta;
-  int64_t n_faces;
-  double *g;
-};
-
-__device__ __forceinline__ bool canon_active(const GradArgs &A, int64_t cell) {
-  return (A.act[cell >> 6] >> (cell & 63)) & 1ull;
-}
-
-__global__ void k_face_gradient(GradArgs A) {
-  int64_t f = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (f >= A.n_faces) return;
-  int64_t o = A.owner[f];
-  int64_t t = A.other[f];
-  int k = A.kind[f];
-  double h = ldexp(1.0, -int(A.level[o >> 6]));
-  double g = 0.0;
-  bool ao = canon_active(A, o);
-  if (k == 0) {
-    if (ao && A.bc[A.dir[f]] == 1) g = -(h / A.theta) * A.lam[o] * A.p[o];
-  } else if (ao && canon_active(A, t)) {
-    if (k == 1) {
-      g = -h * (A.lam[o] - A.lam[t]) * (A.p[o] - A.p[t]);
-    } else {
-      // mean of p over the active siblings of the fine owner
-      int64_t base = o & ~int64_t(7);
-      double s = 0.0;
-      int n = 0;
-      for (int q = 0; q < 8; ++q)
-        if (canon_active(A, base + q)) {
-          s += A.p[base + q];
-          ++n;
-        }
-      double pbar = n ? s / double(n) : 0.0;
-      g = -(h / 2.0) * (A.lam[o] - A.lam[t]) * (pbar - A.p[t]);
-    }
-  }
-  A.g[f] = g;
-}
-
-// activity masks in canonical leaf-brick order
-__global__ void k_canonical_act(const BrickMeta *meta, const int32_t *canon, uint32_t nlb,
-                                uint64_t *out) {
-  uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b < nlb) out[canon[b]] = act_mask(meta[b]);
-}
-
 }  // namespace mfmg

@@ -18,143 +18,226 @@
 // of the owner) makes div(u_new) = div(u) - A p.
 #pragma once
 
-#include "kernels.hpp"
+#include "face_kernels.hpp"
 #include "pcg_kernels.hpp"
 
 namespace mfmg {
 
 struct DivArgs {
-  Topo T;
-  const int64_t *fbase;   // per device leaf cell: first owned face
-  const uint8_t *fmask;   // per device leaf cell: owned directions
-  const int32_t *canon;   // device leaf brick -> canonical leaf brick
+  FaceTables F;
   const double *beta;     // canonical face order
   const double *u;        // canonical face order
   double *div;            // canonical leaf order
 };
 
-__device__ __forceinline__ int64_t div_face(const DivArgs &A, uint32_t cell, int d) {
-  return A.fbase[cell] + __popc(unsigned(A.fmask[cell]) & ((1u << d) - 1u));
-}
-
-// flow along the + axis through face f of area h^2
-__device__ __forceinline__ double div_flow(const DivArgs &A, int64_t f, double h2) {
-  return A.beta[f] * h2 * A.u[f];
-}
-
-// One wave per device leaf brick, one lane per cell: the outflow through
-// each of its six sides, summed in direction order (a side towards finer
-// leaves adds its four sub-faces in a fixed order).
-__global__ void __launch_bounds__(kBlock) k_divergence(DivArgs A) {
-  uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  if (b >= A.T.nlb) return;
-  const BrickMeta M = A.T.meta[b];
-  double h = ldexp(1.0, -M.level);
-  double hf = ldexp(1.0, -(M.level + 1));
-  uint32_t cell = b * 64u + m;
-  double div = 0.0;
-  for (int d = 0; d < 6; ++d) {
-    int a = d >> 1;
-    int p = dev_partner(m, d);
-    double sgn = (d & 1) ? 1.0 : -1.0;
-    double flow;
-    if (!dev_outside(m, d)) {
-      flow = (d & 1) ? div_flow(A, div_face(A, b * 64u + p, d - 1), h * h)
-                     : div_flow(A, div_face(A, cell, d), h * h);
-    } else {
-      int32_t nb = M.nbr[d];
-      if (nb == dWall || nb <= dCoarseBase) {
-        flow = div_flow(A, div_face(A, cell, d), h * h);
-      } else if (uint32_t(nb) < A.T.nlb) {
-        flow = (d & 1) ? div_flow(A, div_face(A, uint32_t(nb) * 64u + p, d - 1), h * h)
-                       : div_flow(A, div_face(A, cell, d), h * h);
-      } else {
-        // finer neighbours: the leaf children of inner cell p of brick nb
-        int32_t cb = A.T.child[8 * int64_t(nb) + (p >> 3)];
-        int base = (p & 7) << 3;
-        int o0 = a == 0 ? 1 : 0;
-        int o1 = a == 2 ? 1 : 2;
-        int abit = (d & 1) ? 0 : 1;
-        flow = 0.0;
-        for (int n = 0; n < 4; ++n) {
-          int t = (abit << a) | ((n & 1) << o0) | ((n >> 1) << o1);
-          flow = flow + div_flow(A, div_face(A, uint32_t(cb) * 64u + (base | t), d ^ 1), hf * hf);
+// One wave per leaf brick, one lane per cell: the outflow through each of its
+// six sides except those towards finer leaves, summed in direction order.  A
+// brick's own faces are loaded in order and their flows handed to the cells
+// through LDS; the flow through a plus face inside the brick is the neighbour
+// lane's minus face's.  A plus side reads the neighbour brick's minus faces,
+// which lie in two thirds of the cache lines of its whole range, so a
+// workgroup takes eight bricks consecutive in Morton order and half of these
+// neighbours' flows come from its LDS.
+constexpr int kDivWaves = 8;
+__global__ void __launch_bounds__(kDivWaves * kWave) k_divergence(DivArgs A) {
+  __shared__ double slots[kDivWaves][kFaceSlots];
+  const uint32_t w = wave_id();
+  const FaceLane L = face_lane();
+  // each XCD takes one contiguous eighth of the groups (wave_loop)
+  const uint32_t groups = (A.F.T.nlb + kDivWaves - 1) / kDivWaves;
+  const uint32_t chunk = (groups + 7u) >> 3;
+  const uint32_t lo = (blockIdx.x & 7u) * chunk;
+  const uint32_t hi = lo + chunk < groups ? lo + chunk : groups;
+  for (uint32_t g = lo + (blockIdx.x >> 3); g < hi; g += gridDim.x >> 3) {
+    const uint32_t b0 = g * kDivWaves;
+    const uint32_t b = b0 + w;
+    const bool here = b < A.F.T.nlb;
+    BrickMeta M = load_meta(A.F.T.meta, here ? b : b0);
+    const double h = ldexp(1.0, -M.level);
+    const double h2 = h * h;
+    double be[3] = {0.0, 0.0, 0.0}, uu[3] = {0.0, 0.0, 0.0};
+    const uint32_t nf = here ? face_total(M.flags) : 0u;
+    const int64_t own = A.F.base(here ? b : b0);
+    double bo[4], uo[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t k = uint32_t(i * kWave + L.m);
+      bo[i] = k < nf ? (A.beta + own)[k] : 0.0;
+      uo[i] = k < nf ? (A.u + own)[k] : 0.0;
+    }
+    // the leaf beyond each plus side: in this workgroup (its slot), else loaded
+    uint32_t at[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int d = 2 * a + 1;
+      const uint32_t n = uint32_t(M.nbr[d]);
+      at[a] = 0u;
+      if (n < A.F.T.nlb) {
+        const uint32_t flags = load_meta(A.F.T.meta, n).flags;
+        const uint32_t k = first_slot(flags, uint32_t(dev_partner(L.m, d)), L.cntp[a]) +
+                           before_minus(flags, L.out, d - 1);
+        if (n - b0 < uint32_t(kDivWaves)) {
+          at[a] = (n - b0) * kFaceSlots + k;
+        } else if ((L.out >> d) & 1u) {
+          const int64_t f0 = A.F.base(n);
+          be[a] = (A.beta + f0)[k];
+          uu[a] = (A.u + f0)[k];
         }
       }
     }
-    div = div + sgn * flow;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) slots[w][i * kWave + L.m] = bo[i] * h2 * uo[i];
+    __syncthreads();
+    double div = 0.0;
+    uint32_t slot = w * kFaceSlots + first_slot(M.flags, uint32_t(L.m), L.cnt);
+    const double *s = &slots[0][0];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int d = 2 * a + 1;
+      const bool out = (L.out >> d) & 1u;
+      double f = 0.0;
+      if (owns_face(M.flags, L.out, d - 1)) f = s[slot++];
+      double t = shfl(f, dev_partner(L.m, d));
+      if (out) {
+        const uint32_t n = uint32_t(M.nbr[d]);
+        if (owns_plus(M.flags, d)) t = s[slot++];
+        else if (n - b0 < uint32_t(kDivWaves)) t = s[at[a]];
+        else t = be[a] * h2 * uu[a];
+      }
+      div = div - f + t;
+    }
+    if (here) (A.div + int64_t(load_uniform(A.F.canon, b)) * 64)[uint32_t(L.m)] = div;
+    __syncthreads();  // the slots are read before the next group's are stored
   }
-  A.div[int64_t(A.canon[b]) * 64 + m] = div;
+}
+
+// The sides towards finer leaves, added on the bricks that have any (one wave
+// per leaf brick; in k_divergence itself they cost every brick their
+// registers: 1125 us together): each face's 64 sub-faces are one per lane
+// (fine_cell), and each face cell adds its four in order.  The dependent
+// loads (child ids, their records, the faces) are requested for all sides at
+// once.
+__global__ void __launch_bounds__(kBlock) k_divergence_fine(DivArgs A) {
+  const uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
+  const int m = threadIdx.x & (kWave - 1);
+  if (b >= A.F.T.nlb) return;
+  const BrickMeta M = load_meta(A.F.T.meta, b);
+  if (!(M.flags & kFlagInner)) return;
+  uint32_t flags[6];
+  int64_t f0[6];
+  int q[6];
+#pragma unroll
+  for (int d = 0; d < 6; ++d)
+    if ((M.flags >> (8 + d)) & 1u) {
+      int o;
+      q[d] = fine_cell(d, m, o);
+      const uint32_t cb = uint32_t(A.F.T.child[8 * int64_t(M.nbr[d]) + o]);
+      flags[d] = A.F.T.meta[cb].flags;
+      f0[d] = A.F.fbase[uint64_t(cb) * 64u];
+    }
+  double be[6], uu[6];
+#pragma unroll
+  for (int d = 0; d < 6; ++d)
+    if ((M.flags >> (8 + d)) & 1u) {
+      const int64_t f = f0[d] + face_slot(flags[d], q[d], d ^ 1);
+      be[d] = A.beta[f];
+      uu[d] = A.u[f];
+    }
+  double *div = A.div + int64_t(load_uniform(A.F.canon, b)) * 64 + m;
+  const double hf = ldexp(1.0, -(M.level + 1));
+  const double hf2 = hf * hf;
+  double sum = *div;
+#pragma unroll
+  for (int d = 0; d < 6; ++d)
+    if ((M.flags >> (8 + d)) & 1u) {
+      const double s = fine_sum(be[d] * hf2 * uu[d], face_interleaved(m, d >> 1));
+      sum = sum + (dev_outside(m, d) ? ((d & 1) ? s : -s) : 0.0);
+    }
+  *div = sum;
 }
 
 struct FluxArgs {
-  const int64_t *owner, *other;  // canonical face list
-  const int8_t *dir, *kind;
-  const int8_t *level;           // per canonical leaf brick
-  const uint64_t *act;           // per canonical leaf brick
+  FaceTables F;
   const double *beta;
   const double *p;               // canonical leaf order
   int bc[6];
   double theta;
-  int64_t n_faces;
   double *u;                     // canonical face order, updated in place
 };
 
-__device__ __forceinline__ bool flux_active(const FluxArgs &A, int64_t cell) {
-  return (A.act[cell >> 6] >> (cell & 63)) & 1ull;
-}
-
-// One thread per canonical face: u_f -= s_o F_f / (beta_f h_o^2).
-__global__ void k_project_velocity(FluxArgs A) {
-  int64_t f = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (f >= A.n_faces) return;
-  double beta = A.beta[f];
-  if (!(beta > 0.0)) return;
-  int64_t o = A.owner[f];
-  int64_t t = A.other[f];
-  int k = A.kind[f];
-  int d = A.dir[f];
-  double h = ldexp(1.0, -int(A.level[o >> 6]));
-  double F = 0.0;
-  if (flux_active(A, o)) {
-    if (k == 0) {
-      if (A.bc[d] == 1) F = beta * (h / A.theta) * A.p[o];
-    } else if (flux_active(A, t)) {
-      if (k == 1) {
-        F = beta * h * (A.p[o] - A.p[t]);
-      } else {
-        int64_t base = o & ~int64_t(7);
-        double s = 0.0;
-        int n = 0;
-        for (int q = 0; q < 8; ++q)
-          if (flux_active(A, base + q)) {
-            s += A.p[base + q];
-            ++n;
-          }
-        double pbar = n ? s / double(n) : 0.0;
-        F = beta * h * (pbar - A.p[t]) / 2.0;
-      }
+// One wave per leaf brick: u_f -= s_o F_f / (beta_f h_o^2) on the faces its
+// cells own.  F_f is proportional to beta_f, so the step is the pressure
+// difference over the cell size (a multiplication by a power of two), halved
+// at a T-junction and over theta at a wall.
+// The faces are loaded and stored in order, the cells' steps going through LDS.
+__global__ void __launch_bounds__(kBlock) k_project_velocity(FluxArgs A) {
+  __shared__ double slots[kWavesPerBlock][kFaceSlots];
+  double *sq = slots[wave_id()];
+  const FaceLane L = face_lane();
+  const double inv_theta = 1.0 / A.theta;
+  const WaveLoop W = wave_loop(A.F.T.nlb);
+  for (uint32_t b = W.first; b < W.end; b += W.step) {
+    const BrickMeta M = load_meta(A.F.T.meta, b);
+    const double *const x[1] = {A.p};
+    const double po[1] = {
+        (A.p + int64_t(load_uniform(A.F.canon, b)) * 64)[uint32_t(L.m)]};
+    const int64_t f0 = A.F.base(b);
+    const uint32_t nf = face_total(M.flags);
+    double beta[4], u[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t k = uint32_t(i * kWave + L.m);
+      beta[i] = k < nf ? (A.beta + f0)[k] : 0.0;
+      u[i] = k < nf ? (A.u + f0)[k] : 0.0;
     }
+    const AcrossFaces<1> N = across_faces<1>(A.F, M, L.m, x, po);
+    const double inv_h = ldexp(1.0, M.level);
+    const bool act = (act_mask(M) >> L.m) & 1ull;
+    const double pbar = (M.flags & kFlagT) ? active_mean(M, L.m, po[0]) : 0.0;
+    uint32_t slot = first_slot(M.flags, uint32_t(L.m), L.cnt);
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      if ((d & 1) && !owns_plus(M.flags, d)) continue;
+      const bool out = (L.out >> d) & 1u;
+      double q = 0.0;
+      if (act && N.on[d]) q = (po[0] - N.v[0][d]) * inv_h;
+      if (M.nbr[d] == dWall) {
+        const double w = act && A.bc[d] == 1 ? po[0] * inv_theta * inv_h : 0.0;
+        q = out ? w : q;
+      } else if ((M.flags >> d) & 1u) {
+        const double w = act && N.on[d] ? (pbar - N.v[0][d]) * (0.5 * inv_h) : 0.0;
+        q = out ? w : q;
+      }
+      if (owns_face(M.flags, L.out, d)) sq[slot++] = (d & 1) ? -q : q;
+    }
+    wave_lds_fence();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t k = uint32_t(i * kWave + L.m);
+      if (k < nf && beta[i] > 0.0) (A.u + f0)[k] = u[i] + sq[k];
+    }
+    wave_lds_fence();
   }
-  double sgn = (d & 1) ? 1.0 : -1.0;
-  A.u[f] -= sgn * F / (beta * h * h);
 }
 
-// Parts of RMS_V over the active leaves of a canonical-order divergence:
-// what = 0: sum of div_i^2 / V_i (= V_i (div_i / V_i)^2), 1: sum of V_i.
+// Parts of RMS_V over the active leaves of a canonical-order divergence: the
+// partials of the sum of div_i^2 / V_i (= V_i (div_i / V_i)^2) go to
+// P.partials, those of the sum of V_i to `vol`.
 __global__ void __launch_bounds__(kBlock) k_div_rms_part(PcgArgs P, const double *div,
-                                                         int what) {
-  double part = 0.0;
+                                                         double *vol) {
+  double part = 0.0, vpart = 0.0;
   LEAF_LOOP(P) {
-    const BrickMeta M = P.T.meta[b];
+    const BrickMeta M = load_meta(P.T.meta, b);
     if ((act_mask(M) >> m) & 1ull) {
       double V = ldexp(1.0, -3 * M.level);
       double x = div[int64_t(P.canon[b]) * 64 + m];
-      part += what ? V : x * x / V;
+      part += x * x / V;
+      vpart += V;
     }
   }
   block_partial(part, P.partials);
+  __syncthreads();  // block_partial's shared slots are read before they change
+  block_partial(vpart, vol);
 }
 
 }  // namespace mfmg
