@@ -24,7 +24,9 @@
  *   - "device" pointers are HIP device memory of the current device; "host"
  *     pointers are ordinary host memory.  The caller owns every buffer it
  *     passes; the library owns only the objects it returns, which the
- *     matching mfmg_destroy_* call frees.
+ *     matching mfmg_destroy_* call frees.  Their device memory is kept for the
+ *     next objects (at most 8 GiB per device; blocks not used again for a
+ *     while, and all of them when an allocation fails, go back to the driver).
  *   - stream is a hipStream_t (NULL = the default stream).  Every call
  *     enqueues its device work on that stream and returns after the work it
  *     needs has completed; statistics are valid on return.

@@ -7,7 +7,9 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
+#include <list>
 #include <mutex>
+#include <new>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -49,6 +51,115 @@ mfmg_status hip_fail(const HipError &e) {
               std::string(e.what) + ": " + hipGetErrorString(e.e));
 }
 
+// Device memory of the library's objects.  hipMalloc and hipFree map, clear
+// and unmap pages: a program that rebuilds its octree and hierarchy every step
+// (4 GB of them at 26.3M leaves) spent most of the rebuild in them (123 ms, of
+// which the kernels are 5; 7.3 ms with this pool).  Freed blocks are kept per
+// device and handed out again by size, which is rounded up by at most an
+// eighth.  At most kPoolBytes are kept (the least recently freed go back to
+// the driver first), a block not asked for within kPoolAge frees goes back
+// too, and everything does when an allocation fails.  A block is put back only
+// after the device has finished its work (as hipFree waited), so any stream
+// and thread may take it.
+class DevicePool {
+ public:
+  static size_t rounded(size_t bytes) {
+    size_t step = 512;
+    while (step * 8 < bytes) step *= 2;
+    return (bytes + step - 1) / step * step;
+  }
+  // bytes: a rounded size
+  hipError_t get(size_t bytes, void **out) {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      for (auto it = kept_.rbegin(); it != kept_.rend(); ++it)
+        if (it->bytes == bytes) {
+          *out = it->p;
+          held_ -= bytes;
+          kept_.erase(std::next(it).base());
+          return hipSuccess;
+        }
+    }
+    hipError_t e = hipMalloc(out, bytes);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      std::lock_guard<std::mutex> lock(mu_);
+      trim(0, 0);
+      e = hipMalloc(out, bytes);
+    }
+    return e;
+  }
+  void put(void *p, size_t bytes) {
+    std::lock_guard<std::mutex> lock(mu_);
+    try {
+      kept_.push_back(Block{p, bytes, ++frees_});
+    } catch (const std::bad_alloc &) {
+      (void)hipFree(p);
+      return;
+    }
+    held_ += bytes;
+    trim(kPoolBytes, frees_ > kPoolAge ? frees_ - kPoolAge : 0);
+  }
+
+ private:
+  static constexpr size_t kPoolBytes = size_t(8) << 30;
+  static constexpr uint64_t kPoolAge = 512;
+  struct Block {
+    void *p;
+    size_t bytes;
+    uint64_t when;
+  };
+  void trim(size_t most, uint64_t oldest) {
+    while (!kept_.empty() && (held_ > most || kept_.front().when < oldest)) {
+      (void)hipFree(kept_.front().p);
+      held_ -= kept_.front().bytes;
+      kept_.pop_front();
+    }
+  }
+  std::mutex mu_;
+  std::list<Block> kept_;  // least recently freed first
+  size_t held_ = 0;
+  uint64_t frees_ = 0;
+};
+
+// The pool of a device.  Never destroyed: the runtime may be gone by the time
+// static objects are, and the driver takes the memory back at exit.
+DevicePool &device_pool(int dev) {
+  static std::mutex mu;
+  static std::vector<DevicePool *> *pools = new std::vector<DevicePool *>();
+  std::lock_guard<std::mutex> lock(mu);
+  while (pools->size() <= size_t(dev)) pools->push_back(new DevicePool());
+  return *(*pools)[size_t(dev)];
+}
+
+// While one is alive and armed, the buffers that this thread frees are known
+// to have no work pending (their stream, or the device, has drained).
+thread_local int t_drained = 0;
+struct Drained {
+  bool on = false;
+  void arm() {
+    if (!on) ++t_drained;
+    on = true;
+  }
+  ~Drained() {
+    if (on) --t_drained;
+  }
+};
+
+// Device current for a scope (an object may be destroyed with another one
+// current).
+struct DeviceScope {
+  int was = -1;
+  explicit DeviceScope(int dev) {
+    int now = -1;
+    if (hipGetDevice(&now) == hipSuccess && now != dev && hipSetDevice(dev) == hipSuccess)
+      was = now;
+  }
+  ~DeviceScope() {
+    if (was >= 0) (void)hipSetDevice(was);
+  }
+};
+
 template <class T>
 struct DevBuf {
   T *p = nullptr;
@@ -56,22 +167,77 @@ struct DevBuf {
   DevBuf() = default;
   DevBuf(const DevBuf &) = delete;
   DevBuf &operator=(const DevBuf &) = delete;
-  ~DevBuf() {
-    if (p) (void)hipFree(p);
-  }
+  ~DevBuf() { release(); }
   void alloc(size_t count) {
-    if (p) (void)hipFree(p);
-    p = nullptr;
-    n = count;
+    release();
     if (count == 0) return;
-    HIP_CHECK(hipMalloc(&p, count * sizeof(T)));
+    bytes_ = DevicePool::rounded(count * sizeof(T));
+    HIP_CHECK(hipGetDevice(&dev_));
+    HIP_CHECK(device_pool(dev_).get(bytes_, reinterpret_cast<void **>(&p)));
+    n = count;
   }
   void upload(const std::vector<T> &v, hipStream_t s) {
     alloc(v.size());
     if (!v.empty())
       HIP_CHECK(hipMemcpyAsync(p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s));
   }
+
+ private:
+  size_t bytes_ = 0;
+  int dev_ = 0;
+  void release() {
+    if (!p) return;
+    DeviceScope scope(dev_);
+    if (!t_drained) (void)hipDeviceSynchronize();
+    device_pool(dev_).put(p, bytes_);
+    p = nullptr;
+    n = 0;
+  }
 };
+
+// Pinned host memory that a solve's kernels and copies write, one page per
+// hierarchy; freed pages are kept (at most kPinnedKept) and used again.
+struct HostPage {
+  Scalars S;  // the scalars read back after a solve
+  int done;   // stop flag written by k_finish
+};
+constexpr size_t kPinnedKept = 16;
+struct PinnedPages {
+  std::mutex mu;
+  std::vector<HostPage *> kept;
+};
+PinnedPages &pinned_pages() {
+  static PinnedPages *p = new PinnedPages();
+  return *p;
+}
+HostPage *take_page() {
+  PinnedPages &P = pinned_pages();
+  {
+    std::lock_guard<std::mutex> lock(P.mu);
+    if (!P.kept.empty()) {
+      HostPage *h = P.kept.back();
+      P.kept.pop_back();
+      return h;
+    }
+  }
+  HostPage *h = nullptr;
+  HIP_CHECK(hipHostMalloc(&h, sizeof(HostPage), hipHostMallocMapped | hipHostMallocPortable));
+  return h;
+}
+void give_page(HostPage *h) {
+  PinnedPages &P = pinned_pages();
+  {
+    std::lock_guard<std::mutex> lock(P.mu);
+    if (P.kept.size() < kPinnedKept) {
+      try {
+        P.kept.push_back(h);
+        return;
+      } catch (const std::bad_alloc &) {
+      }
+    }
+  }
+  (void)hipHostFree(h);
+}
 
 inline unsigned grid_for(int64_t bricks) {
   int64_t g = (bricks + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -163,6 +329,7 @@ struct DeviceTopology {
   DevBuf<int32_t> canon;              // device leaf brick -> canonical leaf brick
   std::vector<Range> range;           // per level
   uint32_t nlb = 0, nb = 0;
+  int device = 0;                     // current device when it was made
 };
 
 // An octree built on the host keeps its host topology (and makes its device
@@ -186,6 +353,7 @@ struct mfmg_coeffs {
 
 struct mfmg_hierarchy {
   const mfmg_coeffs *co = nullptr;
+  int device = 0;  // current device when it was built
   mfmg_mg_params prm{};
   int L = 0, lc = 0;
   DevBuf<BrickMeta> meta;  // topology records with this hierarchy's activity masks
@@ -223,8 +391,9 @@ struct mfmg_hierarchy {
   std::vector<uint32_t> couple_lo, couple_n;
   DevBuf<float> T32[4];
   DevBuf<double> rA;              // adjoint PCG residual
-  Scalars *hostS = nullptr;      // pinned: the scalars read back after a solve
-  int *host_done = nullptr;      // pinned, mapped: stop flag written by k_finish
+  HostPage *page = nullptr;      // pinned, mapped
+  Scalars *hostS = nullptr;      // in it: the scalars read back after a solve
+  int *host_done = nullptr;      // in it: stop flag written by k_finish
   int *host_done_dev = nullptr;  // its device address
   hipEvent_t iter_ev[2] = {nullptr, nullptr};
   hipStream_t cap_stream = nullptr;                 // capture-only stream of the graphs
@@ -241,8 +410,7 @@ struct mfmg_hierarchy {
   ~mfmg_hierarchy() {
     drop_graphs();
     if (cap_stream) (void)hipStreamDestroy(cap_stream);
-    if (hostS) (void)hipHostFree(hostS);
-    if (host_done) (void)hipHostFree(host_done);
+    if (page) give_page(page);
     for (hipEvent_t e : iter_ev)
       if (e) (void)hipEventDestroy(e);
   }
@@ -355,7 +523,21 @@ extern "C" mfmg_status mfmg_octree_faces(const mfmg_octree *t, int64_t *owner, i
   return MFMG_OK;
 }
 
-extern "C" void mfmg_destroy_octree(mfmg_octree *t) { delete t; }
+// Destroys an object whose buffers may still be in use on some stream: one
+// wait for the device instead of one per buffer.
+template <class T>
+static void destroy_drained(T *t, int dev) {
+  if (!t) return;
+  DeviceScope scope(dev);
+  Drained quiet;
+  if (hipDeviceSynchronize() == hipSuccess) quiet.arm();
+  delete t;
+}
+
+extern "C" void mfmg_destroy_octree(mfmg_octree *t) {
+  if (t && t->dt) destroy_drained(t, t->dt->device);
+  else delete t;
+}
 
 // --------------------------------------------------------------------------
 // device topology and coefficients
@@ -364,6 +546,7 @@ extern "C" void mfmg_destroy_octree(mfmg_octree *t) { delete t; }
 // then inner bricks) to its device id.
 static void build_device_topology(const Topology &T, DeviceTopology &D, hipStream_t s) {
   int64_t nlb = T.n_leaf_bricks, nb = T.n_bricks;
+  HIP_CHECK(hipGetDevice(&D.device));
   D.nlb = uint32_t(nlb);
   D.nb = uint32_t(nb);
   std::vector<int32_t> perm(nb, -1);
@@ -455,6 +638,7 @@ static std::shared_ptr<DeviceTopology> device_topology(const mfmg_octree *t, hip
 
 // exclusive scan of x[0, n) in place on stream s; *total (device) = sum
 static void scan_exclusive(int64_t *x, int64_t n, int64_t *total, hipStream_t s) {
+  Drained quiet;
   int64_t tiles = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
   DevBuf<int64_t> t;
   t.alloc(size_t(tiles));
@@ -463,6 +647,7 @@ static void scan_exclusive(int64_t *x, int64_t n, int64_t *total, hipStream_t s)
   hipLaunchKernelGGL(k_scan_add, dim3(unsigned(tiles)), dim3(256), 0, s, x, n,
                      (const int64_t *)t.p);
   HIP_CHECK(hipStreamSynchronize(s));  // t is freed on return
+  quiet.arm();
 }
 
 static unsigned key_grid(uint64_t nk) {
@@ -474,6 +659,7 @@ static unsigned key_grid(uint64_t nk) {
 static std::string build_octree_device(const mfmg_refine_spec *spec,
                                        const std::vector<Prim> &prims, hipStream_t s,
                                        mfmg_octree &t) {
+  Drained quiet;
   if (spec->node_size != kBrick) return "node_size must be 4";
   int lmin = spec->min_level, lmax = spec->max_level;
   if (lmin < kMinLevel || lmax > kMaxLevel || lmin > lmax)
@@ -553,6 +739,7 @@ static std::string build_octree_device(const mfmg_refine_spec *spec,
                        inner_lo[l], bkey.p, blev.p);
   std::shared_ptr<DeviceTopology> dp(new DeviceTopology());
   DeviceTopology &D = *dp;
+  HIP_CHECK(hipGetDevice(&D.device));
   D.nlb = uint32_t(nlb);
   D.nb = uint32_t(nb);
   D.range.assign(lmax + 1, Range{0, 0, 0, 0});
@@ -605,6 +792,7 @@ static std::string build_octree_device(const mfmg_refine_spec *spec,
   HIP_CHECK(hipMemcpyAsync(&eh, err.p, sizeof(int), hipMemcpyDeviceToHost, s));
   HIP_CHECK(hipGetLastError());
   HIP_CHECK(hipStreamSynchronize(s));
+  quiet.arm();
   if (eh) return "octree is not 2:1 balanced";
   t.on_host = false;
   t.min_level = lmin;
@@ -802,7 +990,9 @@ extern "C" mfmg_status mfmg_coeffs_leaf(const mfmg_coeffs *co, double *out, void
   return MFMG_OK;
 }
 
-extern "C" void mfmg_destroy_coeffs(mfmg_coeffs *co) { delete co; }
+extern "C" void mfmg_destroy_coeffs(mfmg_coeffs *co) {
+  if (co) destroy_drained(co, co->dt->device);
+}
 
 // --------------------------------------------------------------------------
 // hierarchy
@@ -843,6 +1033,7 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     std::unique_ptr<mfmg_hierarchy> h(new mfmg_hierarchy());
     const DeviceTopology &D = *co->dt;
     h->co = co;
+    HIP_CHECK(hipGetDevice(&h->device));
     h->prm = *prm;
     h->lc = prm->coarsest_level;
     h->L = 0;
@@ -904,8 +1095,9 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
                                         int64_t(level_grid(nlb)) + kMaxReduceBlocks));
     h->S.alloc(1);
     HIP_CHECK(hipMemsetAsync(h->S.p, 0, sizeof(Scalars), s));
-    HIP_CHECK(hipHostMalloc(&h->hostS, sizeof(Scalars), hipHostMallocDefault));
-    HIP_CHECK(hipHostMalloc(&h->host_done, sizeof(int), hipHostMallocMapped));
+    h->page = take_page();
+    h->hostS = &h->page->S;
+    h->host_done = &h->page->done;
     HIP_CHECK(hipHostGetDevicePointer((void **)&h->host_done_dev, h->host_done, 0));
     *h->host_done = 0;
     for (hipEvent_t &e : h->iter_ev)
@@ -1072,7 +1264,9 @@ extern "C" mfmg_status mfmg_hierarchy_level_coeffs(const mfmg_hierarchy *h, int 
   return MFMG_OK;
 }
 
-extern "C" void mfmg_destroy_hierarchy(mfmg_hierarchy *h) { delete h; }
+extern "C" void mfmg_destroy_hierarchy(mfmg_hierarchy *h) {
+  if (h) destroy_drained(h, h->device);
+}
 
 // --------------------------------------------------------------------------
 // cycle driver
@@ -1378,6 +1572,7 @@ void alloc_transpose(const mfmg_hierarchy *hc, DevBuf<V> (&T)[4]) {
 // (those with an inner face neighbour), per level, made at first use.
 static void ensure_coupling_lists(mfmg_hierarchy *h, hipStream_t s) {
   if (!h->couple_n.empty()) return;
+  Drained quiet;
   const DeviceTopology &D = *h->co->dt;
   uint32_t nlb = D.nlb;
   std::vector<int64_t> pos(size_t(nlb) + 1, 0);
@@ -1405,6 +1600,7 @@ static void ensure_coupling_lists(mfmg_hierarchy *h, hipStream_t s) {
     h->couple_n[l] = uint32_t(pos[R.leaf_lo + R.n_leaf] - pos[R.leaf_lo]);
   }
   HIP_CHECK(hipStreamSynchronize(s));  // work is freed on return
+  quiet.arm();
 }
 
 // The transposed cycle's arrays and lists, made at first use.
