@@ -1268,398 +1268,381 @@ __global__ void __launch_bounds__(1024) k_coarsest(LevelArgs<V, CL, CI> A, int n
   }
 }
 
+// ---------------------------------------------------------------------------
 // The FAS step of level f = lc + 1 in one workgroup (Algorithm 4 on that
 // level: FAS right-hand side, pre-smoothing, residual restriction, mu
 // coarsest solves, prolongation, post-smoothing) when level f is a complete
-// grid of at most kCoarsestBricks bricks without T-junctions and the
-// coarsest level has at most kBottomCoarse bricks.  Both iterates stay in
-// LDS and each wave keeps the coefficients of its bricks in registers, so
+// grid (no T-junction) of at most 16^3 cells.  Both iterates stay in LDS, so
 // the dozen launches of a few microseconds each that the separate kernels
-// take become one.  Every value read and the order of every sum are those
-// of k_fas_rhs, k_smooth, k_restrict, k_coarsest and k_prolong, and the
-// arrays in memory end as those kernels leave them.  MULTI: the kernel
-// takes `visits` consecutive FAS steps of level f (the level above's mu),
-// both iterates staying in LDS from one to the next; otherwise one step per
-// launch.  fas = 0 skips the FAS right-hand side of the first step (a
-// W-cycle's later visits: it is already in B).  The FP64 cycle takes one
-// step per launch: with the loop its registers spill further (120 against
-// 88 bytes per lane) and the W-cycle got slower.
-// TR: the same step of the transposed cycle (fas_T of level f) when the
-// coarsest level has no leaves: fas = 1 starts from a zero iterate, the
-// restriction hands the plain residual sums down and the coarsest iterate
-// starts from zero, and pscale times it is the correction that comes back.
-constexpr int kBottomCoarse = 1024 / kWave;
+// take become one.  The sums and their order are those of k_fas_rhs,
+// k_smooth, k_restrict, k_coarsest and k_prolong, and the arrays in memory
+// end as those kernels leave them.  `visits` consecutive FAS steps of level f
+// (the level above's mu) are taken in one launch.  fas = 0 skips the FAS
+// right-hand side of the first one (a W-cycle's later visits: it is already
+// in B).
+// TR: the same step of the transposed cycle: fas = 1 starts from a zero
+// iterate, the restriction hands the plain residual sums down, the coarsest
+// iterate starts from zero and pscale times it is the correction.
+//
+// What bounds it: one CU's LDS reads, the barriers and the set-up's loads.  A
+// thread holds pairs of cells that are neighbours along x, one of each colour,
+// so every lane has a cell to update in every half-sweep, and neighbouring
+// lanes read neighbouring LDS words.  Six face coefficients per cell, in the
+// stencil's order, come from a table made with the hierarchy (k_bottom_table):
+// a brick per wave with its coefficients formed at each launch took 21 us per
+// FP32 V-cycle step (8.5 of it set-up, 0.75 per half-sweep of 16^3 cells with
+// half of the lanes idle) and 29 us in FP64, where it spilled registers; this
+// form takes 12.3 and 24.5 us (a W-cycle's two visits, FP32: 34 -> 21 us).
+// ---------------------------------------------------------------------------
 
-// Six local neighbour indices in [-1, 63] packed as bytes (-1: wall).
-__device__ __forceinline__ uint64_t pack_nbr(const BrickMeta &M, const Range &R, uint32_t nlb) {
-  uint64_t v = 0;
-#pragma unroll
-  for (int d = 0; d < 6; ++d) {
-    int32_t nb = M.nbr[d];
-    int32_t loc = nb < 0 ? -1
-                  : uint32_t(nb) < nlb ? nb - int32_t(R.leaf_lo)
-                                       : int32_t(R.n_leaf) + nb - int32_t(R.inner_lo);
-    v |= uint64_t(uint8_t(int8_t(loc))) << (8 * d);
-  }
-  return v;
-}
-__device__ __forceinline__ int32_t unpack_nbr(uint64_t v, int d) {
-  return int32_t(int8_t(uint8_t(v >> (8 * d))));
+// Position of pair (x >> 1, y, z) of a grid of 2^f cells per axis.  The low
+// bits of y and z follow the x bits, so that the four pairs of a parent cell
+// are lanes of one wave and a wave's reads spread over the LDS banks.
+__host__ __device__ __forceinline__ uint32_t pair_index(int f, uint32_t xh, uint32_t y,
+                                                        uint32_t z) {
+  return xh | ((y & 1u) << (f - 1)) | ((z & 1u) << f) | ((y >> 1) << (f + 1)) |
+         ((z >> 1) << (2 * f));
 }
 
-// Fixed part of the stencil of one brick (slot index i of its level) in
-// k_bottom: the six face coefficients as the stencil sees them (own k_a on
-// the minus side, the partner's or the plus-face table's on the plus side),
-// their sum in the stencil's order, and the LDS index of each neighbour
-// value (partner p in this brick or in the neighbouring one; at a wall the
-// index `zero`: an LDS entry that holds 0, or kBottomWall), two 16-bit
-// indices per word.
-template <class V, class CL>
-__device__ __forceinline__ void bottom_faces(const LaneC<V, CL> &L, uint32_t i, uint64_t nbr,
-                                             const V (&kown)[3], const V (&kpl)[3],
-                                             uint32_t zero, V (&k)[6], V &c,
-                                             uint32_t (&lds)[3]) {
-#pragma unroll
-  for (int d = 0; d < 6; ++d) {
-    int a = d >> 1;
-    int p = L.p[d];
-    int32_t nl = unpack_nbr(nbr, d);
-    int32_t nbase = L.out[d] ? (nl >= 0 ? nl * 64 : -1) : int32_t(i) * 64;
-    uint32_t idx = nbase >= 0 ? uint32_t(nbase + p) : zero;
-    if (d & 1) {
-      V ks = shfl(kown[a], p);
-      k[d] = L.out[d] ? kpl[a] : ks;
-      lds[a] |= idx << 16;
-    } else {
-      k[d] = kown[a];
-      lds[a] = idx;
-    }
-  }
-  c = ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
-}
-
-// Neighbour sum of k_bottom's stencil over an LDS iterate (bottom_faces).
-// FP64: a wall reads the zero entry, so the six reads take no branch (mixed
-// W-cycle of the large workload, FP64: 9.98 -> 9.69 ms); FP32: a wall's
-// index is kBottomWall and its read is skipped (reading the zero entry made
-// the FP32 half-sweeps slower: W-cycle 6.24 -> 6.34 ms).  The sums are the
-// same either way.
-constexpr uint32_t kBottomWall = 0xffffu;
+// Table of a level: per pair 12 face coefficients (six of the even-x cell, six
+// of the odd-x one) and one unit of indices, as 16-byte units, unit q of pair
+// p at q * pairs + p.  Index unit: element of the even-x cell in the level
+// arrays (the odd-x cell follows it), activity bits, inner-brick bit.
 template <class V>
-__device__ __forceinline__ V bottom_sum(const V *su, const V (&k)[6], const uint32_t (&lds)[3]) {
-  V S = V(0);
-#pragma unroll
-  for (int d = 0; d < 6; ++d) {
-    uint32_t idx = (lds[d >> 1] >> (16 * (d & 1))) & 0xffffu;
-    V v;
-    if constexpr (sizeof(V) == 8) v = su[idx];
-    else v = idx != kBottomWall ? su[idx] : V(0);
-    S += k[d] * v;
-  }
-  return S;
-}
+struct BottomUnits {
+  static constexpr int kPer = 16 / int(sizeof(V));  // coefficients per unit
+  static constexpr int kCoef = 12 / kPer;
+  static constexpr int kAll = kCoef + 1;
+};
 
-// k_bottom's set-up loads of a brick's own face coefficients (axes 1-3),
-// raw: the store that does not hold the brick is addressed out of range and
-// reads 0, so the loads of all slots issue without a branch between them.
-template <class V, class CL, class CI, int CP>
-__device__ __forceinline__ void own_coef_raw(const LevelView<V, CL, CI, CP> &X, uint32_t b,
-                                             bool inner, uint32_t m, CI (&ri)[3],
-                                             CL (&rl)[3]) {
+template <class V, class CL, class CI>
+__global__ void __launch_bounds__(kBlock) k_bottom_table(LevelArgs<V, CL, CI> A, int f,
+                                                         uint4 *tab) {
+  const LaneC<V, CL> L = lane_consts<V, CL>();
+  const LevelView<V, CL, CI> X = level_view(A);
+  const uint32_t i = blockIdx.x * kWavesPerBlock + wave_id();
+  if (i >= A.R.n()) return;
+  const bool inner = i >= A.R.n_leaf;
+  const uint32_t b = A.R.brick(i);
+  const BrickMeta M = load_meta(X.meta, b);
+  const int m = int(L.m);
+  V k[6];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    uint32_t comp = uint32_t(1 + a);
-    uint32_t oi = inner ? ((b - X.nlb) * 256u + comp * 64u) * uint32_t(sizeof(CI)) : kOutOfRange;
-    uint32_t ol = inner ? kOutOfRange : (b * 256u + comp * 64u) * uint32_t(sizeof(CL));
-    ri[a] = bload_bytes<CI, coef_pol(CP)>(X.ci, m * uint32_t(sizeof(CI)), oi);
-    rl[a] = bload_bytes<CL, coef_pol(CP)>(X.cl, m * uint32_t(sizeof(CL)), ol);
+    V kown = inner ? own_coef<true>(X, b, 1 + a, L.m) : own_coef<false>(X, b, 1 + a, L.m);
+    V kl = V(bload_bytes<CL>(X.pf, L.foff[a], b * uint32_t(48 * sizeof(CL))));
+    V ks = shfl(kown, L.p[2 * a + 1]);
+    k[2 * a] = kown;
+    k[2 * a + 1] = L.out[2 * a + 1] ? kl : ks;
   }
-}
-// The coefficient own_coef gives, from own_coef_raw's values.
-template <class V, class CL, class CI, int CP>
-__device__ __forceinline__ V own_coef_of(const LevelView<V, CL, CI, CP> &X, bool inner, CI ri,
-                                         CL rl) {
-  if (inner) {
-    V v = V(ri);
-    if constexpr (std::is_same<CL, CI>::value) return v;
-    else return v * X.iscale;
+  const uint32_t x = uint32_t(M.coord[0] * 4 + dev_cx(m)), y = uint32_t(M.coord[1] * 4 + dev_cy(m)),
+                 z = uint32_t(M.coord[2] * 4 + dev_cz(m));
+  const uint32_t np = 1u << (3 * f - 1), p = pair_index(f, x >> 1, y, z), e = x & 1u;
+  constexpr uint32_t per = uint32_t(BottomUnits<V>::kPer);
+#pragma unroll
+  for (uint32_t d = 0; d < 6; ++d) {
+    const uint32_t q = e * 6u + d;
+    reinterpret_cast<V *>(tab + (q / per) * np + p)[q % per] = k[d];
   }
-  return V(rl);
+  if (e == 0) {
+    const uint64_t act = act_mask(M);
+    const uint32_t bits = uint32_t((act >> m) & 3ull) | (inner ? 4u : 0u);
+    tab[uint32_t(BottomUnits<V>::kCoef) * np + p] = uint4{b * 64u + uint32_t(m), bits, 0u, 0u};
+  }
 }
 
-template <class V, class CL, class CI, bool MULTI, bool TR = false>
-__global__ void __launch_bounds__(1024) k_bottom(LevelArgs<V, CL, CI> Af, LevelArgs<V, CL, CI> Ac,
-                                                 int nu_pre, int nu_post, int nu_coarse, int half,
-                                                 int mu, int fas, int visits, V scale,
-                                                 V pscale) {
-  if (Af.done && *Af.done) return;
-  // the iterates of level f and of the coarsest level, each with a zero
-  // entry after it that FP64's wall reads take (bottom_sum)
-  constexpr uint32_t kZf = kCoarsestBricks * 64, kZc = kBottomCoarse * 64;
-  constexpr uint32_t kWf = sizeof(V) == 8 ? kZf : kBottomWall;
-  constexpr uint32_t kWc = sizeof(V) == 8 ? kZc : kBottomWall;
-  __shared__ V uf[kZf + 1];
-  __shared__ V uc[kZc + 1];
-  __shared__ V bc[kBottomCoarse * 64];    // restricted residual of its inner cells
-  __shared__ V sc[kBottomCoarse * 64];    // u* of its inner cells
-  const LaneC<V, CL> L = lane_consts<V, CL>();
-  const LevelView<V, CL, CI> Xf = level_view(Af);
-  const LevelView<V, CL, CI> Xc = level_view(Ac);
-  const uint32_t w = wave_id();
-  const uint32_t nw = blockDim.x / kWave;
-  const uint32_t nf = Af.R.n(), nc = Ac.R.n();
-  const uint32_t m = L.m;
-  // FP32: the set-up issues every slot's loads before it uses any (set-up
-  // of a V-cycle's launch 12.2 -> 8.5 us; before, each inner coefficient
-  // load waited in a branch of its own), and the half-sweeps read every
-  // slot's neighbours before any slot writes.  FP64 goes slot by slot: the
-  // values held would add to its register spills.
-  constexpr bool kBatch = sizeof(V) == 4;
-  if (threadIdx.x == 0) {
-    uf[kZf] = V(0);
-    uc[kZc] = V(0);
-  }
-  // per slot: right-hand side, the six face coefficients as the stencil
-  // sees them and their sum (the diagonal), and the LDS index of each of the
-  // six neighbour values (two 16-bit indices per word); all fixed for the
-  // whole kernel, so the half-sweeps only read LDS and add
-  V rf[kCoarsestSlots], kf[kCoarsestSlots][6], cf[kCoarsestSlots];
-  uint32_t lf[kCoarsestSlots][3];
-  uint64_t af[kCoarsestSlots];
-  uint32_t parf[kCoarsestSlots];  // 64 x (parent's local index) + 8 x octant
-  if constexpr (kBatch) {
-    CI ri[kCoarsestSlots][3];
-    CL rl[kCoarsestSlots][3], rp[kCoarsestSlots][3];
-    V ru[kCoarsestSlots];
+// One pair of a level in k_bottom.  The LDS iterate is one array per colour,
+// indexed by pair; entry `pairs` of each holds 0, the value at a wall.  A
+// cell's neighbours all lie in the other colour's array, and the y and z ones
+// at the same entries for both cells of the pair.
+template <class V>
+struct BottomPair {
+  V k[2][6];         // by colour
+  V rc[2];           // 1 / diagonal
+  V rhs[2];
+  uint32_t x[2][2];  // entries of the -x and +x neighbours, by colour
+  uint32_t y[2], z[2];
+  uint32_t at;       // element of the even-x cell in the level arrays
+  uint32_t bits;     // 1, 2: active by colour; 4: inner brick; 8: the pair
+                     // exists; 16: the colour-0 cell is the odd-x one
+};
+// stride between the colours' arrays
+__host__ __device__ constexpr uint32_t bottom_stride(uint32_t pairs) { return pairs + 32u; }
+
+template <class V>
+__device__ __forceinline__ V diag_of(const V (&k)[6]) {
+  return ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
+}
+
+template <class V>
+__device__ __forceinline__ BottomPair<V> bottom_pair(const uint4 *tab, int f, uint32_t p) {
+  BottomPair<V> P;
+  const uint32_t np = 1u << (3 * f - 1), n = 1u << f;
+  P.bits = 0;
+  if (p >= np) return P;
+  uint4 unit[BottomUnits<V>::kAll];
 #pragma unroll
-    for (int j = 0; j < kCoarsestSlots; ++j) {
-      uint32_t i = w + uint32_t(j) * nw;
-      if (i >= nf) continue;
-      uint32_t b = Af.R.brick(i);
-      own_coef_raw(Xf, b, i >= Af.R.n_leaf, m, ri[j], rl[j]);
+  for (int q = 0; q < BottomUnits<V>::kAll; ++q) unit[q] = tab[uint32_t(q) * np + p];
+  const uint32_t xh = p & ((n >> 1) - 1u);
+  const uint32_t y = ((p >> (f - 1)) & 1u) | (((p >> (f + 1)) & ((n >> 1) - 1u)) << 1);
+  const uint32_t z = ((p >> f) & 1u) | ((p >> (2 * f)) << 1);
+  const uint32_t e0 = (y + z) & 1u;  // x parity of the colour-0 cell
+  V ke[2][6];
+  constexpr int per = BottomUnits<V>::kPer;
 #pragma unroll
-      for (int a = 0; a < 3; ++a)
-        rp[j][a] = bload_bytes<CL>(Xf.pf, L.foff[a], b * uint32_t(48 * sizeof(CL)));
-      rf[j] = bload<V>(Xf.b, m, b * 64u);
-      ru[j] = bload<V>(Xf.u, m, b * 64u);
-    }
+  for (int e = 0; e < 2; ++e)
 #pragma unroll
-    for (int j = 0; j < kCoarsestSlots; ++j) {
-      uint32_t i = w + uint32_t(j) * nw;
-      if (i >= nf) continue;
-      bool inner = i >= Af.R.n_leaf;
-      const BrickMeta M = load_meta(Xf.meta, Af.R.brick(i));
-      af[j] = act_mask(M);
-      V kown[3], kpl[3];
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        kown[a] = own_coef_of(Xf, inner, ri[j][a], rl[j][a]);
-        kpl[a] = V(rp[j][a]);
+    for (int d = 0; d < 6; ++d) {
+      const int q = e * 6 + d;
+      const uint4 un = unit[q / per];
+      if constexpr (sizeof(V) == 4) {
+        const uint32_t w = q % per == 0 ? un.x : (q % per == 1 ? un.y : (q % per == 2 ? un.z : un.w));
+        ke[e][d] = __builtin_bit_cast(V, w);
+      } else {
+        const uint64_t w = q % per == 0 ? (uint64_t(un.y) << 32) | un.x : (uint64_t(un.w) << 32) | un.z;
+        ke[e][d] = __builtin_bit_cast(V, w);
       }
-      bottom_faces(L, i, pack_nbr(M, Af.R, Xf.nlb), kown, kpl, kWf, kf[j], cf[j], lf[j]);
-      parf[j] = (Ac.R.n_leaf + uint32_t(M.parent) - Ac.R.inner_lo) * 64u +
-                uint32_t(octant_of(M)) * 8u;
-      uf[i * 64u + m] = TR && fas ? V(0) : ru[j];
     }
-  } else {
 #pragma unroll
-    for (int j = 0; j < kCoarsestSlots; ++j) {
-      uint32_t i = w + uint32_t(j) * nw;
-      if (i >= nf) continue;
-      bool inner = i >= Af.R.n_leaf;
-      uint32_t b = Af.R.brick(i);
-      const BrickMeta M = load_meta(Xf.meta, b);
-      af[j] = act_mask(M);
-      V kown[3], kpl[3];
-      for (int a = 0; a < 3; ++a) {
-        kown[a] = inner ? own_coef<true>(Xf, b, 1 + a, m) : own_coef<false>(Xf, b, 1 + a, m);
-        kpl[a] = V(bload_bytes<CL>(Xf.pf, L.foff[a], b * uint32_t(48 * sizeof(CL))));
-      }
-      bottom_faces(L, i, pack_nbr(M, Af.R, Xf.nlb), kown, kpl, kWf, kf[j], cf[j], lf[j]);
-      parf[j] = (Ac.R.n_leaf + uint32_t(M.parent) - Ac.R.inner_lo) * 64u +
-                uint32_t(octant_of(M)) * 8u;
-      rf[j] = bload<V>(Xf.b, m, b * 64u);
-      uf[i * 64u + m] = TR && fas ? V(0) : bload<V>(Xf.u, m, b * 64u);
+  for (int d = 0; d < 6; ++d) {
+    P.k[0][d] = e0 ? ke[1][d] : ke[0][d];
+    P.k[1][d] = e0 ? ke[0][d] : ke[1][d];
+  }
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if constexpr (sizeof(V) == 4) P.rc[c] = __builtin_amdgcn_rcpf(diag_of(P.k[c]));
+    else P.rc[c] = V(1) / diag_of(P.k[c]);
+  }
+  const uint32_t ix = unit[BottomUnits<V>::kCoef].x, bits = unit[BottomUnits<V>::kCoef].y;
+  P.at = ix;
+  const uint32_t act = bits & 3u;
+  P.bits = (e0 ? (act >> 1) | ((act & 1u) << 1) : act) | (bits & 4u) | 8u | (e0 << 4);
+  const uint32_t xm = xh > 0u ? p - 1u : np, xp = xh + 1u < (n >> 1) ? p + 1u : np;
+#pragma unroll
+  for (uint32_t c = 0; c < 2; ++c) {  // the even-x cell's +x neighbour is in the pair
+    const bool odd = (e0 ^ c) != 0u;
+    P.x[c][0] = odd ? p : xm;
+    P.x[c][1] = odd ? xp : p;
+  }
+  P.y[0] = y > 0u ? pair_index(f, xh, y - 1u, z) : np;
+  P.y[1] = y + 1u < n ? pair_index(f, xh, y + 1u, z) : np;
+  P.z[0] = z > 0u ? pair_index(f, xh, y, z - 1u) : np;
+  P.z[1] = z + 1u < n ? pair_index(f, xh, y, z + 1u) : np;
+  return P;
+}
+
+// Neighbour sum of the pair's colour-c cell, face coefficients k; s: the other
+// colour's LDS array.
+template <class V>
+__device__ __forceinline__ V bottom_sum(const V *s, const BottomPair<V> &P, const V (&k)[6],
+                                        int c) {
+  V S = k[0] * s[P.x[c][0]];
+  S += k[1] * s[P.x[c][1]];
+  S += k[2] * s[P.y[0]];
+  S += k[3] * s[P.y[1]];
+  S += k[4] * s[P.z[0]];
+  S += k[5] * s[P.z[1]];
+  return S;
+}
+// a over the diagonal of the coefficients k, rc its reciprocal (FP32: as
+// div_by; FP64: the quotient by the reciprocal, corrected once, which rounds
+// as the division does).
+template <class V>
+__device__ __forceinline__ V bottom_div(const V (&k)[6], V rc, V a) {
+  if constexpr (sizeof(V) == 4) return a * rc;
+  const V q = a * rc;
+  return fma(fma(-q, diag_of(k), a), rc, q);
+}
+// Sum over the four pairs of a parent cell (lane bits f - 1 and f).
+template <class T>
+__device__ __forceinline__ T parent_sum(T v, int f) {
+  v = v + shfl_xor(v, 1 << (f - 1));
+  return v + shfl_xor(v, 1 << f);
+}
+
+template <class V>
+struct BottomArgs {
+  const uint4 *tf, *tc;  // tables of level f and of the coarsest level
+  int f;
+  V *U, *B, *Ustar;
+  uint32_t nlb;
+  int nu_pre, nu_post, nu_coarse, half, mu, fas, visits;
+  V scale, pscale;
+  const int *done;
+};
+
+constexpr int kBottomLevel = 4;                            // finest f it takes
+constexpr int kBottomPairs = 1 << (3 * kBottomLevel - 1);  // 2048
+// Threads of the workgroup: 1024 hold two fine pairs each in FP32; FP64's
+// would not fit 128 registers (112 bytes of spills per lane, 26.6 against 24.5
+// us), so half the threads hold four.
+template <class V>
+constexpr int kBottomThreads = sizeof(V) == 8 ? 512 : 1024;
+
+template <class V, bool TR = false>
+__global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
+  if (A.done && *A.done) return;
+  constexpr int kSlots = kBottomPairs / kBottomThreads<V>;
+  constexpr uint32_t nt = uint32_t(kBottomThreads<V>);
+  constexpr uint32_t sf = bottom_stride(kBottomPairs), sg = bottom_stride(kBottomPairs / 8);
+  __shared__ V uf[2 * sf];
+  __shared__ V uc[2 * sg];
+  __shared__ V bc[2 * sg];  // restricted residual of the coarse cells
+  __shared__ V sc[2 * sg];  // their u*
+  typedef V V2 __attribute__((ext_vector_type(2)));
+  const int f = A.f, fc = A.f - 1;
+  const uint32_t np = 1u << (3 * f - 1), npc = 1u << (3 * fc - 1);
+  const uint32_t tid = threadIdx.x;
+  if (tid < 2u) {
+    uf[tid * sf + np] = V(0);
+    uc[tid * sg + npc] = V(0);
+  }
+  BottomPair<V> P[kSlots];
+#pragma unroll
+  for (int j = 0; j < kSlots; ++j) {
+    const uint32_t p = tid + uint32_t(j) * nt;
+    P[j] = bottom_pair<V>(A.tf, f, p);
+    if (P[j].bits & 8u) {
+      const bool odd = P[j].bits & 16u;
+      const V2 b2 = *reinterpret_cast<const V2 *>(A.B + P[j].at);
+      V2 u2 = V2{V(0), V(0)};
+      if (!(TR && A.fas)) u2 = *reinterpret_cast<const V2 *>(A.U + P[j].at);
+      P[j].rhs[0] = odd ? b2.y : b2.x;
+      P[j].rhs[1] = odd ? b2.x : b2.y;
+      uf[p] = odd ? u2.y : u2.x;
+      uf[sf + p] = odd ? u2.x : u2.y;
     }
   }
-  // the coarsest level: coefficients (loaded now, used after the
-  // restriction); its leaf bricks keep their iterate and right-hand side
-  V rc = V(0);
-  V kc[6], cc = V(0);
-  uint32_t lc[3] = {0xffffffffu, 0xffffffffu, 0xffffffffu};
-  uint64_t ac = 0;
-  bool cin = false;
-  if (w < nc) {
-    cin = w >= Ac.R.n_leaf;
-    uint32_t b = Ac.R.brick(w);
-    const BrickMeta M = load_meta(Xc.meta, b);
-    ac = act_mask(M);
-    V kown[3], kpl[3];
-    for (int a = 0; a < 3; ++a) {
-      kown[a] = cin ? own_coef<true>(Xc, b, 1 + a, m) : own_coef<false>(Xc, b, 1 + a, m);
-      kpl[a] = V(bload_bytes<CL>(Xc.pf, L.foff[a], b * uint32_t(48 * sizeof(CL))));
-    }
-    bottom_faces(L, w, pack_nbr(M, Ac.R, Xc.nlb), kown, kpl, kWc, kc, cc, lc);
-    if (!cin) {
-      rc = bload<V>(Xc.b, m, b * 64u);
-      uc[w * 64u + m] = bload<V>(Xc.u, m, b * 64u);
-    }
+  BottomPair<V> C = bottom_pair<V>(A.tc, fc, tid);
+  // the parent's entry on the coarsest level (its colour's array included)
+  uint32_t par[kSlots];
+#pragma unroll
+  for (int j = 0; j < kSlots; ++j) {
+    const uint32_t p = tid + uint32_t(j) * nt;
+    const uint32_t xh = p & ((1u << (f - 1)) - 1u);
+    const uint32_t py = (p >> (f + 1)) & ((1u << (f - 1)) - 1u), pz = p >> (2 * f);
+    par[j] = ((xh + py + pz) & 1u) * sg + pair_index(fc, xh >> 1, py, pz);
   }
   __syncthreads();
 
-  // neighbour sum and diagonal of slot j of level f from the LDS iterate
-  auto stencil_f = [&](int j, uint32_t i, V &c) {
-    (void)i;
-    c = cf[j];
-    return bottom_sum(uf, kf[j], lf[j]);
-  };
-  // (FP32: every slot's neighbour sum is read before any slot writes: a
-  // cell of the colour reads only cells of the other colour, which no lane
-  // writes in this half-sweep; the other lanes' sums are not used.)
-  auto half_sweep_f = [&](int colour) {
-    if constexpr (kBatch) {
-      V S[kCoarsestSlots];
+  // (the colour is a type, so that its arrays' offsets are constants)
+  auto half_sweep_f = [&](auto colour) {
+    constexpr int c = decltype(colour)::value;
 #pragma unroll
-      for (int j = 0; j < kCoarsestSlots; ++j) {
-        uint32_t i = w + uint32_t(j) * nw;
-        if (i < nf) S[j] = bottom_sum(uf, kf[j], lf[j]);
-      }
-#pragma unroll
-      for (int j = 0; j < kCoarsestSlots; ++j) {
-        uint32_t i = w + uint32_t(j) * nw;
-        if (i >= nf) continue;
-        bool act = (af[j] >> m) & 1ull;
-        if (act && L.colour == colour) uf[i * 64u + m] = div_by(rf[j] + S[j], cf[j]);
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < kCoarsestSlots; ++j) {
-        uint32_t i = w + uint32_t(j) * nw;
-        if (i >= nf) continue;
-        V c;
-        V S = stencil_f(j, i, c);
-        bool act = (af[j] >> m) & 1ull;
-        if (act && L.colour == colour) uf[i * 64u + m] = div_by(rf[j] + S, c);
-      }
+    for (int j = 0; j < kSlots; ++j) {
+      if (!(P[j].bits & 8u)) continue;
+      const V S = bottom_sum(uf + (1 - c) * sf, P[j], P[j].k[c], c);
+      if (P[j].bits & (1u << c))
+        uf[c * sf + tid + uint32_t(j) * nt] =
+            bottom_div(P[j].k[c], P[j].rc[c], P[j].rhs[c] + S);
     }
     __syncthreads();
   };
-
-  auto stencil_c = [&](V &c) {
-    c = cc;
-    return bottom_sum(uc, kc, lc);
-  };
-  for (int visit = 0; visit < (MULTI ? visits : 1); ++visit) {
-    // FAS right-hand side of the inner bricks: b += A u*
-    if (!TR && visit == 0 && fas) {
-#pragma unroll
-      for (int j = 0; j < kCoarsestSlots; ++j) {
-        uint32_t i = w + uint32_t(j) * nw;
-        if (i >= nf || i < Af.R.n_leaf) continue;
-        V c;
-        V S = stencil_f(j, i, c);
-        V u = uf[i * 64u + m];
-        bool act = (af[j] >> m) & 1ull;
-        rf[j] = act ? rf[j] + (c * u - S) : V(0);
-        bstore<V>(Xf.b, m, Af.R.brick(i) * 64u, rf[j]);
-      }
-      __syncthreads();  // every wave's reads of uf before the first writes
+  auto half_sweep_c = [&](auto colour) {
+    constexpr int c = decltype(colour)::value;
+    if (C.bits & (1u << c)) {
+      const V S = bottom_sum(uc + (1 - c) * sg, C, C.k[c], c);
+      uc[c * sg + tid] = bottom_div(C.k[c], C.rc[c], C.rhs[c] + S);
     }
-    for (int it = 0; it < nu_pre; ++it) {
-      half_sweep_f(0);
-      half_sweep_f(1);
+    __syncthreads();
+  };
+  const std::integral_constant<int, 0> red{};
+  const std::integral_constant<int, 1> black{};
+  for (int visit = 0; visit < A.visits; ++visit) {
+    // FAS right-hand side of the inner bricks: b += A u*
+    if (!TR && visit == 0 && A.fas) {
+#pragma unroll
+      for (int j = 0; j < kSlots; ++j) {
+        if ((P[j].bits & 12u) != 12u) continue;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const V S = bottom_sum(uf + (1 - c) * sf, P[j], P[j].k[c], c);
+          const V u = uf[c * sf + tid + uint32_t(j) * nt];
+          P[j].rhs[c] = P[j].bits & (1u << c) ? P[j].rhs[c] + (diag_of(P[j].k[c]) * u - S) : V(0);
+        }
+        const bool odd = P[j].bits & 16u;
+        *reinterpret_cast<V2 *>(A.B + P[j].at) =
+            V2{odd ? P[j].rhs[1] : P[j].rhs[0], odd ? P[j].rhs[0] : P[j].rhs[1]};
+      }
+      __syncthreads();  // every thread's reads of uf before the first writes
+    }
+    for (int it = 0; it < A.nu_pre; ++it) {
+      half_sweep_f(red);
+      half_sweep_f(black);
     }
     // residual restriction and u* to the coarsest level
 #pragma unroll
-    for (int j = 0; j < kCoarsestSlots; ++j) {
-      uint32_t i = w + uint32_t(j) * nw;
-      if (i >= nf) continue;
-      V c;
-      V S = stencil_f(j, i, c);
-      V u = uf[i * 64u + m];
-      bool act = (af[j] >> m) & 1ull;
-      V r = act ? rf[j] - (c * u - S) : V(0);
-      V rs = group8_sum(r);
-      V us = group8_sum(act ? u : V(0));
-      int cnt = __popcll((af[j] >> (m & 56u)) & 0xffull);
-      if ((m & 7u) == 0) {
-        uint32_t q = parf[j] + (m >> 3);
-        V ust = !TR && cnt ? div_by(us, V(cnt)) : V(0);
-        bc[q] = rs * scale;
-        uc[q] = ust;
-        sc[q] = ust;
-      }
-    }
-    __syncthreads();
-
-    // the coarsest level: FAS right-hand side, mu solves
-    if (w < nc && cin) {
-      V c;
-      V S = stencil_c(c);
-      V u = uc[w * 64u + m];
-      bool act = (ac >> m) & 1ull;
-      rc = act ? bc[w * 64u + m] + (c * u - S) : V(0);  // (TR: u = 0)
-    }
-    __syncthreads();
-    for (int rep = 0; rep < mu; ++rep)
-      for (int it = 0; it < nu_coarse; ++it)
-        for (int h2 = 0; h2 < 2; ++h2) {
-          int colour = it < half ? h2 : 1 - h2;
-          if (w < nc) {
-            V c;
-            V S = stencil_c(c);
-            bool act = (ac >> m) & 1ull;
-            if (act && L.colour == colour) uc[w * 64u + m] = div_by(rc + S, c);
-          }
-          __syncthreads();
+    for (int j = 0; j < kSlots; ++j) {
+      V r[2] = {V(0), V(0)}, u[2] = {V(0), V(0)};
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        if (P[j].bits & (1u << c)) {
+          const V S = bottom_sum(uf + (1 - c) * sf, P[j], P[j].k[c], c);
+          u[c] = uf[c * sf + tid + uint32_t(j) * nt];
+          r[c] = P[j].rhs[c] - (diag_of(P[j].k[c]) * u[c] - S);
         }
-
-    // prolongation of the correction (FP32: every slot's reads before the
-    // writes), post-smoothing
-    if constexpr (kBatch) {
-      V un[kCoarsestSlots];
-#pragma unroll
-      for (int j = 0; j < kCoarsestSlots; ++j) {
-        uint32_t i = w + uint32_t(j) * nw;
-        if (i >= nf) continue;
-        uint32_t q = parf[j] + (m >> 3);
-        un[j] = uf[i * 64u + m] + (TR ? pscale * uc[q] : uc[q] - sc[q]);
-      }
-#pragma unroll
-      for (int j = 0; j < kCoarsestSlots; ++j) {
-        uint32_t i = w + uint32_t(j) * nw;
-        if (i < nf && ((af[j] >> m) & 1ull)) uf[i * 64u + m] = un[j];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < kCoarsestSlots; ++j) {
-        uint32_t i = w + uint32_t(j) * nw;
-        if (i >= nf) continue;
-        uint32_t q = parf[j] + (m >> 3);
-        V corr = TR ? pscale * uc[q] : uc[q] - sc[q];
-        if ((af[j] >> m) & 1ull) uf[i * 64u + m] = uf[i * 64u + m] + corr;
+      const V rs = parent_sum(r[0] + r[1], f);
+      const V us = parent_sum(u[0] + u[1], f);
+      const int cnt = parent_sum(__popc(P[j].bits & 3u), f);
+      if ((P[j].bits & 8u) && !(tid & (3u << (f - 1)))) {
+        const V ust = !TR && cnt ? div_by(us, V(cnt)) : V(0);
+        bc[par[j]] = rs * A.scale;
+        uc[par[j]] = ust;
+        sc[par[j]] = ust;
       }
     }
     __syncthreads();
-    for (int it = 0; it < nu_post; ++it) {
-      half_sweep_f(1);
-      half_sweep_f(0);
+    // the coarsest level: FAS right-hand side (TR: u = 0), mu solves
+    if (C.bits & 8u) {
+#pragma unroll
+      for (uint32_t c = 0; c < 2; ++c) {
+        const V S = bottom_sum(uc + (1 - c) * sg, C, C.k[c], int(c));
+        const uint32_t own = c * sg + tid;
+        C.rhs[c] = C.bits & (1u << c) ? bc[own] + (diag_of(C.k[c]) * uc[own] - S) : V(0);
+      }
+    }
+    __syncthreads();
+    for (int rep = 0; rep < A.mu; ++rep)
+      for (int it = 0; it < A.nu_coarse; ++it) {
+        if (it < A.half) {
+          half_sweep_c(red);
+          half_sweep_c(black);
+        } else {
+          half_sweep_c(black);
+          half_sweep_c(red);
+        }
+      }
+    // prolongation of the correction, post-smoothing
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j) {
+      if (!(P[j].bits & 8u)) continue;
+      const V corr = TR ? A.pscale * uc[par[j]] : uc[par[j]] - sc[par[j]];
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        if (P[j].bits & (1u << c)) uf[c * sf + tid + uint32_t(j) * nt] += corr;
+    }
+    __syncthreads();
+    for (int it = 0; it < A.nu_post; ++it) {
+      half_sweep_f(black);
+      half_sweep_f(red);
     }
   }
 
   // the arrays as the separate kernels leave them
 #pragma unroll
-  for (int j = 0; j < kCoarsestSlots; ++j) {
-    uint32_t i = w + uint32_t(j) * nw;
-    if (i < nf) bstore<V>(Xf.u, m, Af.R.brick(i) * 64u, uf[i * 64u + m]);
+  for (int j = 0; j < kSlots; ++j) {
+    if (!(P[j].bits & 8u)) continue;
+    const bool odd = P[j].bits & 16u;
+    const uint32_t p = tid + uint32_t(j) * nt;
+    const V u0 = uf[p], u1 = uf[sf + p];
+    *reinterpret_cast<V2 *>(A.U + P[j].at) = V2{odd ? u1 : u0, odd ? u0 : u1};
   }
-  if (!TR && w < nc) {
-    uint32_t b = Ac.R.brick(w);
-    bstore<V>(Xc.u, m, b * 64u, uc[w * 64u + m]);
-    if (cin) {
-      bstore<V>(Xc.b, m, b * 64u, rc);
-      bstore<V>(Xc.us, m, (b - Xc.nlb) * 64u, sc[w * 64u + m]);
-    }
+  if (!TR && (C.bits & 8u)) {
+    const bool odd = C.bits & 16u;
+    auto pair = [&](V a, V b) { return V2{odd ? b : a, odd ? a : b}; };
+    *reinterpret_cast<V2 *>(A.U + C.at) = pair(uc[tid], uc[sg + tid]);
+    *reinterpret_cast<V2 *>(A.B + C.at) = pair(C.rhs[0], C.rhs[1]);
+    *reinterpret_cast<V2 *>(A.Ustar + (C.at - A.nlb * 64u)) = pair(sc[tid], sc[sg + tid]);
   }
 }
 

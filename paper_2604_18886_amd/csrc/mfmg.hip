@@ -367,7 +367,7 @@ struct mfmg_hierarchy {
   std::vector<char> stream_lv;  // per level: the cycle's stencils stream their coefficients
   bool stream_composite = false;  // the same for the composite operator
   bool fuse_bottom = false;       // level lc + 1 and the coarsest level in one kernel (k_bottom)
-  bool fuse_bottom_T = false;     // the same for the transposed cycle
+  DevBuf<uint4> bot_f, bot_c;     // k_bottom's tables of the two levels
   bool fuse_prolong = true;       // prolongation folded into the post-smoothing (k_smooth PR)
   std::vector<char> fold_fas;     // per level: FAS right-hand side folded into k_smooth_fas
   // work vectors (device order)
@@ -997,6 +997,8 @@ extern "C" void mfmg_destroy_coeffs(mfmg_coeffs *co) {
 // --------------------------------------------------------------------------
 // hierarchy
 // --------------------------------------------------------------------------
+static void build_bottom(mfmg_hierarchy *h, hipStream_t s);
+
 extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg_params *prm,
                                             void *stream, mfmg_hierarchy **out) {
   if (!co || !prm || !out) return fail(MFMG_ERR_INVALID_ARG, "NULL argument");
@@ -1126,31 +1128,18 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
       h->stream_composite = double(nlb) * (64 * (2 * 8.0 + 3.75 * 8.0) + 64) > stream_threshold();
     }
     {
-      // k_bottom takes level lc + 1 (below the finest) and the coarsest
-      // level when the former is a grid of at most kCoarsestBricks bricks
-      // without T-junctions and the latter has at most kBottomCoarse bricks.
-      // MFMG_FUSE_BOTTOM=0 (read at each build) keeps the separate kernels.
+      // k_bottom takes level lc + 1 (below the finest) and the coarsest level
+      // when the former is a complete grid of at most 16^3 cells (so it has
+      // no T-junction and the coarsest level no leaves): one workgroup holds
+      // two pairs of its cells per thread.  MFMG_FUSE_BOTTOM=0 (read at each
+      // build) keeps the separate kernels.
       const char *e = std::getenv("MFMG_FUSE_BOTTOM");
       int f = h->lc + 1;
-      bool ok = !(e && e[0] == '0') && f < h->L && D.range[f].n() <= uint32_t(kCoarsestBricks) &&
-                D.range[h->lc].n() <= uint32_t(kBottomCoarse);
-      if (ok) {
-        const Range &R = D.range[f];
-        for (uint32_t i = 0; i < R.n_leaf; ++i)
-          if (mh[R.leaf_lo + i].flags & kFlagT) ok = false;
-        std::vector<BrickMeta> mi(R.n_inner);
-        if (R.n_inner) {
-          HIP_CHECK(hipMemcpyAsync(mi.data(), h->meta.p + R.inner_lo,
-                                   size_t(R.n_inner) * sizeof(BrickMeta), hipMemcpyDeviceToHost,
-                                   s));
-          HIP_CHECK(hipStreamSynchronize(s));
-        }
-        for (const BrickMeta &M : mi)
-          if (M.flags & kFlagT) ok = false;
-      }
-      h->fuse_bottom = ok;
-      // (k_bottom's transposed form takes a coarsest level without leaves)
-      h->fuse_bottom_T = ok && D.range[h->lc].n_leaf == 0;
+      h->fuse_bottom = !(e && e[0] == '0') && f < h->L && f <= kBottomLevel &&
+                       D.range[f].n() == (uint32_t(1) << (3 * (f - 2))) &&
+                       D.range[h->lc].n() == (uint32_t(1) << (3 * (f - 3))) &&
+                       D.range[h->lc].n_leaf == 0;
+      if (h->fuse_bottom) build_bottom(h.get(), s);
     }
     {
       // MFMG_FUSE_PROLONG=0 (read at each build) keeps the separate
@@ -1365,6 +1354,14 @@ struct Cycle {
       }
   }
 
+  // k_bottom's arguments (p.mu visits of level lc + 1)
+  BottomArgs<V> bottom_args(int nu_pre, int nu_post, int half, int fas, V scale) const {
+    const mfmg_mg_params &p = h->prm;
+    return BottomArgs<V>{h->bot_f.p, h->bot_c.p, h->lc + 1, U, B, Ust, h->co->dt->nlb,
+                         nu_pre, nu_post, p.nu_coarse, half, p.mu, fas, p.mu, scale,
+                         V(p.beta_mg / p.alpha), done};
+  }
+
   // zero_start: the level's iterate is zero and its bricks are all leaves
   // (the finest level at the start of a cycle), so the first half-sweep
   // needs no neighbour values and also clears the iterate.
@@ -1388,17 +1385,8 @@ struct Cycle {
       hipLaunchKernelGGL((k_restrict<V, CL, CI>), dim3(stencil_grid<V>(A.R.n())), dim3(kBlock),
                          0, s, A, scale);
     if (l - 1 == h->lc + 1 && h->fuse_bottom) {
-      auto F = args(l - 1, false);
-      auto Cc = args(h->lc, false);
-      if constexpr (sizeof(V) == 4)
-        hipLaunchKernelGGL((k_bottom<V, CL, CI, true>), dim3(1), dim3(1024), 0, s, F, Cc,
-                           p.nu_pre, p.nu_post, p.nu_coarse, p.nu_coarse / 2, p.mu, 1, p.mu,
-                           scale, V(0));
-      else
-        for (int k = 0; k < p.mu; ++k)
-          hipLaunchKernelGGL((k_bottom<V, CL, CI, false>), dim3(1), dim3(1024), 0, s, F, Cc,
-                             p.nu_pre, p.nu_post, p.nu_coarse, p.nu_coarse / 2, p.mu,
-                             int(k == 0), 1, scale, V(0));
+      BottomArgs<V> F = bottom_args(p.nu_pre, p.nu_post, p.nu_coarse / 2, 1, scale);
+      hipLaunchKernelGGL((k_bottom<V>), dim3(1), dim3(F.f == kBottomLevel ? kBottomThreads<V> : 256), 0, s, F);
     } else {
       auto C = args(l - 1, true);
       bool fold = h->fold_fas[size_t(l - 1)] && p.nu_pre > 0;
@@ -1428,17 +1416,31 @@ struct Cycle {
   }
 };
 
+Cycle<float, float, __half> cycle32(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
+  return {h, h->coef32.p, h->coef16.p, h->pf32.p, h->U32.p, h->B32.p, h->S32.p, done, s};
+}
+// FP64 inner coefficients directly follow the leaf ones in coef64
+Cycle<double, double, double> cycle64(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
+  return {h, h->coef64.p, h->coef64.p + int64_t(h->co->dt->nlb) * 256, h->pf64.p,
+          h->U64.p, h->B64.p, h->S64.p, done, s};
+}
+
 void run_cycle(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
-  if (h->prm.precision == MFMG_MIXED) {
-    Cycle<float, float, __half> c{h, h->coef32.p, h->coef16.p, h->pf32.p,
-                                  h->U32.p, h->B32.p, h->S32.p, done, s};
-    c.run();
-  } else {
-    // FP64 inner coefficients directly follow the leaf ones in coef64
-    Cycle<double, double, double> c{h, h->coef64.p, h->coef64.p + int64_t(h->co->dt->nlb) * 256,
-                                    h->pf64.p, h->U64.p, h->B64.p, h->S64.p, done, s};
-    c.run();
+  if (h->prm.precision == MFMG_MIXED) cycle32(h, s, done).run();
+  else cycle64(h, s, done).run();
+}
+
+// k_bottom's tables of the levels lc + 1 and lc.
+template <class V, class CL, class CI>
+void build_bottom_of(mfmg_hierarchy *h, const Cycle<V, CL, CI> &c) {
+  DevBuf<uint4> *tab[2] = {&h->bot_c, &h->bot_f};
+  for (int k = 0; k < 2; ++k) {
+    auto A = c.args(h->lc + k, false);
+    tab[k]->alloc(size_t(BottomUnits<V>::kAll) << (3 * (h->lc + k) - 1));
+    hipLaunchKernelGGL((k_bottom_table<V, CL, CI>), dim3(grid_for(A.R.n())), dim3(kBlock), 0, c.s,
+                       A, h->lc + k, tab[k]->p);
   }
+  HIP_CHECK(hipGetLastError());
 }
 
 // Transpose of the cycle (exact adjoint of run_cycle's linear map), in
@@ -1456,8 +1458,9 @@ struct CycleT {
   static constexpr int kCpolLevel = Cycle<V, CL, CI>::kCpolLevel;
 
   LevelArgs<V, CL, CI> args(int l) const {
-    return Cycle<V, CL, CI>{h, leafc, innerc, pf, Y, G, Sb, done, s}.args(l, false);
+    return forward().args(l, false);
   }
+  Cycle<V, CL, CI> forward() const { return {h, leafc, innerc, pf, Y, G, Sb, done, s}; }
   bool stream(int l) const { return h->stream_lv[size_t(l)]; }
   template <int PR>
   void half_sweep(int l, const LevelArgs<V, CL, CI> &A, int colour) const {
@@ -1518,19 +1521,11 @@ struct CycleT {
     if (!first && C.R.n_leaf && C.R.n_inner)
       hipLaunchKernelGGL((k_T_revisit<V, CL, CI>), dim3(stencil_grid<V>(C.R.n_inner)),
                          dim3(kBlock), 0, s, C);
-    V pscale = V(p.beta_mg / p.alpha);
-    if (l - 1 == h->lc + 1 && h->fuse_bottom_T) {
-      auto Cc = args(h->lc);
-      int half = p.nu_coarse - p.nu_coarse / 2;
-      if constexpr (sizeof(V) == 4)
-        hipLaunchKernelGGL((k_bottom<V, CL, CI, true, true>), dim3(1), dim3(1024), 0, s, C, Cc,
-                           p.nu_post, p.nu_pre, p.nu_coarse, half, p.mu, int(first), p.mu, V(1),
-                           pscale);
-      else
-        for (int k = 0; k < p.mu; ++k)
-          hipLaunchKernelGGL((k_bottom<V, CL, CI, false, true>), dim3(1), dim3(1024), 0, s, C,
-                             Cc, p.nu_post, p.nu_pre, p.nu_coarse, half, p.mu,
-                             int(first && k == 0), 1, V(1), pscale);
+    if (l - 1 == h->lc + 1 && h->fuse_bottom) {
+      BottomArgs<V> F = forward().bottom_args(p.nu_post, p.nu_pre,
+                                              p.nu_coarse - p.nu_coarse / 2, int(first), V(1));
+      hipLaunchKernelGGL((k_bottom<V, true>), dim3(1), dim3(F.f == kBottomLevel ? kBottomThreads<V> : 256), 0,
+                         s, F);
     } else {
       for (int k = 0; k < p.mu; ++k) fas(l - 1, first && k == 0);
     }
@@ -1623,6 +1618,15 @@ void run_cycle_T(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
     c.run();
   }
 }
+
+}  // namespace
+
+static void build_bottom(mfmg_hierarchy *h, hipStream_t s) {
+  if (h->prm.precision == MFMG_MIXED) build_bottom_of(h, cycle32(h, s, nullptr));
+  else build_bottom_of(h, cycle64(h, s, nullptr));
+}
+
+namespace {
 
 PcgArgs pcg_args(mfmg_hierarchy *h) {
   PcgArgs P;
@@ -2289,14 +2293,10 @@ extern "C" mfmg_status mfmg_profile(mfmg_hierarchy *h, int what, int level, int 
     auto launch = [&]() {
       if (what == MFMG_PROFILE_SMOOTH) {
         if (mixed) {
-          Cycle<float, float, __half> c{h, h->coef32.p, h->coef16.p, h->pf32.p,
-                                        h->U32.p, h->B32.p, h->S32.p, nullptr, s};
+          auto c = cycle32(h, s, nullptr);
           c.half_sweep(level, c.args(level, false), 0);
         } else {
-          Cycle<double, double, double> c{h, h->coef64.p,
-                                          h->coef64.p + int64_t(h->co->dt->nlb) * 256,
-                                          h->pf64.p, h->U64.p, h->B64.p, h->S64.p,
-                                          nullptr, s};
+          auto c = cycle64(h, s, nullptr);
           c.half_sweep(level, c.args(level, false), 0);
         }
       } else if (what == MFMG_PROFILE_CYCLE) {
