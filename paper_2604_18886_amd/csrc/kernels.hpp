@@ -106,8 +106,7 @@ __device__ __forceinline__ int octant_of(const BrickMeta &M) {
 
 // Coefficient arrays of one multigrid level: leaf bricks read CL values,
 // inner bricks read CI values multiplied by iscale (FP16 inner coefficients
-// are stored divided by the cell size of their level).  When CL == CI the
-// inner coefficients directly follow the leaf ones in one array.
+// are stored divided by the cell size of their level).
 template <class V, class CL, class CI>
 struct Coefs {
   const CL *leaf;
@@ -217,20 +216,6 @@ __global__ void __launch_bounds__(kBlock) k_assemble(AssembleArgs A) {
   cf[192 + m] = dk[4];
 }
 
-// Active-cell masks of bricks [lo, lo + n): bit m set when c_m != 0.
-__global__ void __launch_bounds__(kBlock) k_active_mask(const double *coef, uint32_t lo,
-                                                        uint32_t n, BrickMeta *meta) {
-  uint32_t i = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  if (i >= n) return;
-  uint32_t b = lo + i;
-  uint64_t mask = __ballot(coef[b * 256u + m] != 0.0);
-  if (m == 0) {
-    meta[b].act[0] = uint32_t(mask);
-    meta[b].act[1] = uint32_t(mask >> 32);
-  }
-}
-
 // The parent-neighbour table (ParentNbrs), one thread per brick.
 __global__ void __launch_bounds__(kBlock) k_parent_nbrs(Topo T, ParentNbrs *out) {
   uint32_t b = blockIdx.x * kBlock + threadIdx.x;
@@ -248,52 +233,6 @@ __global__ void __launch_bounds__(kBlock) k_parent_nbrs(Topo T, ParentNbrs *out)
   out[b] = r;
 }
 
-// Algorithm 3: coarse coefficients of the inner bricks [lo, lo + n) from
-// their children, one lane per coarse cell.
-__global__ void __launch_bounds__(kBlock) k_coarsen(uint32_t lo, uint32_t n, Topo T,
-                                                    double *coef, double alpha) {
-  uint32_t i = blockIdx.x * kWavesPerBlock + wave_id();
-  int q = threadIdx.x & (kWave - 1);
-  if (i >= n) return;
-  uint32_t b = lo + i;
-  int32_t cb = T.child[8 * int64_t(b) + (q >> 3)];
-  const double *cc = coef + uint32_t(cb) * 256u;
-  int base = (q & 7) << 3;
-  double c = 0.0, kx = 0.0, ky = 0.0, kz = 0.0;
-  int cnt = 0;
-  for (int t = 0; t < 8; ++t) {
-    int ch = base | t;
-    double ci = cc[ch];
-    bool on = ci != 0.0;
-    if (on) {
-      ++cnt;
-      c = c + ci / alpha;
-    }
-    double kk[3] = {cc[64 + ch], cc[128 + ch], cc[192 + ch]};
-    for (int a = 0; a < 3; ++a) {
-      if ((t >> a) & 1) {
-        int sib = base | (t ^ (1 << a));
-        if (on && cc[sib] != 0.0) c = c + 2.0 / alpha * (-kk[a]);
-      } else {
-        if (a == 0) kx = kx + kk[0] / alpha;
-        if (a == 1) ky = ky + kk[1] / alpha;
-        if (a == 2) kz = kz + kk[2] / alpha;
-      }
-    }
-  }
-  if (cnt == 0) c = 0.0;
-  double *o = coef + b * 256u;
-  o[q] = c;
-  o[64 + q] = kx;
-  o[128 + q] = ky;
-  o[192 + q] = kz;
-}
-
-// FP64 coefficients -> FP32 copies (leaf bricks)
-__global__ void k_convert_leaf(const double *src, float *dst, int64_t n) {
-  int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = float(src[i]);
-}
 // FP16 copy of an inner coefficient scaled to c / h_l (through FP32, round to
 // nearest even).  A non-zero value that would land below FP16's normal range
 // (2^-14) is stored as 2^-14 with its sign: a sliver face keeps a small
@@ -306,16 +245,98 @@ __device__ __forceinline__ __half half_coef(double v) {
   return q;
 }
 
-// FP64 inner coefficients -> FP16 copies of c / h_l
-__global__ void __launch_bounds__(kBlock) k_convert_inner(const double *coef, Topo T,
-                                                          __half *dst) {
-  uint32_t i = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  uint32_t b = T.nlb + i;
-  if (b >= T.nb) return;
-  double inv_h = ldexp(1.0, T.meta[b].level);
-  for (int comp = 0; comp < 4; ++comp)
-    dst[i * 256u + comp * 64 + m] = half_coef(coef[b * 256u + comp * 64 + m] * inv_h);
+// FP64 coefficients of brick b: the assembled leaves and the inner bricks of
+// Algorithm 3 are in two arrays.
+struct CoefPair {
+  const double *leaf;
+  double *inner;  // of brick nlb on
+  uint32_t nlb;
+  __device__ __forceinline__ const double *of(uint32_t b) const {
+    return b < nlb ? leaf + uint64_t(b) * 256u : inner + uint64_t(b - nlb) * 256u;
+  }
+};
+
+// One pass over the bricks of a level (levels in decreasing order): their
+// active-cell masks (bit m set when c_m != 0), their FP32 or FP16 copies of
+// the mixed cycle (c32, c16; null in FP64) and, by Algorithm 3, the
+// coefficients of their parents' cells: one wave per brick, whose 8 sibling
+// groups give 8 cells of its parent.  Bound by HBM: each coefficient is read
+// once, in full lines, where one lane per parent cell read its 8 children 64
+// bytes apart and the masks and copies took passes of their own (26.3M
+// leaves: 1070 us for the three, 310 us in this pass).  The sums run in the children's
+// order, one lane per parent cell and component, over values handed through
+// LDS.
+__global__ void __launch_bounds__(kBlock) k_coarsen(Range R, Topo T, BrickMeta *meta, CoefPair K,
+                                                    double alpha, float *c32, __half *c16) {
+  __shared__ double lds[kWavesPerBlock][7][64];
+  const uint32_t w = wave_id();
+  const int m = threadIdx.x & (kWave - 1);
+  const uint32_t i = blockIdx.x * kWavesPerBlock + w;
+  if (i >= R.n()) return;
+  const uint32_t b = R.brick(i);
+  const BrickMeta &M = meta[b];
+  const int32_t parent = M.parent;
+  const int oct = octant_of(M);
+  const double *src = K.of(b);
+  double v[4];
+#pragma unroll
+  for (int comp = 0; comp < 4; ++comp) v[comp] = src[comp * 64 + m];
+  const uint64_t mask = __ballot(v[0] != 0.0);
+  if (c32 && b < K.nlb) {
+#pragma unroll
+    for (int comp = 0; comp < 4; ++comp) c32[uint64_t(b) * 256u + comp * 64 + m] = float(v[comp]);
+  } else if (c16 && b >= K.nlb) {
+    const double inv_h = ldexp(1.0, M.level);
+#pragma unroll
+    for (int comp = 0; comp < 4; ++comp)
+      c16[uint64_t(b - K.nlb) * 256u + comp * 64 + m] = half_coef(v[comp] * inv_h);
+  }
+  if (m == 0) {
+    meta[b].act[0] = uint32_t(mask);
+    meta[b].act[1] = uint32_t(mask >> 32);
+  }
+  if (parent < 0) return;
+  double(*s)[64] = lds[w];
+#pragma unroll
+  for (int comp = 0; comp < 4; ++comp) s[comp][m] = v[comp] / alpha;
+#pragma unroll
+  for (int a = 0; a < 3; ++a) s[4 + a][m] = -v[1 + a];
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (m >= 32) return;
+  const int q = m & 7, comp = m >> 3, base = q << 3;
+  const uint32_t on = uint32_t(mask >> base) & 0xffu;
+  double c = 0.0;
+  if (comp == 0) {
+    const double twice = 2.0 / alpha;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      if (!((on >> t) & 1u)) continue;
+      c = c + s[0][base | t];
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        if (((t >> a) & 1) && ((on >> (t ^ (1 << a))) & 1u))
+          c = fma(twice, s[4 + a][base | t], c);
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      if (!((t >> (comp - 1)) & 1)) c = c + s[comp][base | t];
+  }
+  K.inner[uint64_t(uint32_t(parent) - K.nlb) * 256u + uint32_t(comp * 64 + oct * 8 + q)] = c;
+}
+
+// Number of active leaf cells (added to *n, which is zero before).
+__global__ void __launch_bounds__(256) k_count_active(const BrickMeta *meta, uint32_t nlb,
+                                                      unsigned long long *n) {
+  __shared__ unsigned long long part[4];
+  unsigned long long c = 0;
+  for (uint32_t b = blockIdx.x * 256u + threadIdx.x; b < nlb; b += gridDim.x * 256u)
+    c += uint32_t(__popc(meta[b].act[0]) + __popc(meta[b].act[1]));
+  c = wave_sum(c);
+  if ((threadIdx.x & 63u) == 0) part[threadIdx.x >> 6] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicAdd(n, part[0] + part[1] + part[2] + part[3]);
 }
 
 // Plus-face coefficients of every brick, for the level kernels: entry
@@ -328,9 +349,10 @@ __global__ void __launch_bounds__(kBlock) k_convert_inner(const double *coef, To
 // the diagonal is the sum of the six face coefficients the stencil sees
 // (Eq. 3; Algorithm 3 keeps this on every level).  A cell on several +walls
 // carries that part on the first of them.
-template <class CL>
-__global__ void __launch_bounds__(kBlock) k_plus_faces(Topo T, const double *coef,
-                                                       const double *tc, CL *pf, int half_inner) {
+// pf32 (may be null): the mixed cycle's copy, with the rounding of an inner
+// neighbour's store.
+__global__ void __launch_bounds__(kBlock) k_plus_faces(Topo T, CoefPair K, const double *tc,
+                                                       double *pf64, float *pf32) {
   uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
   int e = threadIdx.x & (kWave - 1);
   if (b >= T.nb || e >= 48) return;
@@ -341,7 +363,7 @@ __global__ void __launch_bounds__(kBlock) k_plus_faces(Topo T, const double *coe
   c[a == 2 ? 1 : 2] = f >> 2;
   int m = dev_morton(c[0], c[1], c[2]);
   const BrickMeta M = T.meta[b];
-  const double *own = coef + uint64_t(b) * 256u;
+  const double *own = K.of(b);
   double kp[3];
   bool wall[3];
   bool inner_nbr = false;
@@ -356,7 +378,7 @@ __global__ void __launch_bounds__(kBlock) k_plus_faces(Topo T, const double *coe
     }
     int32_t n = M.nbr[dd];
     if (n >= 0) {
-      kp[ax] = coef[uint64_t(n) * 256u + (1 + ax) * 64 + p];
+      kp[ax] = K.of(uint32_t(n))[(1 + ax) * 64 + p];
       if (ax == a) inner_nbr = uint32_t(n) >= T.nlb;
     } else if ((M.flags >> dd) & 1u) {
       kp[ax] = tc[uint32_t(M.tplus) * 48u + ax * 16 + dev_face_index(m, ax)];
@@ -370,11 +392,14 @@ __global__ void __launch_bounds__(kBlock) k_plus_faces(Topo T, const double *coe
     v = first == a ? own[m] - (own[64 + m] + own[128 + m] + own[192 + m]) -
                          (kp[0] + kp[1] + kp[2])
                    : 0.0;
-  } else if (half_inner && inner_nbr) {
+  }
+  pf64[b * 48u + e] = v;
+  if (!pf32) return;
+  if (!wall[a] && inner_nbr) {
     float hv = __half2float(half_coef(v * ldexp(1.0, M.level)));
     v = double(hv * ldexpf(1.0f, -M.level));
   }
-  pf[b * 48u + e] = CL(v);
+  pf32[b * 48u + e] = float(v);
 }
 
 // ---------------------------------------------------------------------------

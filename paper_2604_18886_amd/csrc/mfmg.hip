@@ -358,7 +358,11 @@ struct mfmg_hierarchy {
   int L = 0, lc = 0;
   DevBuf<BrickMeta> meta;  // topology records with this hierarchy's activity masks
   DevBuf<ParentNbrs> pnb;  // parent-neighbour table (fused prolongation)
-  DevBuf<double> coef64;   // nb * 256 (leaf part = assembled, inner = Algorithm 3)
+  DevBuf<double> inner64;  // (nb - nlb) * 256, Algorithm 3 (leaf part: co->coef)
+  const double *coef64_of(uint32_t b) const {  // FP64 coefficients of brick b
+    return b < co->dt->nlb ? co->coef.p + uint64_t(b) * 256
+                           : inner64.p + uint64_t(b - co->dt->nlb) * 256;
+  }
   DevBuf<float> coef32;    // nlb * 256 (mixed)
   DevBuf<__half> coef16;   // (nb - nlb) * 256 (mixed)
   DevBuf<double> pf64;     // plus-face coefficients, nb * 48 (FP64 cycle, composite operator)
@@ -1033,6 +1037,7 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
   hipStream_t s = (hipStream_t)stream;
   try {
     std::unique_ptr<mfmg_hierarchy> h(new mfmg_hierarchy());
+    Drained quiet;  // (armed at the end, when the temporaries are freed)
     const DeviceTopology &D = *co->dt;
     h->co = co;
     HIP_CHECK(hipGetDevice(&h->device));
@@ -1045,39 +1050,30 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     h->meta.alloc(D.nb);
     HIP_CHECK(hipMemcpyAsync(h->meta.p, D.meta.p, size_t(D.nb) * sizeof(BrickMeta),
                              hipMemcpyDeviceToDevice, s));
-    h->coef64.alloc(size_t(nb) * 256);
-    HIP_CHECK(hipMemcpyAsync(h->coef64.p, co->coef.p, size_t(nlb) * 256 * sizeof(double),
-                             hipMemcpyDeviceToDevice, s));
-    hipLaunchKernelGGL(k_active_mask, dim3(grid_for(nlb)), dim3(kBlock), 0, s,
-                       (const double *)h->coef64.p, 0u, uint32_t(nlb), h->meta.p);
+    h->inner64.alloc(size_t(nb - nlb) * 256 + 1);
+    bool mixed = prm->precision == MFMG_MIXED;
+    if (mixed) {
+      h->coef32.alloc(size_t(nlb) * 256);
+      h->coef16.alloc(size_t(nb - nlb) * 256 + 1);
+      h->pf32.alloc(size_t(nb) * 48);
+    }
     Topo topo = make_topo(D, h->meta.p);
     h->pnb.alloc(size_t(nb));
     if (nb > 0)
       hipLaunchKernelGGL(k_parent_nbrs, dim3(unsigned((nb + kBlock - 1) / kBlock)), dim3(kBlock),
                          0, s, topo, h->pnb.p);
-    for (int l = T.max_level - 1; l >= kMinLevel; --l) {
+    CoefPair K{co->coef.p, h->inner64.p, D.nlb};
+    for (int l = T.max_level; l >= kMinLevel; --l) {
       const Range &R = D.range[l];
-      if (R.n_inner == 0) continue;
-      hipLaunchKernelGGL(k_coarsen, dim3(grid_for(R.n_inner)), dim3(kBlock), 0, s, R.inner_lo,
-                         R.n_inner, topo, h->coef64.p, prm->alpha);
-      hipLaunchKernelGGL(k_active_mask, dim3(grid_for(R.n_inner)), dim3(kBlock), 0, s,
-                         (const double *)h->coef64.p, R.inner_lo, R.n_inner, h->meta.p);
+      if (R.n() == 0) continue;
+      hipLaunchKernelGGL(k_coarsen, dim3(grid_for(R.n())), dim3(kBlock), 0, s, R, topo, h->meta.p,
+                         K, prm->alpha, h->coef32.p, h->coef16.p);
     }
     HIP_CHECK(hipGetLastError());
     h->pf64.alloc(size_t(nb) * 48);
-    hipLaunchKernelGGL(k_plus_faces<double>, dim3(grid_for(nb)), dim3(kBlock), 0, s, topo,
-                       (const double *)h->coef64.p, (const double *)co->tc.p, h->pf64.p, 0);
-    if (prm->precision == MFMG_MIXED) {
-      h->coef32.alloc(size_t(nlb) * 256);
-      h->coef16.alloc(size_t(nb - nlb) * 256 + 1);
-      hipLaunchKernelGGL(k_convert_leaf, dim3(grid_elems(nlb * 256, 256)), dim3(256), 0, s,
-                         (const double *)h->coef64.p, h->coef32.p, nlb * 256);
-      if (nb > nlb)
-        hipLaunchKernelGGL(k_convert_inner, dim3(grid_for(nb - nlb)), dim3(kBlock), 0, s,
-                           (const double *)h->coef64.p, topo, h->coef16.p);
-      h->pf32.alloc(size_t(nb) * 48);
-      hipLaunchKernelGGL(k_plus_faces<float>, dim3(grid_for(nb)), dim3(kBlock), 0, s, topo,
-                         (const double *)h->coef64.p, (const double *)co->tc.p, h->pf32.p, 1);
+    hipLaunchKernelGGL(k_plus_faces, dim3(grid_for(nb)), dim3(kBlock), 0, s, topo, K,
+                       (const double *)co->tc.p, h->pf64.p, h->pf32.p);
+    if (mixed) {
       h->U32.alloc(size_t(nb) * 64);
       h->B32.alloc(size_t(nb) * 64);
       h->S32.alloc(size_t(nb - nlb) * 64 + 1);
@@ -1105,18 +1101,16 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     for (hipEvent_t &e : h->iter_ev)
       HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
     // active leaf count (for the null-space mean)
-    std::vector<BrickMeta> mh(nlb);
-    HIP_CHECK(hipMemcpyAsync(mh.data(), h->meta.p, size_t(nlb) * sizeof(BrickMeta),
-                             hipMemcpyDeviceToHost, s));
-    HIP_CHECK(hipGetLastError());
-    HIP_CHECK(hipStreamSynchronize(s));
-    int64_t na = 0;
-    for (const BrickMeta &M : mh) na += __builtin_popcount(M.act[0]) + __builtin_popcount(M.act[1]);
-    h->n_active = double(na);
+    DevBuf<unsigned long long> na;
+    na.alloc(1);
+    HIP_CHECK(hipMemsetAsync(na.p, 0, sizeof(unsigned long long), s));
+    hipLaunchKernelGGL(k_count_active, dim3(std::min(grid_elems(nlb, 256), 1024u)), dim3(256), 0,
+                       s, (const BrickMeta *)h->meta.p, D.nlb, na.p);
+    unsigned long long na_host = 0;
+    HIP_CHECK(hipMemcpyAsync(&na_host, na.p, sizeof(na_host), hipMemcpyDeviceToHost, s));
     {
       // bytes one half-sweep of a level touches: iterate and right-hand
       // side, four coefficients' worth of face data, the brick records
-      bool mixed = prm->precision == MFMG_MIXED;
       double V = mixed ? 4.0 : 8.0, CL = mixed ? 4.0 : 8.0, CI = mixed ? 2.0 : 8.0;
       h->stream_lv.assign(size_t(T.max_level) + 1, 0);
       for (int l = kMinLevel; l <= T.max_level; ++l) {
@@ -1161,6 +1155,10 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
                          D.range[l].n_inner > 0;
       }
     }
+    HIP_CHECK(hipGetLastError());
+    HIP_CHECK(hipStreamSynchronize(s));
+    quiet.arm();
+    h->n_active = double(na_host);
     *out = h.release();
   } catch (const HipError &e) {
     return hip_fail(e);
@@ -1242,7 +1240,7 @@ extern "C" mfmg_status mfmg_hierarchy_level_coeffs(const mfmg_hierarchy *h, int 
     std::vector<BrickMeta> recs;
     level_order(h, level, ids, recs, s);
     for (size_t i = 0; i < ids.size(); ++i)
-      HIP_CHECK(hipMemcpyAsync(out + i * 256, h->coef64.p + int64_t(ids[i]) * 256,
+      HIP_CHECK(hipMemcpyAsync(out + i * 256, h->coef64_of(uint32_t(ids[i])),
                                256 * sizeof(double), hipMemcpyDeviceToDevice, s));
     HIP_CHECK(hipStreamSynchronize(s));
   } catch (const HipError &e) {
@@ -1419,9 +1417,8 @@ struct Cycle {
 Cycle<float, float, __half> cycle32(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
   return {h, h->coef32.p, h->coef16.p, h->pf32.p, h->U32.p, h->B32.p, h->S32.p, done, s};
 }
-// FP64 inner coefficients directly follow the leaf ones in coef64
 Cycle<double, double, double> cycle64(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
-  return {h, h->coef64.p, h->coef64.p + int64_t(h->co->dt->nlb) * 256, h->pf64.p,
+  return {h, h->co->coef.p, h->inner64.p, h->pf64.p,
           h->U64.p, h->B64.p, h->S64.p, done, s};
 }
 
@@ -1612,8 +1609,7 @@ void run_cycle_T(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
                                    h->T32[0].p, h->T32[1].p, h->T32[2].p, h->T32[3].p, done, s};
     c.run();
   } else {
-    CycleT<double, double, double> c{h, h->coef64.p,
-                                     h->coef64.p + int64_t(h->co->dt->nlb) * 256, h->pf64.p,
+    CycleT<double, double, double> c{h, h->co->coef.p, h->inner64.p, h->pf64.p,
                                      h->T64[0].p, h->T64[1].p, h->T64[2].p, h->T64[3].p, done, s};
     c.run();
   }
@@ -1631,7 +1627,7 @@ namespace {
 PcgArgs pcg_args(mfmg_hierarchy *h) {
   PcgArgs P;
   P.T = make_topo(*h->co->dt, h->meta.p);
-  P.C = h->coef64.p;
+  P.C = h->co->coef.p;
   P.PF = h->pf64.p;
   P.canon = h->co->dt->canon.p;
   P.S = h->S.p;

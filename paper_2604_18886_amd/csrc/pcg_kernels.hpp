@@ -11,7 +11,7 @@ namespace mfmg {
 
 struct PcgArgs {
   Topo T;
-  const double *C;       // FP64 coefficients of all bricks (device order)
+  const double *C;       // FP64 coefficients of the leaf bricks (device order)
   const double *PF;      // FP64 plus-face coefficients of all bricks, 48 per brick
   const int32_t *canon;  // device leaf brick -> canonical leaf brick
   Scalars *S;
@@ -61,7 +61,7 @@ __device__ __forceinline__ LevelView<double, double, double, CP> composite_view(
   V.b = V.u;
   V.us = V.u;
   V.cl = make_rsrc(P.C, nlb * 256 * sizeof(double));
-  V.ci = make_rsrc(P.C + nlb * 256, (nb - nlb) * 256 * sizeof(double));
+  V.ci = V.cl;  // (the operator's rows are leaf rows)
   V.pf = make_rsrc(P.PF, nb * 48 * sizeof(double));
   V.meta = P.T.meta;
   V.nlb = P.T.nlb;
