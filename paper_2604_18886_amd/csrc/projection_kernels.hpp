@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(kDivWaves * kWave) k_divergence(DivArgs A) {
       if (out) {
         const uint32_t n = uint32_t(M.nbr[d]);
         if (owns_plus(M.flags, d)) t = s[slot++];
-        else if (n - b0 < uint32_t(kDivWaves)) t = s[at[a]];
+        else if (n < A.F.T.nlb && n - b0 < uint32_t(kDivWaves)) t = s[at[a]];
         else t = be[a] * h2 * uu[a];
       }
       div = div - f + t;

@@ -32,6 +32,9 @@ def _spec(seed):
 
 SPECS = {**{f"random{s}": _spec(s) for s in range(4)},
          "one_brick": problems.uniform_spec(2),
+         # coarse leaves in the last group of bricks, next to the first inner one
+         "far_corner": {"min_level": 3, "max_level": 4, "node_size": 4,
+                        "prims": [problems.sphere_prim((1, 1, 1), 0.01)]},
          "corner": {"min_level": 2, "max_level": 5, "node_size": 4,
                     "prims": [problems.sphere_prim((0, 0, 0), 0.01)]}}
 
