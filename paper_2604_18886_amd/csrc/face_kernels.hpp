@@ -7,8 +7,8 @@
 // uniform), and values across in-brick faces are lane exchanges.
 //
 // 26.3M leaves, 81M faces, against one thread per face or cell through tables
-// (18 bytes per face, 9 per cell) with dependent loads: divergence 950 -> 623
-// us, velocity update 1276 -> 541 us, per-face gradient 1062 -> 443 us.  The
+// (18 bytes per face, 9 per cell) with dependent loads: divergence 950 -> 579
+// us, velocity update 1276 -> 504 us, per-face gradient 1062 -> 443 us.  The
 // per-face arrays alone take 240 to 350 us at the copy rate; the rest is
 // instruction issue (about 800 per brick, scalar ones among them): neither
 // more waves per SIMD nor fewer cache requests (faces in order through LDS,
@@ -138,9 +138,9 @@ __device__ __forceinline__ T load_uniform(const T *p, uint32_t i) {
 
 struct FaceTables {
   Topo T;
-  const int64_t *fbase;  // per leaf cell (device order): id of its first owned face
+  const int64_t *fbase;  // per leaf brick (device order): id of its first face
   const int32_t *canon;  // device leaf brick -> canonical leaf brick
-  __device__ __forceinline__ int64_t base(uint32_t b) const { return load_uniform(fbase, b * 64u); }
+  __device__ __forceinline__ int64_t base(uint32_t b) const { return load_uniform(fbase, b); }
 };
 
 // Local Morton index, in its own brick, of the fine cell that lane m = 4 j + s
@@ -242,6 +242,224 @@ __device__ __forceinline__ double active_mean(const BrickMeta &M, int m, double 
   const double s = group8_sum((amask >> m) & 1ull ? x : 0.0);
   const int n = __popcll((amask >> (m & 56)) & 0xffull);
   return n ? s / double(n) : 0.0;
+}
+
+// The loop of a workgroup over groups of W bricks consecutive in Morton order
+// (each XCD one contiguous eighth of the groups, as wave_loop).
+struct GroupLoop {
+  uint32_t first, end, step;
+};
+template <int W>
+__device__ __forceinline__ GroupLoop group_loop(uint32_t nlb) {
+  const uint32_t groups = (nlb + W - 1) / W;
+  const uint32_t chunk = (groups + 7u) >> 3;
+  const uint32_t lo = (blockIdx.x & 7u) * chunk;
+  return {lo + (blockIdx.x >> 3), lo + chunk < groups ? lo + chunk : groups, gridDim.x >> 3};
+}
+constexpr int kGroupWaves = 8;
+
+// ---------------------------------------------------------------------------
+// coefficient assembly
+// ---------------------------------------------------------------------------
+struct AssembleArgs {
+  FaceTables F;
+  const double *beta;  // canonical face order
+  int bc[6];
+  double theta;
+  double *coef;        // nlb * 256
+  double *tc;          // n_tplus * 48
+};
+
+// Sides towards finer leaves: per cell on such a side the sum of its 4
+// sub-face coefficients over 2, left in the cell's minus-face coefficient of
+// the side's axis for k_assemble (a cell lies on at most one side per axis).
+// The sub-faces are one per lane (fine_cell); the dependent loads (child ids,
+// their records, the faces) are requested for all sides at once.
+__global__ void __launch_bounds__(kBlock) k_assemble_fine(AssembleArgs A) {
+  const uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
+  const int m = threadIdx.x & (kWave - 1);
+  if (b >= A.F.T.nlb) return;
+  const BrickMeta M = load_meta(A.F.T.meta, b);
+  if (!(M.flags & kFlagInner)) return;
+  uint32_t fl[6];
+  int64_t f0[6];
+  int q[6];
+#pragma unroll
+  for (int d = 0; d < 6; ++d)
+    if ((M.flags >> (8 + d)) & 1u) {
+      int o;
+      q[d] = fine_cell(d, m, o);
+      const uint32_t cb = uint32_t(A.F.T.child[8 * int64_t(M.nbr[d]) + o]);
+      fl[d] = A.F.T.meta[cb].flags;
+      f0[d] = A.F.fbase[cb];
+    }
+  double be[6];
+#pragma unroll
+  for (int d = 0; d < 6; ++d)
+    if ((M.flags >> (8 + d)) & 1u) be[d] = A.beta[f0[d] + face_slot(fl[d], q[d], d ^ 1)];
+  const double hf = ldexp(1.0, -(M.level + 1));
+  double *cf = A.coef + uint64_t(b) * 256u;
+#pragma unroll
+  for (int d = 0; d < 6; ++d)
+    if ((M.flags >> (8 + d)) & 1u) {
+      const double s = fine_sum(be[d] * hf * 0.5, face_interleaved(m, d >> 1));
+      if (dev_outside(m, d)) cf[(1 + (d >> 1)) * 64 + m] = s;
+    }
+}
+
+// Leaf coefficients (Eq. 3): per direction the face coefficient beta S / h
+// (same level or the fine side of a T-junction), beta S / (theta h) at a
+// Dirichlet wall, 0 at a Neumann wall, and for a finer neighbour the sum of
+// its 4 sub-face coefficients over 2; c is the sum over directions.  Laid
+// out as k_divergence; the sums of a side towards finer leaves are taken
+// before, by k_assemble_fine.  Moves beta once and the coefficients once (1.5
+// GB at 26.3M leaves, 240 us at the copy rate); one lane per cell with tables
+// of 9 bytes per cell and dependent loads took 750 us, this form with the
+// sub-faces in the same kernel 760 us (their code costs every brick), the two
+// 561 us.
+__global__ void __launch_bounds__(kGroupWaves * kWave) k_assemble(AssembleArgs A) {
+  __shared__ double slots[kGroupWaves][kFaceSlots];
+  const uint32_t w = wave_id();
+  const FaceLane L = face_lane();
+  const GroupLoop G = group_loop<kGroupWaves>(A.F.T.nlb);
+  for (uint32_t g = G.first; g < G.end; g += G.step) {
+    const uint32_t b0 = g * kGroupWaves, b = b0 + w;
+    const bool here = b < A.F.T.nlb;
+    const BrickMeta M = load_meta(A.F.T.meta, here ? b : b0);
+    const double h = ldexp(1.0, -M.level);
+    const uint32_t nf = here ? face_total(M.flags) : 0u;
+    const int64_t own = A.F.base(here ? b : b0);
+    double bo[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t k = uint32_t(i * kWave + L.m);
+      bo[i] = k < nf ? (A.beta + own)[k] : 0.0;
+    }
+    // beta of the leaf beyond each plus side: in this workgroup (its slot),
+    // else loaded
+    double bn[3];
+    uint32_t at[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const int d = 2 * a + 1;
+      const uint32_t n = uint32_t(M.nbr[d]);
+      bn[a] = 0.0;
+      at[a] = 0u;
+      if (n < A.F.T.nlb) {
+        const uint32_t flags = load_meta(A.F.T.meta, n).flags;
+        const uint32_t k = first_slot(flags, uint32_t(dev_partner(L.m, d)), L.cntp[a]) +
+                           before_minus(flags, L.out, d - 1);
+        if (n - b0 < uint32_t(kGroupWaves)) at[a] = (n - b0) * kFaceSlots + k;
+        else if ((L.out >> d) & 1u) bn[a] = (A.beta + A.F.base(n))[k];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) slots[w][i * kWave + L.m] = bo[i];
+    __syncthreads();
+    uint32_t slot = w * kFaceSlots + first_slot(M.flags, uint32_t(L.m), L.cnt);
+    const double *s = &slots[0][0];
+    double k[6];
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      const int a = d >> 1;
+      const bool out = (L.out >> d) & 1u;
+      const bool wall = M.nbr[d] == dWall;
+      double x = 0.0;
+      if ((d & 1) && !owns_plus(M.flags, d)) {
+        const uint32_t n = uint32_t(M.nbr[d]);
+        x = (n < A.F.T.nlb && n - b0 < uint32_t(kGroupWaves) ? s[at[a]] : bn[a]) * h;
+      } else if (owns_face(M.flags, L.out, d)) {
+        x = s[slot++];
+        x = out && wall ? (A.bc[d] == 1 ? x * (h / A.theta) : 0.0) : x * h;
+      }
+      if (((M.flags >> (8 + d)) & 1u) && here && out)  // k_assemble_fine's
+        x = (A.coef + uint64_t(b) * 256u)[uint32_t((1 + a) * 64 + L.m)];
+      if ((d & 1) && here && ((M.flags >> d) & 1u) && out)
+        A.tc[uint32_t(M.tplus) * 48u + uint32_t(a * 16 + dev_face_index(L.m, a))] = x;
+      k[d] = x;
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double t = shfl(k[2 * a], dev_partner(L.m, 2 * a + 1));
+      k[2 * a + 1] = (L.out >> (2 * a + 1)) & 1u ? k[2 * a + 1] : t;
+    }
+    if (here) {
+      double *cf = A.coef + uint64_t(b) * 256u;
+      cf[L.m] = k[0] + k[1] + k[2] + k[3] + k[4] + k[5];
+      cf[64 + L.m] = k[0];
+      cf[128 + L.m] = k[2];
+      cf[192 + L.m] = k[4];
+    }
+    __syncthreads();  // the slots are read before the next group's are stored
+  }
+}
+
+// Faces in canonical order: owner cell, direction, the leaf cell on the other
+// side (-1 at a wall) and the kind (0 wall, 1 same level, 2 coarser).  The
+// cells' entries go through LDS, so that a brick's range is stored in order
+// (writes 18 bytes per face; 81M faces 880 -> 354 us against one lane storing
+// its cell's faces).
+__global__ void __launch_bounds__(kBlock) k_oct_faces(FaceTables F, int64_t *owner, int8_t *dir,
+                                                      int64_t *other, int8_t *kind) {
+  __shared__ int64_t so[kWavesPerBlock][kFaceSlots];
+  __shared__ uint16_t sd[kWavesPerBlock][kFaceSlots];
+  int64_t *o = so[wave_id()];
+  uint16_t *e = sd[wave_id()];
+  const FaceLane L = face_lane();
+  const WaveLoop W = wave_loop(F.T.nlb);
+  for (uint32_t b = W.first; b < W.end; b += W.step) {
+    const BrickMeta M = load_meta(F.T.meta, b);
+    const int64_t c0 = int64_t(load_uniform(F.canon, b)) * 64;
+    uint32_t slot = first_slot(M.flags, uint32_t(L.m), L.cnt);
+#pragma unroll
+    for (int d = 0; d < 6; ++d) {
+      if ((d & 1) && !owns_plus(M.flags, d)) continue;
+      const int32_t n = M.nbr[d];
+      int64_t across = -1;  // beyond the brick's face d (wave uniform parts)
+      int k = 0;
+      if (n <= dCoarseBase) {
+        across = int64_t(load_uniform(F.canon, uint32_t(dev_decode_coarse(n)))) * 64 +
+                 coarse_local(M, L.m, d);
+        k = 2;
+      } else if (n >= 0 && uint32_t(n) < F.T.nlb) {
+        across = int64_t(load_uniform(F.canon, uint32_t(n))) * 64 + dev_partner(L.m, d);
+        k = 1;
+      }
+      if (!owns_face(M.flags, L.out, d)) continue;
+      const bool out = (L.out >> d) & 1u;
+      o[slot] = out ? across : c0 + dev_partner(L.m, d);
+      e[slot] = uint16_t(L.m | (d << 6) | ((out ? k : 1) << 9));
+      ++slot;
+    }
+    wave_lds_fence();
+    const int64_t f0 = F.base(b);
+    const uint32_t nf = face_total(M.flags);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t k = uint32_t(i * kWave + L.m);
+      if (k < nf) {
+        const uint32_t x = e[k];
+        (owner + f0)[k] = c0 + int64_t(x & 63u);
+        (other + f0)[k] = o[k];
+        (dir + f0)[k] = int8_t((x >> 6) & 7u);
+        (kind + f0)[k] = int8_t(x >> 9);
+      }
+    }
+    wave_lds_fence();
+  }
+}
+
+// Per leaf brick: its number of faces, at its canonical position.
+__global__ void k_face_counts(const BrickMeta *meta, const int32_t *canon, uint32_t nlb,
+                              int64_t *count) {
+  const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b < nlb) count[canon[b]] = int64_t(face_total(meta[b].flags));
+}
+// and from their exclusive scan the id of its first face
+__global__ void k_face_bases(const int32_t *canon, uint32_t nlb, const int64_t *scan,
+                             int64_t *fbase) {
+  const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
+  if (b < nlb) fbase[b] = scan[canon[b]];
 }
 
 // Per-face gradient of the adjoint: dL/dbeta_f = -lambda^T (dA/dbeta_f) p

@@ -143,79 +143,8 @@ __device__ __forceinline__ int coarse_local(const BrickMeta &M, int m, int d) {
 }
 
 // ---------------------------------------------------------------------------
-// assembly
+// hierarchy build (the assembly is in face_kernels.hpp)
 // ---------------------------------------------------------------------------
-struct AssembleArgs {
-  Topo T;
-  const int64_t *fbase;  // per device leaf cell: canonical id of its first owned face
-  const uint8_t *fmask;  // per device leaf cell: owned directions
-  const double *beta;    // canonical face order
-  int bc[6];
-  double theta;
-  double *coef;          // nlb * 256
-  double *tc;            // n_tplus * 48
-};
-
-__device__ __forceinline__ int64_t face_id(const AssembleArgs &A, uint32_t cell, int d) {
-  return A.fbase[cell] + __popc(unsigned(A.fmask[cell]) & ((1u << d) - 1u));
-}
-
-// Leaf coefficients (Eq. 3): per direction the face coefficient
-// beta S / h (same level or the fine side of a T-junction), beta S/(theta h)
-// at a Dirichlet wall, 0 at a Neumann wall, and for a finer neighbour the
-// sum of its 4 sub-face coefficients over 2; c is the sum over directions.
-__global__ void __launch_bounds__(kBlock) k_assemble(AssembleArgs A) {
-  uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  if (b >= A.T.nlb) return;
-  const BrickMeta M = A.T.meta[b];
-  double h = ldexp(1.0, -M.level);
-  double hf = ldexp(1.0, -(M.level + 1));
-  double dk[6];
-  uint32_t cell = b * 64u + m;
-  for (int d = 0; d < 6; ++d) {
-    int a = d >> 1;
-    int p = dev_partner(m, d);
-    double k = 0.0;
-    if (!dev_outside(m, d)) {
-      k = (d & 1) ? A.beta[face_id(A, b * 64u + p, d - 1)] * h
-                  : A.beta[face_id(A, cell, d)] * h;
-    } else {
-      int32_t nb = M.nbr[d];
-      if (nb == dWall) {
-        k = A.bc[d] == 1 ? A.beta[face_id(A, cell, d)] * (h / A.theta) : 0.0;
-      } else if (nb >= 0 && uint32_t(nb) < A.T.nlb) {
-        k = (d & 1) ? A.beta[face_id(A, uint32_t(nb) * 64u + p, d - 1)] * h
-                    : A.beta[face_id(A, cell, d)] * h;
-      } else if (nb >= 0) {
-        // finer neighbours: the leaf children of inner cell p of brick nb
-        int32_t cb = A.T.child[8 * int64_t(nb) + (p >> 3)];
-        int base = (p & 7) << 3;
-        int o0 = a == 0 ? 1 : 0;
-        int o1 = a == 2 ? 1 : 2;
-        int abit = (d & 1) ? 0 : 1;
-        double acc = 0.0;
-        for (int n = 0; n < 4; ++n) {
-          int t = (abit << a) | ((n & 1) << o0) | ((n >> 1) << o1);
-          acc = acc + A.beta[face_id(A, uint32_t(cb) * 64u + (base | t), d ^ 1)] * hf / 2.0;
-        }
-        k = acc;
-      } else {
-        // coarser neighbour: this cell owns the T-face
-        k = A.beta[face_id(A, cell, d)] * h;
-        if (d & 1) A.tc[uint32_t(M.tplus) * 48u + a * 16 + dev_face_index(m, a)] = k;
-      }
-    }
-    dk[d] = k;
-  }
-  double c = dk[0] + dk[1] + dk[2] + dk[3] + dk[4] + dk[5];
-  double *cf = A.coef + b * 256u;
-  cf[m] = c;
-  cf[64 + m] = dk[0];
-  cf[128 + m] = dk[2];
-  cf[192 + m] = dk[4];
-}
-
 // The parent-neighbour table (ParentNbrs), one thread per brick.
 __global__ void __launch_bounds__(kBlock) k_parent_nbrs(Topo T, ParentNbrs *out) {
   uint32_t b = blockIdx.x * kBlock + threadIdx.x;

@@ -281,6 +281,11 @@ inline int64_t cap32(int64_t bricks) {
 inline unsigned level_grid(int64_t bricks) {
   return grid_waves(bricks, waves_override() ? waves_override() : cap32(bricks));
 }
+// workgroups of kGroupWaves waves over the leaf bricks (group_loop)
+inline unsigned group_grid(int64_t bricks) {
+  int64_t groups = (bricks + kGroupWaves - 1) / kGroupWaves;
+  return unsigned(8 * std::min<int64_t>((groups + 7) / 8, kWavesPerXcd32 / kGroupWaves));
+}
 // stencils on values of type V
 template <class V>
 inline unsigned stencil_grid(int64_t bricks) {
@@ -324,8 +329,7 @@ inline unsigned grid_reduce(int64_t bricks) {
 struct DeviceTopology {
   DevBuf<BrickMeta> meta;             // act = 0
   DevBuf<int32_t> child;              // 8 per device brick
-  DevBuf<int64_t> fbase;              // per device leaf cell
-  DevBuf<uint8_t> fmask;              // per device leaf cell
+  DevBuf<int64_t> fbase;              // per device leaf brick: id of its first face
   DevBuf<int32_t> canon;              // device leaf brick -> canonical leaf brick
   std::vector<Range> range;           // per level
   uint32_t nlb = 0, nb = 0;
@@ -604,17 +608,11 @@ static void build_device_topology(const Topology &T, DeviceTopology &D, hipStrea
       child[8 * int64_t(perm[b]) + o] = c >= 0 ? perm[c] : -1;
     }
   }
-  std::vector<int64_t> fbase(nlb * kCells);
-  std::vector<uint8_t> fmask(nlb * kCells);
-  for (int64_t b = 0; b < nlb; ++b)
-    for (int m = 0; m < kCells; ++m) {
-      fbase[int64_t(perm[b]) * kCells + m] = T.cell_fbase[b * kCells + m];
-      fmask[int64_t(perm[b]) * kCells + m] = T.cell_fmask[b * kCells + m];
-    }
+  std::vector<int64_t> fbase(nlb);
+  for (int64_t b = 0; b < nlb; ++b) fbase[perm[b]] = T.cell_fbase[b * kCells];
   D.meta.upload(meta_host, s);
   D.child.upload(child, s);
   D.fbase.upload(fbase, s);
-  D.fmask.upload(fmask, s);
   D.canon.upload(canon, s);
   HIP_CHECK(hipStreamSynchronize(s));
 }
@@ -753,8 +751,7 @@ static std::string build_octree_device(const mfmg_refine_spec *spec,
   D.meta.alloc(nb);
   D.child.alloc(8 * nb);
   D.canon.alloc(nlb);
-  D.fbase.alloc(nlb * kCells);
-  D.fmask.alloc(nlb * kCells);
+  D.fbase.alloc(nlb);
   DevBuf<int32_t> inv;
   DevBuf<int> err;
   inv.alloc(nlb);
@@ -784,13 +781,13 @@ static std::string build_octree_device(const mfmg_refine_spec *spec,
   scan_exclusive(work.p, int64_t(nlb), totals.p, s);
   hipLaunchKernelGGL(k_oct_tplus, dim3(grid_elems(int64_t(nlb), 256)), dim3(256), 0, s,
                      D.meta.p, (const int32_t *)inv.p, uint32_t(nlb), (const int64_t *)work.p);
-  hipLaunchKernelGGL(k_oct_fmask, dim3(grid_for(int64_t(nlb))), dim3(kBlock), 0, s,
+  hipLaunchKernelGGL(k_face_counts, dim3(grid_elems(int64_t(nlb), 256)), dim3(256), 0, s,
                      (const BrickMeta *)D.meta.p, (const int32_t *)D.canon.p, uint32_t(nlb),
-                     D.fmask.p, work.p);
+                     work.p);
   scan_exclusive(work.p, int64_t(nlb), totals.p + 1, s);
-  hipLaunchKernelGGL(k_oct_fbase, dim3(grid_for(int64_t(nlb))), dim3(kBlock), 0, s,
-                     (const uint8_t *)D.fmask.p, (const int32_t *)D.canon.p, uint32_t(nlb),
-                     (const int64_t *)work.p, D.fbase.p);
+  hipLaunchKernelGGL(k_face_bases, dim3(grid_elems(int64_t(nlb), 256)), dim3(256), 0, s,
+                     (const int32_t *)D.canon.p, uint32_t(nlb), (const int64_t *)work.p,
+                     D.fbase.p);
   int64_t th2[2];
   HIP_CHECK(hipMemcpyAsync(th2, totals.p, sizeof(th2), hipMemcpyDeviceToHost, s));
   HIP_CHECK(hipMemcpyAsync(&eh, err.p, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -824,10 +821,9 @@ static mfmg_status faces_to(const mfmg_octree *t, int64_t *owner, int8_t *dir, i
                             int8_t *kind, hipStream_t s) {
   std::shared_ptr<DeviceTopology> D = device_topology(t, s);
   if (D->nlb)
-    hipLaunchKernelGGL(k_oct_faces, dim3(grid_for(D->nlb)), dim3(kBlock), 0, s,
-                       (const BrickMeta *)D->meta.p, (const int32_t *)D->canon.p,
-                       (const int64_t *)D->fbase.p, (const uint8_t *)D->fmask.p, D->nlb, owner,
-                       dir, other, kind);
+    hipLaunchKernelGGL(k_oct_faces, dim3(level_grid(D->nlb)), dim3(kBlock), 0, s,
+                       FaceTables{make_topo(*D, D->meta.p), D->fbase.p, D->canon.p}, owner, dir,
+                       other, kind);
   HIP_CHECK(hipGetLastError());
   return MFMG_OK;
 }
@@ -947,16 +943,17 @@ extern "C" mfmg_status mfmg_assemble_coeffs(const mfmg_octree *tree, const doubl
     co->coef.alloc(size_t(tree->nlb) * 256);
     co->tc.alloc(size_t(tree->n_tplus) * 48 + 1);
     AssembleArgs A;
-    A.T = make_topo(*co->dt, co->dt->meta.p);
-    A.fbase = co->dt->fbase.p;
-    A.fmask = co->dt->fmask.p;
+    A.F = FaceTables{make_topo(*co->dt, co->dt->meta.p), co->dt->fbase.p, co->dt->canon.p};
     A.beta = face_beta;
     for (int d = 0; d < 6; ++d) A.bc[d] = bc->bc[d];
     A.theta = bc->theta;
     A.coef = co->coef.p;
     A.tc = co->tc.p;
-    if (tree->nlb)
-      hipLaunchKernelGGL(k_assemble, dim3(grid_for(tree->nlb)), dim3(kBlock), 0, s, A);
+    if (tree->nlb) {
+      hipLaunchKernelGGL(k_assemble_fine, dim3(grid_for(tree->nlb)), dim3(kBlock), 0, s, A);
+      hipLaunchKernelGGL(k_assemble, dim3(group_grid(tree->nlb)), dim3(kGroupWaves * kWave), 0, s,
+                         A);
+    }
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(s));
     *out = co.release();
@@ -2338,9 +2335,8 @@ extern "C" mfmg_status mfmg_divergence(mfmg_hierarchy *h, const double *face_bet
     A.u = face_u;
     A.div = div;
     if (D.nlb) {
-      int64_t groups = (int64_t(D.nlb) + kDivWaves - 1) / kDivWaves;
-      unsigned g = unsigned(8 * std::min<int64_t>((groups + 7) / 8, kWavesPerXcd32 / kDivWaves));
-      hipLaunchKernelGGL(k_divergence, dim3(g), dim3(kDivWaves * kWave), 0, s, A);
+      hipLaunchKernelGGL(k_divergence, dim3(group_grid(D.nlb)), dim3(kGroupWaves * kWave), 0, s,
+                         A);
       hipLaunchKernelGGL(k_divergence_fine, dim3(grid_for(D.nlb)), dim3(kBlock), 0, s, A);
     }
     HIP_CHECK(hipGetLastError());

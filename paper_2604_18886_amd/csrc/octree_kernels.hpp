@@ -404,59 +404,6 @@ __global__ void k_oct_tplus(BrickMeta *meta, const int32_t *inv, uint32_t nlb,
   M->tplus = (M->flags & 0x2au) ? int32_t(pos[j]) : -1;
 }
 
-// Directions whose face a leaf cell owns: a wall, a coarser neighbour, or a
-// same-level leaf neighbour on the minus side (finer neighbours own the
-// split faces).
-__device__ __forceinline__ uint32_t oct_owned(const BrickMeta &M, uint32_t nlb, int m) {
-  int p[3] = {dev_cx(m), dev_cy(m), dev_cz(m)};
-  uint32_t mask = 0;
-  for (int d = 0; d < 6; ++d) {
-    int a = d >> 1;
-    bool inside = (d & 1) ? p[a] < kBrick - 1 : p[a] > 0;
-    bool own;
-    if (inside) {
-      own = (d & 1) == 0;
-    } else {
-      int32_t n = M.nbr[d];
-      if (n == kWall || n <= kCoarseBase) own = true;
-      else own = uint32_t(n) < nlb && (d & 1) == 0;
-    }
-    if (own) mask |= 1u << d;
-  }
-  return mask;
-}
-
-// One wave per device leaf brick: owned-face masks and the brick's face
-// count at its canonical position.
-__global__ void __launch_bounds__(kBlock) k_oct_fmask(const BrickMeta *meta, const int32_t *canon,
-                                                      uint32_t nlb, uint8_t *fmask,
-                                                      int64_t *bcount) {
-  uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  if (b >= nlb) return;
-  uint32_t mask = oct_owned(meta[b], nlb, m);
-  fmask[uint64_t(b) * 64 + m] = uint8_t(mask);
-  uint32_t n = wave_sum(uint32_t(__popc(mask)));
-  if (m == 0) bcount[canon[b]] = int64_t(n);
-}
-
-// first face id of each cell: the brick's base plus the faces of the lanes
-// before it
-__global__ void __launch_bounds__(kBlock) k_oct_fbase(const uint8_t *fmask, const int32_t *canon,
-                                                      uint32_t nlb, const int64_t *bbase,
-                                                      int64_t *fbase) {
-  uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  if (b >= nlb) return;
-  uint32_t n = __popc(fmask[uint64_t(b) * 64 + m]);
-  uint32_t incl = n;
-  for (int w = 1; w < kWave; w <<= 1) {
-    uint32_t t = __shfl_up(incl, w, kWave);
-    if (m >= w) incl += t;
-  }
-  fbase[uint64_t(b) * 64 + m] = bbase[canon[b]] + int64_t(incl - n);
-}
-
 // ---------------------------------------------------------------------------
 // exclusive scan of int64 (three passes; one workgroup adds the tile sums)
 // ---------------------------------------------------------------------------
@@ -530,58 +477,6 @@ __global__ void __launch_bounds__(kBlock) k_oct_leaves(const BrickMeta *meta, co
   ijk[3 * c] = M.coord[0] * kBrick + dev_cx(m);
   ijk[3 * c + 1] = M.coord[1] * kBrick + dev_cy(m);
   ijk[3 * c + 2] = M.coord[2] * kBrick + dev_cz(m);
-}
-
-// faces in canonical order: owner cell, direction, the leaf cell on the
-// other side (-1 at a wall) and the kind (0 wall, 1 same level, 2 coarser)
-__global__ void __launch_bounds__(kBlock) k_oct_faces(const BrickMeta *meta, const int32_t *canon,
-                                                      const int64_t *fbase, const uint8_t *fmask,
-                                                      uint32_t nlb, int64_t *owner, int8_t *dir,
-                                                      int64_t *other, int8_t *kind) {
-  uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
-  int m = threadIdx.x & (kWave - 1);
-  if (b >= nlb) return;
-  const BrickMeta M = meta[b];
-  int64_t c = int64_t(canon[b]) * 64 + m;
-  int64_t f = fbase[uint64_t(b) * 64 + m];
-  uint32_t mask = fmask[uint64_t(b) * 64 + m];
-  int p[3] = {dev_cx(m), dev_cy(m), dev_cz(m)};
-  for (int d = 0; d < 6; ++d) {
-    if (!((mask >> d) & 1u)) continue;
-    int a = d >> 1;
-    int q[3] = {p[0], p[1], p[2]};
-    q[a] += (d & 1) ? 1 : -1;
-    int64_t o;
-    int k;
-    if (q[a] >= 0 && q[a] < kBrick) {
-      o = int64_t(canon[b]) * 64 + dev_morton(q[0], q[1], q[2]);
-      k = 1;
-    } else {
-      int32_t n = M.nbr[d];
-      if (n == kWall) {
-        o = -1;
-        k = 0;
-      } else if (n >= 0) {
-        o = int64_t(canon[n]) * 64 + dev_morton(q[0] & 3, q[1] & 3, q[2] & 3);
-        k = 1;
-      } else {
-        int32_t J = kCoarseBase - n;
-        const BrickMeta &MJ = meta[J];
-        int cc[3];
-        for (int e = 0; e < 3; ++e) {
-          int64_t g = int64_t(M.coord[e]) * kBrick + q[e];
-          cc[e] = int((g >> 1) - int64_t(MJ.coord[e]) * kBrick);
-        }
-        o = int64_t(canon[J]) * 64 + dev_morton(cc[0], cc[1], cc[2]);
-        k = 2;
-      }
-    }
-    owner[f] = c;
-    dir[f] = int8_t(d);
-    other[f] = o;
-    kind[f] = int8_t(k);
-    ++f;
-  }
 }
 
 }  // namespace mfmg

@@ -38,18 +38,13 @@ struct DivArgs {
 // which lie in two thirds of the cache lines of its whole range, so a
 // workgroup takes eight bricks consecutive in Morton order and half of these
 // neighbours' flows come from its LDS.
-constexpr int kDivWaves = 8;
-__global__ void __launch_bounds__(kDivWaves * kWave) k_divergence(DivArgs A) {
-  __shared__ double slots[kDivWaves][kFaceSlots];
+__global__ void __launch_bounds__(kGroupWaves * kWave) k_divergence(DivArgs A) {
+  __shared__ double slots[kGroupWaves][kFaceSlots];
   const uint32_t w = wave_id();
   const FaceLane L = face_lane();
-  // each XCD takes one contiguous eighth of the groups (wave_loop)
-  const uint32_t groups = (A.F.T.nlb + kDivWaves - 1) / kDivWaves;
-  const uint32_t chunk = (groups + 7u) >> 3;
-  const uint32_t lo = (blockIdx.x & 7u) * chunk;
-  const uint32_t hi = lo + chunk < groups ? lo + chunk : groups;
-  for (uint32_t g = lo + (blockIdx.x >> 3); g < hi; g += gridDim.x >> 3) {
-    const uint32_t b0 = g * kDivWaves;
+  const GroupLoop G = group_loop<kGroupWaves>(A.F.T.nlb);
+  for (uint32_t g = G.first; g < G.end; g += G.step) {
+    const uint32_t b0 = g * kGroupWaves;
     const uint32_t b = b0 + w;
     const bool here = b < A.F.T.nlb;
     BrickMeta M = load_meta(A.F.T.meta, here ? b : b0);
@@ -76,7 +71,7 @@ __global__ void __launch_bounds__(kDivWaves * kWave) k_divergence(DivArgs A) {
         const uint32_t flags = load_meta(A.F.T.meta, n).flags;
         const uint32_t k = first_slot(flags, uint32_t(dev_partner(L.m, d)), L.cntp[a]) +
                            before_minus(flags, L.out, d - 1);
-        if (n - b0 < uint32_t(kDivWaves)) {
+        if (n - b0 < uint32_t(kGroupWaves)) {
           at[a] = (n - b0) * kFaceSlots + k;
         } else if ((L.out >> d) & 1u) {
           const int64_t f0 = A.F.base(n);
@@ -101,7 +96,7 @@ __global__ void __launch_bounds__(kDivWaves * kWave) k_divergence(DivArgs A) {
       if (out) {
         const uint32_t n = uint32_t(M.nbr[d]);
         if (owns_plus(M.flags, d)) t = s[slot++];
-        else if (n < A.F.T.nlb && n - b0 < uint32_t(kDivWaves)) t = s[at[a]];
+        else if (n < A.F.T.nlb && n - b0 < uint32_t(kGroupWaves)) t = s[at[a]];
         else t = be[a] * h2 * uu[a];
       }
       div = div - f + t;
@@ -133,7 +128,7 @@ __global__ void __launch_bounds__(kBlock) k_divergence_fine(DivArgs A) {
       q[d] = fine_cell(d, m, o);
       const uint32_t cb = uint32_t(A.F.T.child[8 * int64_t(M.nbr[d]) + o]);
       flags[d] = A.F.T.meta[cb].flags;
-      f0[d] = A.F.fbase[uint64_t(cb) * 64u];
+      f0[d] = A.F.fbase[cb];
     }
   double be[6], uu[6];
 #pragma unroll
