@@ -995,31 +995,55 @@ __global__ void __launch_bounds__(kBlock) k_smooth(LevelArgs<V, CL, CI> A, int c
   }
 }
 
-// The first half-sweep of a level whose bricks are all leaves, from a zero
-// iterate: every neighbour, ghost and wall value is 0, so the sweep sets
-// u = b / c on the cells of the colour and 0 on all others (which also
-// clears the iterate).
+// First half-sweep of a level from a zero iterate (the finest level; levels in
+// correction form; the transposed cycle's first visits): every neighbour, ghost
+// and wall value is 0, so u = b / c on the active
+// cells of the colour, 0 on all others.  On inner bricks the diagonal is the
+// sum of the six face coefficients, as in every half-sweep (the stored FP16
+// diagonal is rounded on its own).  It also clears the iterate.
+template <bool INNER, class V, class CL, class CI, int CP>
+__device__ __forceinline__ void first_sweep_brick(const LevelView<V, CL, CI, CP> &X,
+                                             const LaneC<V, CL> &L, uint32_t b, int colour) {
+  const BrickMeta M = load_meta(X.meta, b);
+  bool act = (act_mask(M) >> L.m) & 1ull;
+  if constexpr (!INNER) {  // leaves store it unrounded
+    V c = own_coef<false>(X, b, 0, L.m);
+    V g = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
+    bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(g, c) : V(0));
+    return;
+  }
+  V k[6];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    V kown = own_coef<INNER>(X, b, 1 + a, L.m);
+    V kl = V(bload_bytes<CL, side_pol(CP)>(X.pf, L.foff[a], b * uint32_t(48 * sizeof(CL))));
+    V ks = shfl(kown, L.p[2 * a + 1]);
+    k[2 * a] = kown;
+    k[2 * a + 1] = L.out[2 * a + 1] ? kl : ks;
+  }
+  V rhs = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
+  V c = ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
+  bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(rhs, c) : V(0));
+}
+
 template <class V, class CL, class CI, int CP = kCpolDefault>
-__global__ void __launch_bounds__(kBlock) k_smooth_zero(LevelArgs<V, CL, CI> A, int colour) {
+__global__ void __launch_bounds__(kBlock) k_first_sweep(LevelArgs<V, CL, CI> A, int colour) {
   if (A.done && *A.done) return;
   const LaneC<V, CL> L = lane_consts<V, CL>();
   const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
-  const WaveLoop W = wave_loop(A.R.n_leaf);
+  const WaveLoop W = wave_loop(A.R.n());
   for (uint32_t i = W.first; i < W.end; i += W.step) {
-    uint32_t b = A.R.leaf_lo + i;
-    const BrickMeta M = load_meta(X.meta, b);
-    bool act = (act_mask(M) >> L.m) & 1ull;
-    V c = own_coef<false>(X, b, 0, L.m);
-    V rhs = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
-    bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(rhs, c) : V(0));
+    if (i < A.R.n_leaf) first_sweep_brick<false>(X, L, A.R.leaf_lo + i, colour);
+    else first_sweep_brick<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
   }
 }
 
 // Residual, restriction and FAS initial guess from one brick of level l to
 // its parent cells:  b_P = beta_mg (1/alpha) sum_children r,
 // u_P = u*_P = mean of the active children (k_fas_rhs then adds
-// A^{l-1} u* on inner cells).
-template <bool INNER, class V, class CL, class CI, int CP>
+// A^{l-1} u* on inner cells).  CORR: level l - 1 is in correction form, where
+// the iterate is u - u*: u_P = u*_P = 0, and no k_fas_rhs follows.
+template <bool INNER, bool CORR, class V, class CL, class CI, int CP>
 __device__ __forceinline__ void restrict_brick(const LevelView<V, CL, CI, CP> &X,
                                                const LaneC<V, CL> &L,
                                                uint32_t b, V scale) {
@@ -1040,22 +1064,22 @@ __device__ __forceinline__ void restrict_brick(const LevelView<V, CL, CI, CP> &X
   if ((L.m & 7u) == 0) {
     uint32_t base = uint32_t(M.parent) * 64u + uint32_t(octant_of(M)) * 8u;
     uint32_t q = L.m >> 3;
-    V ust = cnt ? div_by(us, V(cnt)) : V(0);
+    V ust = !CORR && cnt ? div_by(us, V(cnt)) : V(0);
     bstore<V>(X.b, q, base, rs * scale);
     bstore<V>(X.u, q, base, ust);
     bstore<V>(X.us, q, base - X.nlb * 64u, ust);
   }
 }
 
-template <class V, class CL, class CI, int CP = kCpolDefault>
+template <class V, class CL, class CI, int CP = kCpolDefault, bool CORR = false>
 __global__ void __launch_bounds__(kBlock) k_restrict(LevelArgs<V, CL, CI> A, V scale) {
   if (A.done && *A.done) return;
   const LaneC<V, CL> L = lane_consts<V, CL>();
   const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
   const WaveLoop W = wave_loop(A.R.n());
   for (uint32_t i = W.first; i < W.end; i += W.step) {
-    if (i < A.R.n_leaf) restrict_brick<false>(X, L, A.R.leaf_lo + i, scale);
-    else restrict_brick<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), scale);
+    if (i < A.R.n_leaf) restrict_brick<false, CORR>(X, L, A.R.leaf_lo + i, scale);
+    else restrict_brick<true, CORR>(X, L, A.R.inner_lo + (i - A.R.n_leaf), scale);
   }
 }
 
@@ -1078,46 +1102,6 @@ __global__ void __launch_bounds__(kBlock) k_fas_rhs(LevelArgs<V, CL, CI> A) {
     V S = stencil_sum(X, L, b, M, u, k0, k1, k2, c);
     bool act = (act_mask(M) >> L.m) & 1ull;
     bstore<V>(X.b, L.m, b * 64u, act ? rhs + (c * u - S) : V(0));
-  }
-}
-
-// The first pre-smoothing half-sweep of a level with the FAS right-hand
-// side folded in, for a level with no leaf at or below it (all its bricks
-// are inner, none has a T-face).  Right after the restriction u = u* on
-// every cell, so one neighbour sum S of u* gives both b += c u* - S (stored
-// on every cell, as k_fas_rhs) and, on the cells of the colour,
-// u = (b + S) / c (as k_smooth).  The sum is read from the u* array, which
-// this launch does not write, so no brick's sum can see another brick's
-// update; values and sums are those of k_fas_rhs and k_smooth.  A
-// neighbour that is not an inner brick (none, on such a level) would read
-// as a wall.
-template <class V, class CL, class CI, int CP = kCpolDefault>
-__global__ void __launch_bounds__(kBlock) k_smooth_fas(LevelArgs<V, CL, CI> A, int colour) {
-  if (A.done && *A.done) return;
-  const LaneC<V, CL> L = lane_consts<V, CL>();
-  const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
-  LevelView<V, CL, CI, CP> Xs = X;  // u = u*, indexed by brick id - nlb
-  Xs.u = X.us;
-  const WaveLoop W = wave_loop(A.R.n_inner);
-  for (uint32_t i = W.first; i < W.end; i += W.step) {
-    uint32_t b = A.R.inner_lo + i;
-    const BrickMeta M = load_meta(X.meta, b);
-    BrickMeta Ms = M;
-#pragma unroll
-    for (int d = 0; d < 6; ++d)
-      Ms.nbr[d] = M.nbr[d] >= int32_t(X.nlb) ? M.nbr[d] - int32_t(X.nlb) : -1;
-    Ms.flags = M.flags & ~uint32_t(kFlagT);
-    V k0 = own_coef<true>(X, b, 1, L.m);
-    V k1 = own_coef<true>(X, b, 2, L.m);
-    V k2 = own_coef<true>(X, b, 3, L.m);
-    V u = bload<V>(X.us, L.m, (b - X.nlb) * 64u);
-    V rhs = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
-    V c;
-    V S = stencil_sum(Xs, L, b, Ms, u, k0, k1, k2, c);
-    bool act = (act_mask(M) >> L.m) & 1ull;
-    V rf = act ? rhs + (c * u - S) : V(0);
-    bstore<V>(X.b, L.m, b * 64u, rf);
-    if (act && L.colour == colour) bstore<V>(X.u, L.m, b * 64u, div_by(rf + S, c));
   }
 }
 
@@ -1234,9 +1218,10 @@ __global__ void __launch_bounds__(1024) k_coarsest(LevelArgs<V, CL, CI> A, int n
 // (the level above's mu) are taken in one launch.  fas = 0 skips the FAS
 // right-hand side of the first one (a W-cycle's later visits: it is already
 // in B).
-// TR: the same step of the transposed cycle: fas = 1 starts from a zero
-// iterate, the restriction hands the plain residual sums down, the coarsest
-// iterate starts from zero and pscale times it is the correction.
+// CORR: the step in correction form (level f without leaves, where the iterate
+// is u - u*, and the transposed cycle): fas = 1 starts from a zero iterate,
+// the coarsest iterate starts from zero too and pscale times it is the
+// correction.
 //
 // What bounds it: one CU's LDS reads, the barriers and the set-up's loads.  A
 // thread holds pairs of cells that are neighbours along x, one of each colour,
@@ -1328,19 +1313,14 @@ __device__ __forceinline__ V diag_of(const V (&k)[6]) {
   return ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
 }
 
+// Coefficients, reciprocal diagonals, element and bits of pair g of a table of
+// `pairs` pairs; e0: the x parity of its colour-0 cell.
 template <class V>
-__device__ __forceinline__ BottomPair<V> bottom_pair(const uint4 *tab, int f, uint32_t p) {
-  BottomPair<V> P;
-  const uint32_t np = 1u << (3 * f - 1), n = 1u << f;
-  P.bits = 0;
-  if (p >= np) return P;
+__device__ __forceinline__ void pair_coefs(BottomPair<V> &P, const uint4 *tab, uint32_t pairs,
+                                           uint32_t g, uint32_t e0) {
   uint4 unit[BottomUnits<V>::kAll];
 #pragma unroll
-  for (int q = 0; q < BottomUnits<V>::kAll; ++q) unit[q] = tab[uint32_t(q) * np + p];
-  const uint32_t xh = p & ((n >> 1) - 1u);
-  const uint32_t y = ((p >> (f - 1)) & 1u) | (((p >> (f + 1)) & ((n >> 1) - 1u)) << 1);
-  const uint32_t z = ((p >> f) & 1u) | ((p >> (2 * f)) << 1);
-  const uint32_t e0 = (y + z) & 1u;  // x parity of the colour-0 cell
+  for (int q = 0; q < BottomUnits<V>::kAll; ++q) unit[q] = tab[uint32_t(q) * pairs + g];
   V ke[2][6];
   constexpr int per = BottomUnits<V>::kPer;
 #pragma unroll
@@ -1367,10 +1347,18 @@ __device__ __forceinline__ BottomPair<V> bottom_pair(const uint4 *tab, int f, ui
     if constexpr (sizeof(V) == 4) P.rc[c] = __builtin_amdgcn_rcpf(diag_of(P.k[c]));
     else P.rc[c] = V(1) / diag_of(P.k[c]);
   }
-  const uint32_t ix = unit[BottomUnits<V>::kCoef].x, bits = unit[BottomUnits<V>::kCoef].y;
-  P.at = ix;
-  const uint32_t act = bits & 3u;
+  const uint32_t bits = unit[BottomUnits<V>::kCoef].y, act = bits & 3u;
+  P.at = unit[BottomUnits<V>::kCoef].x;
   P.bits = (e0 ? (act >> 1) | ((act & 1u) << 1) : act) | (bits & 4u) | 8u | (e0 << 4);
+}
+
+// Entries of the neighbours of pair p of a grid of 2^f cells per axis.
+template <class V>
+__device__ __forceinline__ void pair_neighbours(BottomPair<V> &P, int f, uint32_t p, uint32_t e0) {
+  const uint32_t np = 1u << (3 * f - 1), n = 1u << f;
+  const uint32_t xh = p & ((n >> 1) - 1u);
+  const uint32_t y = ((p >> (f - 1)) & 1u) | (((p >> (f + 1)) & ((n >> 1) - 1u)) << 1);
+  const uint32_t z = ((p >> f) & 1u) | ((p >> (2 * f)) << 1);
   const uint32_t xm = xh > 0u ? p - 1u : np, xp = xh + 1u < (n >> 1) ? p + 1u : np;
 #pragma unroll
   for (uint32_t c = 0; c < 2; ++c) {  // the even-x cell's +x neighbour is in the pair
@@ -1382,6 +1370,18 @@ __device__ __forceinline__ BottomPair<V> bottom_pair(const uint4 *tab, int f, ui
   P.y[1] = y + 1u < n ? pair_index(f, xh, y + 1u, z) : np;
   P.z[0] = z > 0u ? pair_index(f, xh, y, z - 1u) : np;
   P.z[1] = z + 1u < n ? pair_index(f, xh, y, z + 1u) : np;
+}
+
+template <class V>
+__device__ __forceinline__ BottomPair<V> bottom_pair(const uint4 *tab, int f, uint32_t p) {
+  BottomPair<V> P;
+  const uint32_t np = 1u << (3 * f - 1), n = 1u << f;
+  P.bits = 0;
+  if (p >= np) return P;
+  const uint32_t y = ((p >> (f - 1)) & 1u) | (((p >> (f + 1)) & ((n >> 1) - 1u)) << 1);
+  const uint32_t z = ((p >> f) & 1u) | ((p >> (2 * f)) << 1);
+  pair_coefs(P, tab, np, p, (y + z) & 1u);
+  pair_neighbours(P, f, p, (y + z) & 1u);
   return P;
 }
 
@@ -1433,7 +1433,7 @@ constexpr int kBottomPairs = 1 << (3 * kBottomLevel - 1);  // 2048
 template <class V>
 constexpr int kBottomThreads = sizeof(V) == 8 ? 512 : 1024;
 
-template <class V, bool TR = false>
+template <class V, bool CORR = false>
 __global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
   if (A.done && *A.done) return;
   constexpr int kSlots = kBottomPairs / kBottomThreads<V>;
@@ -1460,7 +1460,7 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
       const bool odd = P[j].bits & 16u;
       const V2 b2 = *reinterpret_cast<const V2 *>(A.B + P[j].at);
       V2 u2 = V2{V(0), V(0)};
-      if (!(TR && A.fas)) u2 = *reinterpret_cast<const V2 *>(A.U + P[j].at);
+      if (!(CORR && A.fas)) u2 = *reinterpret_cast<const V2 *>(A.U + P[j].at);
       P[j].rhs[0] = odd ? b2.y : b2.x;
       P[j].rhs[1] = odd ? b2.x : b2.y;
       uf[p] = odd ? u2.y : u2.x;
@@ -1504,7 +1504,7 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
   const std::integral_constant<int, 1> black{};
   for (int visit = 0; visit < A.visits; ++visit) {
     // FAS right-hand side of the inner bricks: b += A u*
-    if (!TR && visit == 0 && A.fas) {
+    if (!CORR && visit == 0 && A.fas) {
 #pragma unroll
       for (int j = 0; j < kSlots; ++j) {
         if ((P[j].bits & 12u) != 12u) continue;
@@ -1539,14 +1539,14 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
       const V us = parent_sum(u[0] + u[1], f);
       const int cnt = parent_sum(__popc(P[j].bits & 3u), f);
       if ((P[j].bits & 8u) && !(tid & (3u << (f - 1)))) {
-        const V ust = !TR && cnt ? div_by(us, V(cnt)) : V(0);
+        const V ust = !CORR && cnt ? div_by(us, V(cnt)) : V(0);
         bc[par[j]] = rs * A.scale;
         uc[par[j]] = ust;
         sc[par[j]] = ust;
       }
     }
     __syncthreads();
-    // the coarsest level: FAS right-hand side (TR: u = 0), mu solves
+    // the coarsest level: FAS right-hand side (CORR: u = 0), mu solves
     if (C.bits & 8u) {
 #pragma unroll
       for (uint32_t c = 0; c < 2; ++c) {
@@ -1570,7 +1570,7 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
 #pragma unroll
     for (int j = 0; j < kSlots; ++j) {
       if (!(P[j].bits & 8u)) continue;
-      const V corr = TR ? A.pscale * uc[par[j]] : uc[par[j]] - sc[par[j]];
+      const V corr = CORR ? A.pscale * uc[par[j]] : uc[par[j]] - sc[par[j]];
 #pragma unroll
       for (int c = 0; c < 2; ++c)
         if (P[j].bits & (1u << c)) uf[c * sf + tid + uint32_t(j) * nt] += corr;
@@ -1591,12 +1591,134 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
     const V u0 = uf[p], u1 = uf[sf + p];
     *reinterpret_cast<V2 *>(A.U + P[j].at) = V2{odd ? u1 : u0, odd ? u0 : u1};
   }
-  if (!TR && (C.bits & 8u)) {
+  if (!CORR && (C.bits & 8u)) {
     const bool odd = C.bits & 16u;
     auto pair = [&](V a, V b) { return V2{odd ? b : a, odd ? a : b}; };
     *reinterpret_cast<V2 *>(A.U + C.at) = pair(uc[tid], uc[sg + tid]);
     *reinterpret_cast<V2 *>(A.B + C.at) = pair(C.rhs[0], C.rhs[1]);
     *reinterpret_cast<V2 *>(A.Ustar + (C.at - A.nlb * 64u)) = pair(sc[tid], sc[sg + tid]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// One side of the visit of a complete 32^3 level (the level above k_bottom's) in
+// one launch.  Its half-sweeps take 3 to 4 us each however little they do;
+// here a workgroup takes a tile of 8^3 cells and the 4 cells around it, 16^3
+// in all, as k_bottom takes its level, and the values that go stale at the rim
+// (one cell per half-sweep) are not kept.  That is eight times the work, on 64
+// of 256 CUs, and it replaces five launches on the way down and four on the
+// way up: FP32, two iterations, 6.5 us against 15.2 and 6.4 against 15.3 (with
+// the fused prolongation), and a 32^3 solve 666 -> 546 us.
+// POST = false: from a zero iterate, nu <= 2 iterations (colours 0, 1), the
+// iterate of the tile to W (level-relative elements: other tiles read U's
+// halo in the launch that follows), the residual restricted to level f (times
+// scale).  From zero the first half-sweep needs no neighbours, so the
+// residual of the tile is still exact after three more.
+// POST = true: W plus pscale times the parents' iterate, nu <= 2 iterations
+// (colours 1, 0), the tile to U.
+// ---------------------------------------------------------------------------
+template <class V>
+struct TileArgs {
+  const uint4 *tab, *parents;  // tables of the level and of level f below it
+  V *U, *B, *W;
+  uint32_t base;               // first element of the level
+  int nu;
+  V scale, pscale;
+  const int *done;
+};
+constexpr int kTileLevel = kBottomLevel + 1;
+constexpr unsigned kTiles = 64;  // 4 per axis
+constexpr int kTileCells = 1 << (3 * kTileLevel);
+
+template <class V, bool POST>
+__global__ void __launch_bounds__(kBottomThreads<V>) k_tile(TileArgs<V> A) {
+  if (A.done && *A.done) return;
+  constexpr int kSlots = kBottomPairs / kBottomThreads<V>;
+  constexpr uint32_t nt = uint32_t(kBottomThreads<V>);
+  constexpr uint32_t np = uint32_t(kBottomPairs);
+  constexpr uint32_t sf = bottom_stride(np);
+  constexpr int f = kBottomLevel;  // the region's
+  __shared__ V uf[2 * sf];
+  typedef V V2 __attribute__((ext_vector_type(2)));
+  const uint32_t tid = threadIdx.x;
+  const int t0 = int(blockIdx.x & 3u), t1 = int((blockIdx.x >> 2) & 3u), t2 = int(blockIdx.x >> 4);
+  if (tid < 2u) uf[tid * sf + np] = V(0);
+  BottomPair<V> P[kSlots];
+  uint32_t par[kSlots];  // element of the parent cell; bit 31: the pair is the tile's own
+#pragma unroll
+  for (int j = 0; j < kSlots; ++j) {
+    const uint32_t p = tid + uint32_t(j) * nt;
+    const int lx = int(p & 7u);
+    const int ly = int(((p >> (f - 1)) & 1u) | (((p >> (f + 1)) & 7u) << 1));
+    const int lz = int(((p >> f) & 1u) | ((p >> (2 * f)) << 1));
+    const int x = 4 * t0 - 2 + lx, y = 8 * t1 - 4 + ly, z = 8 * t2 - 4 + lz;
+    const bool here = uint32_t(x) < 16u && uint32_t(y) < 32u && uint32_t(z) < 32u;
+    const bool own = uint32_t(lx - 2) < 4u && uint32_t(ly - 4) < 8u && uint32_t(lz - 4) < 8u;
+    P[j].bits = 0u;
+    par[j] = 0u;
+    V u0 = V(0), u1 = V(0);
+    if (here) {
+      const uint32_t g = pair_index(kTileLevel, uint32_t(x), uint32_t(y), uint32_t(z));
+      pair_coefs(P[j], A.tab, 1u << (3 * kTileLevel - 1), g, uint32_t(y + z) & 1u);
+      const uint32_t gp = pair_index(f, uint32_t(x) >> 1, uint32_t(y) >> 1, uint32_t(z) >> 1);
+      par[j] = (A.parents[uint32_t(BottomUnits<V>::kCoef) * np + gp].x + (uint32_t(x) & 1u)) |
+               (own ? 0x80000000u : 0u);
+      const bool odd = P[j].bits & 16u;
+      const V2 b2 = *reinterpret_cast<const V2 *>(A.B + P[j].at);
+      P[j].rhs[0] = odd ? b2.y : b2.x;
+      P[j].rhs[1] = odd ? b2.x : b2.y;
+      if constexpr (POST) {
+        const V2 w2 = *reinterpret_cast<const V2 *>(A.W + (P[j].at - A.base));
+        const V corr = A.pscale * A.U[par[j] & 0x7fffffffu];
+        u0 = odd ? w2.y : w2.x;
+        u1 = odd ? w2.x : w2.y;
+        if (P[j].bits & 1u) u0 += corr;
+        if (P[j].bits & 2u) u1 += corr;
+      }
+    }
+    pair_neighbours(P[j], f, p, (P[j].bits >> 4) & 1u);
+    uf[p] = u0;
+    uf[sf + p] = u1;
+  }
+  __syncthreads();
+  auto half_sweep = [&](auto colour) {
+    constexpr int c = decltype(colour)::value;
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j)
+      if (P[j].bits & (1u << c)) {
+        const V S = bottom_sum(uf + (1 - c) * sf, P[j], P[j].k[c], c);
+        uf[c * sf + tid + uint32_t(j) * nt] =
+            bottom_div(P[j].k[c], P[j].rc[c], P[j].rhs[c] + S);
+      }
+    __syncthreads();
+  };
+  const std::integral_constant<int, POST ? 1 : 0> first{};
+  const std::integral_constant<int, POST ? 0 : 1> second{};
+  for (int it = 0; it < A.nu; ++it) {
+    half_sweep(first);
+    half_sweep(second);
+  }
+#pragma unroll
+  for (int j = 0; j < kSlots; ++j) {
+    const uint32_t p = tid + uint32_t(j) * nt;
+    const bool own = par[j] >> 31;
+    const bool odd = P[j].bits & 16u;
+    if (own) {
+      const V u0 = uf[p], u1 = uf[sf + p];
+      V *to = POST ? A.U + P[j].at : A.W + (P[j].at - A.base);
+      *reinterpret_cast<V2 *>(to) = V2{odd ? u1 : u0, odd ? u0 : u1};
+    }
+    if constexpr (!POST) {
+      V r[2] = {V(0), V(0)};
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        if (P[j].bits & (1u << c)) {
+          const V S = bottom_sum(uf + (1 - c) * sf, P[j], P[j].k[c], c);
+          r[c] = P[j].rhs[c] - (diag_of(P[j].k[c]) * uf[c * sf + p] - S);
+        }
+      const V rs = parent_sum(r[0] + r[1], f);
+      if (own && !(tid & (3u << (f - 1)))) A.B[par[j] & 0x7fffffffu] = rs * A.scale;
+    }
   }
 }
 
@@ -1620,47 +1742,6 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
 // neighbour sums over the same-level leaves (leaf_neighbour_sum): no
 // operator application is needed for it.
 // ---------------------------------------------------------------------------
-
-// First half-sweep of a level from a zero iterate: y = g / c on the active
-// cells of the colour, 0 on all others.  On inner bricks the diagonal is the
-// sum of the six face coefficients, as in every half-sweep (the stored FP16
-// diagonal is rounded on its own).
-template <bool INNER, class V, class CL, class CI, int CP>
-__device__ __forceinline__ void zero_brick_T(const LevelView<V, CL, CI, CP> &X,
-                                             const LaneC<V, CL> &L, uint32_t b, int colour) {
-  const BrickMeta M = load_meta(X.meta, b);
-  bool act = (act_mask(M) >> L.m) & 1ull;
-  if constexpr (!INNER) {  // leaves store it unrounded (k_smooth_zero reads it too)
-    V c = own_coef<false>(X, b, 0, L.m);
-    V g = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
-    bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(g, c) : V(0));
-    return;
-  }
-  V k[6];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    V kown = own_coef<INNER>(X, b, 1 + a, L.m);
-    V kl = V(bload_bytes<CL, side_pol(CP)>(X.pf, L.foff[a], b * uint32_t(48 * sizeof(CL))));
-    V ks = shfl(kown, L.p[2 * a + 1]);
-    k[2 * a] = kown;
-    k[2 * a + 1] = L.out[2 * a + 1] ? kl : ks;
-  }
-  V rhs = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
-  V c = ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
-  bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(rhs, c) : V(0));
-}
-
-template <class V, class CL, class CI, int CP = kCpolDefault>
-__global__ void __launch_bounds__(kBlock) k_T_zero(LevelArgs<V, CL, CI> A, int colour) {
-  if (A.done && *A.done) return;
-  const LaneC<V, CL> L = lane_consts<V, CL>();
-  const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
-  const WaveLoop W = wave_loop(A.R.n());
-  for (uint32_t i = W.first; i < W.end; i += W.step) {
-    if (i < A.R.n_leaf) zero_brick_T<false>(X, L, A.R.leaf_lo + i, colour);
-    else zero_brick_T<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
-  }
-}
 
 // On a leaf brick with inner same-level neighbours (record M): the sum over
 // the fine cells next to the lane's cell, across all its faces to finer

@@ -376,8 +376,12 @@ struct mfmg_hierarchy {
   bool stream_composite = false;  // the same for the composite operator
   bool fuse_bottom = false;       // level lc + 1 and the coarsest level in one kernel (k_bottom)
   DevBuf<uint4> bot_f, bot_c;     // k_bottom's tables of the two levels
+  DevBuf<uint4> tile_tab;         // k_tile's table of level lc + 2
+  DevBuf<double> tile_w64;        // and its work vectors, by precision
+  DevBuf<float> tile_w32;
   bool fuse_prolong = true;       // prolongation folded into the post-smoothing (k_smooth PR)
-  std::vector<char> fold_fas;     // per level: FAS right-hand side folded into k_smooth_fas
+  std::vector<char> corr_lv;      // per level: in correction form (its iterate is u - u*)
+  bool tile = false;              // level lc + 2 takes k_tile (both cycles)
   // work vectors (device order)
   DevBuf<double> U64, B64, S64;  // FP64 cycle: nb*64, nb*64, (nb-nlb)*64
   DevBuf<float> U32, B32, S32;   // mixed cycle
@@ -1130,7 +1134,6 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
                        D.range[f].n() == (uint32_t(1) << (3 * (f - 2))) &&
                        D.range[h->lc].n() == (uint32_t(1) << (3 * (f - 3))) &&
                        D.range[h->lc].n_leaf == 0;
-      if (h->fuse_bottom) build_bottom(h.get(), s);
     }
     {
       // MFMG_FUSE_PROLONG=0 (read at each build) keeps the separate
@@ -1139,18 +1142,28 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
       h->fuse_prolong = !(e && e[0] == '0');
     }
     {
-      // A level above the coarsest with no leaf at or below it takes its FAS
-      // right-hand side in its first pre-smoothing half-sweep (k_smooth_fas).
-      // MFMG_FUSE_FAS=0 (read at each build) keeps k_fas_rhs.
+      // A level above the coarsest with no leaf at or below it is visited in
+      // correction form: on its cells u* is the mean of finer ones everywhere,
+      // so with e = u - u* the FAS equation A u = b + A u* is A e = b from a
+      // zero iterate, and neither u* nor a FAS right-hand side is formed.
+      // MFMG_FUSE_FAS=0 (read at each build) keeps u and k_fas_rhs.
       const char *e = std::getenv("MFMG_FUSE_FAS");
       bool on = !(e && e[0] == '0');
-      h->fold_fas.assign(D.range.size(), 0);
+      h->corr_lv.assign(D.range.size(), 0);
       bool leaf_below = false;
       for (size_t l = 0; l < D.range.size(); ++l) {
         leaf_below = leaf_below || D.range[l].n_leaf > 0;
-        h->fold_fas[l] = on && int(l) > h->lc && int(l) < h->L && !leaf_below &&
-                         D.range[l].n_inner > 0;
+        h->corr_lv[l] = on && int(l) > h->lc && int(l) < h->L && !leaf_below &&
+                        D.range[l].n_inner > 0;
       }
+      // k_tile takes the level above k_bottom's when that is the complete 32^3
+      // grid, either in correction form or the finest level (all leaves).
+      int t = h->lc + 2;
+      auto few = [](int nu) { return nu == 1 || nu == 2; };
+      h->tile = h->fuse_bottom && h->corr_lv[size_t(h->lc + 1)] && t == kTileLevel &&
+                D.range[t].n() == 512u && few(prm->nu_pre) && few(prm->nu_post) &&
+                h->fuse_prolong && (h->corr_lv[size_t(t)] || (t == h->L && D.range[t].n_inner == 0));
+      if (h->fuse_bottom) build_bottom(h.get(), s);
     }
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(s));
@@ -1318,31 +1331,22 @@ struct Cycle {
     else if (pr == 2) half_sweep_pr<2>(l, A, colour);
     else half_sweep_pr<0>(l, A, colour);
   }
+  // zero: from a zero iterate, which the first half-sweep also writes.
   // prolong: the level's FAS correction is still to be added (the first
   // two half-sweeps fold it in; nu >= 1).
-  // fold: the level's FAS right-hand side is still to be formed, by its
-  // first half-sweep (k_smooth_fas; the level has no leaves, nu >= 1).
-  void smooth(int l, int first, int nu, bool zero_start = false, bool prolong = false,
-              bool fold = false) const {
+  void smooth(int l, int first, int nu, bool zero = false, bool prolong = false) const {
     auto A = args(l, false);
     if (A.R.n() == 0) return;
     for (int it = 0; it < nu; ++it)
       for (int c = 0; c < 2; ++c) {
         int colour = c == 0 ? first : 1 - first;
         dim3 g(stencil_grid<V>(A.R.n()));
-        if (zero_start && it == 0 && c == 0) {
+        if (zero && it == 0 && c == 0) {
           if (stream(l))
-            hipLaunchKernelGGL((k_smooth_zero<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s,
-                               A, colour);
+            hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A,
+                               colour);
           else
-            hipLaunchKernelGGL((k_smooth_zero<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour);
-        } else if (fold && it == 0 && c == 0) {
-          dim3 gi(stencil_grid<V>(A.R.n_inner));
-          if (stream(l))
-            hipLaunchKernelGGL((k_smooth_fas<V, CL, CI, kCpolLevel>), gi, dim3(kBlock), 0, s,
-                               A, colour);
-          else
-            hipLaunchKernelGGL((k_smooth_fas<V, CL, CI>), gi, dim3(kBlock), 0, s, A, colour);
+            hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour);
         } else {
           half_sweep(l, A, colour, prolong && it == 0 ? 1 + c : 0);
         }
@@ -1350,18 +1354,47 @@ struct Cycle {
   }
 
   // k_bottom's arguments (p.mu visits of level lc + 1)
-  BottomArgs<V> bottom_args(int nu_pre, int nu_post, int half, int fas, V scale) const {
+  BottomArgs<V> bottom_args(int nu_pre, int nu_post, int half, int fas, V scale,
+                            V pscale) const {
     const mfmg_mg_params &p = h->prm;
     return BottomArgs<V>{h->bot_f.p, h->bot_c.p, h->lc + 1, U, B, Ust, h->co->dt->nlb,
                          nu_pre, nu_post, p.nu_coarse, half, p.mu, fas, p.mu, scale,
-                         V(p.beta_mg / p.alpha), done};
+                         pscale, done};
   }
 
-  // zero_start: the level's iterate is zero and its bricks are all leaves
-  // (the finest level at the start of a cycle), so the first half-sweep
-  // needs no neighbour values and also clears the iterate.
-  // fold: as for smooth (the first visit of a level of fold_fas).
-  void fas(int l, bool zero_start = false, bool fold = false) const {
+  template <bool CORR>
+  void restrict_to(int l, const LevelArgs<V, CL, CI> &A, V scale) const {
+    dim3 g(stencil_grid<V>(A.R.n()));
+    if (stream(l))
+      hipLaunchKernelGGL((k_restrict<V, CL, CI, kCpolLevel, CORR>), g, dim3(kBlock), 0, s, A,
+                         scale);
+    else
+      hipLaunchKernelGGL((k_restrict<V, CL, CI, kCpolDefault, CORR>), g, dim3(kBlock), 0, s, A,
+                         scale);
+  }
+  // The two sides of k_tile on level lc + 2 (which: 0 this cycle's work
+  // vector, 1 the transposed cycle's).
+  template <bool POST>
+  void tile(int nu, V scale, V pscale, int which = 0) const {
+    const Range &R = h->co->dt->range[size_t(kTileLevel)];
+    V *w;
+    if constexpr (sizeof(V) == 8) w = h->tile_w64.p;
+    else w = h->tile_w32.p;
+    w += which * kTileCells;
+    TileArgs<V> A{h->tile_tab.p, h->bot_f.p, U, B, w, (R.n_leaf ? R.leaf_lo : R.inner_lo) * 64u,
+                  nu, scale, pscale, done};
+    hipLaunchKernelGGL((k_tile<V, POST>), dim3(kTiles), dim3(kBottomThreads<V>), 0, s, A);
+  }
+  template <bool CORR>
+  void bottom(const BottomArgs<V> &F) const {
+    hipLaunchKernelGGL((k_bottom<V, CORR>), dim3(1),
+                       dim3(F.f == kBottomLevel ? kBottomThreads<V> : 256), 0, s, F);
+  }
+
+  // zero: the level's iterate is zero (the finest level at the start of a
+  // cycle, the first visit of a level in correction form), so the first
+  // half-sweep needs no neighbour values and also clears the iterate.
+  void fas(int l, bool zero = false) const {
     const mfmg_mg_params &p = h->prm;
     if (l == h->lc) {
       auto A = args(l, false);
@@ -1370,31 +1403,35 @@ struct Cycle {
                          p.nu_coarse, p.nu_coarse / 2);
       return;
     }
-    smooth(l, 0, p.nu_pre, zero_start, false, fold);
-    auto A = args(l, false);
     V scale = V(p.beta_mg / p.alpha);
-    if (stream(l))
-      hipLaunchKernelGGL((k_restrict<V, CL, CI, kCpolLevel>), dim3(stencil_grid<V>(A.R.n())),
-                         dim3(kBlock), 0, s, A, scale);
-    else
-      hipLaunchKernelGGL((k_restrict<V, CL, CI>), dim3(stencil_grid<V>(A.R.n())), dim3(kBlock),
-                         0, s, A, scale);
+    bool tiled = zero && h->tile && l == kTileLevel;
+    bool corr = h->corr_lv[size_t(l - 1)];  // level l - 1 is in correction form
+    auto A = args(l, false);
+    if (tiled) {
+      tile<false>(p.nu_pre, scale, V(0));
+    } else {
+      smooth(l, 0, p.nu_pre, zero);
+      if (corr) restrict_to<true>(l, A, scale);
+      else restrict_to<false>(l, A, scale);
+    }
     if (l - 1 == h->lc + 1 && h->fuse_bottom) {
-      BottomArgs<V> F = bottom_args(p.nu_pre, p.nu_post, p.nu_coarse / 2, 1, scale);
-      hipLaunchKernelGGL((k_bottom<V>), dim3(1), dim3(F.f == kBottomLevel ? kBottomThreads<V> : 256), 0, s, F);
+      BottomArgs<V> F = bottom_args(p.nu_pre, p.nu_post, p.nu_coarse / 2, 1, scale, V(1));
+      if (corr) bottom<true>(F);
+      else bottom<false>(F);
     } else {
       auto C = args(l - 1, true);
-      bool fold = h->fold_fas[size_t(l - 1)] && p.nu_pre > 0;
-      if (C.R.n() && !fold)
+      if (C.R.n() && !corr)
         hipLaunchKernelGGL((k_fas_rhs<V, CL, CI>), dim3(stencil_grid<V>(C.R.n_inner)),
                            dim3(kBlock), 0, s, C);
-      for (int k = 0; k < p.mu; ++k) fas(l - 1, false, fold && k == 0);
+      for (int k = 0; k < p.mu; ++k) fas(l - 1, corr && k == 0);
     }
-    if (h->fuse_prolong && p.nu_post > 0) {
+    if (tiled) {
+      tile<true>(p.nu_post, V(0), V(1));
+    } else if (h->fuse_prolong && p.nu_post > 0) {
       smooth(l, 1, p.nu_post, false, true);
     } else {
-      hipLaunchKernelGGL((k_prolong<V, CL, CI>), dim3(stencil_grid<V>(A.R.n())), dim3(kBlock),
-                         0, s, A);
+      hipLaunchKernelGGL((k_prolong<V, CL, CI>), dim3(stencil_grid<V>(A.R.n())), dim3(kBlock), 0,
+                         s, A);
       smooth(l, 1, p.nu_post);
     }
   }
@@ -1424,16 +1461,17 @@ void run_cycle(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
   else cycle64(h, s, done).run();
 }
 
-// k_bottom's tables of the levels lc + 1 and lc.
+// k_bottom's tables of the levels lc + 1 and lc, k_tile's of level lc + 2.
 template <class V, class CL, class CI>
-void build_bottom_of(mfmg_hierarchy *h, const Cycle<V, CL, CI> &c) {
-  DevBuf<uint4> *tab[2] = {&h->bot_c, &h->bot_f};
-  for (int k = 0; k < 2; ++k) {
+void build_bottom_of(mfmg_hierarchy *h, const Cycle<V, CL, CI> &c, DevBuf<V> &work) {
+  DevBuf<uint4> *tab[3] = {&h->bot_c, &h->bot_f, &h->tile_tab};
+  for (int k = 0; k < (h->tile ? 3 : 2); ++k) {
     auto A = c.args(h->lc + k, false);
     tab[k]->alloc(size_t(BottomUnits<V>::kAll) << (3 * (h->lc + k) - 1));
     hipLaunchKernelGGL((k_bottom_table<V, CL, CI>), dim3(grid_for(A.R.n())), dim3(kBlock), 0, c.s,
                        A, h->lc + k, tab[k]->p);
   }
+  if (h->tile) work.alloc(2 * size_t(kTileCells));
   HIP_CHECK(hipGetLastError());
 }
 
@@ -1478,9 +1516,9 @@ struct CycleT {
       int colour = (k & 1) ? 1 - first : first;
       if (zero && k == 0) {
         if (stream(l))
-          hipLaunchKernelGGL((k_T_zero<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, colour);
+          hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, colour);
         else
-          hipLaunchKernelGGL((k_T_zero<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour);
+          hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour);
       } else if (prolong && k == 0) {
         half_sweep<1>(l, A, colour);
       } else if (prolong && k == 1) {
@@ -1500,28 +1538,36 @@ struct CycleT {
                          p.nu_coarse - p.nu_coarse / 2);
       return;
     }
-    smooth(l, 0, p.nu_post, first, false);  // forward post-smoothing is (B,R)^nu
-    uint32_t nc = h->couple_n[size_t(l - 1)];
+    V pscale = V(p.beta_mg / p.alpha);
+    bool tiled = first && h->tile && l == kTileLevel;
     unsigned gr = stencil_grid<V>(A.R.n());
-    dim3 g(gr + (nc ? grid_for(nc) : 0));
-    const uint32_t *list = (const uint32_t *)h->couple.p + h->couple_lo[size_t(l - 1)];
-    if (stream(l))
-      hipLaunchKernelGGL((k_T_restrict<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, Cpl,
-                         int(first), list, nc, gr);
-    else
-      hipLaunchKernelGGL((k_T_restrict<V, CL, CI>), g, dim3(kBlock), 0, s, A, Cpl, int(first),
-                         list, nc, gr);
+    if (tiled) {
+      forward().template tile<false>(p.nu_post, V(1), V(0), 1);
+    } else {
+      smooth(l, 0, p.nu_post, first, false);  // forward post-smoothing is (B,R)^nu
+      uint32_t nc = h->couple_n[size_t(l - 1)];
+      dim3 g(gr + (nc ? grid_for(nc) : 0));
+      const uint32_t *list = (const uint32_t *)h->couple.p + h->couple_lo[size_t(l - 1)];
+      if (stream(l))
+        hipLaunchKernelGGL((k_T_restrict<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, Cpl,
+                           int(first), list, nc, gr);
+      else
+        hipLaunchKernelGGL((k_T_restrict<V, CL, CI>), g, dim3(kBlock), 0, s, A, Cpl, int(first),
+                           list, nc, gr);
+    }
     auto C = args(l - 1);
     if (!first && C.R.n_leaf && C.R.n_inner)
       hipLaunchKernelGGL((k_T_revisit<V, CL, CI>), dim3(stencil_grid<V>(C.R.n_inner)),
                          dim3(kBlock), 0, s, C);
     if (l - 1 == h->lc + 1 && h->fuse_bottom) {
-      BottomArgs<V> F = forward().bottom_args(p.nu_post, p.nu_pre,
-                                              p.nu_coarse - p.nu_coarse / 2, int(first), V(1));
-      hipLaunchKernelGGL((k_bottom<V, true>), dim3(1), dim3(F.f == kBottomLevel ? kBottomThreads<V> : 256), 0,
-                         s, F);
+      forward().template bottom<true>(forward().bottom_args(
+          p.nu_post, p.nu_pre, p.nu_coarse - p.nu_coarse / 2, int(first), V(1), pscale));
     } else {
       for (int k = 0; k < p.mu; ++k) fas(l - 1, first && k == 0);
+    }
+    if (tiled) {
+      forward().template tile<true>(p.nu_pre, V(0), pscale, 1);
+      return;
     }
     // forward pre-smoothing is (R,B)^nu
     bool fused = h->fuse_prolong && p.nu_pre > 0;
@@ -1615,8 +1661,8 @@ void run_cycle_T(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
 }  // namespace
 
 static void build_bottom(mfmg_hierarchy *h, hipStream_t s) {
-  if (h->prm.precision == MFMG_MIXED) build_bottom_of(h, cycle32(h, s, nullptr));
-  else build_bottom_of(h, cycle64(h, s, nullptr));
+  if (h->prm.precision == MFMG_MIXED) build_bottom_of(h, cycle32(h, s, nullptr), h->tile_w32);
+  else build_bottom_of(h, cycle64(h, s, nullptr), h->tile_w64);
 }
 
 namespace {
@@ -2246,10 +2292,8 @@ double cycle_bytes(const mfmg_hierarchy *h) {
     lvl += n_all * (2.0 * V + 3.0 * V / 8.0) + cells_coef;  // residual + restriction
     double c_in = double(D.range[l - 1].n_inner) * 64;        // FAS right-hand side
     double c_coef = c_in * 4.0 * CI;
-    // (folded into the first half-sweep of level l - 1: only its store of b)
-    bool fold = l - 1 > h->lc && h->fold_fas[size_t(l - 1)] && p.nu_pre > 0 &&
-                !(l - 1 == h->lc + 1 && h->fuse_bottom);
-    lvl += fold ? c_in * V : c_in * 3.0 * V + c_coef;
+    // (none on a level in correction form)
+    lvl += h->corr_lv[size_t(l - 1)] ? 0.0 : c_in * 3.0 * V + c_coef;
     // prolongation: the parent values, plus the level's iterate unless the
     // post-smoothing takes the prolongation with it
     bool fused = h->fuse_prolong && p.nu_post > 0;
