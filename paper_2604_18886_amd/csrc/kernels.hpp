@@ -1243,10 +1243,11 @@ __host__ __device__ __forceinline__ uint32_t pair_index(int f, uint32_t xh, uint
          ((z >> 1) << (2 * f));
 }
 
-// Table of a level: per pair 12 face coefficients (six of the even-x cell, six
+// Table of a level (k_bottom's and k_tile's): per pair 12 face coefficients (six of the even-x cell, six
 // of the odd-x one) and one unit of indices, as 16-byte units, unit q of pair
 // p at q * pairs + p.  Index unit: element of the even-x cell in the level
-// arrays (the odd-x cell follows it), activity bits, inner-brick bit.
+// arrays (the odd-x cell follows it), activity bits, inner-brick bit, element
+// of their parent cell.
 template <class V>
 struct BottomUnits {
   static constexpr int kPer = 16 / int(sizeof(V));  // coefficients per unit
@@ -1286,7 +1287,8 @@ __global__ void __launch_bounds__(kBlock) k_bottom_table(LevelArgs<V, CL, CI> A,
   if (e == 0) {
     const uint64_t act = act_mask(M);
     const uint32_t bits = uint32_t((act >> m) & 3ull) | (inner ? 4u : 0u);
-    tab[uint32_t(BottomUnits<V>::kCoef) * np + p] = uint4{b * 64u + uint32_t(m), bits, 0u, 0u};
+    const uint32_t parent = uint32_t(M.parent) * 64u + uint32_t(octant_of(M)) * 8u + (L.m >> 3);
+    tab[uint32_t(BottomUnits<V>::kCoef) * np + p] = uint4{b * 64u + uint32_t(m), bits, parent, 0u};
   }
 }
 
@@ -1302,6 +1304,7 @@ struct BottomPair {
   uint32_t x[2][2];  // entries of the -x and +x neighbours, by colour
   uint32_t y[2], z[2];
   uint32_t at;       // element of the even-x cell in the level arrays
+  uint32_t parent;   // element of the parent cell
   uint32_t bits;     // 1, 2: active by colour; 4: inner brick; 8: the pair
                      // exists; 16: the colour-0 cell is the odd-x one
 };
@@ -1349,6 +1352,7 @@ __device__ __forceinline__ void pair_coefs(BottomPair<V> &P, const uint4 *tab, u
   }
   const uint32_t bits = unit[BottomUnits<V>::kCoef].y, act = bits & 3u;
   P.at = unit[BottomUnits<V>::kCoef].x;
+  P.parent = unit[BottomUnits<V>::kCoef].z;
   P.bits = (e0 ? (act >> 1) | ((act & 1u) << 1) : act) | (bits & 4u) | 8u | (e0 << 4);
 }
 
@@ -1601,37 +1605,50 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
 }
 
 // ---------------------------------------------------------------------------
-// One side of the visit of a complete 32^3 level (the level above k_bottom's) in
-// one launch.  Its half-sweeps take 3 to 4 us each however little they do;
+// The visit of a complete level of 16^3 to 64^3 cells (so it has no T-junction;
+// its bricks may be leaves and inner ones) in two or three launches.  The
+// separate kernels take nine or ten, of 3 to 5 us each however little they do;
 // here a workgroup takes a tile of 8^3 cells and the 4 cells around it, 16^3
 // in all, as k_bottom takes its level, and the values that go stale at the rim
-// (one cell per half-sweep) are not kept.  That is eight times the work, on 64
-// of 256 CUs, and it replaces five launches on the way down and four on the
-// way up: FP32, two iterations, 6.5 us against 15.2 and 6.4 against 15.3 (with
-// the fused prolongation), and a 32^3 solve 666 -> 546 us.
-// POST = false: from a zero iterate, nu <= 2 iterations (colours 0, 1), the
-// iterate of the tile to W (level-relative elements: other tiles read U's
-// halo in the launch that follows), the residual restricted to level f (times
-// scale).  From zero the first half-sweep needs no neighbours, so the
-// residual of the tile is still exact after three more.
-// POST = true: W plus pscale times the parents' iterate, nu <= 2 iterations
-// (colours 1, 0), the tile to U.
+// (one cell per half-sweep) are not kept.  That is eight times the work, bound
+// at 32^3 by one CU's set-up and barriers, at 64^3 by the coefficients' reads
+// (eight times a table of 8.4 MB, FP32).  us, two iterations on each side, with
+// the launches replaced: 32^3 FP32, zero 6.5 (15.2), up 6.1 (15.3), from and
+// restrict 5.3 + 4.2 (18.5); 64^3 FP32, zero 13.7 (22), up 10 (17), from and
+// restrict 9.1 + 7.8 (25).
+// nu <= 2 iterations on a side:
+//   kTileZero      the way down from a zero iterate: smoothing (colours 0, 1)
+//                  and restriction.  From zero the first half-sweep needs no
+//                  neighbours, so the residual of the tile is still exact
+//                  after three more.
+//   kTileFrom      the way down from U: FAS right-hand side (fas, to R),
+//                  smoothing.
+//   kTileRestrict  the restriction that follows it.
+//   kTileUp        the parents' correction, smoothing (colours 1, 0), to U.
+// Between them the iterate is in W (by pair: other tiles read U's halo).  R:
+// the level's right-hand side by pair, where it is not B.
 // ---------------------------------------------------------------------------
+enum TileMode { kTileZero, kTileFrom, kTileRestrict, kTileUp };
+constexpr int kTileMin = 4, kTileMax = 6;  // levels
+
 template <class V>
 struct TileArgs {
-  const uint4 *tab, *parents;  // tables of the level and of level f below it
-  V *U, *B, *W;
-  uint32_t base;               // first element of the level
-  int nu;
-  V scale, pscale;
+  const uint4 *tab;
+  V *U, *B, *Ustar, *W, *R;
+  uint32_t nlb;
+  int l, nu;
+  int fas;          // kTileFrom: form the FAS right-hand side of inner cells
+  int corr;         // kTileRestrict, kTileZero: level l - 1 is in correction form
+  int sub;          // kTileUp: the parents' u* is taken off
+  V scale, pscale;  // of the restricted residual, of the parents' iterate
   const int *done;
 };
-constexpr int kTileLevel = kBottomLevel + 1;
-constexpr unsigned kTiles = 64;  // 4 per axis
-constexpr int kTileCells = 1 << (3 * kTileLevel);
 
-template <class V, bool POST>
-__global__ void __launch_bounds__(kBottomThreads<V>) k_tile(TileArgs<V> A) {
+template <class V, int MODE>
+// (FP32 in 64 registers, for two workgroups per CU at 64^3; the way down from
+// zero does not fit them and gained nothing there: 8.0 us at 32^3)
+__global__ void __launch_bounds__(kBottomThreads<V>, sizeof(V) == 4 && MODE != kTileZero ? 8 : 2)
+    k_tile(TileArgs<V> A) {
   if (A.done && *A.done) return;
   constexpr int kSlots = kBottomPairs / kBottomThreads<V>;
   constexpr uint32_t nt = uint32_t(kBottomThreads<V>);
@@ -1641,37 +1658,44 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_tile(TileArgs<V> A) {
   __shared__ V uf[2 * sf];
   typedef V V2 __attribute__((ext_vector_type(2)));
   const uint32_t tid = threadIdx.x;
-  const int t0 = int(blockIdx.x & 3u), t1 = int((blockIdx.x >> 2) & 3u), t2 = int(blockIdx.x >> 4);
+  // a slab of tiles per XCD, whose L2 then holds what its tiles read twice
+  const uint32_t tl = uint32_t(A.l - 3), n = 1u << A.l;
+  const uint32_t tile = (blockIdx.x & 7u) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  const uint32_t t0 = tile & ((1u << tl) - 1u), t1 = (tile >> tl) & ((1u << tl) - 1u),
+                 t2 = tile >> (2u * tl);
   if (tid < 2u) uf[tid * sf + np] = V(0);
   BottomPair<V> P[kSlots];
-  uint32_t par[kSlots];  // element of the parent cell; bit 31: the pair is the tile's own
+  uint32_t pair[kSlots];  // the level's pair; bit 31: it is the tile's own
 #pragma unroll
   for (int j = 0; j < kSlots; ++j) {
     const uint32_t p = tid + uint32_t(j) * nt;
-    const int lx = int(p & 7u);
-    const int ly = int(((p >> (f - 1)) & 1u) | (((p >> (f + 1)) & 7u) << 1));
-    const int lz = int(((p >> f) & 1u) | ((p >> (2 * f)) << 1));
-    const int x = 4 * t0 - 2 + lx, y = 8 * t1 - 4 + ly, z = 8 * t2 - 4 + lz;
-    const bool here = uint32_t(x) < 16u && uint32_t(y) < 32u && uint32_t(z) < 32u;
-    const bool own = uint32_t(lx - 2) < 4u && uint32_t(ly - 4) < 8u && uint32_t(lz - 4) < 8u;
+    const uint32_t lx = p & 7u;
+    const uint32_t ly = ((p >> (f - 1)) & 1u) | (((p >> (f + 1)) & 7u) << 1);
+    const uint32_t lz = ((p >> f) & 1u) | ((p >> (2 * f)) << 1);
+    // (outside the level: at least n, wrapped or not)
+    const uint32_t x = 4u * t0 + lx - 2u, y = 8u * t1 + ly - 4u, z = 8u * t2 + lz - 4u;
+    const bool own = lx - 2u < 4u && ly - 4u < 8u && lz - 4u < 8u;
     P[j].bits = 0u;
-    par[j] = 0u;
+    pair[j] = 0u;
     V u0 = V(0), u1 = V(0);
-    if (here) {
-      const uint32_t g = pair_index(kTileLevel, uint32_t(x), uint32_t(y), uint32_t(z));
-      pair_coefs(P[j], A.tab, 1u << (3 * kTileLevel - 1), g, uint32_t(y + z) & 1u);
-      const uint32_t gp = pair_index(f, uint32_t(x) >> 1, uint32_t(y) >> 1, uint32_t(z) >> 1);
-      par[j] = (A.parents[uint32_t(BottomUnits<V>::kCoef) * np + gp].x + (uint32_t(x) & 1u)) |
-               (own ? 0x80000000u : 0u);
+    if (x < n / 2u && y < n && z < n) {
+      const uint32_t g = pair_index(A.l, x, y, z);
+      pair_coefs(P[j], A.tab, 1u << (3 * A.l - 1), g, (y + z) & 1u);
+      pair[j] = g | (own ? 0x80000000u : 0u);
       const bool odd = P[j].bits & 16u;
-      const V2 b2 = *reinterpret_cast<const V2 *>(A.B + P[j].at);
+      const V *rhs = A.R && !(MODE == kTileFrom && A.fas) ? A.R + 2u * g : A.B + P[j].at;
+      const V2 b2 = *reinterpret_cast<const V2 *>(rhs);
       P[j].rhs[0] = odd ? b2.y : b2.x;
       P[j].rhs[1] = odd ? b2.x : b2.y;
-      if constexpr (POST) {
-        const V2 w2 = *reinterpret_cast<const V2 *>(A.W + (P[j].at - A.base));
-        const V corr = A.pscale * A.U[par[j] & 0x7fffffffu];
+      if constexpr (MODE != kTileZero) {
+        const V *from = MODE == kTileFrom ? A.U + P[j].at : A.W + 2u * g;
+        const V2 w2 = *reinterpret_cast<const V2 *>(from);
         u0 = odd ? w2.y : w2.x;
         u1 = odd ? w2.x : w2.y;
+      }
+      if constexpr (MODE == kTileUp) {
+        V corr = A.pscale * A.U[P[j].parent];
+        if (A.sub) corr = corr - A.Ustar[P[j].parent - A.nlb * 64u];
         if (P[j].bits & 1u) u0 += corr;
         if (P[j].bits & 2u) u1 += corr;
       }
@@ -1681,43 +1705,80 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_tile(TileArgs<V> A) {
     uf[sf + p] = u1;
   }
   __syncthreads();
-  auto half_sweep = [&](auto colour) {
-    constexpr int c = decltype(colour)::value;
-#pragma unroll
-    for (int j = 0; j < kSlots; ++j)
-      if (P[j].bits & (1u << c)) {
-        const V S = bottom_sum(uf + (1 - c) * sf, P[j], P[j].k[c], c);
-        uf[c * sf + tid + uint32_t(j) * nt] =
-            bottom_div(P[j].k[c], P[j].rc[c], P[j].rhs[c] + S);
-      }
-    __syncthreads();
+  auto sum = [&](int j, int c) {
+    return bottom_sum(uf + (1 - c) * sf, P[j], P[j].k[c], c);
   };
-  const std::integral_constant<int, POST ? 1 : 0> first{};
-  const std::integral_constant<int, POST ? 0 : 1> second{};
-  for (int it = 0; it < A.nu; ++it) {
-    half_sweep(first);
-    half_sweep(second);
-  }
+  if constexpr (MODE == kTileFrom) {
+    if (A.fas) {  // b += A u* on inner cells
 #pragma unroll
-  for (int j = 0; j < kSlots; ++j) {
-    const uint32_t p = tid + uint32_t(j) * nt;
-    const bool own = par[j] >> 31;
-    const bool odd = P[j].bits & 16u;
-    if (own) {
-      const V u0 = uf[p], u1 = uf[sf + p];
-      V *to = POST ? A.U + P[j].at : A.W + (P[j].at - A.base);
-      *reinterpret_cast<V2 *>(to) = V2{odd ? u1 : u0, odd ? u0 : u1};
+      for (int j = 0; j < kSlots; ++j) {
+        if (P[j].bits & 4u) {
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const V u = uf[c * sf + tid + uint32_t(j) * nt];
+            const V S = sum(j, c);
+            P[j].rhs[c] = P[j].bits & (1u << c) ? P[j].rhs[c] + (diag_of(P[j].k[c]) * u - S) : V(0);
+          }
+        }
+        const bool odd = P[j].bits & 16u;
+        if (pair[j] >> 31)
+          *reinterpret_cast<V2 *>(A.R + 2u * (pair[j] & 0x7fffffffu)) =
+              V2{odd ? P[j].rhs[1] : P[j].rhs[0], odd ? P[j].rhs[0] : P[j].rhs[1]};
+      }
+      __syncthreads();  // every thread's reads of uf before the first writes
     }
-    if constexpr (!POST) {
-      V r[2] = {V(0), V(0)};
+  }
+  if constexpr (MODE != kTileRestrict) {
+    auto half_sweep = [&](auto colour) {
+      constexpr int c = decltype(colour)::value;
+#pragma unroll
+      for (int j = 0; j < kSlots; ++j)
+        if (P[j].bits & (1u << c)) {
+          const V S = sum(j, c);
+          uf[c * sf + tid + uint32_t(j) * nt] =
+              bottom_div(P[j].k[c], P[j].rc[c], P[j].rhs[c] + S);
+        }
+      __syncthreads();
+    };
+    const std::integral_constant<int, MODE == kTileUp ? 1 : 0> first{};
+    const std::integral_constant<int, MODE == kTileUp ? 0 : 1> second{};
+    for (int it = 0; it < A.nu; ++it) {
+      half_sweep(first);
+      half_sweep(second);
+    }
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j) {
+      const uint32_t p = tid + uint32_t(j) * nt;
+      const bool odd = P[j].bits & 16u;
+      if (pair[j] >> 31) {
+        const V u0 = uf[p], u1 = uf[sf + p];
+        V *to = MODE == kTileUp ? A.U + P[j].at : A.W + 2u * (pair[j] & 0x7fffffffu);
+        *reinterpret_cast<V2 *>(to) = V2{odd ? u1 : u0, odd ? u0 : u1};
+      }
+    }
+  }
+  if constexpr (MODE == kTileZero || MODE == kTileRestrict) {
+#pragma unroll
+    for (int j = 0; j < kSlots; ++j) {
+      V r[2] = {V(0), V(0)}, u[2] = {V(0), V(0)};
 #pragma unroll
       for (int c = 0; c < 2; ++c)
         if (P[j].bits & (1u << c)) {
-          const V S = bottom_sum(uf + (1 - c) * sf, P[j], P[j].k[c], c);
-          r[c] = P[j].rhs[c] - (diag_of(P[j].k[c]) * uf[c * sf + p] - S);
+          u[c] = uf[c * sf + tid + uint32_t(j) * nt];
+          r[c] = P[j].rhs[c] - (diag_of(P[j].k[c]) * u[c] - sum(j, c));
         }
       const V rs = parent_sum(r[0] + r[1], f);
-      if (own && !(tid & (3u << (f - 1)))) A.B[par[j] & 0x7fffffffu] = rs * A.scale;
+      V ust = V(0);
+      if (!A.corr) {
+        const V us = parent_sum(u[0] + u[1], f);
+        const int cnt = parent_sum(__popc(P[j].bits & 3u), f);
+        if (cnt) ust = div_by(us, V(cnt));
+      }
+      if ((pair[j] >> 31) && !(tid & (3u << (f - 1)))) {
+        A.B[P[j].parent] = rs * A.scale;
+        A.U[P[j].parent] = ust;
+        A.Ustar[P[j].parent - A.nlb * 64u] = ust;
+      }
     }
   }
 }

@@ -376,12 +376,14 @@ struct mfmg_hierarchy {
   bool stream_composite = false;  // the same for the composite operator
   bool fuse_bottom = false;       // level lc + 1 and the coarsest level in one kernel (k_bottom)
   DevBuf<uint4> bot_f, bot_c;     // k_bottom's tables of the two levels
-  DevBuf<uint4> tile_tab;         // k_tile's table of level lc + 2
-  DevBuf<double> tile_w64;        // and its work vectors, by precision
-  DevBuf<float> tile_w32;
+  // k_tile's levels (both cycles): table, and per level the vectors W, R and
+  // the transposed cycle's W
+  bool tile_lv[kTileMax + 1] = {};
+  DevBuf<uint4> tile_tab[kTileMax + 1];
+  DevBuf<double> tile_w64[kTileMax + 1];
+  DevBuf<float> tile_w32[kTileMax + 1];
   bool fuse_prolong = true;       // prolongation folded into the post-smoothing (k_smooth PR)
   std::vector<char> corr_lv;      // per level: in correction form (its iterate is u - u*)
-  bool tile = false;              // level lc + 2 takes k_tile (both cycles)
   // work vectors (device order)
   DevBuf<double> U64, B64, S64;  // FP64 cycle: nb*64, nb*64, (nb-nlb)*64
   DevBuf<float> U32, B32, S32;   // mixed cycle
@@ -1156,14 +1158,19 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
         h->corr_lv[l] = on && int(l) > h->lc && int(l) < h->L && !leaf_below &&
                         D.range[l].n_inner > 0;
       }
-      // k_tile takes the level above k_bottom's when that is the complete 32^3
-      // grid, either in correction form or the finest level (all leaves).
-      int t = h->lc + 2;
+      // k_tile takes the complete levels from 16^3 cells above the bottom's,
+      // in correction form or with leaves, to 64^3 in FP32 and 32^3 in FP64.
+      // A visit of a 64^3 level with leaves: FP32 27 us against 42, FP64
+      // (half the threads, twice the bytes) 52 against 46; of a 128^3 level,
+      // FP32: 177 us against 121.
+      // MFMG_FUSE_BOTTOM=0 or MFMG_FUSE_PROLONG=0 keep the separate kernels.
+      const char *eb = std::getenv("MFMG_FUSE_BOTTOM");
       auto few = [](int nu) { return nu == 1 || nu == 2; };
-      h->tile = h->fuse_bottom && h->corr_lv[size_t(h->lc + 1)] && t == kTileLevel &&
-                D.range[t].n() == 512u && few(prm->nu_pre) && few(prm->nu_post) &&
-                h->fuse_prolong && (h->corr_lv[size_t(t)] || (t == h->L && D.range[t].n_inner == 0));
-      if (h->fuse_bottom) build_bottom(h.get(), s);
+      for (int l = kTileMin; l <= std::min(mixed ? kTileMax : kTileMax - 1, h->L); ++l)
+        h->tile_lv[l] = !(eb && eb[0] == '0') && h->fuse_prolong && few(prm->nu_pre) &&
+                        few(prm->nu_post) && l > h->lc + int(h->fuse_bottom) &&
+                        D.range[l].n() == (uint32_t(1) << (3 * (l - 2)));
+      build_bottom(h.get(), s);
     }
     HIP_CHECK(hipGetLastError());
     HIP_CHECK(hipStreamSynchronize(s));
@@ -1372,18 +1379,24 @@ struct Cycle {
       hipLaunchKernelGGL((k_restrict<V, CL, CI, kCpolDefault, CORR>), g, dim3(kBlock), 0, s, A,
                          scale);
   }
-  // The two sides of k_tile on level lc + 2 (which: 0 this cycle's work
-  // vector, 1 the transposed cycle's).
-  template <bool POST>
-  void tile(int nu, V scale, V pscale, int which = 0) const {
-    const Range &R = h->co->dt->range[size_t(kTileLevel)];
+  bool tiled(int l) const { return l <= kTileMax && h->tile_lv[l]; }
+  // k_tile's arguments on level l; fas: its right-hand side is formed there
+  // (and kept in R); which: 2 the transposed cycle's work vector.
+  TileArgs<V> tile_args(int l, bool own_rhs, int which, bool sub, V scale, V pscale) const {
     V *w;
-    if constexpr (sizeof(V) == 8) w = h->tile_w64.p;
-    else w = h->tile_w32.p;
-    w += which * kTileCells;
-    TileArgs<V> A{h->tile_tab.p, h->bot_f.p, U, B, w, (R.n_leaf ? R.leaf_lo : R.inner_lo) * 64u,
-                  nu, scale, pscale, done};
-    hipLaunchKernelGGL((k_tile<V, POST>), dim3(kTiles), dim3(kBottomThreads<V>), 0, s, A);
+    if constexpr (sizeof(V) == 8) w = h->tile_w64[l].p;
+    else w = h->tile_w32[l].p;
+    const size_t cells = size_t(1) << (3 * l);
+    return TileArgs<V>{h->tile_tab[l].p, U, B, Ust, w + size_t(which) * cells,
+                       own_rhs ? w + cells : nullptr, h->co->dt->nlb, l, 0, 0,
+                       int(which || h->corr_lv[size_t(l - 1)]), int(sub), scale, pscale, done};
+  }
+  template <int MODE>
+  void tile(TileArgs<V> A, int nu, bool form = false) const {
+    A.nu = nu;
+    A.fas = int(form);
+    hipLaunchKernelGGL((k_tile<V, MODE>), dim3(1u << (3 * (A.l - 3))), dim3(kBottomThreads<V>), 0,
+                       s, A);
   }
   template <bool CORR>
   void bottom(const BottomArgs<V> &F) const {
@@ -1394,7 +1407,8 @@ struct Cycle {
   // zero: the level's iterate is zero (the finest level at the start of a
   // cycle, the first visit of a level in correction form), so the first
   // half-sweep needs no neighbour values and also clears the iterate.
-  void fas(int l, bool zero = false) const {
+  // form: the first visit (k_tile forms the FAS right-hand side there).
+  void fas(int l, bool zero, bool form) const {
     const mfmg_mg_params &p = h->prm;
     if (l == h->lc) {
       auto A = args(l, false);
@@ -1404,11 +1418,18 @@ struct Cycle {
       return;
     }
     V scale = V(p.beta_mg / p.alpha);
-    bool tiled = zero && h->tile && l == kTileLevel;
     bool corr = h->corr_lv[size_t(l - 1)];  // level l - 1 is in correction form
     auto A = args(l, false);
-    if (tiled) {
-      tile<false>(p.nu_pre, scale, V(0));
+    TileArgs<V> T{};
+    if (tiled(l)) {
+      bool own_rhs = l < h->L && !h->corr_lv[size_t(l)];
+      T = tile_args(l, own_rhs, 0, true, scale, V(1));
+      if (zero) {
+        tile<kTileZero>(T, p.nu_pre);
+      } else {
+        tile<kTileFrom>(T, p.nu_pre, own_rhs && form);
+        tile<kTileRestrict>(T, 0);
+      }
     } else {
       smooth(l, 0, p.nu_pre, zero);
       if (corr) restrict_to<true>(l, A, scale);
@@ -1420,13 +1441,13 @@ struct Cycle {
       else bottom<false>(F);
     } else {
       auto C = args(l - 1, true);
-      if (C.R.n() && !corr)
+      if (C.R.n() && !corr && !tiled(l - 1))
         hipLaunchKernelGGL((k_fas_rhs<V, CL, CI>), dim3(stencil_grid<V>(C.R.n_inner)),
                            dim3(kBlock), 0, s, C);
-      for (int k = 0; k < p.mu; ++k) fas(l - 1, corr && k == 0);
+      for (int k = 0; k < p.mu; ++k) fas(l - 1, corr && k == 0, k == 0);
     }
-    if (tiled) {
-      tile<true>(p.nu_post, V(0), V(1));
+    if (tiled(l)) {
+      tile<kTileUp>(T, p.nu_post);
     } else if (h->fuse_prolong && p.nu_post > 0) {
       smooth(l, 1, p.nu_post, false, true);
     } else {
@@ -1444,7 +1465,7 @@ struct Cycle {
     if (N > 0)
       hipLaunchKernelGGL((k_fill<V>), dim3(grid_elems(N, 256)), dim3(256), 0, s, U + lo, N,
                          V(0));
-    fas(h->L, zero_start);
+    fas(h->L, zero_start, true);
   }
 };
 
@@ -1461,17 +1482,24 @@ void run_cycle(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
   else cycle64(h, s, done).run();
 }
 
-// k_bottom's tables of the levels lc + 1 and lc, k_tile's of level lc + 2.
+// k_bottom's tables of the levels lc + 1 and lc, k_tile's of its levels.
 template <class V, class CL, class CI>
-void build_bottom_of(mfmg_hierarchy *h, const Cycle<V, CL, CI> &c, DevBuf<V> &work) {
-  DevBuf<uint4> *tab[3] = {&h->bot_c, &h->bot_f, &h->tile_tab};
-  for (int k = 0; k < (h->tile ? 3 : 2); ++k) {
-    auto A = c.args(h->lc + k, false);
-    tab[k]->alloc(size_t(BottomUnits<V>::kAll) << (3 * (h->lc + k) - 1));
+void build_bottom_of(mfmg_hierarchy *h, const Cycle<V, CL, CI> &c, DevBuf<V> *work) {
+  auto table = [&](int l, DevBuf<uint4> &tab) {
+    auto A = c.args(l, false);
+    tab.alloc(size_t(BottomUnits<V>::kAll) << (3 * l - 1));
     hipLaunchKernelGGL((k_bottom_table<V, CL, CI>), dim3(grid_for(A.R.n())), dim3(kBlock), 0, c.s,
-                       A, h->lc + k, tab[k]->p);
+                       A, l, tab.p);
+  };
+  if (h->fuse_bottom) {
+    table(h->lc, h->bot_c);
+    table(h->lc + 1, h->bot_f);
   }
-  if (h->tile) work.alloc(2 * size_t(kTileCells));
+  for (int l = kTileMin; l <= kTileMax; ++l)
+    if (h->tile_lv[l]) {
+      table(l, h->tile_tab[l]);
+      work[l].alloc(size_t(3) << (3 * l));
+    }
   HIP_CHECK(hipGetLastError());
 }
 
@@ -1539,10 +1567,20 @@ struct CycleT {
       return;
     }
     V pscale = V(p.beta_mg / p.alpha);
-    bool tiled = first && h->tile && l == kTileLevel;
+    // Above a complete level no leaf lies on the level below, so nothing is
+    // coupled or handed back there: k_tile's steps are the forward ones.
+    const Cycle<V, CL, CI> F = forward();
+    const bool tiled = F.tiled(l);
+    TileArgs<V> T{};
     unsigned gr = stencil_grid<V>(A.R.n());
     if (tiled) {
-      forward().template tile<false>(p.nu_post, V(1), V(0), 1);
+      T = F.tile_args(l, false, 2, false, V(1), pscale);
+      if (first) {
+        F.template tile<kTileZero>(T, p.nu_post);
+      } else {
+        F.template tile<kTileFrom>(T, p.nu_post);
+        F.template tile<kTileRestrict>(T, 0);
+      }
     } else {
       smooth(l, 0, p.nu_post, first, false);  // forward post-smoothing is (B,R)^nu
       uint32_t nc = h->couple_n[size_t(l - 1)];
@@ -1560,13 +1598,13 @@ struct CycleT {
       hipLaunchKernelGGL((k_T_revisit<V, CL, CI>), dim3(stencil_grid<V>(C.R.n_inner)),
                          dim3(kBlock), 0, s, C);
     if (l - 1 == h->lc + 1 && h->fuse_bottom) {
-      forward().template bottom<true>(forward().bottom_args(
-          p.nu_post, p.nu_pre, p.nu_coarse - p.nu_coarse / 2, int(first), V(1), pscale));
+      F.template bottom<true>(F.bottom_args(p.nu_post, p.nu_pre, p.nu_coarse - p.nu_coarse / 2,
+                                            int(first), V(1), pscale));
     } else {
       for (int k = 0; k < p.mu; ++k) fas(l - 1, first && k == 0);
     }
     if (tiled) {
-      forward().template tile<true>(p.nu_pre, V(0), pscale, 1);
+      F.template tile<kTileUp>(T, p.nu_pre);
       return;
     }
     // forward pre-smoothing is (R,B)^nu

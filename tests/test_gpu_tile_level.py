@@ -1,9 +1,8 @@
-"""The 32^3 level above the one-kernel bottom in tiles with a halo, as the
-finest level (all leaves) and as a complete inner level (and not where it has
-both), against the oracle's cycle:
-every wall condition (the halo is cut at the walls), inactive cells, one and
-two smoothing iterations on either side (the halo holds two), V- and
-W-cycles (later visits of the level take the separate kernels), both
+"""Complete levels of 16^3 to 64^3 cells in tiles with a halo, as the finest
+level (all leaves), as an inner level without leaves and as one with both,
+against the oracle's cycle: every wall condition (the halo is cut at the
+walls), inactive cells, one and two smoothing iterations on either side (the
+halo holds two; three take the separate kernels), V- and W-cycles, both
 directions."""
 
 import numpy as np
@@ -19,7 +18,7 @@ BC = {"mixed": (1, 0, 0, 1, 1, 0), "neumann": (0,) * 6}
 
 
 @pytest.mark.parametrize("walls", list(BC))
-@pytest.mark.parametrize("levels", [(5, 5), (6, 6), (5, 6)])
+@pytest.mark.parametrize("levels", [(4, 4), (5, 5), (6, 6), (5, 6), (6, 7)])
 @pytest.mark.parametrize("precision,mu,nu", [(0, 1, (2, 2)), (0, 2, (1, 2)), (1, 1, (2, 1)),
                                              (1, 2, (2, 2)), (1, 1, (1, 1)), (0, 1, (3, 2))])
 def test_cycle_with_tiles(levels, walls, precision, mu, nu):
