@@ -150,7 +150,7 @@ __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, uint32_t lane, 
 struct Scalars {
   double rr0;    // ||r_0||^2
   double rr;     // ||r_k||^2
-  double rz;     // (r_k, z_k)
+  double rz[2];  // (r_k, z_k), at iters & 1: the one before is still being read
   double pAp;    // (p_k, A p_k)
   double alpha;
   double beta;

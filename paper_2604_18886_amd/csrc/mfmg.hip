@@ -1890,15 +1890,20 @@ struct Krylov {
     GA = level_grid(h->co->dt->nlb);
     n2 = int64_t(h->co->dt->nlb) * 32;
   }
+  // partials that the next kernel adds itself (0: k_finish does)
+  static uint32_t folded(unsigned n) { return n <= kFoldParts ? n : 0u; }
   void rz(const double *r, const V *z, int first) const {
     hipLaunchKernelGGL(k_pcg_rz<V>, dim3(GA), dim3(kBlock), 0, s, P, r, z);
+    if (folded(GA)) return;
     hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, P, int64_t(GA), int(kFinRz), first,
                        0.0);
   }
   void pupdate(const V *z, int first) const {
-    hipLaunchKernelGGL(k_pcg_p<V>, dim3(GA), dim3(kBlock), 0, s, P, z, h->pd.p, h->x.p, first);
+    hipLaunchKernelGGL(k_pcg_p<V>, dim3(GA), dim3(kBlock), 0, s, P, z, h->pd.p, h->x.p, first,
+                       folded(GA));
   }
-  void Ap(bool trans) const {
+  // Returns the number of partials of (p, Ap).
+  unsigned Ap(bool trans) const {
     unsigned n = GA;
     if (trans && h->stream_composite)
       hipLaunchKernelGGL(k_pcg_ApT<kCpolStream>, dim3(GA), dim3(kBlock), 0, s, P,
@@ -1913,14 +1918,20 @@ struct Krylov {
       hipLaunchKernelGGL(k_pcg_Ap<>, dim3(GA), dim3(kBlock), 0, s, P, (const double *)h->pd.p,
                          h->Ap.p);
     if (trans) n += couple_T(h, P, h->pd.p, h->Ap.p, GA, &h->S.p->done, s);
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, P, int64_t(n), int(kFinAlpha), 0,
-                       0.0);
+    if (!folded(n))
+      hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, P, int64_t(n), int(kFinAlpha), 0,
+                         0.0);
+    return n;
   }
-  void update(double *r, V *r_low, int defer) const {
+  // parts: of (p, Ap); this kernel's own go behind them, which other
+  // workgroups may still be adding
+  void update(double *r, V *r_low, int defer, unsigned parts) const {
+    PcgArgs Q = P;
+    if (folded(parts)) Q.partials += kMaxReduceBlocks;
     hipLaunchKernelGGL(k_pcg_update<V>, dim3(G), dim3(kBlock), 0, s, P, r, r_low,
-                       (const double *)h->Ap.p, defer, n2);
+                       (const double *)h->Ap.p, defer, n2, folded(parts), Q.partials);
     if (!defer)
-      hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, P, int64_t(G), int(kFinUpdate),
+      hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, Q, int64_t(G), int(kFinUpdate),
                          0, 0.0);
   }
   // after the loop: the iterate's last step, if the solve stopped between a
@@ -1944,8 +1955,8 @@ static void iteration_body(mfmg_hierarchy *h, double *r, V *r_low, V *z, bool nu
                            bool trans, hipStream_t s) {
   Reduce R(h, s);
   Krylov<V> K(h, s);
-  K.Ap(trans);
-  K.update(r, r_low, int(null_space));
+  const unsigned parts = K.Ap(trans);
+  K.update(r, r_low, int(null_space), parts);
   if (null_space) R.shift_mean<V>(r, r_low, std::max(1.0, h->n_active), 1, 0.0);
   run_precond(h, trans, s);
   K.rz(r, z, 0);

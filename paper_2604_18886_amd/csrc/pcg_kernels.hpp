@@ -165,6 +165,39 @@ __device__ __forceinline__ void block_partial(double part, double *partials) {
   }
 }
 
+// Small solves: the kernel that uses a reduction adds its n <= kFoldParts
+// partials itself, every workgroup, in k_finish's order (the same bits), and
+// the launch between them goes.  Mixed solves, us, without -> with: 32^3 (128
+// partials) 558 -> 521, 0.15 M leaves (600) 1675 -> 1600, 64^3 (1024, the
+// line) 889 -> 886.  More partials would cost every workgroup what the launch
+// does.  n = 0: k_finish
+// ran.  False: the solve has stopped (one read of the flag per workgroup, as
+// another may set it meanwhile).
+constexpr uint32_t kFoldParts = 1024;
+__device__ __forceinline__ bool fold_total(const PcgArgs &P, uint32_t n, double &tot) {
+  __shared__ double red[kFoldParts / kWave];
+  __shared__ int stop;
+  if (threadIdx.x == 0) stop = P.S->done;
+  const uint32_t chunks = (n + kWave - 1) / kWave;
+  for (uint32_t c = threadIdx.x / kWave; c < chunks; c += kWavesPerBlock) {
+    const uint32_t i = c * kWave + (threadIdx.x & (kWave - 1));
+    const double v = wave_sum(i < n ? P.partials[i] : 0.0);
+    if ((threadIdx.x & (kWave - 1)) == 0) red[c] = v;
+  }
+  __syncthreads();
+  if (stop) return false;
+  tot = 0.0;
+  for (uint32_t c = 0; c < chunks; ++c) tot += red[c];
+  return true;
+}
+// A scalar that must be positive and finite is not: the solve stops.
+__device__ __forceinline__ void break_down(const PcgArgs &P) {
+  P.S->status = -5;
+  P.S->done = 1;
+  if (P.host_done)
+    __hip_atomic_store(P.host_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // grid-stride loop of one wave over the leaf bricks
 #define LEAF_LOOP(P)                                                     \
   int m = threadIdx.x & (kWave - 1);                                     \
@@ -250,9 +283,27 @@ __global__ void __launch_bounds__(kBlock) k_pcg_rz(PcgArgs P, const double *r, c
 // when the solve stopped before this kernel ran.
 template <class V>
 __global__ void __launch_bounds__(kBlock) k_pcg_p(PcgArgs P, const V *z, double *p, double *x,
-                                                  int first) {
-  if (P.S->done) return;
-  double beta = first ? 0.0 : P.S->beta;
+                                                  int first, uint32_t parts) {
+  double beta = 0.0;
+  if (parts) {
+    double tot;
+    if (!fold_total(P, parts, tot)) return;
+    const bool ok = tot > 0.0 && tot < INFINITY;
+    const int it = P.S->iters;
+    if (ok && !first) beta = tot / P.S->rz[(it - 1) & 1];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if (ok) {
+        P.S->beta = beta;
+        P.S->rz[it & 1] = tot;
+      } else {
+        break_down(P);
+      }
+    }
+    if (!ok) return;
+  } else {
+    if (P.S->done) return;
+    if (!first) beta = P.S->beta;
+  }
   double alpha = P.S->alpha;
   double zs = 1.0 / P.S->rscale;
   uint32_t m = threadIdx.x & (kWave - 1);
@@ -382,7 +433,7 @@ __device__ __forceinline__ void finish_initial(const PcgArgs &P, double tot, dou
   S->status = 0;
   S->done = (tot == 0.0) || !(tot < INFINITY);
   if (!(tot < INFINITY)) S->status = -5;
-  S->rz = 0.0;
+  S->rz[0] = S->rz[1] = 0.0;
   S->rscale = low_scale(P, tot);
   P.hist[0] = tot > 0.0 ? 1.0 : 0.0;
 }
@@ -412,8 +463,8 @@ __global__ void __launch_bounds__(1024) k_finish(PcgArgs P, int64_t n, int op, i
         S->status = -5;
         S->done = 1;
       } else {
-        S->beta = arg ? 0.0 : tot / S->rz;
-        S->rz = tot;
+        S->beta = arg ? 0.0 : tot / S->rz[(S->iters - 1) & 1];
+        S->rz[S->iters & 1] = tot;
       }
       break;
     case kFinAlpha:
@@ -422,7 +473,7 @@ __global__ void __launch_bounds__(1024) k_finish(PcgArgs P, int64_t n, int op, i
         S->status = -5;
         S->done = 1;
       } else {
-        S->alpha = S->rz / tot;
+        S->alpha = S->rz[S->iters & 1] / tot;
       }
       // scale of the residual the update is about to write, from the last
       // norm (a PCG residual changes by modest factors per iteration)
@@ -471,10 +522,27 @@ __global__ void __launch_bounds__(1024) k_finish(PcgArgs P, int64_t n, int op, i
 template <class V>
 __global__ void __launch_bounds__(kBlock) k_pcg_update(PcgArgs P, double *r, V *r_low,
                                                        const double *Ap, int defer,
-                                                       int64_t n2) {
-  if (P.S->done) return;
-  double alpha = P.S->alpha;
-  double sc = P.S->rscale;
+                                                       int64_t n2, uint32_t parts,
+                                                       double *out) {
+  double alpha, sc;
+  if (parts) {
+    double tot;
+    if (!fold_total(P, parts, tot)) return;
+    const bool ok = tot > 0.0 && tot < INFINITY;
+    sc = low_scale(P, P.S->rr);
+    alpha = P.S->rz[P.S->iters & 1] / tot;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      P.S->pAp = tot;
+      P.S->rscale = sc;
+      if (ok) P.S->alpha = alpha;
+      else break_down(P);
+    }
+    if (!ok) return;
+  } else {
+    if (P.S->done) return;
+    alpha = P.S->alpha;
+    sc = P.S->rscale;
+  }
   double part = 0.0;
   double2 *r2 = reinterpret_cast<double2 *>(r);
   const double2 *a2 = reinterpret_cast<const double2 *>(Ap);
@@ -502,7 +570,7 @@ __global__ void __launch_bounds__(kBlock) k_pcg_update(PcgArgs P, double *r, V *
     }
   }
   if (defer) return;  // the null-space shift completes this step
-  block_partial(part, P.partials);
+  block_partial(part, out);
 }
 
 // x += alpha p when the solve stopped after a residual update and before
