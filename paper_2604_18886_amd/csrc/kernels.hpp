@@ -1026,8 +1026,13 @@ __device__ __forceinline__ void first_sweep_brick(const LevelView<V, CL, CI, CP>
   bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(rhs, c) : V(0));
 }
 
+// clear: the iterate of the coarser levels' leaves starts from zero too (the
+// finest level's leaves are the first bricks, theirs follow).  26.3M leaves,
+// FP32: 44.8 us, against 41.3 and 10.8 in a launch of its own; 2.3M leaves 7.0
+// against 6.3 + 4.6.
 template <class V, class CL, class CI, int CP = kCpolDefault>
-__global__ void __launch_bounds__(kBlock) k_first_sweep(LevelArgs<V, CL, CI> A, int colour) {
+__global__ void __launch_bounds__(kBlock) k_first_sweep(LevelArgs<V, CL, CI> A, int colour,
+                                                        int clear) {
   if (A.done && *A.done) return;
   const LaneC<V, CL> L = lane_consts<V, CL>();
   const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
@@ -1035,6 +1040,11 @@ __global__ void __launch_bounds__(kBlock) k_first_sweep(LevelArgs<V, CL, CI> A, 
   for (uint32_t i = W.first; i < W.end; i += W.step) {
     if (i < A.R.n_leaf) first_sweep_brick<false>(X, L, A.R.leaf_lo + i, colour);
     else first_sweep_brick<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
+  }
+  if (clear) {
+    const WaveLoop C = wave_loop(X.nlb - A.R.n_leaf);
+    for (uint32_t i = C.first; i < C.end; i += C.step)
+      bstore<V>(X.u, L.m, (A.R.n_leaf + i) * 64u, V(0));
   }
 }
 

@@ -1351,9 +1351,10 @@ struct Cycle {
         if (zero && it == 0 && c == 0) {
           if (stream(l))
             hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A,
-                               colour);
+                               colour, int(l == h->L));
           else
-            hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour);
+            hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour,
+                               int(l == h->L));
         } else {
           half_sweep(l, A, colour, prolong && it == 0 ? 1 + c : 0);
         }
@@ -1459,12 +1460,12 @@ struct Cycle {
 
   void run() const {
     const Range &RL = h->co->dt->range[h->L];
+    // (its first half-sweep then also clears the coarser leaves; no level in
+    // tiles has any)
     bool zero_start = h->L > h->lc && h->prm.nu_pre > 0 && RL.n_inner == 0 && RL.leaf_lo == 0;
-    int64_t lo = zero_start ? int64_t(RL.n_leaf) * 64 : 0;
-    int64_t N = int64_t(h->co->dt->nlb) * 64 - lo;
+    int64_t N = zero_start ? 0 : int64_t(h->co->dt->nlb) * 64;
     if (N > 0)
-      hipLaunchKernelGGL((k_fill<V>), dim3(grid_elems(N, 256)), dim3(256), 0, s, U + lo, N,
-                         V(0));
+      hipLaunchKernelGGL((k_fill<V>), dim3(grid_elems(N, 256)), dim3(256), 0, s, U, N, V(0));
     fas(h->L, zero_start, true);
   }
 };
@@ -1544,9 +1545,10 @@ struct CycleT {
       int colour = (k & 1) ? 1 - first : first;
       if (zero && k == 0) {
         if (stream(l))
-          hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, colour);
+          hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, colour,
+                             0);
         else
-          hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour);
+          hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour, 0);
       } else if (prolong && k == 0) {
         half_sweep<1>(l, A, colour);
       } else if (prolong && k == 1) {

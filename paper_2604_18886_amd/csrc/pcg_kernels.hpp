@@ -170,9 +170,8 @@ __device__ __forceinline__ void block_partial(double part, double *partials) {
 // the launch between them goes.  Mixed solves, us, without -> with: 32^3 (128
 // partials) 558 -> 521, 0.15 M leaves (600) 1675 -> 1600, 64^3 (1024, the
 // line) 889 -> 886.  More partials would cost every workgroup what the launch
-// does.  n = 0: k_finish
-// ran.  False: the solve has stopped (one read of the flag per workgroup, as
-// another may set it meanwhile).
+// does.  n = 0: k_finish ran.  False: the solve has stopped (one read of the
+// flag per workgroup, as another may set it meanwhile).
 constexpr uint32_t kFoldParts = 1024;
 __device__ __forceinline__ bool fold_total(const PcgArgs &P, uint32_t n, double &tot) {
   __shared__ double red[kFoldParts / kWave];
