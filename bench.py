@@ -89,8 +89,8 @@ def summarize_trace(stats_csv):
     kernels = {}
     with open(stats_csv) as fh:
         for r in csv.DictReader(fh):
-            # "void mfmg::k_smooth<float, float, __half, 256, 0>(mfmg::LevelArgs<...>, int)"
-            # -> "mfmg::k_smooth<float, float, __half, 256, 0>"
+            # "void mfmg::k_smooth<float, float, __half, 256, 0, false>(mfmg::LevelArgs<...>, int)"
+            # -> "mfmg::k_smooth<float, float, __half, 256, 0, false>"
             name = r["Name"].strip()
             if name.startswith("void "):
                 name = name[5:]
@@ -119,8 +119,9 @@ def smooth_precision(kernel_name):
     return None
 
 
-CYCLE_KERNELS = ("k_fill", "k_smooth", "k_restrict", "k_fas_rhs", "k_bottom", "k_prolong",
-                 "k_coarsest")
+CYCLE_KERNELS = ("k_fill", "k_first_sweep", "k_smooth", "k_restrict", "k_fas_rhs", "k_tile",
+                 "k_bottom", "k_prolong", "k_coarsest")
+CYCLE_START = ("k_fill", "k_first_sweep", "k_tile")
 
 
 def summarize_pmc(fetch_csv, write_csv, level):
@@ -129,7 +130,7 @@ def summarize_pmc(fetch_csv, write_csv, level):
     files (FETCH_SIZE, WRITE_SIZE in KiB per dispatch) of a --traffic-pass
     run, each scaled by what the same counter reads for a plain copy of
     COPY_BYTES bytes.  The half-sweeps are the k_smooth dispatches before the
-    first cycle's k_fill; the cycles are every cycle kernel after it, per
+    first cycle's first kernel; the cycles are every cycle kernel from it on, per
     k_bottom dispatch (one per V-cycle).  Returns (precision, record)."""
     import csv
 
@@ -150,11 +151,11 @@ def summarize_pmc(fetch_csv, write_csv, level):
     precisions = set()
     for counter, path in (("FETCH_SIZE", fetch_csv), ("WRITE_SIZE", write_csv)):
         rows = dispatches(path, counter)
-        first_fill = min((d for d, n, _ in rows if "k_fill" in n), default=None)
+        first = min((d for d, n, _ in rows if any(k in n for k in CYCLE_START)), default=None)
         smooth = [v for d, n, v in rows if "k_smooth<" in n
-                  and (first_fill is None or d < first_fill)]
+                  and (first is None or d < first)]
         precisions |= {smooth_precision(n) for _, n, _ in rows if "k_smooth<" in n}
-        cyc = [(d, n, v) for d, n, v in rows if first_fill is not None and d >= first_fill
+        cyc = [(d, n, v) for d, n, v in rows if first is not None and d >= first
                and any(k in n for k in CYCLE_KERNELS)]
         ncyc = sum(1 for _, n, _ in cyc if "k_bottom" in n)
         last = max((d for d, n, _ in rows if any(k in n for k in CYCLE_KERNELS)), default=None)
@@ -642,7 +643,8 @@ def main():
             "kernel": f"k_smooth<float,float,__half> colour half-sweep, level {L}",
             "algorithmic_bytes_per_launch": head["smooth_bytes"],
             "avg_launch_us": head["smooth_ms"] * 1e3,
-            "rocprof_avg_launch_us": traced_launch_us("mfmg::k_smooth<float, float, __half, 256, 0>"),
+            "rocprof_avg_launch_us": traced_launch_us(
+                "mfmg::k_smooth<float, float, __half, 256, 0, false>"),
             "stream_copy_gbs": head["copy_gbs"],
             "frac_of_stream_copy": head["smooth_gbs"] / head["copy_gbs"]}
     cpu = None

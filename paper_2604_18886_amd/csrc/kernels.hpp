@@ -1225,13 +1225,12 @@ __global__ void __launch_bounds__(1024) k_coarsest(LevelArgs<V, CL, CI> A, int n
 // take become one.  The sums and their order are those of k_fas_rhs,
 // k_smooth, k_restrict, k_coarsest and k_prolong, and the arrays in memory
 // end as those kernels leave them.  `visits` consecutive FAS steps of level f
-// (the level above's mu) are taken in one launch.  fas = 0 skips the FAS
-// right-hand side of the first one (a W-cycle's later visits: it is already
-// in B).
+// (the level above's mu) are taken in one launch.
 // CORR: the step in correction form (level f without leaves, where the iterate
-// is u - u*, and the transposed cycle): fas = 1 starts from a zero iterate,
-// the coarsest iterate starts from zero too and pscale times it is the
-// correction.
+// is u - u*, and the transposed cycle): it starts from a zero iterate (fas = 0:
+// from U, on later visits of the transposed W-cycle), the coarsest iterate
+// starts from zero too and pscale times it is the correction; the coarsest
+// level's arrays are not written.
 //
 // What bounds it: one CU's LDS reads, the barriers and the set-up's loads.  A
 // thread holds pairs of cells that are neighbours along x, one of each colour,
@@ -1518,7 +1517,7 @@ __global__ void __launch_bounds__(kBottomThreads<V>) k_bottom(BottomArgs<V> A) {
   const std::integral_constant<int, 1> black{};
   for (int visit = 0; visit < A.visits; ++visit) {
     // FAS right-hand side of the inner bricks: b += A u*
-    if (!CORR && visit == 0 && A.fas) {
+    if (!CORR && visit == 0) {
 #pragma unroll
       for (int j = 0; j < kSlots; ++j) {
         if ((P[j].bits & 12u) != 12u) continue;
