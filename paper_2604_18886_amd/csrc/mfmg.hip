@@ -255,12 +255,20 @@ inline unsigned grid_for(int64_t bricks) {
 // levels, every coarse level) take 2048 waves per XCD in FP32, so that each
 // wave gets four or more bricks rather than two or three (leaf half-sweep of
 // the 2.3 M-leaf cut-sphere workload 11.7 -> 10.8 us, its mixed solve 6.92
-// -> 6.72 ms; the large workload's mixed solve 41.52 -> 41.48 ms).
+// -> 6.72 ms; the large workload's mixed solve 41.52 -> 41.48 ms).  Below 32768
+// bricks a level takes no more waves than are resident at once (8 per SIMD in
+// FP32, 5 in FP64): one round of a few bricks each, where a second round
+// of one brick would run with the chip half empty (solves, us: mixed levels
+// 6..8 3391 -> 3264, band 5..7 2749 -> 2673, 7..9 6630 -> 6562, 6..9 5343 ->
+// 5322; FP64 6..9 7239 -> 7208, band 3463 -> 3427, 7..8 6648 -> 6658).
 // MFMG_WAVES_PER_XCD (read once) overrides the cap, for tuning.
 constexpr int64_t kWavesPerXcd32 = 3072;
 constexpr int64_t kWavesPerXcdSmall32 = 2048;
 constexpr int64_t kSmallLevelBricks = 65536;
 constexpr int64_t kWavesPerXcd64 = 1920;
+constexpr int64_t kOneRoundBricks = 32768;
+constexpr int64_t kOneRound32 = 1024;
+constexpr int64_t kOneRound64 = 640;
 inline int64_t waves_override() {
   static const int64_t v = [] {
     const char *e = std::getenv("MFMG_WAVES_PER_XCD");
@@ -275,6 +283,7 @@ inline unsigned grid_waves(int64_t bricks, int64_t cap) {
   return unsigned(8 * ((waves + kWavesPerBlock - 1) / kWavesPerBlock));
 }
 inline int64_t cap32(int64_t bricks) {
+  if (bricks < kOneRoundBricks) return kOneRound32;
   return bricks < kSmallLevelBricks ? kWavesPerXcdSmall32 : kWavesPerXcd32;
 }
 // reductions and FP32 stencils
@@ -289,8 +298,10 @@ inline unsigned group_grid(int64_t bricks) {
 // stencils on values of type V
 template <class V>
 inline unsigned stencil_grid(int64_t bricks) {
+  int64_t cap = cap32(bricks);
+  if (sizeof(V) == 8) cap = bricks < kOneRoundBricks ? kOneRound64 : kWavesPerXcd64;
   if (waves_override()) return grid_waves(bricks, waves_override());
-  return grid_waves(bricks, sizeof(V) == 8 ? kWavesPerXcd64 : cap32(bricks));
+  return grid_waves(bricks, cap);
 }
 // A stencil launch whose single-use streams (coefficients, plus faces,
 // right-hand side) and iterate together exceed the 256 MB Infinity Cache
