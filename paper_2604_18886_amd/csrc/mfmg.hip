@@ -395,6 +395,7 @@ struct mfmg_hierarchy {
   DevBuf<float> tile_w32[kTileMax + 1];
   bool fuse_prolong = true;       // prolongation folded into the post-smoothing (k_smooth PR)
   std::vector<char> corr_lv;      // per level: in correction form (its iterate is u - u*)
+  bool fuse_fas = true;           // k_smooth_fas on a cycle's first visit of other levels
   // work vectors (device order)
   DevBuf<double> U64, B64, S64;  // FP64 cycle: nb*64, nb*64, (nb-nlb)*64
   DevBuf<float> U32, B32, S32;   // mixed cycle
@@ -1159,9 +1160,10 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
       // correction form: on its cells u* is the mean of finer ones everywhere,
       // so with e = u - u* the FAS equation A u = b + A u* is A e = b from a
       // zero iterate, and neither u* nor a FAS right-hand side is formed.
+      // Other levels form theirs in the first half-sweep (k_smooth_fas).
       // MFMG_FUSE_FAS=0 (read at each build) keeps u and k_fas_rhs.
       const char *e = std::getenv("MFMG_FUSE_FAS");
-      bool on = !(e && e[0] == '0');
+      bool on = h->fuse_fas = !(e && e[0] == '0');
       h->corr_lv.assign(D.range.size(), 0);
       bool leaf_below = false;
       for (size_t l = 0; l < D.range.size(); ++l) {
@@ -1350,9 +1352,11 @@ struct Cycle {
     else half_sweep_pr<0>(l, A, colour);
   }
   // zero: from a zero iterate, which the first half-sweep also writes.
+  // form: the first half-sweep forms the FAS right-hand side (k_smooth_fas).
   // prolong: the level's FAS correction is still to be added (the first
   // two half-sweeps fold it in; nu >= 1).
-  void smooth(int l, int first, int nu, bool zero = false, bool prolong = false) const {
+  void smooth(int l, int first, int nu, bool zero = false, bool prolong = false,
+              bool form = false) const {
     auto A = args(l, false);
     if (A.R.n() == 0) return;
     for (int it = 0; it < nu; ++it)
@@ -1366,6 +1370,12 @@ struct Cycle {
           else
             hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour,
                                int(l == h->L));
+        } else if (form && it == 0 && c == 0) {
+          if (stream(l))
+            hipLaunchKernelGGL((k_smooth_fas<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A,
+                               colour);
+          else
+            hipLaunchKernelGGL((k_smooth_fas<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour);
         } else {
           half_sweep(l, A, colour, prolong && it == 0 ? 1 + c : 0);
         }
@@ -1419,8 +1429,14 @@ struct Cycle {
   // zero: the level's iterate is zero (the finest level at the start of a
   // cycle, the first visit of a level in correction form), so the first
   // half-sweep needs no neighbour values and also clears the iterate.
-  // form: the first visit (k_tile forms the FAS right-hand side there).
-  void fas(int l, bool zero, bool form) const {
+  // form: the first visit since the restriction onto the level (k_tile forms
+  // the FAS right-hand side then); fresh: and the first in the cycle (every
+  // leaf from this level down still has a zero iterate).
+  bool folds_fas(int l, bool fresh) const {
+    return fresh && h->fuse_fas && l > h->lc && l < h->L && !tiled(l) && !h->corr_lv[size_t(l)] &&
+           h->prm.nu_pre > 0;
+  }
+  void fas(int l, bool zero, bool form, bool fresh) const {
     const mfmg_mg_params &p = h->prm;
     if (l == h->lc) {
       auto A = args(l, false);
@@ -1443,7 +1459,7 @@ struct Cycle {
         tile<kTileRestrict>(T, 0);
       }
     } else {
-      smooth(l, 0, p.nu_pre, zero);
+      smooth(l, 0, p.nu_pre, zero, false, folds_fas(l, fresh));
       if (corr) restrict_to<true>(l, A, scale);
       else restrict_to<false>(l, A, scale);
     }
@@ -1453,10 +1469,10 @@ struct Cycle {
       else bottom<false>(F);
     } else {
       auto C = args(l - 1, true);
-      if (C.R.n() && !corr && !tiled(l - 1))
+      if (C.R.n() && !corr && !tiled(l - 1) && !folds_fas(l - 1, fresh))
         hipLaunchKernelGGL((k_fas_rhs<V, CL, CI>), dim3(stencil_grid<V>(C.R.n_inner)),
                            dim3(kBlock), 0, s, C);
-      for (int k = 0; k < p.mu; ++k) fas(l - 1, corr && k == 0, k == 0);
+      for (int k = 0; k < p.mu; ++k) fas(l - 1, corr && k == 0, k == 0, fresh && k == 0);
     }
     if (tiled(l)) {
       tile<kTileUp>(T, p.nu_post);
@@ -1477,7 +1493,7 @@ struct Cycle {
     int64_t N = zero_start ? 0 : int64_t(h->co->dt->nlb) * 64;
     if (N > 0)
       hipLaunchKernelGGL((k_fill<V>), dim3(grid_elems(N, 256)), dim3(256), 0, s, U, N, V(0));
-    fas(h->L, zero_start, true);
+    fas(h->L, zero_start, true, true);
   }
 };
 
@@ -2361,6 +2377,10 @@ double cycle_bytes(const mfmg_hierarchy *h) {
     bool fused = h->fuse_prolong && p.nu_post > 0;
     lvl += n_all * ((fused ? 0.0 : 2.0 * V) + 2.0 * V / 8.0);
     total += visits * lvl;
+    // (its coefficients and u*, once per cycle, are the first half-sweep's)
+    bool folded = h->fuse_fas && p.nu_pre > 0 && l - 1 > h->lc && !h->corr_lv[size_t(l - 1)] &&
+                  !(l - 1 == h->lc + 1 && h->fuse_bottom);
+    if (folded) total -= c_in * 2.0 * V + c_coef;
   }
   return total;
 }
