@@ -995,6 +995,73 @@ __global__ void __launch_bounds__(kBlock) k_smooth(LevelArgs<V, CL, CI> A, int c
   }
 }
 
+// ---------------------------------------------------------------------------
+// reductions of small solves
+// ---------------------------------------------------------------------------
+// Small solves: the kernel that uses a reduction adds its n <= kFoldParts
+// partials itself, every workgroup, in k_finish's order (the same bits), and
+// the launch between them goes.  Mixed solves, us, without -> with: 32^3 (128
+// partials) 558 -> 521, 0.15 M leaves (600) 1675 -> 1600, 64^3 (1024, the
+// line) 889 -> 886.  More partials would cost every workgroup what the launch
+// does.  n = 0: k_finish ran.  False: the solve has stopped (one read of the
+// flag per workgroup, as another may set it meanwhile).
+constexpr uint32_t kFoldParts = 1024;
+__device__ __forceinline__ bool fold_total(const Scalars *S, const double *partials, uint32_t n,
+                                           double &tot) {
+  __shared__ double red[kFoldParts / kWave];
+  __shared__ int stop;
+  if (threadIdx.x == 0) stop = S->done;
+  const uint32_t waves = blockDim.x / kWave;
+  const uint32_t chunks = (n + kWave - 1) / kWave;
+  for (uint32_t c = threadIdx.x / kWave; c < chunks; c += waves) {
+    const uint32_t i = c * kWave + (threadIdx.x & (kWave - 1));
+    const double v = wave_sum(i < n ? partials[i] : 0.0);
+    if ((threadIdx.x & (kWave - 1)) == 0) red[c] = v;
+  }
+  __syncthreads();
+  if (stop) return false;
+  tot = 0.0;
+  for (uint32_t c = 0; c < chunks; ++c) tot += red[c];
+  return true;
+}
+__device__ __forceinline__ void finish_iteration(Scalars *S, double *hist, double tot) {
+  S->xpend = 1;  // the residual update of this iteration is done
+  S->rr = tot;
+  S->iters += 1;
+  hist[S->iters] = S->rr0 > 0.0 ? sqrt(tot / S->rr0) : 0.0;
+  if (!(tot < INFINITY)) {
+    S->status = -5;
+    S->done = 1;
+  } else if (tot <= S->tol2) {
+    S->done = 1;
+  }
+}
+
+// The stop test of an iteration in the first kernel of the cycle that follows:
+// the n partials of ||r||^2 (0: k_finish ran, and S->done tells).  Mixed solves,
+// us, k_finish's launch -> this: 16^3 483 -> 469, 32^3 513 -> 501, levels 5..6
+// 1573 -> 1545, 64^3 (the line) 887 -> 885.
+struct StopTest {
+  Scalars *S;
+  const double *partials;
+  double *hist;
+  int *host_done;
+  uint32_t n;
+};
+// True: the solve has stopped.
+__device__ __forceinline__ bool stop_test(const StopTest &T, const int *done) {
+  if (!T.n) return done && *done;
+  double tot;
+  if (!fold_total(T.S, T.partials, T.n, tot)) return true;
+  const bool stop = !(tot < INFINITY) || tot <= T.S->tol2;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    finish_iteration(T.S, T.hist, tot);
+    if (stop && T.host_done)
+      __hip_atomic_store(T.host_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+  return stop;
+}
+
 // First half-sweep of a level from a zero iterate (the finest level; levels in
 // correction form; the transposed cycle's first visits): every neighbour, ghost
 // and wall value is 0, so u = b / c on the active
@@ -1032,8 +1099,8 @@ __device__ __forceinline__ void first_sweep_brick(const LevelView<V, CL, CI, CP>
 // against 6.3 + 4.6.
 template <class V, class CL, class CI, int CP = kCpolDefault>
 __global__ void __launch_bounds__(kBlock) k_first_sweep(LevelArgs<V, CL, CI> A, int colour,
-                                                        int clear) {
-  if (A.done && *A.done) return;
+                                                        int clear, StopTest T) {
+  if (stop_test(T, A.done)) return;
   const LaneC<V, CL> L = lane_consts<V, CL>();
   const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
   const WaveLoop W = wave_loop(A.R.n());
@@ -1705,6 +1772,7 @@ struct TileArgs {
   int sub;          // kTileUp: the parents' u* is taken off
   V scale, pscale;  // of the restricted residual, of the parents' iterate
   const int *done;
+  StopTest stop;    // kTileZero
 };
 
 template <class V, int MODE>
@@ -1712,7 +1780,11 @@ template <class V, int MODE>
 // zero does not fit them and gained nothing there: 8.0 us at 32^3)
 __global__ void __launch_bounds__(kBottomThreads<V>, sizeof(V) == 4 && MODE != kTileZero ? 8 : 2)
     k_tile(TileArgs<V> A) {
-  if (A.done && *A.done) return;
+  if constexpr (MODE == kTileZero) {
+    if (stop_test(A.stop, A.done)) return;
+  } else {
+    if (A.done && *A.done) return;
+  }
   constexpr int kSlots = kBottomPairs / kBottomThreads<V>;
   constexpr uint32_t nt = uint32_t(kBottomThreads<V>);
   constexpr uint32_t np = uint32_t(kBottomPairs);

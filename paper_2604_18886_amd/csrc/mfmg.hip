@@ -1299,6 +1299,7 @@ struct Cycle {
   V *U, *B, *Ust;
   const int *done;
   hipStream_t s;
+  StopTest stop{};  // taken by the first kernel (takes_stop_test)
   // Policy of a streamed level's single-use loads.  FP32 cycle: only the
   // coefficients stream, so the finest level's iterate, right-hand side and
   // plus-face table stay in the Infinity Cache between half-sweeps (large
@@ -1366,10 +1367,10 @@ struct Cycle {
         if (zero && it == 0 && c == 0) {
           if (stream(l))
             hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A,
-                               colour, int(l == h->L));
+                               colour, int(l == h->L), l == h->L ? stop : StopTest{});
           else
             hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour,
-                               int(l == h->L));
+                               int(l == h->L), l == h->L ? stop : StopTest{});
         } else if (form && it == 0 && c == 0) {
           if (stream(l))
             hipLaunchKernelGGL((k_smooth_fas<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A,
@@ -1411,7 +1412,8 @@ struct Cycle {
     const size_t cells = size_t(1) << (3 * l);
     return TileArgs<V>{h->tile_tab[l].p, U, B, Ust, w + size_t(which) * cells,
                        own_rhs ? w + cells : nullptr, h->co->dt->nlb, l, 0, 0,
-                       int(which || h->corr_lv[size_t(l - 1)]), int(sub), scale, pscale, done};
+                       int(which || h->corr_lv[size_t(l - 1)]), int(sub), scale, pscale, done,
+                       l == h->L ? stop : StopTest{}};
   }
   template <int MODE>
   void tile(TileArgs<V> A, int nu, bool form = false) const {
@@ -1505,9 +1507,24 @@ Cycle<double, double, double> cycle64(const mfmg_hierarchy *h, hipStream_t s, co
           h->U64.p, h->B64.p, h->S64.p, done, s};
 }
 
-void run_cycle(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
-  if (h->prm.precision == MFMG_MIXED) cycle32(h, s, done).run();
-  else cycle64(h, s, done).run();
+// The cycle's first kernel (its transpose's: trans) starts the finest level
+// from zero, and so can take the stop test.
+bool takes_stop_test(const mfmg_hierarchy *h, bool trans) {
+  const Range &R = h->co->dt->range[h->L];
+  return h->L > h->lc && R.n_inner == 0 && R.leaf_lo == 0 &&
+         (trans ? h->prm.nu_post : h->prm.nu_pre) > 0;
+}
+
+void run_cycle(const mfmg_hierarchy *h, hipStream_t s, const int *done, StopTest stop = {}) {
+  if (h->prm.precision == MFMG_MIXED) {
+    auto c = cycle32(h, s, done);
+    c.stop = stop;
+    c.run();
+  } else {
+    auto c = cycle64(h, s, done);
+    c.stop = stop;
+    c.run();
+  }
 }
 
 // k_bottom's tables of the levels lc + 1 and lc, k_tile's of its levels.
@@ -1543,12 +1560,13 @@ struct CycleT {
   V *Y, *G, *Sb, *Cpl;
   const int *done;
   hipStream_t s;
+  StopTest stop{};
   static constexpr int kCpolLevel = Cycle<V, CL, CI>::kCpolLevel;
 
   LevelArgs<V, CL, CI> args(int l) const {
     return forward().args(l, false);
   }
-  Cycle<V, CL, CI> forward() const { return {h, leafc, innerc, pf, Y, G, Sb, done, s}; }
+  Cycle<V, CL, CI> forward() const { return {h, leafc, innerc, pf, Y, G, Sb, done, s, stop}; }
   bool stream(int l) const { return h->stream_lv[size_t(l)]; }
   template <int PR>
   void half_sweep(int l, const LevelArgs<V, CL, CI> &A, int colour) const {
@@ -1573,9 +1591,10 @@ struct CycleT {
       if (zero && k == 0) {
         if (stream(l))
           hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, colour,
-                             0);
+                             0, l == h->L ? stop : StopTest{});
         else
-          hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour, 0);
+          hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour, 0,
+                             l == h->L ? stop : StopTest{});
       } else if (prolong && k == 0) {
         half_sweep<1>(l, A, colour);
       } else if (prolong && k == 1) {
@@ -1713,14 +1732,16 @@ void ensure_transpose(mfmg_hierarchy *h, hipStream_t s) {
 }
 
 // Y = M^T G on the leaves (after ensure_transpose)
-void run_cycle_T(const mfmg_hierarchy *h, hipStream_t s, const int *done) {
+void run_cycle_T(const mfmg_hierarchy *h, hipStream_t s, const int *done, StopTest stop = {}) {
   if (h->prm.precision == MFMG_MIXED) {
     CycleT<float, float, __half> c{h, h->coef32.p, h->coef16.p, h->pf32.p,
-                                   h->T32[0].p, h->T32[1].p, h->T32[2].p, h->T32[3].p, done, s};
+                                   h->T32[0].p, h->T32[1].p, h->T32[2].p, h->T32[3].p, done, s,
+                                   stop};
     c.run();
   } else {
     CycleT<double, double, double> c{h, h->co->coef.p, h->inner64.p, h->pf64.p,
-                                     h->T64[0].p, h->T64[1].p, h->T64[2].p, h->T64[3].p, done, s};
+                                     h->T64[0].p, h->T64[1].p, h->T64[2].p, h->T64[3].p, done, s,
+                                     stop};
     c.run();
   }
 }
@@ -1953,15 +1974,18 @@ struct Krylov {
     return n;
   }
   // parts: of (p, Ap); this kernel's own go behind them, which other
-  // workgroups may still be adding
-  void update(double *r, V *r_low, int defer, unsigned parts) const {
+  // workgroups may still be adding.  later: the cycle can take the stop test
+  // (the result, n = 0 if it was taken here).
+  StopTest update(double *r, V *r_low, int defer, unsigned parts, bool later) const {
     PcgArgs Q = P;
     if (folded(parts)) Q.partials += kMaxReduceBlocks;
     hipLaunchKernelGGL(k_pcg_update<V>, dim3(G), dim3(kBlock), 0, s, P, r, r_low,
                        (const double *)h->Ap.p, defer, n2, folded(parts), Q.partials);
-    if (!defer)
+    StopTest T{P.S, Q.partials, P.hist, P.host_done, later && !defer ? folded(G) : 0u};
+    if (!defer && !T.n)
       hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, s, Q, int64_t(G), int(kFinUpdate),
                          0, 0.0);
+    return T;
   }
   // after the loop: the iterate's last step, if the solve stopped between a
   // residual update and the k_pcg_p that takes it
@@ -1972,9 +1996,10 @@ struct Krylov {
 };
 
 // The preconditioner on the residual copy r_low, or its transpose.
-static void run_precond(const mfmg_hierarchy *h, bool trans, hipStream_t s) {
-  if (trans) run_cycle_T(h, s, &h->S.p->done);
-  else run_cycle(h, s, &h->S.p->done);
+static void run_precond(const mfmg_hierarchy *h, bool trans, hipStream_t s,
+                        StopTest stop = {}) {
+  if (trans) run_cycle_T(h, s, &h->S.p->done, stop);
+  else run_cycle(h, s, &h->S.p->done, stop);
 }
 
 // Loop body of Algorithm 1 (from A p to the next search direction), or of
@@ -1985,9 +2010,9 @@ static void iteration_body(mfmg_hierarchy *h, double *r, V *r_low, V *z, bool nu
   Reduce R(h, s);
   Krylov<V> K(h, s);
   const unsigned parts = K.Ap(trans);
-  K.update(r, r_low, int(null_space), parts);
+  const StopTest stop = K.update(r, r_low, int(null_space), parts, takes_stop_test(h, trans));
   if (null_space) R.shift_mean<V>(r, r_low, std::max(1.0, h->n_active), 1, 0.0);
-  run_precond(h, trans, s);
+  run_precond(h, trans, s, stop);
   K.rz(r, z, 0);
   K.pupdate(z, 0);
 }

@@ -165,30 +165,6 @@ __device__ __forceinline__ void block_partial(double part, double *partials) {
   }
 }
 
-// Small solves: the kernel that uses a reduction adds its n <= kFoldParts
-// partials itself, every workgroup, in k_finish's order (the same bits), and
-// the launch between them goes.  Mixed solves, us, without -> with: 32^3 (128
-// partials) 558 -> 521, 0.15 M leaves (600) 1675 -> 1600, 64^3 (1024, the
-// line) 889 -> 886.  More partials would cost every workgroup what the launch
-// does.  n = 0: k_finish ran.  False: the solve has stopped (one read of the
-// flag per workgroup, as another may set it meanwhile).
-constexpr uint32_t kFoldParts = 1024;
-__device__ __forceinline__ bool fold_total(const PcgArgs &P, uint32_t n, double &tot) {
-  __shared__ double red[kFoldParts / kWave];
-  __shared__ int stop;
-  if (threadIdx.x == 0) stop = P.S->done;
-  const uint32_t chunks = (n + kWave - 1) / kWave;
-  for (uint32_t c = threadIdx.x / kWave; c < chunks; c += kWavesPerBlock) {
-    const uint32_t i = c * kWave + (threadIdx.x & (kWave - 1));
-    const double v = wave_sum(i < n ? P.partials[i] : 0.0);
-    if ((threadIdx.x & (kWave - 1)) == 0) red[c] = v;
-  }
-  __syncthreads();
-  if (stop) return false;
-  tot = 0.0;
-  for (uint32_t c = 0; c < chunks; ++c) tot += red[c];
-  return true;
-}
 // A scalar that must be positive and finite is not: the solve stops.
 __device__ __forceinline__ void break_down(const PcgArgs &P) {
   P.S->status = -5;
@@ -286,7 +262,7 @@ __global__ void __launch_bounds__(kBlock) k_pcg_p(PcgArgs P, const V *z, double 
   double beta = 0.0;
   if (parts) {
     double tot;
-    if (!fold_total(P, parts, tot)) return;
+    if (!fold_total(P.S, P.partials, parts, tot)) return;
     const bool ok = tot > 0.0 && tot < INFINITY;
     const int it = P.S->iters;
     if (ok && !first) beta = tot / P.S->rz[(it - 1) & 1];
@@ -408,20 +384,6 @@ enum FinishOp : int {
   kFinRestart = 8,// ||r||^2 of a restart from the true residual (tolerance kept)
 };
 
-__device__ __forceinline__ void finish_iteration(const PcgArgs &P, double tot) {
-  Scalars *S = P.S;
-  S->xpend = 1;  // the residual update of this iteration is done
-  S->rr = tot;
-  S->iters += 1;
-  P.hist[S->iters] = S->rr0 > 0.0 ? sqrt(tot / S->rr0) : 0.0;
-  if (!(tot < INFINITY)) {
-    S->status = -5;
-    S->done = 1;
-  } else if (tot <= S->tol2) {
-    S->done = 1;
-  }
-}
-
 __device__ __forceinline__ void finish_initial(const PcgArgs &P, double tot, double rtol) {
   Scalars *S = P.S;
   S->rr0 = tot;
@@ -479,7 +441,7 @@ __global__ void __launch_bounds__(1024) k_finish(PcgArgs P, int64_t n, int op, i
       S->rscale = low_scale(P, S->rr);
       break;
     case kFinUpdate:
-      finish_iteration(P, tot);
+      finish_iteration(P.S, P.hist, tot);
       break;
     case kFinTrue:
       S->tr = tot;
@@ -489,7 +451,7 @@ __global__ void __launch_bounds__(1024) k_finish(PcgArgs P, int64_t n, int op, i
       break;
     case kFinShift:
       if (arg == 0) finish_initial(P, tot, rtol);
-      else if (arg == 1) finish_iteration(P, tot);
+      else if (arg == 1) finish_iteration(P.S, P.hist, tot);
       else if (arg == 2) S->tr = tot;
       break;
     case kFinWarm:
@@ -526,7 +488,7 @@ __global__ void __launch_bounds__(kBlock) k_pcg_update(PcgArgs P, double *r, V *
   double alpha, sc;
   if (parts) {
     double tot;
-    if (!fold_total(P, parts, tot)) return;
+    if (!fold_total(P.S, P.partials, parts, tot)) return;
     const bool ok = tot > 0.0 && tot < INFINITY;
     sc = low_scale(P, P.S->rr);
     alpha = P.S->rz[P.S->iters & 1] / tot;
