@@ -1385,9 +1385,16 @@ struct BottomUnits {
   static constexpr int kAll = kCoef + 1;
 };
 
+template <class V>
+__device__ __forceinline__ V diag_of(const V (&k)[6]) {
+  return ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
+}
+
+// tiny: set to 1 when an active cell's diagonal is below FP64's normal range,
+// where bottom_div does not hold (FP64 only).
 template <class V, class CL, class CI>
 __global__ void __launch_bounds__(kBlock) k_bottom_table(LevelArgs<V, CL, CI> A, int f,
-                                                         uint4 *tab) {
+                                                         uint4 *tab, unsigned long long *tiny) {
   const LaneC<V, CL> L = lane_consts<V, CL>();
   const LevelView<V, CL, CI> X = level_view(A);
   const uint32_t i = blockIdx.x * kWavesPerBlock + wave_id();
@@ -1404,6 +1411,9 @@ __global__ void __launch_bounds__(kBlock) k_bottom_table(LevelArgs<V, CL, CI> A,
     V ks = shfl(kown, L.p[2 * a + 1]);
     k[2 * a] = kown;
     k[2 * a + 1] = L.out[2 * a + 1] ? kl : ks;
+  }
+  if constexpr (sizeof(V) == 8) {
+    if (((act_mask(M) >> m) & 1ull) && diag_of(k) < 0x1p-1022) *tiny = 1ull;
   }
   const uint32_t x = uint32_t(M.coord[0] * 4 + dev_cx(m)), y = uint32_t(M.coord[1] * 4 + dev_cy(m)),
                  z = uint32_t(M.coord[2] * 4 + dev_cz(m));
@@ -1440,11 +1450,6 @@ struct BottomPair {
 };
 // stride between the colours' arrays
 __host__ __device__ constexpr uint32_t bottom_stride(uint32_t pairs) { return pairs + 32u; }
-
-template <class V>
-__device__ __forceinline__ V diag_of(const V (&k)[6]) {
-  return ((k[0] + k[1]) + (k[2] + k[3])) + (k[4] + k[5]);
-}
 
 // Coefficients, reciprocal diagonals, element and bits of pair g of a table of
 // `pairs` pairs; e0: the x parity of its colour-0 cell.
@@ -1533,8 +1538,10 @@ __device__ __forceinline__ V bottom_sum(const V *s, const BottomPair<V> &P, cons
   return S;
 }
 // a over the diagonal of the coefficients k, rc its reciprocal (FP32: as
-// div_by; FP64: the quotient by the reciprocal, corrected once, which rounds
-// as the division does).
+// div_by; FP64: the quotient by the reciprocal, corrected once, which agrees
+// with the division to its last bit for finite a and quotients and a diagonal
+// in FP64's normal range; a hierarchy with a smaller one -- the reciprocal of a
+// subnormal number overflows -- keeps the separate kernels, which divide).
 template <class V>
 __device__ __forceinline__ V bottom_div(const V (&k)[6], V rc, V a) {
   if constexpr (sizeof(V) == 4) return a * rc;

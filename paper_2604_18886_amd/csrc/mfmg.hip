@@ -1016,7 +1016,7 @@ extern "C" void mfmg_destroy_coeffs(mfmg_coeffs *co) {
 // --------------------------------------------------------------------------
 // hierarchy
 // --------------------------------------------------------------------------
-static void build_bottom(mfmg_hierarchy *h, hipStream_t s);
+static void build_bottom(mfmg_hierarchy *h, unsigned long long *tiny, hipStream_t s);
 
 extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg_params *prm,
                                             void *stream, mfmg_hierarchy **out) {
@@ -1115,14 +1115,12 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     *h->host_done = 0;
     for (hipEvent_t &e : h->iter_ev)
       HIP_CHECK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    // active leaf count (for the null-space mean)
-    DevBuf<unsigned long long> na;
-    na.alloc(1);
-    HIP_CHECK(hipMemsetAsync(na.p, 0, sizeof(unsigned long long), s));
+    // active leaf count (for the null-space mean); k_bottom_table's flag
+    DevBuf<unsigned long long> counts;
+    counts.alloc(2);
+    HIP_CHECK(hipMemsetAsync(counts.p, 0, 2 * sizeof(unsigned long long), s));
     hipLaunchKernelGGL(k_count_active, dim3(std::min(grid_elems(nlb, 256), 1024u)), dim3(256), 0,
-                       s, (const BrickMeta *)h->meta.p, D.nlb, na.p);
-    unsigned long long na_host = 0;
-    HIP_CHECK(hipMemcpyAsync(&na_host, na.p, sizeof(na_host), hipMemcpyDeviceToHost, s));
+                       s, (const BrickMeta *)h->meta.p, D.nlb, counts.p);
     {
       // bytes one half-sweep of a level touches: iterate and right-hand
       // side, four coefficients' worth of face data, the brick records
@@ -1183,12 +1181,18 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
         h->tile_lv[l] = !(eb && eb[0] == '0') && h->fuse_prolong && few(prm->nu_pre) &&
                         few(prm->nu_post) && l > h->lc + int(h->fuse_bottom) &&
                         D.range[l].n() == (uint32_t(1) << (3 * (l - 2)));
-      build_bottom(h.get(), s);
+      build_bottom(h.get(), counts.p + 1, s);
     }
     HIP_CHECK(hipGetLastError());
+    unsigned long long counted[2] = {0, 0};
+    HIP_CHECK(hipMemcpyAsync(counted, counts.p, sizeof(counted), hipMemcpyDeviceToHost, s));
     HIP_CHECK(hipStreamSynchronize(s));
     quiet.arm();
-    h->n_active = double(na_host);
+    h->n_active = double(counted[0]);
+    if (counted[1]) {  // (bottom_div)
+      h->fuse_bottom = false;
+      std::fill(std::begin(h->tile_lv), std::end(h->tile_lv), false);
+    }
     *out = h.release();
   } catch (const HipError &e) {
     return hip_fail(e);
@@ -1529,12 +1533,13 @@ void run_cycle(const mfmg_hierarchy *h, hipStream_t s, const int *done, StopTest
 
 // k_bottom's tables of the levels lc + 1 and lc, k_tile's of its levels.
 template <class V, class CL, class CI>
-void build_bottom_of(mfmg_hierarchy *h, const Cycle<V, CL, CI> &c, DevBuf<V> *work) {
+void build_bottom_of(mfmg_hierarchy *h, const Cycle<V, CL, CI> &c, DevBuf<V> *work,
+                     unsigned long long *tiny) {
   auto table = [&](int l, DevBuf<uint4> &tab) {
     auto A = c.args(l, false);
     tab.alloc(size_t(BottomUnits<V>::kAll) << (3 * l - 1));
     hipLaunchKernelGGL((k_bottom_table<V, CL, CI>), dim3(grid_for(A.R.n())), dim3(kBlock), 0, c.s,
-                       A, l, tab.p);
+                       A, l, tab.p, tiny);
   };
   if (h->fuse_bottom) {
     table(h->lc, h->bot_c);
@@ -1748,9 +1753,9 @@ void run_cycle_T(const mfmg_hierarchy *h, hipStream_t s, const int *done, StopTe
 
 }  // namespace
 
-static void build_bottom(mfmg_hierarchy *h, hipStream_t s) {
-  if (h->prm.precision == MFMG_MIXED) build_bottom_of(h, cycle32(h, s, nullptr), h->tile_w32);
-  else build_bottom_of(h, cycle64(h, s, nullptr), h->tile_w64);
+static void build_bottom(mfmg_hierarchy *h, unsigned long long *tiny, hipStream_t s) {
+  if (h->prm.precision == MFMG_MIXED) build_bottom_of(h, cycle32(h, s, nullptr), h->tile_w32, tiny);
+  else build_bottom_of(h, cycle64(h, s, nullptr), h->tile_w64, tiny);
 }
 
 namespace {
