@@ -7,7 +7,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <memory>
-#include <list>
 #include <mutex>
 #include <new>
 #include <string>
@@ -15,6 +14,7 @@
 #include <vector>
 
 #include "../../include/mfmg.h"
+#include "device_pool.hpp"
 #include "face_kernels.hpp"
 #include "kernels.hpp"
 #include "octree_kernels.hpp"
@@ -51,84 +51,30 @@ mfmg_status hip_fail(const HipError &e) {
               std::string(e.what) + ": " + hipGetErrorString(e.e));
 }
 
-// Device memory of the library's objects.  hipMalloc and hipFree map, clear
-// and unmap pages: a program that rebuilds its octree and hierarchy every step
-// (4 GB of them at 26.3M leaves) spent most of the rebuild in them (123 ms, of
-// which the kernels are 5; 7.3 ms with this pool).  Freed blocks are kept per
-// device and handed out again by size, which is rounded up by at most an
-// eighth.  At most kPoolBytes are kept (the least recently freed go back to
-// the driver first), a block not asked for within kPoolAge frees goes back
-// too, and everything does when an allocation fails.  A block is put back only
-// after the device has finished its work (as hipFree waited), so any stream
-// and thread may take it.
-class DevicePool {
- public:
-  static size_t rounded(size_t bytes) {
-    size_t step = 512;
-    while (step * 8 < bytes) step *= 2;
-    return (bytes + step - 1) / step * step;
+struct HipMemory {
+  using Status = hipError_t;
+  static hipError_t alloc(size_t bytes, void **out) { return hipMalloc(out, bytes); }
+  static bool out_of_memory(hipError_t e) {
+    if (e != hipErrorOutOfMemory) return false;
+    (void)hipGetLastError();
+    return true;
   }
-  // bytes: a rounded size
-  hipError_t get(size_t bytes, void **out) {
-    {
-      std::lock_guard<std::mutex> lock(mu_);
-      for (auto it = kept_.rbegin(); it != kept_.rend(); ++it)
-        if (it->bytes == bytes) {
-          *out = it->p;
-          held_ -= bytes;
-          kept_.erase(std::next(it).base());
-          return hipSuccess;
-        }
-    }
-    hipError_t e = hipMalloc(out, bytes);
-    if (e == hipErrorOutOfMemory) {
-      (void)hipGetLastError();
-      std::lock_guard<std::mutex> lock(mu_);
-      trim(0, 0);
-      e = hipMalloc(out, bytes);
-    }
-    return e;
+  static void free(void *p) { (void)hipFree(p); }
+  static bool wait() {
+    if (hipDeviceSynchronize() == hipSuccess) return true;
+    (void)hipGetLastError();  // (not the next launch's)
+    return false;
   }
-  void put(void *p, size_t bytes) {
-    std::lock_guard<std::mutex> lock(mu_);
-    try {
-      kept_.push_back(Block{p, bytes, ++frees_});
-    } catch (const std::bad_alloc &) {
-      (void)hipFree(p);
-      return;
-    }
-    held_ += bytes;
-    trim(kPoolBytes, frees_ > kPoolAge ? frees_ - kPoolAge : 0);
-  }
-
- private:
-  static constexpr size_t kPoolBytes = size_t(8) << 30;
-  static constexpr uint64_t kPoolAge = 512;
-  struct Block {
-    void *p;
-    size_t bytes;
-    uint64_t when;
-  };
-  void trim(size_t most, uint64_t oldest) {
-    while (!kept_.empty() && (held_ > most || kept_.front().when < oldest)) {
-      (void)hipFree(kept_.front().p);
-      held_ -= kept_.front().bytes;
-      kept_.pop_front();
-    }
-  }
-  std::mutex mu_;
-  std::list<Block> kept_;  // least recently freed first
-  size_t held_ = 0;
-  uint64_t frees_ = 0;
 };
+using HipPool = DevicePool<HipMemory>;
 
 // The pool of a device.  Never destroyed: the runtime may be gone by the time
 // static objects are, and the driver takes the memory back at exit.
-DevicePool &device_pool(int dev) {
+HipPool &device_pool(int dev) {
   static std::mutex mu;
-  static std::vector<DevicePool *> *pools = new std::vector<DevicePool *>();
+  static std::vector<HipPool *> *pools = new std::vector<HipPool *>();
   std::lock_guard<std::mutex> lock(mu);
-  while (pools->size() <= size_t(dev)) pools->push_back(new DevicePool());
+  while (pools->size() <= size_t(dev)) pools->push_back(new HipPool());
   return *(*pools)[size_t(dev)];
 }
 
@@ -171,7 +117,7 @@ struct DevBuf {
   void alloc(size_t count) {
     release();
     if (count == 0) return;
-    bytes_ = DevicePool::rounded(count * sizeof(T));
+    bytes_ = HipPool::rounded(count * sizeof(T));
     HIP_CHECK(hipGetDevice(&dev_));
     HIP_CHECK(device_pool(dev_).get(bytes_, reinterpret_cast<void **>(&p)));
     n = count;
@@ -188,8 +134,7 @@ struct DevBuf {
   void release() {
     if (!p) return;
     DeviceScope scope(dev_);
-    if (!t_drained) (void)hipDeviceSynchronize();
-    device_pool(dev_).put(p, bytes_);
+    device_pool(dev_).put(p, bytes_, t_drained > 0);
     p = nullptr;
     n = 0;
   }
@@ -556,7 +501,7 @@ static void destroy_drained(T *t, int dev) {
   if (!t) return;
   DeviceScope scope(dev);
   Drained quiet;
-  if (hipDeviceSynchronize() == hipSuccess) quiet.arm();
+  if (device_pool(dev).settle()) quiet.arm();
   delete t;
 }
 

@@ -1,0 +1,82 @@
+// Checks of the device memory pool's decisions on a stand-in device that counts
+// its blocks.  Usage: device_pool_check CASE; exits with 0 when it holds.
+#include <cstdio>
+#include <cstring>
+#include <map>
+#include <set>
+
+#include "device_pool.hpp"
+
+struct Device {
+  using Status = int;  // 0 ok, 1 out of memory
+  static std::map<void *, size_t> live;
+  static size_t used, capacity, next;
+  static bool busy;  // waits are refused
+  static int waits;
+  static int alloc(size_t bytes, void **out) {
+    if (used + bytes > capacity) return 1;
+    *out = reinterpret_cast<void *>(next += 4096);
+    live[*out] = bytes;
+    used += bytes;
+    return 0;
+  }
+  static bool out_of_memory(int e) { return e == 1; }
+  static void free(void *p) {
+    used -= live.at(p);
+    live.erase(p);
+  }
+  static bool wait() {
+    ++waits;
+    return !busy;
+  }
+};
+std::map<void *, size_t> Device::live;
+size_t Device::used = 0, Device::capacity = size_t(1) << 40, Device::next = 0;
+bool Device::busy = false;
+int Device::waits = 0;
+
+using Pool = mfmg::DevicePool<Device>;
+
+#define CHECK(x)                                              \
+  do {                                                        \
+    if (!(x)) {                                               \
+      std::printf("%s:%d: %s\n", __FILE__, __LINE__, #x);     \
+      return 1;                                               \
+    }                                                         \
+  } while (0)
+
+// A block whose work may still be running is handed to nobody, also not by an
+// allocation that finds the device full, until a wait succeeds.
+static int failed_wait() {
+  Pool pool;
+  const size_t n = Pool::rounded(size_t(1) << 20);
+  void *a = nullptr, *b = nullptr, *c = nullptr;
+  CHECK(pool.get(n, &a) == 0);
+  Device::busy = true;
+  pool.put(a, n, false);
+  CHECK(Device::waits == 1);
+  CHECK(pool.get(n, &b) == 0 && b != a);
+  CHECK(Device::live.count(a));
+  Device::capacity = Device::used;
+  CHECK(pool.get(n, &c) == 1 && Device::live.count(a));
+  pool.put(b, n, true);  // its own work has finished: kept at once
+  CHECK(pool.get(n, &c) == 0 && c == b);
+  CHECK(!pool.settle());
+  Device::busy = false;
+  CHECK(pool.get(n, &b) == 0 && !Device::live.count(a));  // full: parked block given back
+  pool.put(b, n, false);
+  CHECK(pool.get(n, &a) == 0 && a == b);  // waited for: kept
+  Device::busy = true;
+  pool.put(a, n, false);
+  Device::busy = false;
+  CHECK(pool.settle());
+  CHECK(pool.get(n, &b) == 0 && b == a);
+  return 0;
+}
+
+int main(int argc, char **argv) {
+  const char *name = argc > 1 ? argv[1] : "";
+  if (!std::strcmp(name, "failed_wait")) return failed_wait();
+  std::printf("unknown case %s\n", name);
+  return 2;
+}
