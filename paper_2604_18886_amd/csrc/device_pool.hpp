@@ -15,7 +15,7 @@ namespace mfmg {
 // its octree and hierarchy every step (4 GB of them at 26.3M leaves) spent most
 // of the rebuild in them (123 ms, of which the kernels are 5; 7.3 ms with this
 // pool).  Freed blocks are kept per device and handed out again by size, which
-// is rounded up by at most a quarter.  At most kMaxBytes are kept (the least
+// is rounded up by less than an eighth.  At most kMaxBytes are kept (the least
 // recently freed go back to the driver first), a block not asked for within
 // kMaxAge frees goes back too, and everything does when an allocation fails.
 //
@@ -34,9 +34,10 @@ class DevicePool {
   static constexpr size_t kMaxBytes = size_t(8) << 30;
   static constexpr uint64_t kMaxAge = 512;
 
+  // A multiple of 512, more than bytes by less than an eighth of it from 4 KiB on.
   static size_t rounded(size_t bytes) {
     size_t step = 512;
-    while (step * 8 < bytes) step *= 2;
+    while (step * 16 < bytes) step *= 2;
     return (bytes + step - 1) / step * step;
   }
 

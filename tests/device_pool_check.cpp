@@ -74,9 +74,29 @@ static int failed_wait() {
   return 0;
 }
 
+// Sizes are rounded up by less than an eighth (by less than 512 bytes below 4
+// KiB), and a larger request never to less.
+static int rounding() {
+  size_t last = 0;
+  for (int k = 0; k < 40; ++k)
+    for (int step = 8; step < 16; ++step)
+      for (int off = -1; off <= 1; ++off) {
+        const size_t n = ((size_t(step) << k) >> 3) + size_t(off);
+        if (n == 0 || n > (size_t(1) << 41)) continue;
+        const size_t r = Pool::rounded(n);
+        CHECK(r >= n && r % 512 == 0);
+        CHECK(n < 4096 ? r - n < 512 : (r - n) * 8 < n);
+        CHECK(Pool::rounded(r) == r);
+        CHECK(off == -1 || r >= last);
+        last = r;
+      }
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const char *name = argc > 1 ? argv[1] : "";
   if (!std::strcmp(name, "failed_wait")) return failed_wait();
+  if (!std::strcmp(name, "rounding")) return rounding();
   std::printf("unknown case %s\n", name);
   return 2;
 }
