@@ -84,6 +84,12 @@ class DevicePool {
     keep(one);
   }
 
+  // as put, but the block goes back to the driver
+  void drop(void *p, size_t bytes, bool drained) {
+    if (drained || Api::wait()) Api::free(p);
+    else put(p, bytes, false);
+  }
+
   // Waits for the device; true if it has finished, and then the blocks parked
   // before the wait are kept.
   bool settle() {

@@ -111,6 +111,8 @@ struct DevBuf {
   T *p = nullptr;
   size_t n = 0;
   DevBuf() = default;
+  // kept: its memory is for the next object (else it goes back to the driver)
+  explicit DevBuf(bool kept) : kept_(kept) {}
   DevBuf(const DevBuf &) = delete;
   DevBuf &operator=(const DevBuf &) = delete;
   ~DevBuf() { release(); }
@@ -131,10 +133,12 @@ struct DevBuf {
  private:
   size_t bytes_ = 0;
   int dev_ = 0;
+  bool kept_ = true;
   void release() {
     if (!p) return;
     DeviceScope scope(dev_);
-    device_pool(dev_).put(p, bytes_, t_drained > 0);
+    if (kept_) device_pool(dev_).put(p, bytes_, t_drained > 0);
+    else device_pool(dev_).drop(p, bytes_, t_drained > 0);
     p = nullptr;
     n = 0;
   }
@@ -2378,7 +2382,7 @@ extern "C" mfmg_status mfmg_profile(mfmg_hierarchy *h, int what, int level, int 
     HIP_CHECK(hipEventCreate(&e0));
     HIP_CHECK(hipEventCreate(&e1));
     bool mixed = h->prm.precision == MFMG_MIXED;
-    DevBuf<char> copy_src, copy_dst;  // 1 GiB each, only for the copy
+    DevBuf<char> copy_src(false), copy_dst(false);  // 1 GiB each, only for the copy
     if (what == MFMG_PROFILE_COPY) {
       copy_src.alloc(kCopyBytes);
       copy_dst.alloc(kCopyBytes);

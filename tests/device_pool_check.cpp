@@ -93,10 +93,28 @@ static int rounding() {
   return 0;
 }
 
+// A dropped block goes back at once, or waits with the parked ones.
+static int dropped() {
+  Pool pool;
+  void *a = nullptr, *b = nullptr;
+  CHECK(pool.get(4096, &a) == 0 && pool.get(4096, &b) == 0);
+  pool.drop(a, 4096, true);
+  CHECK(!Device::live.count(a));
+  Device::busy = true;
+  pool.drop(b, 4096, false);
+  CHECK(Device::live.count(b));
+  CHECK(pool.get(4096, &a) == 0 && a != b);
+  Device::busy = false;
+  pool.drop(a, 4096, false);
+  CHECK(!Device::live.count(a));
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const char *name = argc > 1 ? argv[1] : "";
   if (!std::strcmp(name, "failed_wait")) return failed_wait();
   if (!std::strcmp(name, "rounding")) return rounding();
+  if (!std::strcmp(name, "dropped")) return dropped();
   std::printf("unknown case %s\n", name);
   return 2;
 }

@@ -18,7 +18,7 @@ def checker(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["failed_wait", "rounding"])
+@pytest.mark.parametrize("case", ["failed_wait", "rounding", "dropped"])
 def test_pool(checker, case):
     r = subprocess.run([checker, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
