@@ -25,8 +25,10 @@
  *     pointers are ordinary host memory.  The caller owns every buffer it
  *     passes; the library owns only the objects it returns, which the
  *     matching mfmg_destroy_* call frees.  Their device memory is kept for the
- *     next objects (at most 8 GiB per device; blocks not used again for a
- *     while, and all of them when an allocation fails, go back to the driver).
+ *     next objects (at most 8 GiB per device and at most a quarter of what the
+ *     device then has free; blocks not used again for a while, and all of them
+ *     when an allocation of the library fails or at mfmg_release_memory, go
+ *     back to the driver).
  *   - stream is a hipStream_t (NULL = the default stream).  Every call
  *     enqueues its device work on that stream and returns after the work it
  *     needs has completed; statistics are valid on return.
@@ -61,6 +63,11 @@ typedef struct mfmg_hierarchy mfmg_hierarchy;
 
 /* Thread-local message of the last failing call ("" if none). */
 const char *mfmg_last_error(void);
+
+/* Give the device memory kept from destroyed objects back to the driver, on
+ * every device, for a program's other allocators (one that runs out of memory
+ * can call this and try again).  Waits for the devices that hold any. */
+void mfmg_release_memory(void);
 
 /* ------------------------------------------------------------------ octree
  * Refinement predicates of the paper's grid generator (Section 4.1: a tile

@@ -15,9 +15,13 @@ namespace mfmg {
 // its octree and hierarchy every step (4 GB of them at 26.3M leaves) spent most
 // of the rebuild in them (123 ms, of which the kernels are 5; 7.3 ms with this
 // pool).  Freed blocks are kept per device and handed out again by size, which
-// is rounded up by less than an eighth.  At most kMaxBytes are kept (the least
-// recently freed go back to the driver first), a block not asked for within
-// kMaxAge frees goes back too, and everything does when an allocation fails.
+// is rounded up by less than an eighth.
+//
+// Kept blocks are out of reach of the process's other allocators, so they are
+// bounded: at most kMaxBytes, and at most a quarter of what the device has free
+// besides (the least recently freed go back to the driver first); a block not
+// asked for within kMaxAge frees goes back too, and everything does when an
+// allocation fails or on request (release).
 //
 // A block may be handed to any stream and thread, so it is kept only once the
 // device has finished its work (as hipFree waited).  Where that wait fails (it
@@ -25,8 +29,9 @@ namespace mfmg {
 // running: the block is parked, and kept after a wait that succeeds.
 //
 // Api, all on the current device: Status alloc(bytes, void **), bool
-// out_of_memory(Status) (which also clears the error), void free(void *), bool
-// wait() (for everything queued; false: it may still run).
+// out_of_memory(Status) (which also clears the error), bool free(void *) (false:
+// refused, the block stays), bool wait() (for everything queued; false: it may
+// still run), bool available(size_t *) (free bytes of the device).
 template <class Api>
 class DevicePool {
  public:
@@ -69,7 +74,7 @@ class DevicePool {
     try {
       one.push_back(Block{p, bytes, 0});
     } catch (const std::bad_alloc &) {
-      if (drained || Api::wait()) Api::free(p);
+      if (drained || Api::wait()) (void)Api::free(p);
       return;
     }
     if (!drained) {
@@ -86,8 +91,29 @@ class DevicePool {
 
   // as put, but the block goes back to the driver
   void drop(void *p, size_t bytes, bool drained) {
-    if (drained || Api::wait()) Api::free(p);
-    else put(p, bytes, false);
+    if (!(drained || Api::wait()) || !Api::free(p)) put(p, bytes, false);
+  }
+
+  // Takes the bound on kept blocks from what the device has free now (a few
+  // microseconds, so once per destroyed object and not per block).
+  void rebound() {
+    size_t n = 0;
+    if (!Api::available(&n)) return;
+    std::lock_guard<std::mutex> lock(mu_);
+    most_ = n / 4 < kMaxBytes ? n / 4 : kMaxBytes;
+    trim(most_, 0);
+  }
+
+  // Gives every kept block back to the driver.
+  void release() {
+    bool late = false;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      late = !parked_.empty();
+    }
+    if (late) settle();
+    std::lock_guard<std::mutex> lock(mu_);
+    trim(0, 0);
   }
 
   // Waits for the device; true if it has finished, and then the blocks parked
@@ -117,11 +143,11 @@ class DevicePool {
       held_ += b.bytes;
     }
     kept_.splice(kept_.end(), blocks);
-    trim(kMaxBytes, frees_ > kMaxAge ? frees_ - kMaxAge : 0);
+    trim(most_, frees_ > kMaxAge ? frees_ - kMaxAge : 0);
   }
   void trim(size_t most, uint64_t oldest) {
     while (!kept_.empty() && (held_ > most || kept_.front().when < oldest)) {
-      Api::free(kept_.front().p);
+      if (!Api::free(kept_.front().p)) return;
       held_ -= kept_.front().bytes;
       kept_.pop_front();
     }
@@ -130,6 +156,7 @@ class DevicePool {
   std::list<Block> kept_;    // least recently freed first
   std::list<Block> parked_;  // freed, their work not known to have finished
   size_t held_ = 0;          // bytes in kept_
+  size_t most_ = kMaxBytes;  // and their bound
   uint64_t frees_ = 0;
 };
 

@@ -59,23 +59,41 @@ struct HipMemory {
     (void)hipGetLastError();
     return true;
   }
-  static void free(void *p) { (void)hipFree(p); }
-  static bool wait() {
-    if (hipDeviceSynchronize() == hipSuccess) return true;
-    (void)hipGetLastError();  // (not the next launch's)
-    return false;
+  static bool free(void *p) { return ok(hipFree(p)); }
+  static bool wait() { return ok(hipDeviceSynchronize()); }
+  static bool available(size_t *bytes) {
+    size_t total = 0;
+    return ok(hipMemGetInfo(bytes, &total));
+  }
+
+ private:
+  static bool ok(hipError_t e) {
+    if (e != hipSuccess) (void)hipGetLastError();  // (not the next launch's)
+    return e == hipSuccess;
   }
 };
 using HipPool = DevicePool<HipMemory>;
 
-// The pool of a device.  Never destroyed: the runtime may be gone by the time
-// static objects are, and the driver takes the memory back at exit.
+// One pool per device, made at its first use.  Never destroyed: the runtime may
+// be gone by the time static objects are, and the driver takes the memory back
+// at exit.
+struct Pools {
+  std::mutex mu;
+  std::vector<HipPool *> of;
+};
+Pools &pools() {
+  static Pools *p = new Pools();
+  return *p;
+}
 HipPool &device_pool(int dev) {
-  static std::mutex mu;
-  static std::vector<HipPool *> *pools = new std::vector<HipPool *>();
-  std::lock_guard<std::mutex> lock(mu);
-  while (pools->size() <= size_t(dev)) pools->push_back(new HipPool());
-  return *(*pools)[size_t(dev)];
+  Pools &P = pools();
+  std::lock_guard<std::mutex> lock(P.mu);
+  while (P.of.size() <= size_t(dev)) {
+    std::unique_ptr<HipPool> one(new HipPool());
+    P.of.push_back(one.get());
+    one.release();
+  }
+  return *P.of[size_t(dev)];
 }
 
 // While one is alive and armed, the buffers that this thread frees are known
@@ -505,8 +523,24 @@ static void destroy_drained(T *t, int dev) {
   if (!t) return;
   DeviceScope scope(dev);
   Drained quiet;
-  if (device_pool(dev).settle()) quiet.arm();
+  HipPool &pool = device_pool(dev);
+  if (pool.settle()) quiet.arm();
+  pool.rebound();
   delete t;
+}
+
+extern "C" void mfmg_release_memory(void) {
+  Pools &P = pools();
+  for (size_t dev = 0;; ++dev) {
+    HipPool *pool = nullptr;
+    {
+      std::lock_guard<std::mutex> lock(P.mu);
+      if (dev >= P.of.size()) return;
+      pool = P.of[dev];
+    }
+    DeviceScope scope{int(dev)};
+    pool->release();
+  }
 }
 
 extern "C" void mfmg_destroy_octree(mfmg_octree *t) {

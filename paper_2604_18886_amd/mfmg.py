@@ -76,6 +76,7 @@ _I64P = ctypes.POINTER(ctypes.c_int64)
 # exported symbol -> (restype, argtypes); every symbol of include/mfmg.h
 SIGNATURES = {
     "mfmg_last_error": (ctypes.c_char_p, []),
+    "mfmg_release_memory": (None, []),
     "mfmg_build_octree": (ctypes.c_int, [ctypes.POINTER(_Spec), ctypes.POINTER(_VP)]),
     "mfmg_build_octree_device": (ctypes.c_int, [ctypes.POINTER(_Spec), _VP,
                                                 ctypes.POINTER(_VP)]),
@@ -149,6 +150,22 @@ def _torch():
     return torch
 
 
+def release_memory():
+    """Give the device memory that the library keeps from destroyed objects
+    back to the driver (for torch or other allocators)."""
+    load_library().mfmg_release_memory()
+
+
+def _new(make, *args, **kw):
+    """make(*args, **kw), a torch allocation; when the device is full, once
+    more without the memory that the library keeps."""
+    try:
+        return make(*args, **kw)
+    except _torch().cuda.OutOfMemoryError:
+        release_memory()
+    return make(*args, **kw)
+
+
 def _stream():
     torch = _torch()
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
@@ -210,8 +227,8 @@ class Octree:
     def leaves_device(self):
         """leaves() as device tensors, written on the current stream."""
         torch = _torch()
-        lev = torch.empty(max(1, self.n_leaves), dtype=torch.uint8, device="cuda")
-        ijk = torch.empty((max(1, self.n_leaves), 3), dtype=torch.int32, device="cuda")
+        lev = _new(torch.empty, max(1, self.n_leaves), dtype=torch.uint8, device="cuda")
+        ijk = _new(torch.empty, (max(1, self.n_leaves), 3), dtype=torch.int32, device="cuda")
         _check(_lib.mfmg_octree_leaves_device(self._h, _ptr(lev), _ptr(ijk), _stream()))
         return lev[:self.n_leaves], ijk[:self.n_leaves]
 
@@ -219,10 +236,10 @@ class Octree:
         """faces() as device tensors, written on the current stream."""
         torch = _torch()
         n = max(1, self.n_faces)
-        owner = torch.empty(n, dtype=torch.int64, device="cuda")
-        d = torch.empty(n, dtype=torch.int8, device="cuda")
-        other = torch.empty(n, dtype=torch.int64, device="cuda")
-        kind = torch.empty(n, dtype=torch.int8, device="cuda")
+        owner = _new(torch.empty, n, dtype=torch.int64, device="cuda")
+        d = _new(torch.empty, n, dtype=torch.int8, device="cuda")
+        other = _new(torch.empty, n, dtype=torch.int64, device="cuda")
+        kind = _new(torch.empty, n, dtype=torch.int8, device="cuda")
         _check(_lib.mfmg_octree_faces_device(self._h, _ptr(owner), _ptr(d), _ptr(other),
                                              _ptr(kind), _stream()))
         k = self.n_faces
@@ -270,7 +287,7 @@ class Coeffs:
     def leaf_coeffs(self):
         """Device tensor (4, n_leaves): c, kx, ky, kz."""
         torch = _torch()
-        out = torch.empty((4, self.tree.n_leaves), dtype=torch.float64, device="cuda")
+        out = _new(torch.empty, (4, self.tree.n_leaves), dtype=torch.float64, device="cuda")
         _check(_lib.mfmg_coeffs_leaf(self._h, _ptr(out), _stream()))
         return out
 
@@ -316,7 +333,7 @@ class Hierarchy:
         """Device tensor (n_bricks, 4, 64) of FP64 level coefficients."""
         torch = _torch()
         coords, _ = self.level_bricks(level)
-        out = torch.empty((len(coords), 4, 64), dtype=torch.float64, device="cuda")
+        out = _new(torch.empty, (len(coords), 4, 64), dtype=torch.float64, device="cuda")
         _check(_lib.mfmg_hierarchy_level_coeffs(self._h, level, _ptr(out), _stream()))
         return out
 
@@ -341,7 +358,7 @@ def pcg_solve(h, rhs, p=None, rtol=1e-10, max_iter=200, null_space=-1, history=F
     torch = _torch()
     n = h.n_leaves
     if p is None:
-        p = torch.empty_like(rhs)
+        p = _new(torch.empty_like, rhs)
     if x0 is not None:
         p.copy_(x0)
     sp = _SolveParams(float(rtol), int(max_iter), int(null_space), int(x0 is not None))
@@ -361,8 +378,8 @@ def pcg_solve(h, rhs, p=None, rtol=1e-10, max_iter=200, null_space=-1, history=F
 def pcg_solve_adjoint(h, p, dL_dp, rtol=1e-10, max_iter=200, null_space=-1):
     """lambda with A^T lambda = dL/dp and dL/dbeta per face."""
     torch = _torch()
-    lam = torch.empty_like(dL_dp)
-    g = torch.empty(h.coeffs.tree.n_faces, dtype=torch.float64, device=dL_dp.device)
+    lam = _new(torch.empty_like, dL_dp)
+    g = _new(torch.empty, h.coeffs.tree.n_faces, dtype=torch.float64, device=dL_dp.device)
     sp = _SolveParams(float(rtol), int(max_iter), int(null_space), 0)
     st = SolveStats()
     n = h.n_leaves
@@ -380,7 +397,7 @@ def divergence(h, beta, u):
     torch = _torch()
     nf = h.coeffs.tree.n_faces
     pb, pu = _vec(beta, nf, "beta"), _vec(u, nf, "u")
-    div = torch.empty(h.n_leaves, dtype=torch.float64, device="cuda")
+    div = _new(torch.empty, h.n_leaves, dtype=torch.float64, device="cuda")
     _check(_lib.mfmg_divergence(h._h, pb, pu, _ptr(div), _stream()))
     return div
 
@@ -406,7 +423,7 @@ def divergence_rms_noalloc(h, div, out=None):
     double (out, allocated here when None), queued on the current stream."""
     torch = _torch()
     if out is None:
-        out = torch.empty(1, dtype=torch.float64, device=div.device)
+        out = _new(torch.empty, 1, dtype=torch.float64, device=div.device)
     _check(_lib.mfmg_divergence_rms_noalloc(h._h, _vec(div, h.n_leaves, "div"),
                                             _vec(out, 1, "out"), _stream()))
     return out
@@ -426,7 +443,7 @@ def project(h, beta, u, rtol=1e-10, max_iter=200):
 
 def apply_operator(h, x, transpose=False):
     torch = _torch()
-    y = torch.empty_like(x)
+    y = _new(torch.empty_like, x)
     _check(_lib.mfmg_apply_operator(h._h, _vec(x, h.n_leaves, "x"), _ptr(y), int(transpose),
                                     _stream()))
     return y
@@ -434,7 +451,7 @@ def apply_operator(h, x, transpose=False):
 
 def apply_precond(h, r, transpose=False):
     torch = _torch()
-    z = torch.empty_like(r)
+    z = _new(torch.empty_like, r)
     _check(_lib.mfmg_apply_precond(h._h, _vec(r, h.n_leaves, "r"), _ptr(z), int(transpose),
                                    _stream()))
     return z

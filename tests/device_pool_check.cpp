@@ -3,7 +3,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
-#include <set>
+#include <vector>
 
 #include "device_pool.hpp"
 
@@ -11,7 +11,7 @@ struct Device {
   using Status = int;  // 0 ok, 1 out of memory
   static std::map<void *, size_t> live;
   static size_t used, capacity, next;
-  static bool busy;  // waits are refused
+  static bool busy;  // waits and frees are refused
   static int waits;
   static int alloc(size_t bytes, void **out) {
     if (used + bytes > capacity) return 1;
@@ -21,9 +21,15 @@ struct Device {
     return 0;
   }
   static bool out_of_memory(int e) { return e == 1; }
-  static void free(void *p) {
+  static bool free(void *p) {
+    if (busy) return false;
     used -= live.at(p);
     live.erase(p);
+    return true;
+  }
+  static bool available(size_t *bytes) {
+    *bytes = capacity - used;
+    return true;
   }
   static bool wait() {
     ++waits;
@@ -110,11 +116,87 @@ static int dropped() {
   return 0;
 }
 
+constexpr size_t kMiB = size_t(1) << 20;
+
+// Fills a pool with n kept blocks of the given size.
+static int fill(Pool &pool, int n, size_t bytes, std::vector<void *> &p) {
+  p.assign(size_t(n), nullptr);
+  for (void *&q : p) CHECK(pool.get(bytes, &q) == 0);
+  for (void *q : p) pool.put(q, bytes, true);
+  return 0;
+}
+
+// At most kMaxBytes are kept; the least recently freed blocks go first.
+static int most_kept() {
+  Pool pool;
+  std::vector<void *> p;
+  CHECK(fill(pool, 40, 512 * kMiB, p) == 0);
+  CHECK(Device::used == Pool::kMaxBytes);
+  for (int i = 0; i < 40; ++i) CHECK(Device::live.count(p[size_t(i)]) == (i >= 24));
+  return 0;
+}
+
+// A block not asked for within kMaxAge frees goes back.
+static int ageing() {
+  Pool pool;
+  void *old = nullptr, *b = nullptr;
+  CHECK(pool.get(2 * kMiB, &old) == 0);
+  pool.put(old, 2 * kMiB, true);
+  for (uint64_t i = 0; i < Pool::kMaxAge; ++i) {
+    CHECK(Device::live.count(old));
+    CHECK(pool.get(kMiB, &b) == 0);
+    pool.put(b, kMiB, true);
+  }
+  CHECK(pool.get(kMiB, &b) == 0);
+  pool.put(b, kMiB, true);
+  CHECK(!Device::live.count(old) && Device::live.count(b));
+  return 0;
+}
+
+// An allocation that finds the device full gets what is kept.
+static int full_device() {
+  Pool pool;
+  std::vector<void *> p;
+  Device::capacity = 8 * kMiB;
+  CHECK(fill(pool, 8, kMiB, p) == 0);
+  void *q = nullptr;
+  CHECK(pool.get(8 * kMiB, &q) == 0);
+  CHECK(pool.get(kMiB, &q) == 1);
+  return 0;
+}
+
+// Others can have what is kept: at most a quarter of the free memory stays, and
+// nothing after release (blocks whose free is refused stay kept).
+static int given_back() {
+  Pool pool;
+  std::vector<void *> p;
+  Device::capacity = 100 * kMiB;
+  CHECK(fill(pool, 60, kMiB, p) == 0);
+  pool.rebound();  // 40 MiB free: a quarter is 10 MiB
+  CHECK(Device::used == 10 * kMiB);
+  CHECK(fill(pool, 20, kMiB, p) == 0);
+  CHECK(Device::used == 10 * kMiB);
+  Device::busy = true;
+  pool.release();
+  CHECK(Device::used == 10 * kMiB);
+  void *q = nullptr;
+  CHECK(pool.get(kMiB, &q) == 0 && Device::used == 10 * kMiB);
+  pool.put(q, kMiB, false);  // parked
+  Device::busy = false;
+  pool.release();
+  CHECK(Device::used == 0);
+  return 0;
+}
+
 int main(int argc, char **argv) {
   const char *name = argc > 1 ? argv[1] : "";
   if (!std::strcmp(name, "failed_wait")) return failed_wait();
   if (!std::strcmp(name, "rounding")) return rounding();
   if (!std::strcmp(name, "dropped")) return dropped();
+  if (!std::strcmp(name, "most_kept")) return most_kept();
+  if (!std::strcmp(name, "ageing")) return ageing();
+  if (!std::strcmp(name, "full_device")) return full_device();
+  if (!std::strcmp(name, "given_back")) return given_back();
   std::printf("unknown case %s\n", name);
   return 2;
 }
