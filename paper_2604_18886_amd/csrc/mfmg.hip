@@ -896,6 +896,8 @@ static mfmg_status leaves_from_device(const mfmg_octree *t, uint8_t *level, int3
     HIP_CHECK(hipStreamSynchronize(s));
   } catch (const HipError &e) {
     return hip_fail(e);
+  } catch (const std::bad_alloc &) {
+    return fail(MFMG_ERR_OOM, "host allocation failed");
   }
   return MFMG_OK;
 }
@@ -921,6 +923,8 @@ static mfmg_status faces_from_device(const mfmg_octree *t, int64_t *owner, int8_
     HIP_CHECK(hipStreamSynchronize(s));
   } catch (const HipError &e) {
     return hip_fail(e);
+  } catch (const std::bad_alloc &) {
+    return fail(MFMG_ERR_OOM, "host allocation failed");
   }
   return MFMG_OK;
 }
@@ -988,6 +992,8 @@ extern "C" mfmg_status mfmg_coeffs_leaf(const mfmg_coeffs *co, double *out, void
     HIP_CHECK(hipStreamSynchronize(s));
   } catch (const HipError &e) {
     return hip_fail(e);
+  } catch (const std::bad_alloc &) {
+    return fail(MFMG_ERR_OOM, "host allocation failed");
   }
   return MFMG_OK;
 }
@@ -1784,6 +1790,8 @@ extern "C" mfmg_status mfmg_apply_operator(mfmg_hierarchy *h, const double *x, d
     HIP_CHECK(hipStreamSynchronize(s));
   } catch (const HipError &e) {
     return hip_fail(e);
+  } catch (const std::bad_alloc &) {
+    return fail(MFMG_ERR_OOM, "host allocation failed");
   }
   return MFMG_OK;
 }
@@ -1825,6 +1833,8 @@ extern "C" mfmg_status mfmg_apply_precond(mfmg_hierarchy *h, const double *r, do
     HIP_CHECK(hipStreamSynchronize(s));
   } catch (const HipError &e) {
     return hip_fail(e);
+  } catch (const std::bad_alloc &) {
+    return fail(MFMG_ERR_OOM, "host allocation failed");
   }
   return MFMG_OK;
 }
@@ -2209,6 +2219,8 @@ extern "C" mfmg_status mfmg_pcg_solve(mfmg_hierarchy *h, const double *rhs, doub
                           hipMemcpyDeviceToHost));
   } catch (const HipError &e) {
     return hip_fail(e);
+  } catch (const std::bad_alloc &) {
+    return fail(MFMG_ERR_OOM, "host allocation failed");
   }
   if (st == MFMG_ERR_BREAKDOWN) return fail(st, "PCG breakdown: (r,z) or (p,Ap) not positive");
   if (st == MFMG_NOT_CONVERGED)
@@ -2455,6 +2467,8 @@ extern "C" mfmg_status mfmg_profile(mfmg_hierarchy *h, int what, int level, int 
                                                        : 2.0 * double(kCopyBytes);
   } catch (const HipError &e) {
     return fail(MFMG_ERR_HIP, std::string(e.what) + ": " + hipGetErrorString(e.e));
+  } catch (const std::bad_alloc &) {
+    return fail(MFMG_ERR_OOM, "host allocation failed");
   }
   return MFMG_OK;
 }
@@ -2481,6 +2495,8 @@ extern "C" mfmg_status mfmg_divergence(mfmg_hierarchy *h, const double *face_bet
     HIP_CHECK(hipGetLastError());
   } catch (const HipError &e) {
     return hip_fail(e);
+  } catch (const std::bad_alloc &) {
+    return fail(MFMG_ERR_OOM, "host allocation failed");
   }
   return MFMG_OK;
 }
@@ -2586,6 +2602,8 @@ extern "C" mfmg_status mfmg_divergence_rms(mfmg_hierarchy *h, const double *div,
     HIP_CHECK(hipStreamSynchronize(s));
   } catch (const HipError &e) {
     return hip_fail(e);
+  } catch (const std::bad_alloc &) {
+    return fail(MFMG_ERR_OOM, "host allocation failed");
   }
   return MFMG_OK;
 }
