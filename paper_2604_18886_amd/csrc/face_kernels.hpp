@@ -33,16 +33,10 @@ constexpr uint64_t face_cells(int d) {
 // minus faces.
 constexpr uint32_t kFlagIrregular = 0x2au | (0x15u << 8) | (0x2au << 16);
 
-// Cells of a leaf brick that own their face d, from the brick's flags.
-__device__ __forceinline__ uint64_t owned_cells(uint32_t flags, int d) {
-  if (d & 1) return ((flags >> d) | (flags >> (16 + d))) & 1u ? face_cells(d) : 0ull;
-  return (flags >> (8 + d)) & 1u ? ~face_cells(d) : ~0ull;
-}
-
 // Lane constants for finding a cell's faces without counting bits per brick:
 // a brick's faces before cell m are 3 m, less the face cells before m on each
 // minus face towards finer leaves, plus those on each plus face at a wall or
-// coarser leaf.  These counts (at most 15) are packed, 5 bits per face.
+// coarser leaf.  These counts (at most 16) are packed, 5 bits per face.
 struct FaceLane {
   int m;
   uint32_t out;      // bit d: the cell lies on the brick's face d
@@ -110,6 +104,7 @@ __device__ __forceinline__ bool owns_face(uint32_t flags, uint32_t out, int d) {
 // Number of the brick's faces (at most kBrickFaces).
 constexpr uint32_t kBrickFaces = 240;
 constexpr uint32_t kFaceSlots = 256;  // LDS slots per wave: four full-wave accesses
+static_assert(kBrickFaces <= kFaceSlots, "a brick's faces fit their slots");
 __device__ __forceinline__ uint32_t face_total(uint32_t flags) {
   uint32_t n = 192u;
 #pragma unroll

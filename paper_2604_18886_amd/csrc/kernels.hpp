@@ -195,7 +195,7 @@ struct CoefPair {
 // leaves: 1070 us for the three, 310 us in this pass).  The sums run in the children's
 // order, one lane per parent cell and component, over values handed through
 // LDS.
-__global__ void __launch_bounds__(kBlock) k_coarsen(Range R, Topo T, BrickMeta *meta, CoefPair K,
+__global__ void __launch_bounds__(kBlock) k_coarsen(Range R, BrickMeta *meta, CoefPair K,
                                                     double alpha, float *c32, __half *c16) {
   __shared__ double lds[kWavesPerBlock][7][64];
   const uint32_t w = wave_id();

@@ -1070,7 +1070,7 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     for (int l = T.max_level; l >= kMinLevel; --l) {
       const Range &R = D.range[l];
       if (R.n() == 0) continue;
-      hipLaunchKernelGGL(k_coarsen, dim3(grid_for(R.n())), dim3(kBlock), 0, s, R, topo, h->meta.p,
+      hipLaunchKernelGGL(k_coarsen, dim3(grid_for(R.n())), dim3(kBlock), 0, s, R, h->meta.p,
                          K, prm->alpha, h->coef32.p, h->coef16.p);
     }
     HIP_CHECK(hipGetLastError());
