@@ -1065,15 +1065,17 @@ __device__ __forceinline__ bool stop_test(const StopTest &T, const int *done) {
 // First half-sweep of a level from a zero iterate (the finest level; levels in
 // correction form; the transposed cycle's first visits): every neighbour, ghost
 // and wall value is 0, so u = b / c on the active
-// cells of the colour, 0 on all others.  On inner bricks the diagonal is the
-// sum of the six face coefficients, as in every half-sweep (the stored FP16
-// diagonal is rounded on its own).  It also clears the iterate.
+// cells of the colour, 0 on all others.  The diagonal is the sum of the six face
+// coefficients, as in every half-sweep.  A leaf's stored one is that sum (and a
+// third of the reads), except next to an inner brick: that face's coefficient is
+// Algorithm 3's (half the fine sub-faces' sum for alpha = 2 only, in FP16 in the
+// mixed cycle).  It also clears the iterate.
 template <bool INNER, class V, class CL, class CI, int CP>
 __device__ __forceinline__ void first_sweep_brick(const LevelView<V, CL, CI, CP> &X,
                                              const LaneC<V, CL> &L, uint32_t b, int colour) {
   const BrickMeta M = load_meta(X.meta, b);
   bool act = (act_mask(M) >> L.m) & 1ull;
-  if constexpr (!INNER) {  // leaves store it unrounded
+  if (!INNER && !(M.flags & kFlagInner)) {
     V c = own_coef<false>(X, b, 0, L.m);
     V g = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
     bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(g, c) : V(0));
