@@ -18,8 +18,8 @@ namespace mfmg {
 // is rounded up by less than an eighth.
 //
 // Kept blocks are out of reach of the process's other allocators, so they are
-// bounded: at most kMaxBytes, and at most a quarter of what the device has free
-// besides (the least recently freed go back to the driver first); a block not
+// bounded: at most kMaxBytes, and beyond kMuch at most a quarter of what the
+// device has free besides (the least recently freed go back to the driver first); a block not
 // asked for within kMaxAge frees goes back too, and everything does when an
 // allocation fails or on request (release).
 //
@@ -38,6 +38,7 @@ class DevicePool {
   using Status = typename Api::Status;
   static constexpr size_t kMaxBytes = size_t(8) << 30;
   static constexpr uint64_t kMaxAge = 512;
+  static constexpr size_t kMuch = size_t(64) << 20;
 
   // A multiple of 512, more than bytes by less than an eighth of it from 4 KiB on.
   static size_t rounded(size_t bytes) {
@@ -94,9 +95,14 @@ class DevicePool {
     if (!(drained || Api::wait()) || !Api::free(p)) put(p, bytes, false);
   }
 
-  // Takes the bound on kept blocks from what the device has free now (a few
-  // microseconds, so once per destroyed object and not per block).
+  // Takes the bound on kept blocks from what the device has free now.  Asking
+  // takes some 10 microseconds (a small object is made and destroyed in 25), so
+  // once per destroyed object, not per block, and only when much is kept.
   void rebound() {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (held_ <= kMuch) return;
+    }
     size_t n = 0;
     if (!Api::available(&n)) return;
     std::lock_guard<std::mutex> lock(mu_);

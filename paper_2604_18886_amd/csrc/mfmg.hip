@@ -522,11 +522,13 @@ template <class T>
 static void destroy_drained(T *t, int dev) {
   if (!t) return;
   DeviceScope scope(dev);
-  Drained quiet;
   HipPool &pool = device_pool(dev);
-  if (pool.settle()) quiet.arm();
+  {
+    Drained quiet;
+    if (pool.settle()) quiet.arm();
+    delete t;
+  }
   pool.rebound();
-  delete t;
 }
 
 extern "C" void mfmg_release_memory(void) {

@@ -12,7 +12,7 @@ struct Device {
   static std::map<void *, size_t> live;
   static size_t used, capacity, next;
   static bool busy;  // waits and frees are refused
-  static int waits;
+  static int waits, asked;
   static int alloc(size_t bytes, void **out) {
     if (used + bytes > capacity) return 1;
     *out = reinterpret_cast<void *>(next += 4096);
@@ -28,6 +28,7 @@ struct Device {
     return true;
   }
   static bool available(size_t *bytes) {
+    ++asked;
     *bytes = capacity - used;
     return true;
   }
@@ -39,7 +40,7 @@ struct Device {
 std::map<void *, size_t> Device::live;
 size_t Device::used = 0, Device::capacity = size_t(1) << 40, Device::next = 0;
 bool Device::busy = false;
-int Device::waits = 0;
+int Device::waits = 0, Device::asked = 0;
 
 using Pool = mfmg::DevicePool<Device>;
 
@@ -165,26 +166,30 @@ static int full_device() {
   return 0;
 }
 
-// Others can have what is kept: at most a quarter of the free memory stays, and
-// nothing after release (blocks whose free is refused stay kept).
+// Others can have what is kept: beyond kMuch at most a quarter of the free
+// memory stays, and nothing after release (blocks whose free is refused do).
 static int given_back() {
   Pool pool;
   std::vector<void *> p;
-  Device::capacity = 100 * kMiB;
-  CHECK(fill(pool, 60, kMiB, p) == 0);
-  pool.rebound();  // 40 MiB free: a quarter is 10 MiB
-  CHECK(Device::used == 10 * kMiB);
-  CHECK(fill(pool, 20, kMiB, p) == 0);
-  CHECK(Device::used == 10 * kMiB);
+  Device::capacity = 4096 * kMiB;
+  CHECK(fill(pool, 60, 32 * kMiB, p) == 0);
+  pool.rebound();  // 2176 MiB free: a quarter is 544 MiB
+  CHECK(Device::used == 544 * kMiB);
+  CHECK(fill(pool, 30, 32 * kMiB, p) == 0);
+  CHECK(Device::used == 544 * kMiB);
   Device::busy = true;
   pool.release();
-  CHECK(Device::used == 10 * kMiB);
+  CHECK(Device::used == 544 * kMiB);
   void *q = nullptr;
-  CHECK(pool.get(kMiB, &q) == 0 && Device::used == 10 * kMiB);
-  pool.put(q, kMiB, false);  // parked
+  CHECK(pool.get(32 * kMiB, &q) == 0 && Device::used == 544 * kMiB);
+  pool.put(q, 32 * kMiB, false);  // parked
   Device::busy = false;
   pool.release();
   CHECK(Device::used == 0);
+  Device::asked = 0;
+  CHECK(fill(pool, 2, 32 * kMiB, p) == 0);
+  pool.rebound();
+  CHECK(Device::asked == 0 && Device::used == Pool::kMuch);
   return 0;
 }
 
