@@ -280,8 +280,15 @@ __global__ void __launch_bounds__(256) k_count_active(const BrickMeta *meta, uin
 // carries that part on the first of them.
 // pf32 (may be null): the mixed cycle's copy, with the rounding of an inner
 // neighbour's store.
+// The composite operator reads the same entries on leaf bricks (pfa), except
+// next to an inner brick: the coarse side of a T-junction carries the fine
+// sub-face coefficients' sum over 2, Algorithm 3's coefficient their sum over
+// alpha, so ratio = alpha / 2 times that.  pfa is pf64 unless an FP64 cycle with
+// another alpha than 2 needs both (pfa: leaf bricks only; pf64 then the
+// cycle's).
 __global__ void __launch_bounds__(kBlock) k_plus_faces(Topo T, CoefPair K, const double *tc,
-                                                       double *pf64, float *pf32) {
+                                                       double *pf64, float *pf32, double *pfa,
+                                                       double ratio) {
   uint32_t b = blockIdx.x * kWavesPerBlock + wave_id();
   int e = threadIdx.x & (kWave - 1);
   if (b >= T.nb || e >= 48) return;
@@ -293,36 +300,39 @@ __global__ void __launch_bounds__(kBlock) k_plus_faces(Topo T, CoefPair K, const
   int m = dev_morton(c[0], c[1], c[2]);
   const BrickMeta M = T.meta[b];
   const double *own = K.of(b);
-  double kp[3];
+  double kp[3], kpa[3];
   bool wall[3];
   bool inner_nbr = false;
   for (int ax = 0; ax < 3; ++ax) {
     int dd = 2 * ax + 1;
-    kp[ax] = 0.0;
+    kp[ax] = kpa[ax] = 0.0;
     wall[ax] = false;
     int p = dev_partner(m, dd);
     if (!dev_outside(m, dd)) {
-      kp[ax] = own[(1 + ax) * 64 + p];
+      kp[ax] = kpa[ax] = own[(1 + ax) * 64 + p];
       continue;
     }
     int32_t n = M.nbr[dd];
     if (n >= 0) {
+      const bool inner = uint32_t(n) >= T.nlb;
       kp[ax] = K.of(uint32_t(n))[(1 + ax) * 64 + p];
-      if (ax == a) inner_nbr = uint32_t(n) >= T.nlb;
+      kpa[ax] = inner ? ratio * kp[ax] : kp[ax];
+      if (ax == a) inner_nbr = inner;
     } else if ((M.flags >> dd) & 1u) {
-      kp[ax] = tc[uint32_t(M.tplus) * 48u + ax * 16 + dev_face_index(m, ax)];
+      kp[ax] = kpa[ax] = tc[uint32_t(M.tplus) * 48u + ax * 16 + dev_face_index(m, ax)];
     } else {
       wall[ax] = true;
     }
   }
-  double v = kp[a];
+  double v = kp[a], va = kpa[a];
   if (wall[a]) {
     int first = wall[0] ? 0 : (wall[1] ? 1 : 2);
-    v = first == a ? own[m] - (own[64 + m] + own[128 + m] + own[192 + m]) -
-                         (kp[0] + kp[1] + kp[2])
-                   : 0.0;
+    const double rest = own[m] - (own[64 + m] + own[128 + m] + own[192 + m]);
+    v = first == a ? rest - (kp[0] + kp[1] + kp[2]) : 0.0;
+    va = first == a ? rest - (kpa[0] + kpa[1] + kpa[2]) : 0.0;
   }
-  pf64[b * 48u + e] = v;
+  if (pf64 != pfa) pf64[b * 48u + e] = v;
+  if (pf64 == pfa || b < T.nlb) pfa[b * 48u + e] = va;
   if (!pf32) return;
   if (!wall[a] && inner_nbr) {
     float hv = __half2float(half_coef(v * ldexp(1.0, M.level)));

@@ -348,6 +348,7 @@ struct mfmg_hierarchy {
   DevBuf<float> coef32;    // nlb * 256 (mixed)
   DevBuf<__half> coef16;   // (nb - nlb) * 256 (mixed)
   DevBuf<double> pf64;     // plus-face coefficients, nb * 48 (FP64 cycle, composite operator)
+  DevBuf<double> pfa;      // the composite operator's, nlb * 48, if not pf64 (k_plus_faces)
   DevBuf<float> pf32;      // plus-face coefficients, nb * 48 (mixed cycle)
   double n_active = 0;     // active leaf cells
   std::vector<char> stream_lv;  // per level: the cycle's stencils stream their coefficients
@@ -1077,8 +1078,10 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     }
     HIP_CHECK(hipGetLastError());
     h->pf64.alloc(size_t(nb) * 48);
+    if (!mixed && prm->alpha != 2.0) h->pfa.alloc(size_t(nlb) * 48);
     hipLaunchKernelGGL(k_plus_faces, dim3(grid_for(nb)), dim3(kBlock), 0, s, topo, K,
-                       (const double *)co->tc.p, h->pf64.p, h->pf32.p);
+                       (const double *)co->tc.p, h->pf64.p, h->pf32.p,
+                       h->pfa.p ? h->pfa.p : h->pf64.p, prm->alpha / 2.0);
     if (mixed) {
       h->U32.alloc(size_t(nb) * 64);
       h->B32.alloc(size_t(nb) * 64);
@@ -1755,7 +1758,7 @@ PcgArgs pcg_args(mfmg_hierarchy *h) {
   PcgArgs P;
   P.T = make_topo(*h->co->dt, h->meta.p);
   P.C = h->co->coef.p;
-  P.PF = h->pf64.p;
+  P.PF = h->pfa.p ? h->pfa.p : h->pf64.p;
   P.canon = h->co->dt->canon.p;
   P.S = h->S.p;
   P.partials = h->partials.p;

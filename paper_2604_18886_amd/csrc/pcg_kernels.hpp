@@ -12,7 +12,7 @@ namespace mfmg {
 struct PcgArgs {
   Topo T;
   const double *C;       // FP64 coefficients of the leaf bricks (device order)
-  const double *PF;      // FP64 plus-face coefficients of all bricks, 48 per brick
+  const double *PF;      // FP64 plus-face coefficients of the leaf bricks, 48 per brick
   const int32_t *canon;  // device leaf brick -> canonical leaf brick
   Scalars *S;
   double *partials;
@@ -48,9 +48,9 @@ __device__ __forceinline__ void average_up(double *__restrict__ X, const BrickMe
 
 // The forward composite operator is the finest-level stencil applied to a
 // full-size vector whose inner cells hold the mean of their active children
-// (average_up): an inner neighbour's plus-face coefficient is its Algorithm 3
-// k, the sum of the fine sub-face coefficients over 2 (the coarse side of a
-// T-junction), and the fine side takes the ghost of Eq. (10).  It therefore
+// (average_up): the plus-face coefficient towards an inner neighbour is the sum
+// of the fine sub-face coefficients over 2 (the coarse side of a T-junction;
+// k_plus_faces), and the fine side takes the ghost of Eq. (10).  It therefore
 // runs through stencil_sum, on the FP64 coefficient arrays.
 template <int CP = kCpolDefault>
 __device__ __forceinline__ LevelView<double, double, double, CP> composite_view(const PcgArgs &P,
@@ -62,7 +62,7 @@ __device__ __forceinline__ LevelView<double, double, double, CP> composite_view(
   V.us = V.u;
   V.cl = make_rsrc(P.C, nlb * 256 * sizeof(double));
   V.ci = V.cl;  // (the operator's rows are leaf rows)
-  V.pf = make_rsrc(P.PF, nb * 48 * sizeof(double));
+  V.pf = make_rsrc(P.PF, nlb * 48 * sizeof(double));
   V.meta = P.T.meta;
   V.nlb = P.T.nlb;
   V.iscale = 1.0;
