@@ -280,12 +280,14 @@ __global__ void __launch_bounds__(256) k_count_active(const BrickMeta *meta, uin
 // carries that part on the first of them.
 // pf32 (may be null): the mixed cycle's copy, with the rounding of an inner
 // neighbour's store.
-// The composite operator reads the same entries on leaf bricks (pfa), except
-// next to an inner brick: the coarse side of a T-junction carries the fine
-// sub-face coefficients' sum over 2, Algorithm 3's coefficient their sum over
-// alpha, so ratio = alpha / 2 times that.  pfa is pf64 unless an FP64 cycle with
-// another alpha than 2 needs both (pfa: leaf bricks only; pf64 then the
-// cycle's).
+// The composite operator reads the same entries on leaf bricks, except next to
+// an inner brick: the coarse side of a T-junction carries the fine sub-face
+// coefficients' sum over 2, Algorithm 3's coefficient their sum over alpha.
+// OTHER (alpha != 2; forming both in one kernel for every alpha took 292 us at
+// 26.3M leaves where this one without takes 217): pfa takes the
+// operator's entries, ratio = alpha / 2 times Algorithm 3's there, on leaf
+// bricks; it is pf64 where the cycle does not read that (mixed precision).
+template <bool OTHER>
 __global__ void __launch_bounds__(kBlock) k_plus_faces(Topo T, CoefPair K, const double *tc,
                                                        double *pf64, float *pf32, double *pfa,
                                                        double ratio) {
@@ -300,39 +302,51 @@ __global__ void __launch_bounds__(kBlock) k_plus_faces(Topo T, CoefPair K, const
   int m = dev_morton(c[0], c[1], c[2]);
   const BrickMeta M = T.meta[b];
   const double *own = K.of(b);
-  double kp[3], kpa[3];
+  double kp[3];
   bool wall[3];
   bool inner_nbr = false;
+  uint32_t inner = 0u;  // OTHER: bit ax
   for (int ax = 0; ax < 3; ++ax) {
     int dd = 2 * ax + 1;
-    kp[ax] = kpa[ax] = 0.0;
+    kp[ax] = 0.0;
     wall[ax] = false;
     int p = dev_partner(m, dd);
     if (!dev_outside(m, dd)) {
-      kp[ax] = kpa[ax] = own[(1 + ax) * 64 + p];
+      kp[ax] = own[(1 + ax) * 64 + p];
       continue;
     }
     int32_t n = M.nbr[dd];
     if (n >= 0) {
-      const bool inner = uint32_t(n) >= T.nlb;
       kp[ax] = K.of(uint32_t(n))[(1 + ax) * 64 + p];
-      kpa[ax] = inner ? ratio * kp[ax] : kp[ax];
-      if (ax == a) inner_nbr = inner;
+      if (ax == a) inner_nbr = uint32_t(n) >= T.nlb;
+      if (OTHER && uint32_t(n) >= T.nlb) inner |= 1u << ax;
     } else if ((M.flags >> dd) & 1u) {
-      kp[ax] = kpa[ax] = tc[uint32_t(M.tplus) * 48u + ax * 16 + dev_face_index(m, ax)];
+      kp[ax] = tc[uint32_t(M.tplus) * 48u + ax * 16 + dev_face_index(m, ax)];
     } else {
       wall[ax] = true;
     }
   }
-  double v = kp[a], va = kpa[a];
+  double v = kp[a];
   if (wall[a]) {
     int first = wall[0] ? 0 : (wall[1] ? 1 : 2);
-    const double rest = own[m] - (own[64 + m] + own[128 + m] + own[192 + m]);
-    v = first == a ? rest - (kp[0] + kp[1] + kp[2]) : 0.0;
-    va = first == a ? rest - (kpa[0] + kpa[1] + kpa[2]) : 0.0;
+    v = first == a ? own[m] - (own[64 + m] + own[128 + m] + own[192 + m]) -
+                         (kp[0] + kp[1] + kp[2])
+                   : 0.0;
   }
-  if (pf64 != pfa) pf64[b * 48u + e] = v;
-  if (pf64 == pfa || b < T.nlb) pfa[b * 48u + e] = va;
+  if (!OTHER || pf64 != pfa) pf64[b * 48u + e] = v;
+  if constexpr (OTHER) {
+    double sum = 0.0;
+    for (int ax = 0; ax < 3; ++ax) {
+      if ((inner >> ax) & 1u) kp[ax] = ratio * kp[ax];
+      sum = sum + kp[ax];
+    }
+    double va = kp[a];
+    if (wall[a]) {
+      int first = wall[0] ? 0 : (wall[1] ? 1 : 2);
+      va = first == a ? own[m] - (own[64 + m] + own[128 + m] + own[192 + m]) - sum : 0.0;
+    }
+    if (b < T.nlb) pfa[b * 48u + e] = va;
+  }
   if (!pf32) return;
   if (!wall[a] && inner_nbr) {
     float hv = __half2float(half_coef(v * ldexp(1.0, M.level)));
@@ -1079,13 +1093,13 @@ __device__ __forceinline__ bool stop_test(const StopTest &T, const int *done) {
 // coefficients, as in every half-sweep.  A leaf's stored one is that sum (and a
 // third of the reads), except next to an inner brick: that face's coefficient is
 // Algorithm 3's (half the fine sub-faces' sum for alpha = 2 only, in FP16 in the
-// mixed cycle).  It also clears the iterate.
-template <bool INNER, class V, class CL, class CI, int CP>
+// mixed cycle).  It also clears the iterate.  LONE: no leaf has such a neighbour.
+template <bool INNER, bool LONE, class V, class CL, class CI, int CP>
 __device__ __forceinline__ void first_sweep_brick(const LevelView<V, CL, CI, CP> &X,
                                              const LaneC<V, CL> &L, uint32_t b, int colour) {
   const BrickMeta M = load_meta(X.meta, b);
   bool act = (act_mask(M) >> L.m) & 1ull;
-  if (!INNER && !(M.flags & kFlagInner)) {
+  if (!INNER && (LONE || !(M.flags & kFlagInner))) {
     V c = own_coef<false>(X, b, 0, L.m);
     V g = bload<V, side_pol(CP)>(X.b, L.m, b * 64u);
     bstore<V>(X.u, L.m, b * 64u, act && L.colour == colour ? div_by(g, c) : V(0));
@@ -1109,7 +1123,7 @@ __device__ __forceinline__ void first_sweep_brick(const LevelView<V, CL, CI, CP>
 // finest level's leaves are the first bricks, theirs follow).  26.3M leaves,
 // FP32: 44.8 us, against 41.3 and 10.8 in a launch of its own; 2.3M leaves 7.0
 // against 6.3 + 4.6.
-template <class V, class CL, class CI, int CP = kCpolDefault>
+template <class V, class CL, class CI, int CP = kCpolDefault, bool LONE = true>
 __global__ void __launch_bounds__(kBlock) k_first_sweep(LevelArgs<V, CL, CI> A, int colour,
                                                         int clear, StopTest T) {
   if (stop_test(T, A.done)) return;
@@ -1117,8 +1131,8 @@ __global__ void __launch_bounds__(kBlock) k_first_sweep(LevelArgs<V, CL, CI> A, 
   const LevelView<V, CL, CI, CP> X = level_view<CP>(A);
   const WaveLoop W = wave_loop(A.R.n());
   for (uint32_t i = W.first; i < W.end; i += W.step) {
-    if (i < A.R.n_leaf) first_sweep_brick<false>(X, L, A.R.leaf_lo + i, colour);
-    else first_sweep_brick<true>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
+    if (i < A.R.n_leaf) first_sweep_brick<false, LONE>(X, L, A.R.leaf_lo + i, colour);
+    else first_sweep_brick<true, LONE>(X, L, A.R.inner_lo + (i - A.R.n_leaf), colour);
   }
   if (clear) {
     const WaveLoop C = wave_loop(X.nlb - A.R.n_leaf);
@@ -1219,7 +1233,7 @@ __global__ void __launch_bounds__(kBlock) k_smooth_fas(LevelArgs<V, CL, CI> A, i
       const uint32_t b = A.R.leaf_lo + i;
       const uint32_t flags = load_meta(X.meta, b).flags;
       if (!((flags >> 8) & 0x3fu)) {
-        first_sweep_brick<false>(X, L, b, colour);
+        first_sweep_brick<false, true>(X, L, b, colour);
       } else if constexpr (sizeof(V) == 8) {
         smooth_brick_gathered<false, 0, false>(X, L, half_gather(L, colour), b, colour);
       } else {

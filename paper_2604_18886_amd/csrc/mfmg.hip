@@ -1079,9 +1079,13 @@ extern "C" mfmg_status mfmg_build_hierarchy(const mfmg_coeffs *co, const mfmg_mg
     HIP_CHECK(hipGetLastError());
     h->pf64.alloc(size_t(nb) * 48);
     if (!mixed && prm->alpha != 2.0) h->pfa.alloc(size_t(nlb) * 48);
-    hipLaunchKernelGGL(k_plus_faces, dim3(grid_for(nb)), dim3(kBlock), 0, s, topo, K,
-                       (const double *)co->tc.p, h->pf64.p, h->pf32.p,
-                       h->pfa.p ? h->pfa.p : h->pf64.p, prm->alpha / 2.0);
+    auto plus_faces = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(grid_for(nb)), dim3(kBlock), 0, s, topo, K,
+                         (const double *)co->tc.p, h->pf64.p, h->pf32.p,
+                         h->pfa.p ? h->pfa.p : h->pf64.p, prm->alpha / 2.0);
+    };
+    if (prm->alpha != 2.0) plus_faces(k_plus_faces<true>);
+    else plus_faces(k_plus_faces<false>);
     if (mixed) {
       h->U32.alloc(size_t(nb) * 64);
       h->B32.alloc(size_t(nb) * 64);
@@ -1577,6 +1581,17 @@ struct CycleT {
       hipLaunchKernelGGL((k_smooth<V, CL, CI, kCpolDefault, PR, true>), g, dim3(kBlock), 0, s, A,
                          colour);
   }
+  template <bool LONE>
+  void first_sweep(int l, const LevelArgs<V, CL, CI> &A, int colour) const {
+    dim3 g(stencil_grid<V>(A.R.n()));
+    const StopTest T = l == h->L ? stop : StopTest{};
+    if (stream(l))
+      hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolLevel, LONE>), g, dim3(kBlock), 0, s, A,
+                         colour, 0, T);
+    else
+      hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolDefault, LONE>), g, dim3(kBlock), 0, s, A,
+                         colour, 0, T);
+  }
   // nu iterations of transposed smoothing, colours (first, 1 - first) each.
   // zero: from a zero iterate, which the first half-sweep also writes;
   // prolong: the transposed prolongation is still to be taken (by the first
@@ -1584,16 +1599,12 @@ struct CycleT {
   void smooth(int l, int first, int nu, bool zero, bool prolong) const {
     auto A = args(l);
     if (A.R.n() == 0) return;
-    dim3 g(stencil_grid<V>(A.R.n()));
     for (int k = 0; k < 2 * nu; ++k) {
       int colour = (k & 1) ? 1 - first : first;
       if (zero && k == 0) {
-        if (stream(l))
-          hipLaunchKernelGGL((k_first_sweep<V, CL, CI, kCpolLevel>), g, dim3(kBlock), 0, s, A, colour,
-                             0, l == h->L ? stop : StopTest{});
-        else
-          hipLaunchKernelGGL((k_first_sweep<V, CL, CI>), g, dim3(kBlock), 0, s, A, colour, 0,
-                             l == h->L ? stop : StopTest{});
+        // (leaves and inner bricks on one level may be neighbours)
+        if (A.R.n_leaf && A.R.n_inner) first_sweep<false>(l, A, colour);
+        else first_sweep<true>(l, A, colour);
       } else if (prolong && k == 0) {
         half_sweep<1>(l, A, colour);
       } else if (prolong && k == 1) {
