@@ -25,7 +25,7 @@
  *     pointers are ordinary host memory.  The caller owns every buffer it
  *     passes; the library owns only the objects it returns, which the
  *     matching mfmg_destroy_* call frees.  Their device memory is kept for the
- *     next objects (at most 8 GiB per device, and beyond 64 MiB at most a
+ *     next objects (at most 8 GiB per device, and beyond 1 GiB at most a
  *     quarter of what the device then has free; blocks not used again for a while, and all of them
  *     when an allocation of the library fails or at mfmg_release_memory, go
  *     back to the driver).

@@ -18,7 +18,7 @@ namespace mfmg {
 // is rounded up by less than an eighth.
 //
 // Kept blocks are out of reach of the process's other allocators, so they are
-// bounded: at most kMaxBytes, and beyond kMuch at most a quarter of what the
+// bounded: at most kMaxBytes, and beyond kAsk at most a quarter of what the
 // device has free besides (the least recently freed go back to the driver first); a block not
 // asked for within kMaxAge frees goes back too, and everything does when an
 // allocation fails or on request (release).
@@ -38,7 +38,7 @@ class DevicePool {
   using Status = typename Api::Status;
   static constexpr size_t kMaxBytes = size_t(8) << 30;
   static constexpr uint64_t kMaxAge = 512;
-  static constexpr size_t kMuch = size_t(64) << 20;
+  static constexpr size_t kAsk = size_t(1) << 30;
 
   // A multiple of 512, more than bytes by less than an eighth of it from 4 KiB on.
   static size_t rounded(size_t bytes) {
@@ -96,12 +96,14 @@ class DevicePool {
   }
 
   // Takes the bound on kept blocks from what the device has free now.  Asking
-  // takes some 10 microseconds (a small object is made and destroyed in 25), so
-  // once per destroyed object, not per block, and only when much is kept.
+  // takes some 10 microseconds (a small object is made and destroyed in 25, the
+  // three of 26.3M leaves in 2,700), so not per block: called after an object's
+  // are back, and only once kAsk more have come back.
   void rebound() {
     {
       std::lock_guard<std::mutex> lock(mu_);
-      if (held_ <= kMuch) return;
+      if (back_ < kAsk) return;
+      back_ = 0;
     }
     size_t n = 0;
     if (!Api::available(&n)) return;
@@ -147,6 +149,7 @@ class DevicePool {
     for (Block &b : blocks) {
       b.when = ++frees_;
       held_ += b.bytes;
+      back_ += b.bytes;
     }
     kept_.splice(kept_.end(), blocks);
     trim(most_, frees_ > kMaxAge ? frees_ - kMaxAge : 0);
@@ -163,6 +166,7 @@ class DevicePool {
   std::list<Block> parked_;  // freed, their work not known to have finished
   size_t held_ = 0;          // bytes in kept_
   size_t most_ = kMaxBytes;  // and their bound
+  size_t back_ = 0;          // bytes put back since it was taken
   uint64_t frees_ = 0;
 };
 

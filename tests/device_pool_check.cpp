@@ -166,15 +166,19 @@ static int full_device() {
   return 0;
 }
 
-// Others can have what is kept: beyond kMuch at most a quarter of the free
-// memory stays, and nothing after release (blocks whose free is refused do).
+// Others can have what is kept: once kAsk have come back at most a quarter of
+// the free memory stays, and nothing after release (blocks whose free is refused
+// do).
 static int given_back() {
   Pool pool;
   std::vector<void *> p;
   Device::capacity = 4096 * kMiB;
+  CHECK(fill(pool, 30, 32 * kMiB, p) == 0);
+  pool.rebound();
+  CHECK(Device::asked == 0 && Device::used == 960 * kMiB);
   CHECK(fill(pool, 60, 32 * kMiB, p) == 0);
   pool.rebound();  // 2176 MiB free: a quarter is 544 MiB
-  CHECK(Device::used == 544 * kMiB);
+  CHECK(Device::asked == 1 && Device::used == 544 * kMiB);
   CHECK(fill(pool, 30, 32 * kMiB, p) == 0);
   CHECK(Device::used == 544 * kMiB);
   Device::busy = true;
@@ -186,10 +190,6 @@ static int given_back() {
   Device::busy = false;
   pool.release();
   CHECK(Device::used == 0);
-  Device::asked = 0;
-  CHECK(fill(pool, 2, 32 * kMiB, p) == 0);
-  pool.rebound();
-  CHECK(Device::asked == 0 && Device::used == Pool::kMuch);
   return 0;
 }
 
