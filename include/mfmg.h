@@ -312,8 +312,7 @@ mfmg_status mfmg_divergence(mfmg_hierarchy *h, const double *face_beta,
  * k (p_o - p_t); T-junction: k (mean of p over the fine owner's active
  * siblings - p_t) / 2; Dirichlet wall: k p_o; Neumann wall or an inactive
  * side: 0), so that div(u_new) = div(u) - A p: after a solve of A p = div(u)
- * the divergence left is the solve's residual.  The first call makes the
- * hierarchy's canonical face list (n_faces x 18 bytes), which it keeps. */
+ * the divergence left is the solve's residual. */
 mfmg_status mfmg_project_velocity(mfmg_hierarchy *h, const double *face_beta,
                                   const double *p, double *face_u, void *stream);
 

@@ -1,7 +1,6 @@
-// HIP kernels of the solver: coefficient assembly (Section 2.1, Eq. 3),
-// coarsening (Algorithm 3), the brick stencil with T-junction ghosts
-// (Section 3.1, Eq. 10), red-black Gauss-Seidel and the steps of the
-// FAS-style cycle (Algorithm 4).
+// HIP kernels of the solver: coarsening (Algorithm 3), the brick stencil with
+// T-junction ghosts (Section 3.1, Eq. 10), red-black Gauss-Seidel and the steps
+// of the FAS-style cycle (Algorithm 4).
 //
 // Layout: a brick is 4x4x4 cells = one wavefront; lane m is the cell with
 // local Morton index m.  Device brick ids are level-major: leaf bricks first
@@ -1218,8 +1217,8 @@ __global__ void __launch_bounds__(kBlock) k_fas_rhs(LevelArgs<V, CL, CI> A) {
 // without inner neighbours sees zeros only (first_sweep_brick); the others take
 // a plain half-sweep, whose cells read the other colour.  Against k_fas_rhs and
 // a plain half-sweep, FP32: 45.8 us for 15.6 + 38.1 (level 9 of the 26.3M-leaf
-// workload), 15.7 for 6.3 + 12.9; solves 35.76 -> 35.47 ms, 2.3M leaves 5.33 ->
-// 5.24, FP64 7.21 -> 7.04.
+// workload), 15.7 for 6.3 + 12.9; solves of 2.3M leaves 5.33 -> 5.24 ms, FP64
+// 7.21 -> 7.04 (of 26.3M within their run-to-run spread).
 template <class V, class CL, class CI, int CP = kCpolDefault>
 __global__ void __launch_bounds__(kBlock) k_smooth_fas(LevelArgs<V, CL, CI> A, int colour) {
   if (A.done && *A.done) return;

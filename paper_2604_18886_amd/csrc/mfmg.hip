@@ -166,7 +166,7 @@ struct DevBuf {
 // hierarchy; freed pages are kept (at most kPinnedKept) and used again.
 struct HostPage {
   Scalars S;  // the scalars read back after a solve
-  int done;   // stop flag written by k_finish
+  int done;   // stop flag (S->done, mirrored)
 };
 constexpr size_t kPinnedKept = 16;
 struct PinnedPages {
@@ -387,7 +387,7 @@ struct mfmg_hierarchy {
   DevBuf<double> rA;              // adjoint PCG residual
   HostPage *page = nullptr;      // pinned, mapped
   Scalars *hostS = nullptr;      // in it: the scalars read back after a solve
-  int *host_done = nullptr;      // in it: stop flag written by k_finish
+  int *host_done = nullptr;      // in it: the stop flag
   int *host_done_dev = nullptr;  // its device address
   hipEvent_t iter_ev[2] = {nullptr, nullptr};
   hipStream_t cap_stream = nullptr;                 // capture-only stream of the graphs
@@ -2103,7 +2103,9 @@ static void run_iterations(mfmg_hierarchy *h, double *r, V *r_low, V *z, bool nu
     // The stop flag of iteration it is read on the host only after
     // iteration it + 1 is queued, so the GPU never idles on the round trip;
     // every kernel of an iteration queued after the stop returns at once.
-    // k_finish mirrors the flag into mapped host memory (no copy launch).
+    // The kernel that sets the flag (k_finish, or on small solves the one that
+    // takes the stop test or meets a breakdown) mirrors it into mapped host
+    // memory (no copy launch).
     HIP_CHECK(hipEventRecord(h->iter_ev[it & 1], s));
     if (it > 0) {
       HIP_CHECK(hipEventSynchronize(h->iter_ev[(it - 1) & 1]));

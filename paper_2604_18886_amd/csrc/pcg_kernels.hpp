@@ -302,7 +302,7 @@ __global__ void __launch_bounds__(kBlock) k_pcg_p(PcgArgs P, const V *z, double 
 }
 
 // Ap = A p over the leaf bricks (wave_loop grid); each workgroup stores its
-// partial (p, Ap), k_finish_alpha adds them in fixed order.
+// partial (p, Ap); k_pcg_update or k_finish adds them in fixed order.
 template <int CP = kCpolDefault>
 __global__ void __launch_bounds__(kBlock) k_pcg_Ap(PcgArgs P, const double *p, double *Ap) {
   if (P.S->done) return;
